@@ -106,15 +106,15 @@ typedef struct {
  *              is not computed; out-of-range entries are ignored.  NULL = rows are started by
  *              descending m.  It never changes any result.  Not used when G*Nb > 32768.
  *   queue      [RR_QUEUE_WORDS] int32, optional: row counters for rr_sparse_attn.  With row_order and
- *              queue both non-NULL (bf16, d = 128, B = 128) the launch is one workgroup per compute unit
- *              that draws rows from these counters in the order of row_order, instead of one workgroup
+ *              queue both non-NULL (bf16, d = 128, B = 128) the launch is two workgroups per compute unit
+ *              that draw rows from these counters in the order of row_order, instead of one workgroup
  *              per row: the compute units share the rows dynamically and each fetches its next row's
  *              list while it works.  The words must be zero when a launch starts; the launch leaves them
  *              zero, and rr_estimate / rr_mask_from_dense zero them when they fill row_order.  Two
  *              launches that overlap in time must not share a queue (give each mask its own).  NULL =
  *              one workgroup per row.  It never changes any result.  (Used for contexts of up to 256
- *              blocks, where the start of a row is a visible share of it; longer ones are launched one
- *              workgroup per row either way.)
+ *              blocks and at least as many rows as workgroups, where the start of a row is a visible share of
+ *              it; other calls are launched one workgroup per row either way.)
  * rr_sparse_attn reads only row_count, row_list, row_order and queue; entries of row_list must satisfy
  * 0 <= n <= m, strictly ascending (counts and entries outside these ranges are clamped into them
  * on the device, so a malformed list gives a wrong row but no stray memory access).  A row with

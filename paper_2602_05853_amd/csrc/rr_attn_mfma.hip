@@ -1,8 +1,8 @@
 // Kernel group (3), MFMA form: causal block-sparse flash attention (Sec. 2.1) for bf16 tensors
 // with d = 128 and B = 128 on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate).
 //
-// One workgroup (8 waves, two per SIMD) per (batch, head, query block m); it walks the compacted
-// ascending list of selected key blocks of that row (or every n <= m for the dense baseline).
+// One workgroup (4 waves, one per SIMD; two workgroups per compute unit) per (batch, head, query block m); it
+// walks the compacted ascending list of selected key blocks of that row (or every n <= m for the dense baseline).
 //
 // Transposed products.  S^T = K Q^T and O^T = V^T P^T, so a lane always owns one QUERY (MFMA
 // column = lane % 32): the softmax statistics of a query are per-lane scalars, and the fp32 S^T
@@ -11,13 +11,16 @@
 // is laid out in LDS in exactly the key order in which the S^T accumulators hold the keys
 // (0-3, 8-11 | 4-7, 12-15 of every 16).
 //
-// Work split.  Wave w owns the 32 queries 32*(w % 4) .. +31 and keys 64*(w / 4) .. +63 of every key
-// block (NQT = 1 subtile of 32 queries per wave; the code is written for NQT subtiles, NQT = 2 being
-// four waves of 64 queries whose LDS fragments feed two MFMAs each).  The two key halves of a query
-// are merged once at the end.  A wave's 64 keys are taken in two steps of 32.  Measured on MI355X
-// both splits run at the same speed: under this kernel the chip is power limited (the clock drops
-// from 2.39 GHz to 1.98-2.2 GHz); the 8-wave split needs 11 % fewer cycles but reads twice as much
-// from LDS.  It is kept because it leaves half the registers free (128 + 104 of 512 per lane).
+// Work split.  Wave w owns the 32 queries 32 w .. +31 of the block and every key; a key block is walked as two
+// tiles of 64 keys, a tile in two steps of 32.  Under this kernel the chip is power limited (the clock drops from
+// 2.39 GHz to 1.7 GHz), so the time goes to whatever leaves the matrix pipe idle: the start of a row (order ->
+// count -> list -> first tile, each waiting for the one before) and its end (diagonal block, output).  With 64 KB
+// of tile buffers and at most 256 registers per lane TWO workgroups share a compute unit, and one's start and end
+// run behind the other's tiles.
+// Measured against one workgroup of 8 waves per compute unit with 128 KB of tile buffers (a wave then owned 32
+// queries and one key half of a 128-key tile; the same MFMAs, LDS reads and copies per block), 32 / 8 heads: estimate
+// + sparse 8K tokens 316 -> 276 us, 128K 35.0 -> 32.8 ms, 64K / 64 heads 25.0 -> 22.8 ms, dense 16K 2.14 -> 2.02 ms,
+// eight packed prompts 1.73 -> 1.51 ms.
 //
 // Software pipeline.  On this chip the vector ALU instructions of a SIMD do not run in the shadow
 // of its MFMAs for more than a few cycles per MFMA (measured: 32 MFMAs + the softmax of 32 scores
@@ -51,15 +54,13 @@ namespace rr {
 
 namespace {
 
-constexpr int NQT = 1;                               // 32-query subtiles per wave
-constexpr int kQWaves = 128 / (32 * NQT);            // waves along the queries
-constexpr int kWaves = 2 * kQWaves;                  // x 2 key halves
+constexpr int kWaves = 4;                            // 32 queries each
 constexpr int kThreads = 64 * kWaves;
-constexpr int kRowsPerWave = 128 / kWaves;           // tile rows each wave copies
+constexpr int kTileKeys = 64;
+constexpr int kRowsPerWave = kTileKeys / kWaves;     // tile rows each wave copies
 constexpr int kCopies = kRowsPerWave / 4;            // copy instructions per wave and tile (4 rows each)
-constexpr int kTileBytes = 128 * 256;                // one 128 x 128 bf16 tile
-constexpr int kLdsBytes = 4 * kTileBytes;            // K and V^T, two stages each
-constexpr int kXchgFloats = 66 * NQT;                // per lane: 64 accumulators + max + sum per subtile
+constexpr int kTileBytes = kTileKeys * 256;          // one 64 x 128 bf16 tile
+constexpr int kLdsBytes = 4 * kTileBytes;            // K and V, two stages each
 constexpr int kOutRowBytes = 264;                    // 128 bf16 + 8 bytes of padding
 constexpr float kLazyLog2 = 8.0f;                    // move the softmax reference when exceeded by 2^8
 constexpr float kLazySum = 256.0f;                   // = 2^kLazyLog2: a lane's 16-term sum above it triggers the move
@@ -185,31 +186,28 @@ __device__ __forceinline__ void mfma_qk_first(f32x16& s, const bf16x8& k, const 
 // Idle issue cycles longer than the tail of the last MFMA, then the values pass through empty
 // asm statements: whatever reads them afterwards depends on those statements and therefore
 // cannot be scheduled in front of the idle cycles.
-__device__ __forceinline__ void mfma_settle_s(f32x16 (&s)[NQT]) {
-    if constexpr (NQT == 2) asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" : "+v"(s[0]), "+v"(s[NQT - 1]));
-    else asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" : "+v"(s[0]));
+__device__ __forceinline__ void mfma_settle_s(f32x16& s) {
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" : "+v"(s));
 }
-__device__ __forceinline__ void mfma_settle_acc(f32x16 (&acc)[4][NQT]) {
+__device__ __forceinline__ void mfma_settle_acc(f32x16 (&acc)[4]) {
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15");
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) asm volatile("" : "+a"(acc[dt][qt]));
+    for (int dt = 0; dt < 4; ++dt) asm volatile("" : "+a"(acc[dt]));
 }
 
 // Per-wave state and operand addressing.
 struct Wave {
     const lds_byte_t* lds;
-    int lane, l32, gsel, qi, ki;
+    int lane, l32, gsel;
     float sl2;                         // log2(e) / sqrt(d)
-    bf16x8 qf[NQT][8];                 // Q^T operand: [32-query subtile][16-wide d chunk]
-    f32x16 acc[4][NQT];                // O^T: [32-row d tile][32-query subtile]
-    float mref[NQT];                   // softmax reference of the lane's queries, log2 units
-    float lsum[NQT];                   // this lane's part of the denominators
+    bf16x8 qf[8];                      // Q^T operand: 16-wide d chunks
+    f32x16 acc[4];                     // O^T: 32-row d tiles
+    float mref;                        // softmax reference of the lane's query, log2 units
+    float lsum;                        // this lane's part of the denominator
     // Per-lane LDS byte addresses.  The XOR swizzle makes the chunk part of an address
     // base ^ (32 * kc) for K and base ^ (64 * dt) for V.
-    unsigned ka0;                      // K: row (64 ki + lane%32), chunk gsel, swizzled
-    unsigned va0;                      // V: keys 4 gsel + (lane%16)/4 of the wave's half, d tile 0
+    unsigned ka0;                      // K: row lane%32, chunk gsel, swizzled
+    unsigned va0;                      // V: keys 4 gsel + (lane%16)/4, d tile 0
     // ... and all of them, so that the hot loop forms no address: the chunk part is kaddr[kc] = ka0 ^ 32 kc,
     // vaddr[dt] = va0 ^ 64 dt; buffer, subtile and key-chunk selection ride in the instruction's immediate
     // offset (the loop is unrolled over the buffer parity for that).
@@ -218,9 +216,9 @@ struct Wave {
 
     __device__ __forceinline__ void init_addresses() {
         const unsigned lds0 = (unsigned)(uintptr_t)lds;       // LDS addresses are 32 bits
-        ka0 = lds0 + k_swz(64 * ki + l32, gsel);
+        ka0 = lds0 + k_swz(l32, gsel);
         const int s16 = lane & 15, dhalf = (lane >> 4) & 1;
-        const int key = 64 * ki + 4 * gsel + (s16 >> 2);
+        const int key = 4 * gsel + (s16 >> 2);
         va0 = lds0 + 2 * kTileBytes + 8 * (s16 & 1) + v_swz(key, 2 * dhalf + ((s16 & 3) >> 1));
 #pragma unroll
         for (int kc = 0; kc < 8; ++kc) kaddr[kc] = ka0 ^ (32u * kc);
@@ -253,88 +251,67 @@ struct Wave {
     }
 };
 
-// S^T of one 32-key step, nothing overlapped (pipeline prologue and the diagonal block).
-__device__ __forceinline__ void qk_step(const Wave& w, int buf, int t, f32x16 (&s)[NQT]) {
+// S^T of one 32-key step, nothing overlapped (the diagonal block).
+__device__ __forceinline__ void qk_step(const Wave& w, int buf, int t, f32x16& s) {
 #pragma unroll
     for (int kc = 0; kc < 8; ++kc) {
         const bf16x8 kf = w.kfrag(buf, t, kc);
-#pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) {
-            if (kc == 0) mfma_qk_first(s[qt], kf, w.qf[qt][kc]);
-            else mfma_qk(s[qt], kf, w.qf[qt][kc]);
-        }
+        if (kc == 0) mfma_qk_first(s, kf, w.qf[kc]);
+        else mfma_qk(s, kf, w.qf[kc]);
     }
     mfma_settle_s(s);
 }
 
 // O^T += V^T P^T of one 32-key step, nothing overlapped.
-__device__ __forceinline__ void pv_step(Wave& w, int buf, int t, const bf16x8 (&p)[NQT][2]) {
+__device__ __forceinline__ void pv_step(Wave& w, int buf, int t, const bf16x8 (&p)[2]) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const bf16x8 vf = w.vfrag(buf, t, u);
-#pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) mfma_pv(w.acc[u >> 1][qt], vf, p[qt][u & 1]);
-    }
+    for (int u = 0; u < 8; ++u) mfma_pv(w.acc[u >> 1], w.vfrag(buf, t, u), p[u & 1]);
     mfma_settle_acc(w.acc);
 }
 
-// exp2 of the 32 scores of a step against the current reference; fills P, returns sums and maxima.
-__device__ __forceinline__ void exp_all(const Wave& w, const f32x16 (&s)[NQT], bf16x8 (&p)[NQT][2],
-                                        float (&psum)[NQT], float (&mx)[NQT]) {
+// exp2 of the 16 scores of a step against the current reference; fills P, returns sum and maximum.
+__device__ __forceinline__ void exp_all(const Wave& w, const f32x16& s, bf16x8 (&p)[2], float& psum, float& mx) {
+    const float nb = -w.mref;
+    psum = 0.f;
+    mx = -__builtin_huge_valf();
 #pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
-        const float nb = -w.mref[qt];
-        psum[qt] = 0.f;
-        mx[qt] = -__builtin_huge_valf();
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float e = __builtin_amdgcn_exp2f(fmaf(s[qt][r], w.sl2, nb));
-            psum[qt] += e;
-            mx[qt] = fmaxf(mx[qt], s[qt][r]);
-            p[qt][r >> 3][r & 7] = (__bf16)e;
-        }
+    for (int r = 0; r < 16; ++r) {
+        const float e = __builtin_amdgcn_exp2f(fmaf(s[r], w.sl2, nb));
+        psum += e;
+        mx = fmaxf(mx, s[r]);
+        p[r >> 3][r & 7] = (__bf16)e;
     }
 }
 
-// Moves the softmax reference of the lane's queries up to the new maximum, rescales O^T and the
+// Moves the softmax reference of the lane's query up to the new maximum, rescales O^T and the
 // denominator, and recomputes P of the step at hand.  Rare; entered by the whole wave.
-__device__ __forceinline__ void move_reference(Wave& w, const f32x16 (&s)[NQT], bf16x8 (&p)[NQT][2],
-                                               float (&psum)[NQT], float (&mx)[NQT]) {
+__device__ __forceinline__ void move_reference(Wave& w, const f32x16& s, bf16x8 (&p)[2], float& psum, float mx) {
     mfma_settle_acc(w.acc);                             // O^T is about to be read by vector instructions
+    float top = mx * w.sl2;
+    top = fmaxf(top, __shfl_xor(top, 32));
+    const float nref = fmaxf(w.mref, top);
+    const float use = (nref == -__builtin_huge_valf()) ? 0.f : nref;
+    const float alpha = __builtin_amdgcn_exp2f(w.mref - use);   // 0 while the reference is -inf
+    w.mref = nref;
+    w.lsum *= alpha;
 #pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
-        float top = mx[qt] * w.sl2;
-        top = fmaxf(top, __shfl_xor(top, 32));
-        const float nref = fmaxf(w.mref[qt], top);
-        const float use = (nref == -__builtin_huge_valf()) ? 0.f : nref;
-        const float alpha = __builtin_amdgcn_exp2f(w.mref[qt] - use);   // 0 while the reference is -inf
-        w.mref[qt] = nref;
-        w.lsum[qt] *= alpha;
+    for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+        for (int r = 0; r < 16; ++r) w.acc[dt][r] *= alpha;
+    float sum = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) w.acc[dt][qt][r] *= alpha;
-        float sum = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float e = __builtin_amdgcn_exp2f(fmaf(s[qt][r], w.sl2, -use));
-            sum += e;
-            p[qt][r >> 3][r & 7] = (__bf16)e;
-        }
-        psum[qt] = sum;
+    for (int r = 0; r < 16; ++r) {
+        const float e = __builtin_amdgcn_exp2f(fmaf(s[r], w.sl2, -use));
+        sum += e;
+        p[r >> 3][r & 7] = (__bf16)e;
     }
+    psum = sum;
     mfma_settle_acc(w.acc);                             // ... and was written by them
 }
 
-__device__ __forceinline__ void finish_softmax(Wave& w, const f32x16 (&s)[NQT], bf16x8 (&p)[NQT][2],
-                                               float (&psum)[NQT], float (&mx)[NQT], bool valid = true) {
-    if (!valid) return;                                 // a fill phase of the pipeline: nothing to keep
-    bool need = false;
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) need = need || (mx[qt] * w.sl2 > w.mref[qt] + kLazyLog2);
-    if (__any(need)) move_reference(w, s, p, psum, mx);
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) w.lsum[qt] += psum[qt];
+__device__ __forceinline__ void finish_softmax(Wave& w, const f32x16& s, bf16x8 (&p)[2], float psum, float mx) {
+    if (__any(mx * w.sl2 > w.mref + kLazyLog2)) move_reference(w, s, p, psum, mx);
+    w.lsum += psum;
 }
 
 // Global -> LDS copies of one 128 x 128 bf16 tile, kCopies instructions per wave (4 rows each), issued
@@ -342,7 +319,7 @@ __device__ __forceinline__ void finish_softmax(Wave& w, const f32x16 (&s)[NQT], 
 // cannot tell that the reads go to the other buffer), which turns the prefetch into a blocking
 // copy.  The kernel waits for them itself (wait_vm) before the barrier that hands a buffer over.
 // Lane l lands in LDS slot (row l/16 of the group, physical chunk l%16) and therefore fetches
-// logical chunk (l%16) ^ swizzle(row); the per-lane byte offsets of the 8 row groups are kept in
+// logical chunk (l%16) ^ swizzle(row); the per-lane byte offsets of the wave's row groups are kept in
 // registers, the tile origin is wave-uniform.
 struct Stager {
     const unsigned short* Kp;
@@ -368,34 +345,35 @@ struct Stager {
         asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
                      :: "v"(off[i]), "s"(wave_src), "s"(wave_dst + 4 * i * 256) : "memory");
     }
-    __device__ __forceinline__ const unsigned short* k_src(int n) const { return Kp + ((long long)n * 128 + kRowsPerWave * wv) * ksl; }
-    __device__ __forceinline__ const unsigned short* v_src(int n) const { return Vp + ((long long)n * 128 + kRowsPerWave * wv) * ksl; }
+    // this wave's rows of half `hf` (64 keys) of key block n
+    __device__ __forceinline__ const unsigned short* k_src(int n, int hf) const { return Kp + ((long long)n * 128 + kTileKeys * hf + kRowsPerWave * wv) * ksl; }
+    __device__ __forceinline__ const unsigned short* v_src(int n, int hf) const { return Vp + ((long long)n * 128 + kTileKeys * hf + kRowsPerWave * wv) * ksl; }
     __device__ __forceinline__ unsigned k_dst(int buf) const { return lds0 + buf * kTileBytes + kRowsPerWave * wv * 256; }
     __device__ __forceinline__ unsigned v_dst(int buf) const { return lds0 + (2 + buf) * kTileBytes + kRowsPerWave * wv * 256; }
-    // A tile whose last rows lie past the real length (`rows` real rows, 1 <= rows < 128): those LDS rows get a
-    // copy of the last real row (finite, and masked by token causality wherever a real query meets them).
-    // Offsets are formed on the spot from the tile origin: this path runs once per launch row at most.
-    __device__ __forceinline__ void issue_partial(const unsigned short* base, int n, unsigned dst, bool is_v, int rows,
-                                                  int lane) const {
-        const unsigned short* tile = base + (long long)n * 128 * ksl;
+    // Half `hf` of a block whose last rows lie past the real length (`rows` real rows, 1 <= rows < 128): those LDS
+    // rows get a copy of the last real row (finite, and masked by token causality wherever a real query meets
+    // them).  Offsets are formed on the spot from the block origin: this path runs once per launch row at most.
+    __device__ __forceinline__ void issue_partial(const unsigned short* base, int n, int hf, unsigned dst, bool is_v,
+                                                  int rows, int lane) const {
+        const unsigned short* block = base + (long long)n * 128 * ksl;
         const int r4 = lane >> 4, c = lane & 15;
 #pragma unroll
         for (int i = 0; i < kCopies; ++i) {
             const int row = 4 * i + r4;                      // LDS row inside the wave's rows: decides the swizzle
-            const int src_row = min(kRowsPerWave * wv + row, rows - 1);
+            const int src_row = min(kTileKeys * hf + kRowsPerWave * wv + row, rows - 1);
             const unsigned sw = is_v ? ((row & 7) << 1) : (row & 15);
             const unsigned off = 2u * ((unsigned)(src_row * ksl) + 8u * (c ^ sw));
             asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-                         :: "v"(off), "s"(tile), "s"(dst + 4 * i * 256) : "memory");
+                         :: "v"(off), "s"(block), "s"(dst + 4 * i * 256) : "memory");
         }
     }
-    __device__ __forceinline__ void issue_k(int n, int buf) const {
+    __device__ __forceinline__ void issue_k(int n, int hf, int buf) const {
 #pragma unroll
-        for (int i = 0; i < kCopies; ++i) issue_one(k_src(n), k_dst(buf), koff, i);
+        for (int i = 0; i < kCopies; ++i) issue_one(k_src(n, hf), k_dst(buf), koff, i);
     }
-    __device__ __forceinline__ void issue_v(int n, int buf) const {
+    __device__ __forceinline__ void issue_v(int n, int hf, int buf) const {
 #pragma unroll
-        for (int i = 0; i < kCopies; ++i) issue_one(v_src(n), v_dst(buf), voff, i);
+        for (int i = 0; i < kCopies; ++i) issue_one(v_src(n, hf), v_dst(buf), voff, i);
     }
 };
 
@@ -408,8 +386,8 @@ __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::
 // copies never queue up in front of the arithmetic.  `valid` is false for the two fill phases at either end of a
 // row, whose softmax is thrown away.
 template <bool kFetch, int VOFF, int KOFF>
-__device__ __forceinline__ void phase(Wave& w, const f32x16 (&scur)[NQT], f32x16 (&snext)[NQT],
-                                      const bf16x8 (&pprev)[NQT][2], bf16x8 (&pcur)[NQT][2],
+__device__ __forceinline__ void phase(Wave& w, const f32x16& scur, f32x16& snext,
+                                      const bf16x8 (&pprev)[2], bf16x8 (&pcur)[2],
                                       bool valid, const Stager& st,
                                       const unsigned short* k_src, unsigned k_dst,
                                       const unsigned short* v_src, unsigned v_dst) {
@@ -419,9 +397,8 @@ __device__ __forceinline__ void phase(Wave& w, const f32x16 (&scur)[NQT], f32x16
     bf16x8 vf[2], kf[2];
     vf[0] = w.template vfrag_imm<VOFF>(0);
     kf[0] = w.template kfrag_imm<KOFF>(0);
-    float psum[NQT], nb[NQT];
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) { psum[qt] = 0.f; nb[qt] = -w.mref[qt]; }
+    float psum = 0.f;
+    const float nb = -w.mref;
     bf16x2 ones;
     ones[0] = (__bf16)1.0f;
     ones[1] = (__bf16)1.0f;
@@ -429,7 +406,7 @@ __device__ __forceinline__ void phase(Wave& w, const f32x16 (&scur)[NQT], f32x16
     // one in front of it: stage A (scale and shift of element k) runs at step k, B (its exp2) at step k + 1,
     // C (rounding the pair (2j, 2j+1) to bf16, which is what PV will use) at step 2j + 3, D (adding the pair to
     // the row sum) at step 2j + 4.
-    constexpr int NE = 16 * NQT;
+    constexpr int NE = 16;
     float tq[NE], ev[NE];
     auto step = [&](int sidx) {
         if (sidx >= 1 && sidx - 1 < NE) {                           // B
@@ -437,25 +414,25 @@ __device__ __forceinline__ void phase(Wave& w, const f32x16 (&scur)[NQT], f32x16
             asm volatile("" : "+v"(ev[sidx - 1]));
         }
         if (sidx < NE) {                                            // A
-            tq[sidx] = fmaf(scur[sidx >> 4][sidx & 15], w.sl2, nb[sidx >> 4]);
+            tq[sidx] = fmaf(scur[sidx], w.sl2, nb);
             asm volatile("" : "+v"(tq[sidx]));
         }
         if (sidx >= 3 && (sidx & 1) && (sidx - 3) / 2 < NE / 2) {   // C
-            const int j = (sidx - 3) / 2, eq = (2 * j) >> 4, er = (2 * j) & 15;
+            const int er = sidx - 3;
             bf16x2 pr;
-            pr[0] = (__bf16)ev[2 * j];
-            pr[1] = (__bf16)ev[2 * j + 1];
-            pcur[eq][er >> 3][er & 7] = pr[0];
-            pcur[eq][er >> 3][(er & 7) + 1] = pr[1];
-            asm volatile("" : "+v"(pcur[eq][er >> 3]));
+            pr[0] = (__bf16)ev[er];
+            pr[1] = (__bf16)ev[er + 1];
+            pcur[er >> 3][er & 7] = pr[0];
+            pcur[er >> 3][(er & 7) + 1] = pr[1];
+            asm volatile("" : "+v"(pcur[er >> 3]));
         }
         if (sidx >= 4 && !(sidx & 1) && (sidx - 4) / 2 < NE / 2) {  // D
-            const int j = (sidx - 4) / 2, eq = (2 * j) >> 4, er = (2 * j) & 15;
+            const int er = sidx - 4;
             bf16x2 pr;
-            pr[0] = pcur[eq][er >> 3][er & 7];
-            pr[1] = pcur[eq][er >> 3][(er & 7) + 1];
-            psum[eq] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, psum[eq], false);   // sums what PV will use
-            asm volatile("" : "+v"(psum[eq]));
+            pr[0] = pcur[er >> 3][er & 7];
+            pr[1] = pcur[er >> 3][(er & 7) + 1];
+            psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, psum, false);   // sums what PV will use
+            asm volatile("" : "+v"(psum));
         }
     };
     // The scores of this step were completed by the last QK MFMA of the previous phase (an asm statement, so the
@@ -463,11 +440,7 @@ __device__ __forceinline__ void phase(Wave& w, const f32x16 (&scur)[NQT], f32x16
     // was issued.  The previous phase ends with a PV MFMA, which the matrix pipe accepts 8 wait states after
     // the QK one; the operand reads above and this statement add the rest whatever the compiler puts in
     // between.  The scores pass through the statement, so nothing that reads them can be scheduled in front.
-    {
-        f32x16& first = const_cast<f32x16&>(scur[0]);
-        if constexpr (NQT == 2) asm volatile("s_nop 2" : "+v"(first), "+v"(const_cast<f32x16&>(scur[NQT - 1])));
-        else asm volatile("s_nop 2" : "+v"(first));
-    }
+    asm volatile("s_nop 2" : "+v"(const_cast<f32x16&>(scur)));
     // four steps run ahead of the first MFMA: they fill the softmax pipeline and cover the latency of the first
     // operand reads
     step(0);
@@ -477,30 +450,24 @@ __device__ __forceinline__ void phase(Wave& w, const f32x16 (&scur)[NQT], f32x16
     SCHED_FENCE();
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-        // operand fragments of the next group are requested one group (4 MFMA slots) ahead
+        // operand fragments of the next group are requested one group (2 MFMA slots) ahead
         if (u < 7) {
             vf[(u + 1) & 1] = w.template vfrag_imm<VOFF>(u + 1);
             kf[(u + 1) & 1] = w.template kfrag_imm<KOFF>(u + 1);
         }
 #pragma unroll
-        for (int sl = 0; sl < 2 * NQT; ++sl) {
-            const int qt = sl >> 1;
+        for (int sl = 0; sl < 2; ++sl) {
             // QK before PV: the phase then ends with a PV product, and the scores of the next step are complete
             // one MFMA earlier
-            if ((sl & 1) == 0) {
-                if (u == 0) mfma_qk_first(snext[qt], kf[0], w.qf[qt][0]);
-                else mfma_qk(snext[qt], kf[u & 1], w.qf[qt][u]);
+            if (sl == 0) {
+                if (u == 0) mfma_qk_first(snext, kf[0], w.qf[0]);
+                else mfma_qk(snext, kf[u & 1], w.qf[u]);
+                if (kFetch && (u & 1) == 0) st.issue_one(k_src, k_dst, st.koff, u >> 1);
+                if (kFetch && (u & 1) == 1) st.issue_one(v_src, v_dst, st.voff, u >> 1);
             } else {
-                mfma_pv(w.acc[u >> 1][qt], vf[u & 1], pprev[qt][u & 1]);
+                mfma_pv(w.acc[u >> 1], vf[u & 1], pprev[u & 1]);
             }
-            if constexpr (NQT == 2) {
-                if (kFetch && sl == 0) st.issue_one(k_src, k_dst, st.koff, u);
-                if (kFetch && sl == 2) st.issue_one(v_src, v_dst, st.voff, u);
-            } else {
-                if (kFetch && sl == 0 && (u & 1) == 0) st.issue_one(k_src, k_dst, st.koff, u >> 1);
-                if (kFetch && sl == 0 && (u & 1) == 1) st.issue_one(v_src, v_dst, st.voff, u >> 1);
-            }
-            step(2 * NQT * u + sl + 4);
+            step(2 * u + sl + 4);
             SCHED_FENCE();
         }
     }
@@ -508,21 +475,13 @@ __device__ __forceinline__ void phase(Wave& w, const f32x16 (&scur)[NQT], f32x16
     // exceed 2^8 (the first step of a row, whose reference is -inf, gives +inf): the sum is the
     // trigger, the maximum itself is only computed on the rare path.
     if (valid) {
-        bool need = false;
+        if (__any(!(psum <= kLazySum))) {
+            float mx = -__builtin_huge_valf();
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) need = need || !(psum[qt] <= kLazySum);
-        if (__any(need)) {
-            float mx[NQT];
-#pragma unroll
-            for (int qt = 0; qt < NQT; ++qt) {
-                mx[qt] = -__builtin_huge_valf();
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx[qt] = fmaxf(mx[qt], scur[qt][r]);
-            }
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, scur[r]);
             move_reference(w, scur, pcur, psum, mx);
         }
-#pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) w.lsum[qt] += psum[qt];
+        w.lsum += psum;
     }
 }
 
@@ -558,13 +517,13 @@ __device__ __forceinline__ kernarg_ptr_t kernel_args() {
 }
 
 template <bool kRagged, bool kPersist>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, 2)
 k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // kRagged: the real length ends inside the last block (g.Lr < g.L) or the queries start inside their first
     // block (g.qoff > 0): clamped Q rows, a clamped copy of the partial diagonal tile, predicated stores.  Compiled apart so that the plain launch carries none of it
     // (both forms run at the same rate).
     //
-    // kPersist (sparse launches with a row order and a queue): one workgroup per compute unit that takes row after
+    // kPersist (sparse launches with a row order and a queue): two workgroups per compute unit that take row after
     // row.  Workgroup i starts with launch rank i and then draws ranks x + 8 t (x = i mod 8, the XCD the
     // dispatcher gave it) from the counter of its XCD, so that every rank keeps the XCD the order was made for
     // while the compute units of an XCD share its rows dynamically, and the next row is looked up while the
@@ -578,9 +537,9 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // ---- the next row of a persistent workgroup ----
     // Fetched in five steps, each needing what the one before it loaded: (1) a ticket from the XCD's counter,
     // published to the other waves through LDS, (2) the rank it stands for and that rank's entry of the row
-    // order, (3) the row, its count and its first list entries, (4) its last list entry, (5) done.  They are
+    // order, (3) the row, its count and its first list entry, (4) its last list entry, (5) done.  They are
     // placed in the tail of the current row: the ticket travels during the diagonal pass, the order entry during
-    // the merge, count and first entries during the output stores; only the last entry is waited for.  The ticket
+    // the merge, count and first entry during the output stores; only the last entry is waited for.  The ticket
     // is deliberately NOT drawn earlier (say, at the
     // start of the row, which would hide all five steps): a workgroup that claims its next row a whole row
     // ahead starts it out of step with the rows queued around it, which were ordered to walk the same key
@@ -590,10 +549,10 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         int order_entry;    // as loaded
         bool live;          // the order entry names a row
         int b, h, mq;
-        int count_raw, e0, e1, elast;
+        int count_raw, e0, elast;
     } nx;
     nx.rank = -1; nx.live = false; nx.order_entry = 0;
-    nx.b = nx.h = nx.mq = 0; nx.count_raw = nx.e0 = nx.e1 = nx.elast = 0;
+    nx.b = nx.h = nx.mq = 0; nx.count_raw = nx.e0 = nx.elast = 0;
     const int xcd = (int)blockIdx.x & 7;
     volatile lds_int_t* const ticket_slot = (volatile lds_int_t*)(lds + kLdsBytes);
     int ticket = 0;                                         // lane 0 of wave 0
@@ -637,7 +596,6 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         const int32_t* lp = ka->a.row_list + rid * ka->a.Nb;
         nx.count_raw = ka->a.row_count[rid];
         nx.e0 = lp[0];
-        nx.e1 = lp[ka->a.Nb > 1 ? 1 : 0];
     };
     auto step_last = [&]() {                                // (4)
         if (nx.rank < 0 || !nx.live) return;
@@ -646,7 +604,6 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         // loaded values are the same in every lane: from here on they live in scalar registers
         nx.count_raw = __builtin_amdgcn_readfirstlane(nx.count_raw);
         nx.e0 = __builtin_amdgcn_readfirstlane(nx.e0);
-        nx.e1 = __builtin_amdgcn_readfirstlane(nx.e1);
         const int m = nx.mq + (ka->a.Nb - Nbq);
         int c = nx.count_raw;
         c = c < 0 ? 0 : (c > m + 1 ? m + 1 : c);
@@ -681,12 +638,12 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     const int Nbq = g.Lq >> 7;
     int b, h, mq;
     bool have_row;
-    int pf_count = 0, pf_e0 = 0, pf_e1 = 0, pf_elast = 0;
+    int pf_count = 0, pf_e0 = 0, pf_elast = 0;
     if (kPersist) {
         if (nx.rank < 0) break;                             // the queue is empty: leave
         have_row = nx.live;
         b = nx.b; h = nx.h; mq = nx.mq;
-        pf_count = nx.count_raw; pf_e0 = nx.e0; pf_e1 = nx.e1; pf_elast = nx.elast;
+        pf_count = nx.count_raw; pf_e0 = nx.e0; pf_elast = nx.elast;
     }
     // split launches: which share of the row's block list this workgroup walks
     int part = kSplit ? (int)blockIdx.x % a.nsplit : 0;
@@ -727,11 +684,10 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
 
     Wave w;
     w.lds = lds;
-    w.qi = wv % kQWaves; w.ki = wv / kQWaves;
     w.lane = lane; w.l32 = lane & 31; w.gsel = lane >> 5;
     w.sl2 = scale_log2;
     w.init_addresses();
-    const int qi = w.qi, ki = w.ki, l32 = w.l32, gsel = w.gsel;
+    const int l32 = w.l32, gsel = w.gsel;
     const int kv = h / g.G;
     const long long row_id = ((long long)b * g.Hq + h) * Nbq + mq;
     const unsigned short* Qp = reinterpret_cast<const unsigned short*>(a.Q) + b * g.qsb + h * g.qsh;
@@ -780,258 +736,225 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         it = it < a.Nb - 1 - list_lo ? it : a.Nb - 1 - list_lo;
         return clamp_block(list ? list[it] : first + list_lo + it);
     };
-    // the entries a row needs before its first tile: the first two and the last (the persistent form has them
-    // already)
+    // the entries a row needs before its first tile: the first and the last (the persistent form has them already)
     const int e0_raw = kPersist ? clamp_block(pf_e0) : block_raw(0);
-    const int e1_raw = kPersist ? clamp_block(pf_e1) : block_raw(1);
     const int elast_raw = kPersist ? clamp_block(pf_elast) : block_raw(count > 0 ? count - 1 : 0);
     // the diagonal block, if listed, is the last entry; it is taken after the pipelined blocks
     const bool has_diag = last_part && count > 0 && __builtin_amdgcn_readfirstlane(elast_raw) == m;
     const int cnt = count - (has_diag ? 1 : 0);
 
-    // ---- Q^T operand: this lane's query, d = 16*kc + 8*gsel .. +7, for both 32-query subtiles ----
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
+    // ---- Q^T operand: this lane's query, d = 16*kc + 8*gsel .. +7 ----
+    {
         // (query rows that do not exist -- past the real length, or in front of a step that starts inside its
         // first block -- work on a copy of the nearest real row)
-        int row_in = mq * 128 + 32 * NQT * qi + 32 * qt + l32;
+        int row_in = mq * 128 + 32 * wv + l32;
         if (kRagged) row_in = max(min(row_in - g.qoff, g.Lr - g.q0 - 1), 0);
         const long long row = row_in;
 #pragma unroll
         for (int kc = 0; kc < 8; ++kc)
-            w.qf[qt][kc] = *reinterpret_cast<const bf16x8*>(Qp + row * g.qsl + 16 * kc + 8 * gsel);
+            w.qf[kc] = *reinterpret_cast<const bf16x8*>(Qp + row * g.qsl + 16 * kc + 8 * gsel);
     }
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) w.acc[dt][qt][r] = 0.f;
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) { w.mref[qt] = NEG_INF; w.lsum[qt] = 0.f; }
+        for (int r = 0; r < 16; ++r) w.acc[dt][r] = 0.f;
+    w.mref = NEG_INF;
+    w.lsum = 0.f;
 
-    f32x16 sa[NQT], sb[NQT];
-    bf16x8 pa[NQT][2], pb[NQT][2];
+    f32x16 sa, sb;
+    bf16x8 pa[2], pb[2];
+    const bool ahead = cnt > 0 && has_diag && !partial;      // the pipeline brings the diagonal block in
 
     if (cnt > 0) {
-        // Steps j = 2 i + t over the pipelined blocks i; K(i) sits in K buffer i & 1, V(i) in V
-        // buffer i & 1.  Iteration i runs phases 2i+1 and 2i+2, which use K(i+1) and V(i), and
-        // fetches K(i+2) and V(i+1) behind its barrier.  The same code also fills and drains the
-        // pipeline: iteration -1 computes S(0) and the softmax of step 0 (its PV products use a
-        // zero P against the K(0) tile, which is there and finite), iteration cnt-1 finishes the
-        // last PV products (its QK products read whatever the idle K buffer holds and are
-        // never used).
-        {
-            int n0 = __builtin_amdgcn_readfirstlane(e0_raw);
-            if (partial && n0 == m && m > 0) n0 = m - 1;    // see whole_tile below
-            st.issue_k(n0, 0);
-        }
+        // Tiles tau = 2 i + hf (half hf of the row's i-th pipelined block), steps j = 2 tau + t; K(tau) and V(tau)
+        // sit in buffers tau & 1 = hf.  Tile iteration tau runs phases 2 tau + 1 and 2 tau + 2, which use K(tau+1)
+        // and V(tau), and fetches K(tau+2) and V(tau+1) behind its barrier.  The same code also fills and drains
+        // the pipeline: iteration -1 computes S(0) and the softmax of step 0 (its PV products use a
+        // zero P against the K(0) tile, which is there and finite), iteration 2 cnt - 1 finishes the
+        // last PV products (its QK products are those of the diagonal block's first half, or of whatever the idle
+        // K buffer holds, and are then never used).
+        int n_next = __builtin_amdgcn_readfirstlane(e0_raw);     // block i + 1 of trip i
+        // A partial block m is only ever read by the diagonal pass, whose copies stay inside the real length:
+        // an entry of a malformed list that names it in the middle of the row is moved to block m - 1.
+        // Applied to the scalar copy of an entry, where it is consumed: touching the loaded value any earlier
+        // would move the wait for the list load, and with it a stall, into the middle of the iteration.
+        auto whole_tile = [&](int n) { return (partial && n == m && m > 0) ? m - 1 : n; };
+        n_next = whole_tile(n_next);
+        st.issue_k(n_next, 0, 0);
         wait_vm();
         // The Q^T operand must be complete in its registers here.  Its loads may target the accumulation
         // registers directly, and their first reader would then be an MFMA inside the tile loop: the compiler
         // places its waits for the eight loads there (vmcnt(7) .. vmcnt(0) in front of successive MFMAs), and
         // on every later trip those same waits stall on the tile copies in flight instead -- 6 % of the launch.
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt)
+        for (int kc = 0; kc < 8; ++kc) asm volatile("" : "+a"(w.qf[kc]));
 #pragma unroll
-            for (int kc = 0; kc < 8; ++kc) asm volatile("" : "+a"(w.qf[qt][kc]));
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt)
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { pa[qt][c][e] = (__bf16)0.f; pb[qt][c][e] = (__bf16)0.f; }
-        // The copies being unconditional, the pipeline fetches two entries past its last block.  With a whole
-        // diagonal tile selected those fetches are that tile (list entry cnt): its K and V are then in
-        // LDS (buffers cnt & 1) when the masked pass below starts.  Otherwise the last tile is fetched again.
-        const int last_entry = (has_diag && !partial) ? cnt : cnt - 1;
+            for (int e = 0; e < 8; ++e) { pa[c][e] = (__bf16)0.f; pb[c][e] = (__bf16)0.f; }
+        // The copies being unconditional, the pipeline fetches one block (less its second V half) past its last.
+        // With a whole diagonal block selected that is this block (list entry cnt); otherwise the last one again.
+        const int last_entry = ahead ? cnt : cnt - 1;
         auto entry_raw = [&](int it) { return block_raw(it < last_entry ? it : last_entry); };
-        // A partial block m is only ever read by the diagonal pass, whose copies stay inside the real length:
-        // an entry of a malformed list that names it in the middle of the row is moved to block m - 1.
-        // Applied to the scalar copy of an entry, where it is consumed: touching the loaded value any earlier
-        // would move the wait for the list load, and with it a stall, into the middle of the iteration.
-        auto whole_tile = [&](int n) { return (partial && n == m && m > 0) ? m - 1 : n; };
-        int n1 = whole_tile(__builtin_amdgcn_readfirstlane(e0_raw));            // list entries i+1 and i+2
-        int n2 = whole_tile(__builtin_amdgcn_readfirstlane(last_entry >= 1 ? e1_raw : e0_raw));
-        // One iteration; P = i & 1 is a compile-time constant (the loop is unrolled over it) so that every LDS
-        // offset is an immediate.  `fill` marks iteration -1, which only starts the pipeline: it computes S(0),
+        int n_cur = n_next;
+        // One tile iteration; HF is a compile-time constant so that every LDS offset is an immediate.  `fill`
+        // marks iteration -1, which only starts the pipeline: it computes S(0),
         // S(1) and the softmax of step 0; its PV products multiply whatever the idle V buffer holds and are
         // thrown away by clearing O^T afterwards.  (The fill must stay an ordinary trip of the one loop: peeled
         // off, the compiler knows O^T to be zero there, builds the accumulator tuples of the asm MFMAs from
         // copies and moves the results right behind each MFMA without the wait states an MFMA result needs.)
-        auto iteration = [&](int i, auto parity, bool fill) {
-            constexpr int P = decltype(parity)::value;
-            constexpr int KO = (P ^ 1) * kTileBytes;                       // K buffer (i + 1) & 1
-            constexpr int VO = P * kTileBytes;                             // V buffer i & 1
+        auto tile = [&](auto half, bool fill, bool more, int nv) {
+            constexpr int HF = decltype(half)::value;
+            constexpr int KO = (HF ^ 1) * kTileBytes;
+            constexpr int VO = HF * kTileBytes;
+            // phase 2 tau + 1: softmax | PV(2 tau) QK(2 tau + 2) | fetch K(tau+2) and V(tau+1)
+            phase<true, VO, KO>(w, sb, sa, pa, pb, !fill, st, st.k_src(n_next, HF), st.k_dst(HF),
+                                st.v_src(nv, HF ^ 1), st.v_dst(HF ^ 1));
+            // phase 2 tau + 2: softmax | PV(2 tau + 1) QK(2 tau + 3)
+            phase<false, VO + 32 * 256, KO + 32 * 256>(w, sa, sb, pb, pa, more, st, nullptr, 0, nullptr, 0);
+        };
+        using std::integral_constant;
+        for (int i = -1; i < cnt; ++i) {
+            if (i >= 0) {
+                __syncthreads();
+                tile(integral_constant<int, 0>{}, false, true, n_cur);
+                wait_vm();
+            }
             __syncthreads();
-            // list entry i+3, wanted at the end of this iteration: requested first, so that it is
-            // back long before the wait for the tile copies (loads complete in order)
-            const int n3_raw = entry_raw(i + 3);
-            // phase 2i+1: softmax(2i+1) | PV(2i) QK(2i+2) | fetch K(i+2) and V(i+1)
-            phase<true, VO, KO>(w, sb, sa, pa, pb, !fill, st, st.k_src(n2), st.k_dst(P),
-                                         st.v_src(n1), st.v_dst(P ^ 1));
-            // phase 2i+2: softmax(2i+2) | PV(2i+1) QK(2i+3)
-            phase<false, VO + 32 * 256, KO + 32 * 256>(w, sa, sb, pb, pa, i + 1 < cnt, st, nullptr, 0, nullptr, 0);
-            if (fill) {
+            // list entry i + 2, wanted at the end of this trip: requested in front of the tile copies, so that it
+            // is back long before the wait for them (loads complete in order)
+            const int n2_raw = entry_raw(i + 2);
+            tile(integral_constant<int, 1>{}, i < 0, i + 1 < cnt, n_next);
+            if (i < 0) {
                 mfma_settle_acc(w.acc);
 #pragma unroll
                 for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                    for (int qt = 0; qt < NQT; ++qt)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) w.acc[dt][qt][r] = 0.f;
+                    for (int r = 0; r < 16; ++r) w.acc[dt][r] = 0.f;
                 mfma_settle_acc(w.acc);
             }
             wait_vm();
-            n1 = n2;
-            n2 = whole_tile(__builtin_amdgcn_readfirstlane(n3_raw));
-        };
-        using std::integral_constant;
-        for (int i = -1; i < cnt; i += 2) {
-            iteration(i, integral_constant<int, 1>{}, i < 0);
-            if (i + 1 < cnt) iteration(i + 1, integral_constant<int, 0>{}, false);
+            n_cur = n_next;
+            n_next = whole_tile(__builtin_amdgcn_readfirstlane(n2_raw));
         }
         mfma_settle_acc(w.acc);
+        mfma_settle_s(sa);
+        mfma_settle_s(sb);
     }
 
     if (kPersist) draw_issue();                             // (1): the ticket is back when the diagonal pass is done
     if (has_diag) {
-        // ---- diagonal block: token-causal mask, no overlap ----
+        // ---- diagonal block: token-causal mask, no overlap inside the wave.  Wave w sees the 32-key steps 0 .. w,
+        // the last of them through the mask.  Half hf sits in buffers hf; after the pipeline S of the first half
+        // is in sa and sb already, and only the second half of V is still to come. ----
         __syncthreads();                                    // the pipeline is done; its last copies have landed
-        int dbuf = 0;
-        if (cnt > 0 && !partial) {
-            dbuf = cnt & 1;                                 // fetched by the last two iterations of the pipeline
+        if (ahead) {
+            st.issue_v(m, 1, 1);
         } else {
-            if (partial) {
-                st.issue_partial(st.Kp, m, st.k_dst(0), false, tile_rows, lane);
-                st.issue_partial(st.Vp, m, st.v_dst(0), true, tile_rows, lane);
-            } else {
-                st.issue_k(m, 0);
-                st.issue_v(m, 0);
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                if (partial) {
+                    st.issue_partial(st.Kp, m, hf, st.k_dst(hf), false, tile_rows, lane);
+                    st.issue_partial(st.Vp, m, hf, st.v_dst(hf), true, tile_rows, lane);
+                } else {
+                    st.issue_k(m, hf, hf);
+                    st.issue_v(m, hf, hf);
+                }
             }
             wait_vm();
             __syncthreads();
+            qk_step(w, 0, 0, sa);
+            if (wv >= 1) qk_step(w, 0, 1, sb);
         }
+        auto diag_step = [&](int j, f32x16& s) {            // 32-key step j of the block
+            if (j == wv) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int kbase = 64 * ki + 32 * t;             // first key of this wave's step, inside the block
-            const int qbase = 32 * NQT * qi;                // first query of this wave
-            if (kbase <= qbase + 32 * NQT - 1) {            // else no key of the step precedes any query of the wave
-                qk_step(w, dbuf, t, sa);
-                if (kbase + 31 > qbase) {
-#pragma unroll
-                    for (int qt = 0; qt < NQT; ++qt)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int kabs = kbase + 8 * (r >> 2) + 4 * gsel + (r & 3);
-                            if (kabs > qbase + 32 * qt + l32) sa[qt][r] = NEG_INF;
-                        }
-                }
-                float psum[NQT], mx[NQT];
-                exp_all(w, sa, pa, psum, mx);
-                finish_softmax(w, sa, pa, psum, mx);
-                pv_step(w, dbuf, t, pa);
+                for (int r = 0; r < 16; ++r)
+                    if (8 * (r >> 2) + 4 * gsel + (r & 3) > l32) s[r] = NEG_INF;
             }
+            float psum, mx;
+            exp_all(w, s, pa, psum, mx);
+            finish_softmax(w, s, pa, psum, mx);
+            pv_step(w, j >> 1, j & 1, pa);
+        };
+        diag_step(0, sa);
+        if (wv >= 1) diag_step(1, sb);
+        if (ahead) {
+            wait_vm();
+            __syncthreads();
+        }
+        if (wv >= 2) {
+            qk_step(w, 1, 0, sa);
+            diag_step(2, sa);
+        }
+        if (wv >= 3) {
+            qk_step(w, 1, 1, sb);
+            diag_step(3, sb);
         }
     }
     if (kPersist) draw_publish();
     __syncthreads();
-    if (kPersist) step_rank();                              // (2): the order entry arrives during the merge
+    if (kPersist) step_rank();                              // (2): the order entry arrives during the normalisation
 
-    // ---- merge the two key halves of every query, normalise, write ----
-    float l_tot[NQT];
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) l_tot[qt] = w.lsum[qt] + __shfl_xor(w.lsum[qt], 32);
-
-    float* xch = reinterpret_cast<float*>(lds_generic) + qi * (kXchgFloats * 64);
-    if (ki == 1) {
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int qt = 0; qt < NQT; ++qt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) xch[((dt * NQT + qt) * 16 + r) * 64 + lane] = w.acc[dt][qt][r];
-#pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) {
-            xch[(64 * NQT + qt) * 64 + lane] = w.mref[qt];
-            xch[(65 * NQT + qt) * 64 + lane] = l_tot[qt];
-        }
-    }
-    __syncthreads();
-    if (ki == 0) {
-        unsigned char* ost = lds_generic + kQWaves * kXchgFloats * 64 * 4 + qi * (32 * NQT * kOutRowBytes);
+    // ---- normalise, write ----
+    {
+        const float l = w.lsum + __shfl_xor(w.lsum, 32);
+        const float inv = l > 0.f ? 1.0f / l : 0.f;
+        unsigned char* ost = lds_generic + wv * (32 * kOutRowBytes);      // the tile buffers are free
         // row of Q / O of this wave's first query (negative in front of a step that starts inside its first
         // block), and the rows of the wave that exist: rows_lo <= x < rows_q (may be empty in the ragged form)
-        const long long wrow0 = (long long)mq * 128 + 32 * NQT * qi - (kRagged ? g.qoff : 0);
-        const int rows_q = kRagged ? (int)min((long long)(32 * NQT), (long long)(g.Lr - g.q0) - wrow0) : 32 * NQT;
+        const long long wrow0 = (long long)mq * 128 + 32 * wv - (kRagged ? g.qoff : 0);
+        const int rows_q = kRagged ? (int)min((long long)32, (long long)(g.Lr - g.q0) - wrow0) : 32;
         const int rows_lo = kRagged ? (int)max(0ll, -wrow0) : 0;
         // a split launch writes its part's result (normalised over the part's own blocks) and lse to the
         // workspace, rows contiguous; the merge kernel weighs the parts by their lse
         const long long rows_call = g.Lr - g.q0;
         float* lse_base = split ? a.part_lse + (long long)part * g.batch * g.Hq * rows_call : a.lse;
         float* lse = lse_base ? lse_base + ((long long)b * g.Hq + h) * rows_call + wrow0 : nullptr;
-        if (planned && split) lse = a.part_lse + (long long)plan_slot * 128 + 32 * NQT * qi;   // a slot holds a whole tile
+        if (planned && split) lse = a.part_lse + (long long)plan_slot * 128 + 32 * wv;   // a slot holds a whole tile
+        if (lse && gsel == 0 && l32 < rows_q && l32 >= rows_lo) lse[l32] = l > 0.f ? w.mref * 0.6931471805599453f + logf(l) : NEG_INF;
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) {
-            const float m1 = xch[(64 * NQT + qt) * 64 + lane], l1 = xch[(65 * NQT + qt) * 64 + lane];
-            const float m0 = w.mref[qt], l0 = l_tot[qt];
-            const float mm = fmaxf(m0, m1);
-            const float a0 = (m0 == NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(m0 - mm);
-            const float a1 = (m1 == NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
-            const float l = l0 * a0 + l1 * a1;
-            const float inv = l > 0.f ? 1.0f / l : 0.f;
-            const float w0 = a0 * inv, w1 = a1 * inv;
-            if (lse && gsel == 0 && 32 * qt + l32 < rows_q && 32 * qt + l32 >= rows_lo) lse[32 * qt + l32] = l > 0.f ? mm * 0.6931471805599453f + logf(l) : NEG_INF;
+        for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
+            for (int rg = 0; rg < 4; ++rg) {
+                float v[4];
 #pragma unroll
-                for (int rg = 0; rg < 4; ++rg) {
-                    float v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int r0 = 4 * rg + e;
-                        v[e] = w.acc[dt][qt][r0] * w0 + xch[((dt * NQT + qt) * 16 + r0) * 64 + lane] * w1;
+                for (int e = 0; e < 4; ++e) v[e] = w.acc[dt][4 * rg + e] * inv;
+                if (split) {
+                    // a part's result stays fp32 (the merge rounds once, at the end): straight from the
+                    // registers, 16 bytes per lane
+                    if (l32 < rows_q && l32 >= rows_lo) {
+                        float* dst = planned
+                            ? a.part_O + ((long long)plan_slot * 128 + 32 * wv + l32) * g.d + 32 * dt + 8 * rg + 4 * gsel
+                            : a.part_O + (((long long)part * g.batch * g.Hq + (long long)b * g.Hq + h) * rows_call +
+                                          wrow0 + l32) * g.d + 32 * dt + 8 * rg + 4 * gsel;
+                        *reinterpret_cast<f32x4*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
                     }
-                    if (split) {
-                        // a part's result stays fp32 (the merge rounds once, at the end): straight from the
-                        // registers, 16 bytes per lane
-                        const int q = 32 * qt + l32;
-                        if (q < rows_q && q >= rows_lo) {
-                            float* dst = planned
-                                ? a.part_O + ((long long)plan_slot * 128 + 32 * NQT * qi + q) * g.d + 32 * dt + 8 * rg + 4 * gsel
-                                : a.part_O + (((long long)part * g.batch * g.Hq + (long long)b * g.Hq + h) * rows_call +
-                                              wrow0 + q) * g.d + 32 * dt + 8 * rg + 4 * gsel;
-                            *reinterpret_cast<f32x4*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
-                        }
-                    } else {
-                        u32x2 o = {f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16),
-                                   f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16)};
-                        *reinterpret_cast<u32x2*>(ost + (32 * qt + l32) * kOutRowBytes + 2 * (32 * dt + 8 * rg + 4 * gsel)) = o;
-                    }
+                } else {
+                    u32x2 o = {f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16),
+                               f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16)};
+                    *reinterpret_cast<u32x2*>(ost + l32 * kOutRowBytes + 2 * (32 * dt + 8 * rg + 4 * gsel)) = o;
                 }
-        }
-        if (kPersist) step_row();                           // (3): the order entry came in during the merge
+            }
+        if (kPersist) step_row();                           // (3): the order entry came in during the normalisation
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         unsigned short* Op = reinterpret_cast<unsigned short*>(a.O) + b * g.qsb + h * g.qsh + wrow0 * g.qsl;
 #pragma unroll
-        for (int k = 0; k < 8 * NQT; ++k) {
+        for (int k = 0; k < 8; ++k) {
             const int idx = lane + 64 * k, row = idx >> 4, ch = idx & 15;
             const u32x2 lo = *reinterpret_cast<const u32x2*>(ost + row * kOutRowBytes + 16 * ch);
             const u32x2 hi = *reinterpret_cast<const u32x2*>(ost + row * kOutRowBytes + 16 * ch + 8);
             u32x4 o = {lo[0], lo[1], hi[0], hi[1]};
             if (!split && row < rows_q && row >= rows_lo) *reinterpret_cast<u32x4*>(Op + (long long)row * g.qsl + 8 * ch) = o;
         }
-        if (kPersist) step_last();                          // (4): count and first entries came in during the stores
-    } else if (kPersist) {
-        step_row();                                         // the waves that only handed their half over: (3), (4)
-        step_last();
+        if (kPersist) step_last();                          // (4): count and first entry came in during the stores
     }
    }  // have_row
     if (!kPersist) break;
     // what is left of the look-ahead (all of it after a rank without a row).  The barrier keeps the next row's
-    // tile copies behind this row's last reads of the exchange and staging areas.
+    // tile copies behind this row's last reads of the staging area.
     if (!have_row) { draw_issue(); draw_publish(); }
     __syncthreads();
     if (!have_row) { step_rank(); step_row(); step_last(); }
@@ -1069,10 +992,10 @@ int interleave_groups(const Geom& g) {
     return gi;
 }
 
-constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens
+constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens, see launch_attn_mfma_bf16
 
-// workgroups of a persistent launch: one per compute unit (a workgroup's tile buffers fill the LDS of one), a
-// multiple of 8 so that workgroup i sits on XCD i mod 8
+// workgroups of a persistent launch: two per compute unit, as many as it holds at once, a multiple of 8 so that
+// workgroup i sits on XCD i mod 8
 int persistent_workgroups() {
     static std::atomic<int> cached[64];                    // zero-initialised; per device, written once
     int dev = 0;
@@ -1080,7 +1003,7 @@ int persistent_workgroups() {
     int n = cached[dev].load(std::memory_order_relaxed);
     if (n == 0) {
         if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        n = n / 8 * 8;
+        n = 2 * n / 8 * 8;
         cached[dev].store(n, std::memory_order_relaxed);
     }
     return n;
@@ -1303,12 +1226,14 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     const bool ragged = g.Lr != g.L || g.qoff != 0 || a.nsplit > 1 || planned;   // split launches use the ragged instantiation
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     const long long rows = (long long)g.batch * g.Hq * (g.Lq / 128);
-    const int cus = persistent_workgroups();
-    // Persistent workgroups pay where rows are short, i.e. where the start of a row is a visible share of it:
-    // measured on the 128K workload's generator at other lengths, +15 % at 8K tokens, +9 % at 16K, +2 % at 32K,
-    // level or slightly behind from 64K on (there the launch is limited by power, not by the gaps between rows).
-    const bool persist = a.row_order != nullptr && a.queue != nullptr && cus >= 8 && a.Nb <= kPersistMaxBlocks &&
-                         a.nsplit == 1 && !planned;
+    const int resident = persistent_workgroups();
+    // Persistent workgroups pay where rows are short, i.e. where the start of a row is a visible share of it, and
+    // a workgroup takes several: measured with two workgroups per compute unit, estimate + sparse against one
+    // workgroup per row: 280 -> 274 us at 8K tokens (4 rows each), 905 -> 898 us at 18K, level at 32K (and beyond: the
+    // launch is limited by power there, not by the gaps between rows); with fewer rows than workgroups the look-ahead only
+    // costs (1139 tokens, 252 rows: 67 against 72 us).
+    const bool persist = a.row_order != nullptr && a.queue != nullptr && resident >= 8 && a.Nb <= kPersistMaxBlocks &&
+                         a.nsplit == 1 && !planned && rows >= resident;
     const unsigned grid_rows = grid_size(g, g.Lq / 128, a.row_order != nullptr);
     dim3 grid(grid_rows * (unsigned)a.nsplit + (planned ? (unsigned)a.split_budget : 0u));
     if (planned) {
@@ -1316,7 +1241,7 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
         const hipError_t pe = hipGetLastError();
         if (pe != hipSuccess) return pe;
     }
-    if (persist) grid = dim3((unsigned)(rows < cus ? (rows + 7) / 8 * 8 : cus));
+    if (persist) grid = dim3((unsigned)resident);
     const int lds_bytes = kLdsBytes + (persist ? 16 : 0);
     auto launch = [&](auto kernel) -> hipError_t {
         hipError_t e = allow_dynamic_lds((const void*)kernel, lds_bytes);
