@@ -1,12 +1,32 @@
-// Kernel group (3), generic form: causal block-sparse attention (Sec. 2.1) in fp32 on the
-// vector ALUs, for every shape the MFMA kernel does not take (fp32 tensors, d != 128, B != 128).
+// Kernel group (3), generic form: causal block-sparse attention (Sec. 2.1) on the matrix cores for every shape
+// the bf16 d = 128, B = 128 kernel does not take: fp32 tensors, any d (a multiple of 8 up to 256), any B up to 128.
 //
-// One workgroup per (batch, head, query block m).  The query block, the running output and one
-// key/value block at a time live in LDS as fp32; each of the four waves takes four query rows at
-// a time and walks them over the staged block with an online softmax: lane j scores key j (and
-// j+64) against the four rows, the wave reduces max and sum, lane c then accumulates output
-// column c (c+64, ...) of the four rows.  Token causality (j <= i) is applied inside the diagonal block only.
+// Precision.  Nothing is held in fewer than 32 bits: fp32 tensors use the fp32 matrix instructions throughout
+// (v_mfma_f32_16x16x4); bf16 tensors form the scores in one bf16 product (exact products, fp32 sums) and split every
+// probability exactly into three bf16 terms (3 x 8 of its 24 significant bits) for the product with V.
+//
+// Work split.  One workgroup per 16 QT queries of a query block; its four waves walk the row's keys 32 at a time
+// (two tiles of 16 keys, which may belong to different blocks, so that a block of 48 keys wastes nothing), wave w
+// the pairs w, w + 4, ..., each with an online softmax of its own, and meet once, in LDS, at the end.  What bounds
+// this path is the length of the longest row (the protected last one keeps every block) on the few hundred query
+// blocks of such a call: 16 queries and a quarter of the keys are the smallest piece of it that still fills a matrix
+// tile.  Fragments go from global memory (K and V of these shapes stay in L2) straight to registers: with keys
+// split over the waves no two of them would share a staged tile, and there is no barrier before the merge.
+//
+// Transposed products, S^T = K Q^T and O^T = V^T P^T: a lane owns one query (column lane % 16), and the accumulator
+// layout of S^T (keys 4 (lane / 16) + 0..3 of a tile) is the B operand of the second product.  V^T fragments need
+// consecutive keys of one channel per lane; which channel a lane's row stands for is free, so lane x = lane % 16 loads
+// W consecutive channels W x .. W x + W - 1 of each of its keys and these W values belong to W different tiles: with
+// fp32 they are the fragments as loaded, with bf16 one byte permutation per register pairs two keys.
+//
+// Measured against the form before it (one workgroup per query block, fp32 vector FMAs on operands staged in LDS, where
+// every multiply-add waited for an LDS read): fp32, 1024 tokens, 4 / 2 heads of 64: 576 -> 19 us; fp32, 4096 tokens, 8 / 2
+// heads of 128: 5954 -> 196 us (55 TFLOP/s of selected blocks); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 209 us.
+//
+// Softmax: base 2, the reference is moved only when a wave's sum of a step exceeds 2^8 (all terms of a row share it).
 #include "rr_common.hpp"
+
+#include <type_traits>
 
 namespace rr {
 
@@ -14,166 +34,434 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kRows = 4;                 // query rows a wave works on at a time
+constexpr float kLazySum = 256.0f;
 
-template <typename T>
-__global__ void __launch_bounds__(kThreads)
-k_attn_generic(Geom g, AttnArgs a, float scale) {
-    extern __shared__ __align__(16) unsigned char lds[];
+// f(W, base) for every piece of a row of 16 NT channels that a lane loads at once: W channels, lane x those from
+// base + W x on
+template <int WMAX, int NT, typename F>
+__device__ __forceinline__ void for_pieces(F&& f) {
+    using std::integral_constant;
+    constexpr int full = NT / WMAX;
+    if constexpr (full > 0) f(integral_constant<int, WMAX>{}, integral_constant<int, 0>{});
+    if constexpr (full > 1) f(integral_constant<int, WMAX>{}, integral_constant<int, 16 * WMAX>{});
+    if constexpr (full > 2) f(integral_constant<int, WMAX>{}, integral_constant<int, 32 * WMAX>{});
+    if constexpr (full > 3) f(integral_constant<int, WMAX>{}, integral_constant<int, 48 * WMAX>{});
+    static_assert(full <= 4, "at most 256 channels");
+    constexpr int r8 = WMAX * full;
+    if constexpr (WMAX > 4 && ((NT - r8) & 4)) f(integral_constant<int, 4>{}, integral_constant<int, 16 * r8>{});
+    constexpr int r4 = r8 + (WMAX > 4 ? ((NT - r8) & 4) : 0);
+    if constexpr ((NT - r4) & 2) f(integral_constant<int, 2>{}, integral_constant<int, 16 * r4>{});
+    constexpr int r2 = r4 + ((NT - r4) & 2);
+    if constexpr ((NT - r2) & 1) f(integral_constant<int, 1>{}, integral_constant<int, 16 * r2>{});
+}
+
+// Fragments of one element type for rows of up to 16 NT channels.
+//   KF   K (or Q) operand of one 16-row tile: this lane's channels of row lane % 16
+//   VF   V^T operand of one pair of tiles (32 keys): this lane's 8 keys
+template <typename T, int NT> struct Frag;
+
+template <int NT> struct Frag<float, NT> {
+    static constexpr int kW = 4;
+    f32x4 k[NT];                                     // chunk i: channels 16 i + 4 g .. +3
+    struct V { float v[8][NT]; };                    // [tile * 4 + r][channel tile]
+
+    __device__ __forceinline__ void load(const float* row, int d, int gq) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int c = 16 * i + 4 * gq;
+            if (i < NT - 1) {
+                k[i] = *reinterpret_cast<const f32x4*>(row + c);
+            } else {
+                const bool in = c < d;                // channels that do not exist are zero on both sides
+                const f32x4 v = *reinterpret_cast<const f32x4*>(row + (in ? c : 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) k[i][e] = in ? v[e] : 0.f;
+            }
+        }
+    }
+    __device__ static __forceinline__ void load_v(V& o, int key, const float* row, int d, int x) {
+        for_pieces<kW, NT>([&](auto w, auto base) {
+            constexpr int W = decltype(w)::value, B0 = decltype(base)::value;
+            const int c = min(B0 + W * x, d - W);     // channels past d are never stored
+            typedef __attribute__((ext_vector_type(W))) float vec;
+            if constexpr (W == 1) {
+                o.v[key][B0 / 16] = row[c];
+            } else {
+                const vec v = *reinterpret_cast<const vec*>(row + c);
+#pragma unroll
+                for (int e = 0; e < W; ++e) o.v[key][B0 / 16 + e] = v[e];
+            }
+        });
+    }
+    // scores of the two tiles of a pair; interleaved so that consecutive MFMAs do not depend on each other
+    template <int QT>
+    __device__ static __forceinline__ void qk(f32x4 (&s)[QT][2], const Frag (&kf)[2], const Frag (&qf)[QT]) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int u = 0; u < QT; ++u)
+                        s[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t].k[i][e], qf[u].k[i][e], s[u][t], 0, 0, 0);
+    }
+    template <int QT>
+    __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][8]) {
+#pragma unroll
+        for (int key = 0; key < 8; ++key)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int u = 0; u < QT; ++u)
+                    acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.v[key][t], p[u][key], acc[u][t], 0, 0, 0);
+    }
+};
+
+template <int NT> struct Frag<bf16_t, NT> {
+    static constexpr int kW = 8;
+    static constexpr int KC = (NT + 1) / 2;
+    u32x4 k[KC];                                     // chunk i: channels 32 i + 8 g .. +7
+    struct V { unsigned v[8][(NT + 1) / 2]; };       // [tile * 4 + r]: the channels as loaded, two to a register
+
+    __device__ __forceinline__ void load(const bf16_t* row, int d, int gq) {
+#pragma unroll
+        for (int i = 0; i < KC; ++i) {
+            const int c = 32 * i + 8 * gq;
+            if (i < KC - 1) {
+                k[i] = *reinterpret_cast<const u32x4*>(row + c);
+            } else {
+                const bool in = c < d;
+                const u32x4 v = *reinterpret_cast<const u32x4*>(row + (in ? c : 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) k[i][e] = in ? v[e] : 0u;
+            }
+        }
+    }
+    __device__ static __forceinline__ void load_v(V& o, int key, const bf16_t* row, int d, int x) {
+        for_pieces<kW, NT>([&](auto w, auto base) {
+            constexpr int W = decltype(w)::value, B0 = decltype(base)::value;
+            const int c = min(B0 + W * x, d - W);
+            if constexpr (W == 1) {
+                o.v[key][B0 / 32] = row[c].bits;
+            } else if constexpr (W == 2) {
+                o.v[key][B0 / 32] = *reinterpret_cast<const unsigned*>(row + c);
+            } else {
+                typedef __attribute__((ext_vector_type(W / 2))) unsigned vec;
+                const vec v = *reinterpret_cast<const vec*>(row + c);
+#pragma unroll
+                for (int e = 0; e < W / 2; ++e) o.v[key][B0 / 32 + e] = v[e];
+            }
+        });
+    }
+    template <int QT>
+    __device__ static __forceinline__ void qk(f32x4 (&s)[QT][2], const Frag (&kf)[2], const Frag (&qf)[QT]) {
+#pragma unroll
+        for (int i = 0; i < KC; ++i)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int u = 0; u < QT; ++u)
+                    s[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t].k[i]),
+                                                                      __builtin_bit_cast(bf16x8, qf[u].k[i]), s[u][t], 0, 0, 0);
+    }
+    template <int QT>
+    __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][8]) {
+        // p = hi + mid + lo, every term the leading 8 significant bits of what is left (truncated, so exact)
+        u32x4 plane[QT][3];
+#pragma unroll
+        for (int u = 0; u < QT; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                unsigned a = __float_as_uint(p[u][2 * j]), b = __float_as_uint(p[u][2 * j + 1]);
+                float ra = p[u][2 * j], rb = p[u][2 * j + 1];
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    plane[u][pl][j] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+                    if (pl < 2) {
+                        ra -= __uint_as_float(a & 0xFFFF0000u);
+                        rb -= __uint_as_float(b & 0xFFFF0000u);
+                        a = __float_as_uint(ra);
+                        b = __float_as_uint(rb);
+                    }
+                }
+            }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            u32x4 vt;                                // 8 keys of this lane's channel of tile t
+            const unsigned sel = (t & 1) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) vt[j] = __builtin_amdgcn_perm(v.v[2 * j + 1][t / 2], v.v[2 * j][t / 2], sel);
+            const bf16x8 vb = __builtin_bit_cast(bf16x8, vt);
+#pragma unroll
+            for (int pl = 2; pl >= 0; --pl)          // the small terms first
+#pragma unroll
+                for (int u = 0; u < QT; ++u)
+                    acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, __builtin_bit_cast(bf16x8, plane[u][pl]),
+                                                                        acc[u][t], 0, 0, 0);
+        }
+    }
+};
+
+__device__ __forceinline__ void store4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ __forceinline__ void store4(bf16_t* p, const f32x4& v) {
+    const u32x2 o = {f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16),
+                     f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16)};
+    *reinterpret_cast<u32x2*>(p) = o;
+}
+
+template <int NT> constexpr int out_pitch() { return 16 * NT + 4; }
+
+template <typename T, int NT, int QT>
+__global__ void __launch_bounds__(kThreads, NT > 8 ? 1 : 2)
+k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
+    using F = Frag<T, NT>;
+    constexpr int kQ = 16 * QT, kPitch = out_pitch<NT>();
+    __shared__ __align__(16) float s_o[kWaves][kQ][kPitch];
+    __shared__ float s_ref[kWaves][kQ], s_l[kWaves][kQ];
+
     const int B = a.B, d = g.d, Nb = a.Nb;
-    const int dk = d + 1;                                    // padded key rows: lane j reads row j
-    float* Qs = reinterpret_cast<float*>(lds);               // [B][d]
-    float* Os = Qs + B * d;                                  // [B][d]
-    float* Ks = Os + B * d;                                  // [B][d+1]
-    float* Vs = Ks + B * dk;                                 // [B][d]
-    float* Ps = Vs + B * d;                                  // [kWaves][kRows][B]
-    float* Ms = Ps + kWaves * kRows * B;                     // [B] running max
-    float* Lsum = Ms + B;                                    // [B] running denominator
-
-    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    const int t = threadIdx.x, lane = t & 63, x = lane & 15, gq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int Nbq = g.Lq / B;                         // rows of the launch (chunked prefill: the last query blocks)
-    const int m = Nb - 1 - (int)blockIdx.x;
+    // heaviest rows first (blockIdx.y), heads fastest, and of those the KV head: the XCDs, which take consecutive
+    // workgroups in turn, then each keep the keys of few KV heads in L2
+    const int m = Nb - 1 - (int)blockIdx.y;
     const int mq = m - (Nb - Nbq);
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int kv = h / g.G;
+    const int sub = (int)blockIdx.x / g.Hq, hx = (int)blockIdx.x - sub * g.Hq;
+    const int hl = hx / g.Hkv, kv = hx - hl * g.Hkv;
+    const int h = kv * g.G + hl, b = blockIdx.z;
     const long long row_id = ((long long)b * g.Hq + h) * Nbq + mq;
-    // row x of the block (position m B + x) is row mq B + x - qoff of Q and O: a step that starts inside its
+    // row y of the block (position m B + y) is row mq B + y - qoff of Q and O: a step that starts inside its
     // first block has no rows for the first qoff positions of that block
     const long long row0 = (long long)mq * B - g.qoff;
     const T* Q = reinterpret_cast<const T*>(a.Q) + b * g.qsb + h * g.qsh + row0 * g.qsl;
     const T* K = reinterpret_cast<const T*>(a.K) + b * g.ksb + kv * g.ksh;
     const T* V = reinterpret_cast<const T*>(a.V) + b * g.ksb + kv * g.ksh;
-    T* O = reinterpret_cast<T*>(a.O) + b * g.qsb + h * g.qsh + row0 * g.qsl;
     const float NEG_INF = -__builtin_huge_valf();
-    constexpr int VEC = Elem<T>::kVec;
-    const int chunks = d / VEC;
 
-    // rows that do not exist (past the real length, in front of the step) are computed on a copy of the nearest
-    // real row and not stored: the real rows of this block are x = rows_lo .. rows_q - 1 (at least one)
+    // the rows of the block that exist (at least one), and this workgroup's share of them
     const int rows_lo = mq == 0 ? g.qoff : 0;
     const int rows_q = (int)min((long long)B, (long long)(g.Lr - g.q0) - row0);
-    for (int idx = t; idx < B * chunks; idx += kThreads) {
-        const int r = idx / chunks, c = (idx - r * chunks) * VEC;
-        float v[VEC];
-        Elem<T>::load16(Q + (long long)max(min(r, rows_q - 1), rows_lo) * g.qsl + c, v);
+    const int y0 = kQ * sub;
+    if (y0 >= rows_q || y0 + kQ <= rows_lo) return;
+    const int y_last = min(y0 + kQ, rows_q) - 1;
+
+    F qf[QT];
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) { Qs[r * d + c + i] = v[i]; Os[r * d + c + i] = 0.f; }
-    }
-    for (int r = t; r < B; r += kThreads) { Ms[r] = NEG_INF; Lsum[r] = 0.f; }
+    for (int u = 0; u < QT; ++u)                      // rows that do not exist: a copy of the nearest real one, not stored
+        qf[u].load(Q + (long long)max(min(y0 + 16 * u + x, rows_q - 1), rows_lo) * g.qsl, d, gq);
 
     // a caller-made list is not trusted with addresses: count held to [0, m+1], entries to [0, m]
     int first = (!a.row_list && a.seq_first) ? a.seq_first[m] : 0;   // dense walk of packed sequences
     first = first < 0 ? 0 : (first > m ? m : first);
     int count = a.row_list ? a.row_count[row_id] : (m + 1 - first);
-    count = count < 0 ? 0 : (count > m + 1 ? m + 1 : count);
+    count = __builtin_amdgcn_readfirstlane(count < 0 ? 0 : (count > m + 1 ? m + 1 : count));
     const int32_t* list = a.row_list ? a.row_list + row_id * Nb : nullptr;
+    auto block_of = [&](int it) {
+        it = it < count ? it : count - 1;
+        const int n = list ? list[it] : first + it;
+        return n < 0 ? 0 : (n > m ? m : n);
+    };
 
-    for (int it = 0; it < count; ++it) {
-        int n = list ? list[it] : first + it;
-        n = n < 0 ? 0 : (n > m ? m : n);
-        __syncthreads();                                      // previous block fully consumed
-        for (int idx = t; idx < B * chunks; idx += kThreads) {
-            const int r = idx / chunks, c = (idx - r * chunks) * VEC;
-            float kvv[VEC], vv[VEC];
-            const long long krow = min(n * B + r, g.Lr - 1);   // keys past the real length: only in the diagonal block, masked there
-            Elem<T>::load16(K + krow * g.ksl + c, kvv);
-            Elem<T>::load16(V + krow * g.ksl + c, vv);
+    // the row's keys: tiles of 16, TB to a block; of a diagonal block at the end of the list only those a query sees
+    const int TB = (B + 15) >> 4;
+    int tiles = count * TB;
+    if (count > 0 && __builtin_amdgcn_readfirstlane(block_of(count - 1)) == m) tiles -= TB - 1 - (y_last >> 4);
+    const int pairs = (tiles + 1) >> 1;
+    const int step_it = 8 / TB, step_sub = 8 - step_it * TB;     // four pairs on
+    int it = (2 * w) / TB, ts = 2 * w - it * TB;                 // first tile of the pair: entry `it`, tile `ts` of it
+
+    f32x4 acc[QT][NT];
+    float ref[QT], lsum[QT];
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) { Ks[r * dk + c + i] = kvv[i]; Vs[r * d + c + i] = vv[i]; }
-        }
-        __syncthreads();
-        const bool diag = (n == m);
-        // four query rows at a time per wave: every key / value element read from LDS feeds four FMAs
-        float* P = Ps + w * (kRows * B);
-        for (int r0 = kRows * w; r0 < B; r0 += kRows * kWaves) {
-            float mx[kRows];
+    for (int u = 0; u < QT; ++u) {
+        ref[u] = NEG_INF;
+        lsum[u] = 0.f;
 #pragma unroll
-            for (int u = 0; u < kRows; ++u) mx[u] = NEG_INF;
-            for (int j = lane; j < B; j += 64) {
-                float s[kRows];
+        for (int c = 0; c < NT; ++c) acc[u][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    F kf[2];
+    int n[2], kk[2];                                             // block and first key inside it, of both tiles
+    auto locate = [&]() {
+        const bool wrap = ts + 1 == TB;
+        n[0] = __builtin_amdgcn_readfirstlane(block_of(it));
+        n[1] = __builtin_amdgcn_readfirstlane(block_of(wrap ? it + 1 : it));
+        kk[0] = 16 * ts;
+        kk[1] = wrap ? 0 : 16 * (ts + 1);
+    };
+    // keys past the end of a block or of the context: a copy of the last one of the block, masked
+    auto key_row = [&](int tl, int k) { return (long long)min(n[tl] * B + min(kk[tl] + k, B - 1), g.Lr - 1) * g.ksl; };
+    if (w < pairs) {
+        locate();
 #pragma unroll
-                for (int u = 0; u < kRows; ++u) s[u] = 0.f;
-                const float* k = Ks + j * dk;
-                for (int c = 0; c < d; ++c) {
-                    const float kc = k[c];
+        for (int tl = 0; tl < 2; ++tl) kf[tl].load(K + key_row(tl, x), d, gq);
+    }
+    for (int pr = w; pr < pairs; pr += kWaves) {
+        typename F::V vf;
 #pragma unroll
-                    for (int u = 0; u < kRows; ++u) s[u] = fmaf(Qs[min(r0 + u, B - 1) * d + c], kc, s[u]);
+        for (int key = 0; key < 8; ++key) F::load_v(vf, key, V + key_row(key >> 2, 4 * gq + (key & 3)), d, x);
+
+        f32x4 s[QT][2];
+#pragma unroll
+        for (int u = 0; u < QT; ++u)
+#pragma unroll
+            for (int tl = 0; tl < 2; ++tl) s[u][tl] = f32x4{0.f, 0.f, 0.f, 0.f};
+        F::template qk<QT>(s, kf, qf);
+
+        const bool lone = 2 * pr + 1 >= tiles;                   // the second tile does not exist
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+            const bool diag = n[tl] == m, none = tl == 1 && lone;
+            if (diag || kk[tl] + 16 > B || none) {
+#pragma unroll
+                for (int u = 0; u < QT; ++u) {
+                    // last key of the lane's four that its query sees: inside the block, and up to the query's own
+                    // position in the diagonal one (token causality)
+                    int last = diag ? min(B - 1, y0 + 16 * u + x) : B - 1;
+                    last = none ? -1 : last - kk[tl] - 4 * gq;
+                    f32x4 v = s[u][tl];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = r > last ? NEG_INF : v[r];
+                    s[u][tl] = v;
                 }
-#pragma unroll
-                for (int u = 0; u < kRows; ++u) {
-                    float v = s[u] * scale;
-                    if (diag && j > r0 + u) v = NEG_INF;      // token causality inside the diagonal block
-                    P[u * B + j] = v;
-                    mx[u] = fmaxf(mx[u], v);
-                }
-            }
-            float alpha[kRows];
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                const int r = min(r0 + u, B - 1);
-                mx[u] = wave_max(mx[u]);
-                const float m_old = Ms[r];
-                const float m_new = fmaxf(m_old, mx[u]);      // finite: key 0 of a block is visible to every row
-                float lsum = 0.f;
-                for (int j = lane; j < B; j += 64) {
-                    const float p = expf(P[u * B + j] - m_new);
-                    P[u * B + j] = p;
-                    lsum += p;
-                }
-                lsum = wave_sum(lsum);
-                alpha[u] = expf(m_old - m_new);               // exp(-inf) = 0 on the first block
-                if (lane == 0 && r0 + u < B) { Ms[r] = m_new; Lsum[r] = Lsum[r] * alpha[u] + lsum; }
-            }
-            for (int c = lane; c < d; c += 64) {
-                float acc[kRows];
-#pragma unroll
-                for (int u = 0; u < kRows; ++u) acc[u] = Os[min(r0 + u, B - 1) * d + c] * alpha[u];
-                for (int j = 0; j < B; ++j) {
-                    const float vj = Vs[j * d + c];
-#pragma unroll
-                    for (int u = 0; u < kRows; ++u) acc[u] = fmaf(P[u * B + j], vj, acc[u]);
-                }
-#pragma unroll
-                for (int u = 0; u < kRows; ++u)
-                    if (r0 + u < B) Os[(r0 + u) * d + c] = acc[u];
             }
         }
+        // the next pair's keys travel during the softmax and the second product
+        it += step_it;
+        ts += step_sub;
+        if (ts >= TB) { ts -= TB; ++it; }
+        if (pr + kWaves < pairs) {
+            locate();
+#pragma unroll
+            for (int tl = 0; tl < 2; ++tl) kf[tl].load(K + key_row(tl, x), d, gq);
+        }
+
+        float p[QT][8];
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            float sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                p[u][i] = __builtin_amdgcn_exp2f(fmaf(s[u][i >> 2][i & 3], scale_log2, -ref[u]));
+                sum += p[u][i];
+            }
+            // (a reference of -inf, nothing seen yet, gives inf or nan and lands here as well)
+            if (__any(!(sum <= kLazySum))) {
+                float mx = NEG_INF;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) mx = fmaxf(mx, s[u][i >> 2][i & 3]);
+                mx = fmaxf(mx, __shfl_xor(mx, 16));
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float nref = fmaxf(ref[u], mx * scale_log2);
+                const float use = nref == NEG_INF ? 0.f : nref;
+                const float alpha = __builtin_amdgcn_exp2f(ref[u] - use);       // 0 while the reference is -inf
+                ref[u] = nref;
+                lsum[u] *= alpha;
+#pragma unroll
+                for (int c = 0; c < NT; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[u][c][r] *= alpha;
+                sum = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    p[u][i] = __builtin_amdgcn_exp2f(fmaf(s[u][i >> 2][i & 3], scale_log2, -use));
+                    sum += p[u][i];
+                }
+            }
+            lsum[u] += sum;
+        }
+        F::template pv<QT>(acc, vf, p);
+    }
+
+    // ---- the four waves' shares, brought to one reference ----
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        float l = lsum[u];
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        const int q = 16 * u + x;
+        if (gq == 0) { s_ref[w][q] = ref[u]; s_l[w][q] = l; }
+        for_pieces<F::kW, NT>([&](auto wd, auto base) {
+            // accumulator row 4 g + r of tile e of a piece is channel base + W (4 g + r) + e
+            constexpr int W = decltype(wd)::value, B0 = decltype(base)::value;
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                f32x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = acc[u][B0 / 16 + (4 * i + e) % W][(4 * i + e) / W];
+                *reinterpret_cast<f32x4*>(&s_o[w][q][B0 + 4 * W * gq + 4 * i]) = o;
+            }
+        });
     }
     __syncthreads();
-    for (int idx = rows_lo * d + t; idx < rows_q * d; idx += kThreads) {
-        const int r = idx / d, c = idx - r * d;
-        const float l = Lsum[r];
-        Elem<T>::store1(O + (long long)r * g.qsl + c, l > 0.f ? Os[idx] / l : 0.f);
+    T* O = reinterpret_cast<T*>(a.O) + b * g.qsb + h * g.qsh + row0 * g.qsl;
+    float* lse = a.lse ? a.lse + ((long long)b * g.Hq + h) * (g.Lr - g.q0) + row0 : nullptr;
+    for (int idx = t; idx < kQ * 4 * NT; idx += kThreads) {
+        const int q = idx / (4 * NT), c = 4 * (idx - q * (4 * NT));
+        const int y = y0 + q;
+        float top = NEG_INF;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) top = fmaxf(top, s_ref[i][q]);
+        float l = 0.f;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+            const float f = s_ref[i][q] == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(s_ref[i][q] - top);
+            l = fmaf(f, s_l[i][q], l);
+            const f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[i][q][c]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(f, v[e], o[e]);
+        }
+        if (y >= rows_lo && y < rows_q) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = l > 0.f ? o[e] / l : 0.f;
+            if (c < d) store4(O + (long long)y * g.qsl + c, o);
+            if (lse && c == 0) lse[y] = l > 0.f ? top * 0.6931471805599453f + logf(l) : NEG_INF;
+        }
     }
-    if (a.lse) {
-        float* lse = a.lse + ((long long)b * g.Hq + h) * (g.Lr - g.q0) + row0;
-        for (int r = rows_lo + t; r < rows_q; r += kThreads) lse[r] = Lsum[r] > 0.f ? Ms[r] + logf(Lsum[r]) : NEG_INF;
-    }
-}
-
-size_t attn_generic_lds(int B, int d) {
-    return sizeof(float) * ((size_t)B * d * 3 + (size_t)B * (d + 1) + (size_t)kWaves * kRows * B + 2 * (size_t)B);
 }
 
 }  // namespace
 
-bool attn_generic_fits(int B, int d) { return attn_generic_lds(B, d) <= 150 * 1024; }
+// Shapes the entry points accept on this path: B (4 d + 19) fp32 words within 150 KB.
+bool attn_generic_fits(int B, int d) {
+    return sizeof(float) * ((size_t)B * (4 * (size_t)d + 19)) <= 150 * 1024;
+}
 
 hipError_t launch_attn_generic(const Geom& g, int dtype, const AttnArgs& a, hipStream_t st) {
-    const size_t lds = attn_generic_lds(a.B, g.d);
-    const float scale = (float)(1.0 / sqrt((double)g.d));
-    dim3 grid(g.Lq / a.B, g.Hq, g.batch);
-    hipError_t e;
-    if (dtype == RR_BF16) {
-        e = allow_dynamic_lds((const void*)k_attn_generic<bf16_t>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_attn_generic<bf16_t>, grid, dim3(kThreads), lds, st, g, a, scale);
-    } else {
-        e = allow_dynamic_lds((const void*)k_attn_generic<float>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_attn_generic<float>, grid, dim3(kThreads), lds, st, g, a, scale);
+    const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
+    auto launch = [&](auto kernel, int qt) -> hipError_t {
+        const unsigned subs = (unsigned)((a.B + 16 * qt - 1) / (16 * qt));
+        dim3 grid((unsigned)g.Hq * subs, g.Lq / a.B, g.batch);
+        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, g, a, scale_log2);
+        return hipGetLastError();
+    };
+    const int nt = (g.d + 15) / 16;
+#define RR_GENERIC_CASE(N)                                                                                        \
+    return dtype == RR_BF16 ? launch(k_attn_generic<bf16_t, N, (N > 8 ? 1 : 2)>, (N > 8 ? 1 : 2))                 \
+                            : launch(k_attn_generic<float, N, 1>, 1)
+    switch (nt) {
+        case 1: RR_GENERIC_CASE(1);
+        case 2: RR_GENERIC_CASE(2);
+        case 3: RR_GENERIC_CASE(3);
+        case 4: RR_GENERIC_CASE(4);
+        case 5: RR_GENERIC_CASE(5);
+        case 6: RR_GENERIC_CASE(6);
+        case 7: RR_GENERIC_CASE(7);
+        case 8: RR_GENERIC_CASE(8);
+        case 9: RR_GENERIC_CASE(9);
+        case 10: RR_GENERIC_CASE(10);
+        case 11: RR_GENERIC_CASE(11);
+        case 12: RR_GENERIC_CASE(12);
+        case 13: RR_GENERIC_CASE(13);
+        case 14: RR_GENERIC_CASE(14);
+        case 15: RR_GENERIC_CASE(15);
+        case 16: RR_GENERIC_CASE(16);
+        default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+#undef RR_GENERIC_CASE
 }
 
 }  // namespace rr

@@ -1,0 +1,58 @@
+"""Attention on the path for every shape that is not bf16, d = 128, B = 128: block sizes and head widths at the edges
+of its tiles (16 queries or 32, 16 keys, channels in chunks of 16 and 32), both types, lengths that end inside a
+block and inside a tile, rows with no block, one block, a block other than the diagonal one only, against the
+oracle's attention under the same mask."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+from oracle import rr_oracle as oracle
+
+pytestmark = pytest.mark.gpu
+
+# B, d: blocks shorter than a tile, one past a tile, three tiles, the largest; widths of half a chunk, of every piece of
+# a row a lane may load (16, 32, 64, 128 channels), the widest
+SHAPES = [(1, 8), (7, 8), (15, 40), (16, 24), (17, 16), (31, 56), (32, 256), (33, 136), (48, 80), (64, 64), (64, 128),
+          (128, 48), (100, 72), (24, 232), (36, 200), (40, 112)]
+
+
+def _inputs(L, Hq, Hkv, d, dtype, seed):
+    rng = np.random.default_rng(seed)
+    x = {"Q": 2.0 * rng.standard_normal((Hq, L, d)), "K": rng.standard_normal((Hkv, L, d)),
+         "V": rng.standard_normal((Hkv, L, d))}
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    return {k: torch.from_numpy(v.astype(np.float32)).to(tdt).float().numpy() for k, v in x.items()}
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,d", SHAPES)
+def test_generic_attention_matches_the_oracle(B, d, dtype):
+    import paper_2602_05853_amd as rr
+    Nb = 9
+    L = Nb * B - B // 3
+    x = _inputs(L, 4, 2, d, dtype, seed=1000 * B + d)
+    rng = np.random.default_rng(B + d)
+    mask = np.tril(rng.random((4, Nb, Nb)) < 0.5).astype(np.uint8)
+    mask[:, Nb - 1] = 1                                     # the protected last row
+    mask[1, 4] = 0                                          # a row with nothing selected
+    mask[2, 5], mask[2, 5, 5] = 0, 1                        # the diagonal block alone
+    mask[3, 6], mask[3, 6, 2] = 0, 1                        # one block, not the diagonal one
+    t = gu.to_device(x, dtype)
+    print(f"[generic] B={B} d={d} {dtype} L={L}", flush=True)
+    O = torch.full_like(t["Q"], float("nan"))
+    lse = torch.full(t["Q"].shape[:3], float("nan"), dtype=torch.float32, device="cuda:0")
+    rr.rr_sparse_attn(t["Q"], t["K"], t["V"], gu.blockmask_from_dense(mask, B), O=O, lse=lse)
+    torch.cuda.synchronize()
+    want, want_lse = oracle.sparse_attention(x["Q"], x["K"], x["V"], mask, B)
+    worst, mean = gu.attention_errors(O[0], want)
+    got_lse = lse[0].cpu().numpy()
+    empty = np.isinf(want_lse)
+    assert np.array_equal(empty, np.isneginf(got_lse))
+    lse_err = np.abs(got_lse[~empty] - want_lse[~empty]).max()
+    if dtype == "bf16":
+        assert worst <= gu.BF16_MAX_ABS and mean <= gu.BF16_MEAN_ABS
+    else:
+        assert worst <= gu.F32_MAX_ABS
+    # the scores and their sum are formed in 32 bits for both types
+    assert lse_err <= gu.F32_MAX_ABS
