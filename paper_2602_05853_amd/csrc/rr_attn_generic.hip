@@ -5,13 +5,13 @@
 // (v_mfma_f32_16x16x4); bf16 tensors form the scores in one bf16 product (exact products, fp32 sums) and split every
 // probability exactly into three bf16 terms (3 x 8 of its 24 significant bits) for the product with V.
 //
-// Work split.  One workgroup per 16 QT queries of a query block; its four waves walk the row's keys 32 at a time
-// (two tiles of 16 keys, which may belong to different blocks, so that a block of 48 keys wastes nothing), wave w
-// the pairs w, w + 4, ..., each with an online softmax of its own, and meet once, in LDS, at the end.  What bounds
-// this path is the length of the longest row (the protected last one keeps every block) on the few hundred query
-// blocks of such a call: 16 queries and a quarter of the keys are the smallest piece of it that still fills a matrix
-// tile.  Fragments go from global memory (K and V of these shapes stay in L2) straight to registers: with keys
-// split over the waves no two of them would share a staged tile, and there is no barrier before the merge.
+// Work split.  One workgroup per 16 QT queries of a query block; its KW waves walk the row's keys in steps of one or two
+// tiles of 16 keys (which may belong to different blocks, so that a block of 48 keys wastes nothing), wave w the
+// steps w, w + KW, ..., each with an online softmax of its own, and meet once, in LDS, at the end.  What bounds this
+// path is the length of the longest row (the protected last one keeps every block) on the few hundred query blocks
+// of such a call, and the traffic between L2 and the compute units (launch_attn_generic chooses QT for both).
+// Fragments go from global memory (K and V of these shapes stay in L2) straight to registers: with keys split over
+// the waves no two of them would share a staged tile, and there is no barrier before the merge.
 //
 // Transposed products, S^T = K Q^T and O^T = V^T P^T: a lane owns one query (column lane % 16), and the accumulator
 // layout of S^T (keys 4 (lane / 16) + 0..3 of a tile) is the B operand of the second product.  V^T fragments need
@@ -21,7 +21,7 @@
 //
 // Measured against the form before it (one workgroup per query block, fp32 vector FMAs on operands staged in LDS, where
 // every multiply-add waited for an LDS read): fp32, 1024 tokens, 4 / 2 heads of 64: 576 -> 19 us; fp32, 4096 tokens, 8 / 2
-// heads of 128: 5954 -> 196 us (55 TFLOP/s of selected blocks); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 209 us.
+// heads of 128: 5954 -> 174 us (62 TFLOP/s of selected blocks); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 183 us.
 //
 // Softmax: base 2, the reference is moved only when a wave's sum of a step exceeds 2^8 (all terms of a row share it).
 #include "rr_common.hpp"
@@ -32,8 +32,6 @@ namespace rr {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
 constexpr float kLazySum = 256.0f;
 
 // f(W, base) for every piece of a row of 16 NT channels that a lane loads at once: W channels, lane x those from
@@ -58,12 +56,12 @@ __device__ __forceinline__ void for_pieces(F&& f) {
 // Fragments of one element type for rows of up to 16 NT channels.
 //   KF   K (or Q) operand of one 16-row tile: this lane's channels of row lane % 16
 //   VF   V^T operand of one pair of tiles (32 keys): this lane's 8 keys
-template <typename T, int NT> struct Frag;
+template <typename T, int NT, int TL> struct Frag;
 
-template <int NT> struct Frag<float, NT> {
+template <int NT, int TL> struct Frag<float, NT, TL> {
     static constexpr int kW = 4;
     f32x4 k[NT];                                     // chunk i: channels 16 i + 4 g .. +3
-    struct V { float v[8][NT]; };                    // [tile * 4 + r][channel tile]
+    struct V { float v[4 * TL][NT]; };                    // [tile * 4 + r][channel tile]
 
     __device__ __forceinline__ void load(const float* row, int d, int gq) {
 #pragma unroll
@@ -95,21 +93,21 @@ template <int NT> struct Frag<float, NT> {
     }
     // scores of the two tiles of a pair; interleaved so that consecutive MFMAs do not depend on each other
     template <int QT>
-    __device__ static __forceinline__ void qk(f32x4 (&s)[QT][2], const Frag (&kf)[2], const Frag (&qf)[QT]) {
+    __device__ static __forceinline__ void qk(f32x4 (&s)[QT][TL], const Frag (&kf)[TL], const Frag (&qf)[QT]) {
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < TL; ++t)
 #pragma unroll
                     for (int u = 0; u < QT; ++u)
                         s[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t].k[i][e], qf[u].k[i][e], s[u][t], 0, 0, 0);
     }
     template <int QT>
-    __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][8]) {
+    __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][4 * TL]) {
 #pragma unroll
-        for (int key = 0; key < 8; ++key)
+        for (int key = 0; key < 4 * TL; ++key)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -118,7 +116,8 @@ template <int NT> struct Frag<float, NT> {
     }
 };
 
-template <int NT> struct Frag<bf16_t, NT> {
+template <int NT, int TL> struct Frag<bf16_t, NT, TL> {
+    static_assert(TL == 2, "the second product takes 32 keys");
     static constexpr int kW = 8;
     static constexpr int KC = (NT + 1) / 2;
     u32x4 k[KC];                                     // chunk i: channels 32 i + 8 g .. +7
@@ -155,18 +154,18 @@ template <int NT> struct Frag<bf16_t, NT> {
         });
     }
     template <int QT>
-    __device__ static __forceinline__ void qk(f32x4 (&s)[QT][2], const Frag (&kf)[2], const Frag (&qf)[QT]) {
+    __device__ static __forceinline__ void qk(f32x4 (&s)[QT][TL], const Frag (&kf)[TL], const Frag (&qf)[QT]) {
 #pragma unroll
         for (int i = 0; i < KC; ++i)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < TL; ++t)
 #pragma unroll
                 for (int u = 0; u < QT; ++u)
                     s[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t].k[i]),
                                                                       __builtin_bit_cast(bf16x8, qf[u].k[i]), s[u][t], 0, 0, 0);
     }
     template <int QT>
-    __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][8]) {
+    __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][4 * TL]) {
         // p = hi + mid + lo, every term the leading 8 significant bits of what is left (truncated, so exact)
         u32x4 plane[QT][3];
 #pragma unroll
@@ -212,13 +211,19 @@ __device__ __forceinline__ void store4(bf16_t* p, const f32x4& v) {
 
 template <int NT> constexpr int out_pitch() { return 16 * NT + 4; }
 
-template <typename T, int NT, int QT>
-__global__ void __launch_bounds__(kThreads, NT > 8 ? 1 : 2)
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) int32_t* scalar_list_t;   // read with scalar loads
+#else
+typedef const int32_t* scalar_list_t;                                    // the host pass only parses the kernel
+#endif
+
+template <typename T, int NT, int QT, int TL, int KW, int OCC>
+__global__ void __launch_bounds__(64 * KW, OCC)
 k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
-    using F = Frag<T, NT>;
-    constexpr int kQ = 16 * QT, kPitch = out_pitch<NT>();
-    __shared__ __align__(16) float s_o[kWaves][kQ][kPitch];
-    __shared__ float s_ref[kWaves][kQ], s_l[kWaves][kQ];
+    using F = Frag<T, NT, TL>;
+    constexpr int kQ = 16 * QT, kPitch = out_pitch<NT>(), kThreads = 64 * KW;
+    __shared__ __align__(16) float s_o[KW][kQ][kPitch];
+    __shared__ float s_ref[KW][kQ], s_l[KW][kQ];
 
     const int B = a.B, d = g.d, Nb = a.Nb;
     const int t = threadIdx.x, lane = t & 63, x = lane & 15, gq = lane >> 4;
@@ -257,20 +262,20 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
     first = first < 0 ? 0 : (first > m ? m : first);
     int count = a.row_list ? a.row_count[row_id] : (m + 1 - first);
     count = __builtin_amdgcn_readfirstlane(count < 0 ? 0 : (count > m + 1 ? m + 1 : count));
-    const int32_t* list = a.row_list ? a.row_list + row_id * Nb : nullptr;
-    auto block_of = [&](int it) {
-        it = it < count ? it : count - 1;
-        const int n = list ? list[it] : first + it;
-        return n < 0 ? 0 : (n > m ? m : n);
+    const scalar_list_t list = (scalar_list_t)(a.row_list ? a.row_list + row_id * Nb : nullptr);
+    auto entry = [&](int i) {                                    // as loaded
+        i = i < count ? i : count - 1;
+        return list ? list[i] : first + i;
     };
+    auto clamp_block = [&](int n) { return n < 0 ? 0 : (n > m ? m : n); };
 
     // the row's keys: tiles of 16, TB to a block; of a diagonal block at the end of the list only those a query sees
     const int TB = (B + 15) >> 4;
     int tiles = count * TB;
-    if (count > 0 && __builtin_amdgcn_readfirstlane(block_of(count - 1)) == m) tiles -= TB - 1 - (y_last >> 4);
-    const int pairs = (tiles + 1) >> 1;
-    const int step_it = 8 / TB, step_sub = 8 - step_it * TB;     // four pairs on
-    int it = (2 * w) / TB, ts = 2 * w - it * TB;                 // first tile of the pair: entry `it`, tile `ts` of it
+    if (count > 0 && clamp_block(entry(count - 1)) == m) tiles -= TB - 1 - (y_last >> 4);
+    const int steps = (tiles + TL - 1) / TL;
+    const int step_it = (TL * KW) / TB, step_sub = TL * KW - step_it * TB;   // KW steps on
+    int it = (TL * w) / TB, ts = TL * w - it * TB;               // first tile of the step: entry `it`, tile `ts` of it
 
     f32x4 acc[QT][NT];
     float ref[QT], lsum[QT];
@@ -282,38 +287,66 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
         for (int c = 0; c < NT; ++c) acc[u][c] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    F kf[2];
-    int n[2], kk[2];                                             // block and first key inside it, of both tiles
-    auto locate = [&]() {
-        const bool wrap = ts + 1 == TB;
-        n[0] = __builtin_amdgcn_readfirstlane(block_of(it));
-        n[1] = __builtin_amdgcn_readfirstlane(block_of(wrap ? it + 1 : it));
-        kk[0] = 16 * ts;
-        kk[1] = wrap ? 0 : 16 * (ts + 1);
-    };
-    // keys past the end of a block or of the context: a copy of the last one of the block, masked
-    auto key_row = [&](int tl, int k) { return (long long)min(n[tl] * B + min(kk[tl] + k, B - 1), g.Lr - 1) * g.ksl; };
-    if (w < pairs) {
-        locate();
+    // Rows of a tile this lane reads, relative to its first key: row x of K, rows 4 g .. +3 of V.  Keys past the end of
+    // the block or of the context are read as a copy of its last one, and masked.
+    long long k_off = (long long)x * g.ksl, v_off[4];
 #pragma unroll
-        for (int tl = 0; tl < 2; ++tl) kf[tl].load(K + key_row(tl, x), d, gq);
+    for (int r = 0; r < 4; ++r) v_off[r] = (long long)(4 * gq + r) * g.ksl;
+    F kf[TL];
+    int n[TL], kk[TL], n_next[TL];                               // block and first key inside it; entries of the next step
+    auto request = [&]() {                                       // the entries of the step at (it, ts)
+#pragma unroll
+        for (int tl = 0; tl < TL; ++tl) n_next[tl] = entry(ts + tl >= TB ? it + 1 : it);
+    };
+    auto advance = [&]() {
+        it += step_it;
+        ts += step_sub;
+        if (ts >= TB) { ts -= TB; ++it; }
+    };
+    auto last_key = [&](int tl) { return min(B - 1 - kk[tl], g.Lr - 1 - n[tl] * B - kk[tl]); };   // of the tile, if < 15
+    auto load_keys = [&]() {                                     // the entries of (it, ts) are in n_next
+#pragma unroll
+        for (int tl = 0; tl < TL; ++tl) {
+            n[tl] = clamp_block(n_next[tl]);
+            kk[tl] = 16 * (ts + tl >= TB ? ts + tl - TB : ts + tl);
+            const T* base = K + (long long)(n[tl] * B + kk[tl]) * g.ksl;
+            const int last = last_key(tl);
+            long long off = k_off;
+            if (last < 15) off = (long long)min(x, last) * g.ksl;
+            kf[tl].load(base + off, d, gq);
+        }
+    };
+    if (w < steps) {
+        request();
+        load_keys();
+        advance();
+        request();
     }
-    for (int pr = w; pr < pairs; pr += kWaves) {
+    for (int st = w; st < steps; st += KW) {
         typename F::V vf;
 #pragma unroll
-        for (int key = 0; key < 8; ++key) F::load_v(vf, key, V + key_row(key >> 2, 4 * gq + (key & 3)), d, x);
+        for (int tl = 0; tl < TL; ++tl) {
+            const T* base = V + (long long)(n[tl] * B + kk[tl]) * g.ksl;
+            const int last = last_key(tl);
+            if (last < 15) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) F::load_v(vf, 4 * tl + r, base + (long long)min(4 * gq + r, last) * g.ksl, d, x);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) F::load_v(vf, 4 * tl + r, base + v_off[r], d, x);
+            }
+        }
 
-        f32x4 s[QT][2];
+        f32x4 s[QT][TL];
 #pragma unroll
         for (int u = 0; u < QT; ++u)
 #pragma unroll
-            for (int tl = 0; tl < 2; ++tl) s[u][tl] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int tl = 0; tl < TL; ++tl) s[u][tl] = f32x4{0.f, 0.f, 0.f, 0.f};
         F::template qk<QT>(s, kf, qf);
 
-        const bool lone = 2 * pr + 1 >= tiles;                   // the second tile does not exist
 #pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
-            const bool diag = n[tl] == m, none = tl == 1 && lone;
+        for (int tl = 0; tl < TL; ++tl) {
+            const bool diag = n[tl] == m, none = TL * st + tl >= tiles;      // (a tile past the last one)
             if (diag || kk[tl] + 16 > B || none) {
 #pragma unroll
                 for (int u = 0; u < QT; ++u) {
@@ -328,22 +361,20 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
                 }
             }
         }
-        // the next pair's keys travel during the softmax and the second product
-        it += step_it;
-        ts += step_sub;
-        if (ts >= TB) { ts -= TB; ++it; }
-        if (pr + kWaves < pairs) {
-            locate();
-#pragma unroll
-            for (int tl = 0; tl < 2; ++tl) kf[tl].load(K + key_row(tl, x), d, gq);
+        // the next step's keys travel during the softmax and the second product, the entries of the one after it
+        // through all of the next step
+        if (st + KW < steps) {
+            load_keys();
+            advance();
+            request();
         }
 
-        float p[QT][8];
+        float p[QT][4 * TL];
 #pragma unroll
         for (int u = 0; u < QT; ++u) {
             float sum = 0.f;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < 4 * TL; ++i) {
                 p[u][i] = __builtin_amdgcn_exp2f(fmaf(s[u][i >> 2][i & 3], scale_log2, -ref[u]));
                 sum += p[u][i];
             }
@@ -351,7 +382,7 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
             if (__any(!(sum <= kLazySum))) {
                 float mx = NEG_INF;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) mx = fmaxf(mx, s[u][i >> 2][i & 3]);
+                for (int i = 0; i < 4 * TL; ++i) mx = fmaxf(mx, s[u][i >> 2][i & 3]);
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 const float nref = fmaxf(ref[u], mx * scale_log2);
@@ -365,7 +396,7 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
                     for (int r = 0; r < 4; ++r) acc[u][c][r] *= alpha;
                 sum = 0.f;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
+                for (int i = 0; i < 4 * TL; ++i) {
                     p[u][i] = __builtin_amdgcn_exp2f(fmaf(s[u][i >> 2][i & 3], scale_log2, -use));
                     sum += p[u][i];
                 }
@@ -375,7 +406,7 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
         F::template pv<QT>(acc, vf, p);
     }
 
-    // ---- the four waves' shares, brought to one reference ----
+    // ---- the waves' shares, brought to one reference ----
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
         float l = lsum[u];
@@ -403,11 +434,11 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
         const int y = y0 + q;
         float top = NEG_INF;
 #pragma unroll
-        for (int i = 0; i < kWaves; ++i) top = fmaxf(top, s_ref[i][q]);
+        for (int i = 0; i < KW; ++i) top = fmaxf(top, s_ref[i][q]);
         float l = 0.f;
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < kWaves; ++i) {
+        for (int i = 0; i < KW; ++i) {
             const float f = s_ref[i][q] == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(s_ref[i][q] - top);
             l = fmaf(f, s_l[i][q], l);
             const f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[i][q][c]);
@@ -432,36 +463,46 @@ bool attn_generic_fits(int B, int d) {
 
 hipError_t launch_attn_generic(const Geom& g, int dtype, const AttnArgs& a, hipStream_t st) {
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
-    auto launch = [&](auto kernel, int qt) -> hipError_t {
-        const unsigned subs = (unsigned)((a.B + 16 * qt - 1) / (16 * qt));
+    auto launch = [&](auto kernel, int queries, int waves) -> hipError_t {
+        const unsigned subs = (unsigned)((a.B + queries - 1) / queries);
         dim3 grid((unsigned)g.Hq * subs, g.Lq / a.B, g.batch);
-        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, g, a, scale_log2);
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, st, g, a, scale_log2);
         return hipGetLastError();
     };
-    const int nt = (g.d + 15) / 16;
-#define RR_GENERIC_CASE(N)                                                                                        \
-    return dtype == RR_BF16 ? launch(k_attn_generic<bf16_t, N, (N > 8 ? 1 : 2)>, (N > 8 ? 1 : 2))                 \
-                            : launch(k_attn_generic<float, N, 1>, 1)
-    switch (nt) {
-        case 1: RR_GENERIC_CASE(1);
-        case 2: RR_GENERIC_CASE(2);
-        case 3: RR_GENERIC_CASE(3);
-        case 4: RR_GENERIC_CASE(4);
-        case 5: RR_GENERIC_CASE(5);
-        case 6: RR_GENERIC_CASE(6);
-        case 7: RR_GENERIC_CASE(7);
-        case 8: RR_GENERIC_CASE(8);
-        case 9: RR_GENERIC_CASE(9);
-        case 10: RR_GENERIC_CASE(10);
-        case 11: RR_GENERIC_CASE(11);
-        case 12: RR_GENERIC_CASE(12);
-        case 13: RR_GENERIC_CASE(13);
-        case 14: RR_GENERIC_CASE(14);
-        case 15: RR_GENERIC_CASE(15);
-        case 16: RR_GENERIC_CASE(16);
+    // Queries per workgroup.  What a workgroup reads of K and V serves its queries only, and the kernel's reads of L2 are
+    // its limit on long launches (10-12 TB/s with 16 queries a workgroup); but a row's keys are one workgroup's
+    // work, and the longest row (the protected last one keeps every block) should not outlast the rest.  So: few
+    // queries where the launch has fewer such workgroups than fill the chip twice, more where it has more.  Measured:
+    // fp32, 4096 tokens, 8 heads of 128: 16 queries on four waves 183 us, 32 on eight 176 (dense, 32 heads: 1.80 and
+    // 1.51 ms); fp32, 1024 tokens, 4 heads of 64: 19 and 26 us; bf16, 8153 tokens, 16 heads of 64: 32 queries 211 us,
+    // 64 queries 182 us (dense 439 and 358 us; wider heads have no registers for 64).
+    const long long rows = (long long)g.batch * g.Hq * (g.Lq / a.B);
+    auto blocks = [&](int queries) { return rows * ((a.B + queries - 1) / queries); };
+    auto pick = [&](auto tiles) -> hipError_t {
+        constexpr int N = decltype(tiles)::value;
+        if constexpr (N > 8) {
+            return dtype == RR_BF16 ? launch(k_attn_generic<bf16_t, N, 1, 2, 4, 1>, 16, 4)
+                                    : launch(k_attn_generic<float, N, 1, 1, 4, 1>, 16, 4);
+        } else {
+            if (dtype == RR_BF16) {
+                if constexpr (N <= 4)
+                    if (a.B > 32 && blocks(64) >= 512) return launch(k_attn_generic<bf16_t, N, 4, 2, 4, 2>, 64, 4);
+                return launch(k_attn_generic<bf16_t, N, 2, 2, 4, 2>, 32, 4);
+            }
+            if (a.B > 16 && blocks(32) >= 512) return launch(k_attn_generic<float, N, 2, 1, 8, 2>, 32, 8);
+            return launch(k_attn_generic<float, N, 1, 1, 8, 2>, 16, 8);
+        }
+    };
+    using std::integral_constant;
+    switch ((g.d + 15) / 16) {
+#define RR_GENERIC_CASE(N) case N: return pick(integral_constant<int, N>{})
+        RR_GENERIC_CASE(1); RR_GENERIC_CASE(2); RR_GENERIC_CASE(3); RR_GENERIC_CASE(4);
+        RR_GENERIC_CASE(5); RR_GENERIC_CASE(6); RR_GENERIC_CASE(7); RR_GENERIC_CASE(8);
+        RR_GENERIC_CASE(9); RR_GENERIC_CASE(10); RR_GENERIC_CASE(11); RR_GENERIC_CASE(12);
+        RR_GENERIC_CASE(13); RR_GENERIC_CASE(14); RR_GENERIC_CASE(15); RR_GENERIC_CASE(16);
+#undef RR_GENERIC_CASE
         default: return hipErrorInvalidValue;
     }
-#undef RR_GENERIC_CASE
 }
 
 }  // namespace rr

@@ -25,15 +25,18 @@ def _inputs(L, Hq, Hkv, d, dtype, seed):
     return {k: torch.from_numpy(v.astype(np.float32)).to(tdt).float().numpy() for k, v in x.items()}
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("B,d", SHAPES)
-def test_generic_attention_matches_the_oracle(B, d, dtype):
+# launches of 512 workgroups and more: more queries to a workgroup (64 for narrow bf16 heads, 32 for fp32)
+LARGE = [(40, 64, "bf16"), (64, 40, "bf16"), (128, 16, "bf16"), (48, 72, "bf16"), (33, 128, "f32"), (64, 24, "f32")]
+
+
+@pytest.mark.parametrize("B,d,dtype,Hq,Nb", [(B, d, t, 4, 9) for B, d in SHAPES for t in ("bf16", "f32")] +
+                         [(B, d, t, 16, 33) for B, d, t in LARGE])
+def test_generic_attention_matches_the_oracle(B, d, dtype, Hq, Nb):
     import paper_2602_05853_amd as rr
-    Nb = 9
     L = Nb * B - B // 3
-    x = _inputs(L, 4, 2, d, dtype, seed=1000 * B + d)
+    x = _inputs(L, Hq, Hq // 2, d, dtype, seed=1000 * B + d)
     rng = np.random.default_rng(B + d)
-    mask = np.tril(rng.random((4, Nb, Nb)) < 0.5).astype(np.uint8)
+    mask = np.tril(rng.random((Hq, Nb, Nb)) < 0.5).astype(np.uint8)
     mask[:, Nb - 1] = 1                                     # the protected last row
     mask[1, 4] = 0                                          # a row with nothing selected
     mask[2, 5], mask[2, 5, 5] = 0, 1                        # the diagonal block alone
