@@ -224,7 +224,19 @@ k_estimate_generic(Geom g, EstimateArgs a, EstPlan p, float scale) {
         r.dense = a.dense ? a.dense + row_id * Nb : nullptr;
         r.list = a.row_list + row_id * Nb;
         r.count = a.row_count + row_id;
-        select_row_wave(RowInLds(frac, nlo, m, t), r, t);
+        if (Nb <= 256) {                               // in registers: the bisection reads the row some twenty times
+            RowInRegs<4> row;
+            row.c0 = nlo >> 6;
+            row.c1 = (m >> 6) + 1;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int n = 64 * c + t;
+                row.v[c] = (n >= nlo && n <= m) ? frac[n] : 0.f;
+            }
+            select_row_wave(row, r, t);
+        } else {
+            select_row_wave(RowInLds(frac, nlo, m, t), r, t);
+        }
     }
 }
 
@@ -274,6 +286,8 @@ k_select_rows(Geom g, EstimateArgs a, const float* __restrict__ mass, long long 
     if (NCH > 0) {
         // the row fits in registers: 64 * NCH >= Nb
         RowInRegs<(NCH > 0 ? NCH : 1)> row;
+        row.c0 = __builtin_amdgcn_readfirstlane(nlo) >> 6;
+        row.c1 = (__builtin_amdgcn_readfirstlane(m) >> 6) + 1;
         float part = 0.f;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
