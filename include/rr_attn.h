@@ -285,11 +285,11 @@ int rr_dense_attn_packed(const rr_shape* shape, const void* Q, const void* K, co
  * softmax attention over its share with its own log-sum-exp, and a second kernel merges the shares (Sec. 2.1:
  * the softmax is one sum over the selected keys, so shares combine by their log-sum-exp).  The shares are kept
  * in fp32 and the result is rounded once: it agrees with the one-workgroup-per-row form to the rounding of the
- * tensor type, not bit for bit (the sums are taken in another order).  A step of one or two positions with at
- * most 8 query rows per KV head (the decode stage the paper's "Future Work" names; its experiments decode
- * densely, Sec. 4.1) runs on a kernel of its own: a workgroup reads a range of key blocks of ONE KV head once
- * and serves all its query heads from it (sparse: the union of their lists, every row skipping what it did not
- * select), without matrix instructions; same workspace, same merge, same agreement.
+ * tensor type, not bit for bit (the sums are taken in another order).  A step with at most 32
+ * query rows per KV head (the decode stage the paper's "Future Work" names; its experiments decode densely, Sec. 4.1),
+ * deep in the context or of one or two positions and at most 8 rows, runs on a kernel of its own: a workgroup reads a
+ * range of key blocks of ONE KV head once and serves all its query heads from it (sparse: the union of their lists, every
+ * row skipping what it did not select); same workspace, same merge, same agreement.
  * A chunk of a long prompt (several query blocks per head against a context of 128 blocks or more, at most 4096
  * rows) has many short rows and a few nearly as long as the context, and an unsplit launch takes as long as its
  * longest row: with a workspace a small kernel first plans, from the row counts, which rows are cut into parts of

@@ -122,7 +122,7 @@ int run_attn(const rr_shape* shape, const void* Q, const void* K, const void* V,
     a.plan_cut = nullptr;
     bool decode = false;
     if (workspace && use_mfma_attn(g, shape->dtype, B) && !seq_first && attn_decode_parts(g, B) >= 1) {
-        // one or two new positions: the kernel that reads K and V once per KV head for all its query heads
+        // few query rows per KV head: the kernel that reads K and V once per KV head for all its query heads
         const size_t need = attn_decode_bytes(g, B);
         if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return RR_ERR_WORKSPACE;
         a.nsplit = attn_decode_parts(g, B);

@@ -1,27 +1,33 @@
-// Attention of a very short step (one or two new tokens) against a long context: the decode-stage use of the
-// path (the paper's "Future Work"; its experiments decode densely, Sec. 4.1).  bf16, d = 128, B = 128.
+// Attention of a short step (one token or a few) against a long context: the decode-stage use of the path (the paper's
+// "Future Work"; its experiments decode densely, Sec. 4.1).  bf16, d = 128, B = 128, up to 32 query rows per KV head.
 //
-// Such a step has G * T query rows per KV head (T tokens, G query heads), far too few for a 128-row matrix tile,
-// and its cost is reading K and V once.  So: no matrix instructions, no LDS staging.  One workgroup takes a
-// range of key blocks of ONE KV head and serves all G * T rows from the same loaded keys (the GQA sharing);
-// a wavefront reads four keys per load instruction (16 lanes x 16 bytes = one key row), every lane keeps the
-// 8 channels of its chunk, the dot products are finished with butterflies inside the 16 lanes (DPP).  Each
-// group of 16 lanes runs its own online softmax over the keys it sees; the 16 streams of a workgroup are merged
-// at the end and the part's normalised output and log-sum-exp go to the workspace.  A second kernel merges the
-// parts (the softmax over the selected keys is one sum, Sec. 2.1, so parts combine exactly up to rounding).
+// Such a step has G * T query rows per KV head (T tokens, G query heads), too few for a 128-row matrix tile, and its
+// cost is reading K and V once.  One workgroup takes a range of key blocks of ONE KV head and serves all G T rows from
+// the same keys (the GQA sharing): the rows are the columns of one or two 16 x 16 matrix tiles, the scores one bf16
+// product (exact products, fp32 sums), the probabilities split exactly into three bf16 terms for the product with V, so
+// that nothing is held in fewer than 32 bits and no row costs vector work per key but its exponential.  Wave w takes keys
+// 32 w .. +31 of every block of the range, straight from memory to registers, its next keys requested before the softmax
+// of the present ones; each wave runs its own online softmax, the four are merged at the end and the part's normalised
+// output and log-sum-exp go to the workspace.  A second kernel merges the parts (the softmax over the selected keys is
+// one sum, Sec. 2.1, so parts combine exactly up to rounding).
 //
 // Sparse steps walk the union of the rows' block lists: a key block is loaded when any row of the KV head
 // selected it, and a row skips the blocks it did not select (its scores are masked), so every row still sees
 // exactly the blocks of its own list.
-#include "rr_common.hpp"
+//
+// What bounds it: the stream of K and V.  Measured, dense, against fp32 vector dot products on the same split (up to 8 rows,
+// 16 lanes to a key) and, above 8 rows, a 128-row tile per query head and key range (which reads K and V once per
+// query head): 128K tokens, 32 / 8 heads, one token 112 -> 101 us (5.3 TB/s), two 176 -> 105; 64 / 8 heads, one token 175 ->
+// 104; 28 / 4 heads, one token 98 -> 56, four 286 -> 61; 16K tokens, one token 27 -> 23; 64K, 8 tokens 143 -> 54.
+#include "rr_attn_frag.hpp"
 
 namespace rr {
 
 namespace {
 
 constexpr int kDecThreads = 256;
-constexpr int kDecMaxRows = 8;          // G * T
-constexpr int kDecMaxTokens = 2;
+constexpr int kDecMaxRows = 32;         // G * T
+constexpr int kDecMaxLen = 1024;        // key blocks a part may have
 constexpr int kDecMaxParts = 256;
 constexpr int kDecBlock = 128;
 
@@ -33,256 +39,176 @@ struct DecodeArgs {
     float scale_log2;   // log2(e) / sqrt(d)
 };
 
-template <int CTRL>
-__device__ __forceinline__ float dec_dpp(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-// sum over the 16 lanes of a DPP row; every lane gets it
-__device__ __forceinline__ float row16_sum(float v) {
-    v += dec_dpp<0xB1>(v);      // quad_perm [1,0,3,2]
-    v += dec_dpp<0x4E>(v);      // quad_perm [2,3,0,1]
-    v += dec_dpp<0x141>(v);     // row_half_mirror
-    v += dec_dpp<0x140>(v);     // row_mirror
-    return v;
-}
-
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-
-// 8-channel dot product of two packed bf16 chunks, fp32 accumulation (v_dot2c_f32_bf16).  The pairs are taken
-// from the whole vector with shuffles: bit-casting single 32-bit elements picked by a loop index made the
-// compiler use the first pair four times.
-__device__ __forceinline__ float dot8(const bf16x8& a, const bf16x8& b) {
-    float s = 0.f;
-    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 0, 1), __builtin_shufflevector(b, b, 0, 1), s, false);
-    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 2, 3), __builtin_shufflevector(b, b, 2, 3), s, false);
-    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 4, 5), __builtin_shufflevector(b, b, 4, 5), s, false);
-    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 6, 7), __builtin_shufflevector(b, b, 6, 7), s, false);
-    return s;
-}
-
-__device__ __forceinline__ void unpack8(const u32x4& x, float (&f)[8]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        f[2 * i] = __uint_as_float(x[i] << 16);
-        f[2 * i + 1] = __uint_as_float(x[i] & 0xFFFF0000u);
-    }
-}
-
-// RM: rows the instantiation carries (the smallest of 1, 2, 4, 8 that holds G * T); rows beyond G * T repeat row
-// 0 and are never stored.
-template <int RM>
+// QT: 16-column tiles of query rows, for G T <= 16 or 32; columns beyond G T repeat the last row and are never stored.
+template <int QT>
 __global__ void __launch_bounds__(kDecThreads, 2)
 k_attn_decode(Geom g, DecodeArgs da) {
-    __shared__ float s_m[4][RM], s_l[4][RM];
-    __shared__ float s_o[4][RM][128];
+    using F = Frag<bf16_t, 8, 2>;
+    constexpr int kQ = 16 * QT, kPitch = 132;
+    __shared__ __align__(16) float s_o[4][kQ][kPitch];
+    __shared__ float s_ref[4][kQ], s_l[4][kQ];
+    __shared__ unsigned s_sel[kDecMaxLen];                  // which lists hold a block of the range
+    __shared__ int s_act[kDecMaxLen];                       // the blocks that any does, as offsets into the range
+    __shared__ int s_nact;
     const AttnArgs& a = da.a;
     const int part = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int kq = lane >> 4, c = lane & 15;
+    const int tid = threadIdx.x, lane = tid & 63, x = lane & 15, gq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T = da.T, R = g.G * T;
-    const int Nbq = g.Lq / kDecBlock, m_first = (g.L - g.Lq) / kDecBlock;
+    const int Nbq = g.Lq / kDecBlock, m_first = (g.L - g.Lq) / kDecBlock;      // one query block, or two
     const long long nrows = (long long)g.batch * g.Hq * T;
     const float NEG_INF = -__builtin_huge_valf();
+    const int lists = g.G * Nbq;                             // at most 32: two query blocks need two tokens
 
-    const unsigned short* Qp = reinterpret_cast<const unsigned short*>(a.Q);
-    const unsigned short* Kp = reinterpret_cast<const unsigned short*>(a.K) + b * g.ksb + kv * g.ksh + c * 8;
-    const unsigned short* Vp = reinterpret_cast<const unsigned short*>(a.V) + b * g.ksb + kv * g.ksh + c * 8;
+    const bf16_t* Q = reinterpret_cast<const bf16_t*>(a.Q) + b * g.qsb;
+    const bf16_t* K = reinterpret_cast<const bf16_t*>(a.K) + b * g.ksb + kv * g.ksh;
+    const bf16_t* V = reinterpret_cast<const bf16_t*>(a.V) + b * g.ksb + kv * g.ksh;
 
-    bf16x8 q[RM];
-    int qpos[RM], mrow[RM], cnt[RM], lpos[RM], cur[RM];     // cur: the list entry at lpos, read one block ahead
-    const int32_t* list[RM];
-    const int n_lo = part * da.len;
-    const int n_hi = n_lo + da.len < da.nblocks ? n_lo + da.len : da.nblocks;
+    // rows that do not exist repeat the last one and are not stored
+    F qf[QT];
+    int qpos[QT];
+    unsigned mine[QT];                                       // the row's bit in s_sel
 #pragma unroll
-    for (int r = 0; r < RM; ++r) {
-        const int rr = r < R ? r : 0;
-        const int hl = rr / T, t = rr - hl * T, h = kv * g.G + hl;
-        q[r] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(Qp + b * g.qsb + h * g.qsh + (long long)t * g.qsl + c * 8));
-        qpos[r] = g.q0 + t;
-        mrow[r] = qpos[r] / kDecBlock;
-        list[r] = nullptr;
-        cnt[r] = 0;
-        lpos[r] = 0;
-        cur[r] = 0x7fffffff;
-        if (a.row_list) {
-            const long long rid = ((long long)b * g.Hq + h) * Nbq + (mrow[r] - m_first);
+    for (int u = 0; u < QT; ++u) {
+        const int rr = min(16 * u + x, R - 1), hl = rr / T, tk = rr - hl * T;
+        qf[u].load(Q + (kv * g.G + hl) * g.qsh + (long long)tk * g.qsl, 128, gq);
+        qpos[u] = g.q0 + tk;
+        mine[u] = 1u << (hl * Nbq + qpos[u] / kDecBlock - m_first);
+    }
+
+    const int n_lo = part * da.len;
+    const int n_hi = min(n_lo + da.len, da.nblocks), span = max(n_hi - n_lo, 0);
+    const unsigned all = lists >= 32 ? 0xFFFFFFFFu : (1u << lists) - 1u;
+    for (int i = tid; i < span; i += kDecThreads) s_sel[i] = a.row_list ? 0u : all;
+    __syncthreads();
+    if (a.row_list) {
+        // every list read whole by the workgroup at once (no search: a chain of dependent loads is longer than that);
+        // an entry counts where it lies in the range, whatever the list's order
+        for (int l = w; l < lists; l += 4) {
+            const int hl = l / Nbq, mq = l - hl * Nbq;
+            const long long rid = ((long long)b * g.Hq + kv * g.G + hl) * Nbq + mq;
             int cn = a.row_count[rid];
             cn = cn < 0 ? 0 : (cn > a.Nb ? a.Nb : cn);
-            cnt[r] = cn;
-            list[r] = a.row_list + rid * a.Nb;
-        }
-    }
-    // Where the part starts in every row's list: the number of entries below n_lo, counted by the whole workgroup
-    // at once (a binary search would be a chain of dependent loads per row, longer than the part's real work).
-    if (a.row_list && n_lo > 0) {
-        __shared__ int s_below[4][RM];
-        int below[RM], most = 0;
-#pragma unroll
-        for (int r = 0; r < RM; ++r) {
-            below[r] = 0;
-            most = cnt[r] > most ? cnt[r] : most;
-        }
-        for (int j = tid; j < most; j += kDecThreads) {
-#pragma unroll
-            for (int r = 0; r < RM; ++r) {                  // the loads of all rows together, none predicated
-                const int e = list[r][j < cnt[r] ? j : 0];
-                below[r] += (j < cnt[r] && e < n_lo) ? 1 : 0;
+            const int32_t* list = a.row_list + rid * a.Nb;
+#pragma unroll 4
+            for (int j = lane; j < cn; j += 64) {
+                const int e = list[j];
+                if (e >= n_lo && e < n_hi && e <= m_first + mq) atomicOr(&s_sel[e - n_lo], 1u << l);
             }
-        }
-#pragma unroll
-        for (int r = 0; r < RM; ++r) {
-#pragma unroll
-            for (int sft = 32; sft >= 1; sft >>= 1) below[r] += __shfl_xor(below[r], sft);
-            if (lane == 0) s_below[wv][r] = below[r];
         }
         __syncthreads();
-#pragma unroll
-        for (int r = 0; r < RM; ++r) lpos[r] = s_below[0][r] + s_below[1][r] + s_below[2][r] + s_below[3][r];
     }
-    if (a.row_list) {
-#pragma unroll
-        for (int r = 0; r < RM; ++r)
-            if (lpos[r] < cnt[r]) cur[r] = list[r][lpos[r]];
-    }
-
-    float mref[RM], lsum[RM], acc[RM][8];
-#pragma unroll
-    for (int r = 0; r < RM; ++r) {
-        mref[r] = NEG_INF;
-        lsum[r] = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[r][e] = 0.f;
-    }
-
-    for (int n = n_lo; n < n_hi; ++n) {
-        bool sel[RM];
-        bool any = false;
-        if (a.row_list) {
-            // Block n is in a row's list when the entry the row stands at equals n.  The entry for the next trip
-            // is requested here, for every row without a branch or a wait in between, and first looked at in the
-            // next trip, so its latency hides behind this block's work.  (An entry below n cannot occur in an
-            // ascending list; were one there, it is passed over, one per trip.)
-            int nxt[RM];
-#pragma unroll
-            for (int r = 0; r < RM; ++r) {
-                sel[r] = cur[r] == n;
-                lpos[r] += cur[r] <= n ? 1 : 0;
-                const int idx = lpos[r] < cnt[r] ? lpos[r] : 0;           // always inside the row's Nb entries
-                nxt[r] = list[r][idx];
-            }
-#pragma unroll
-            for (int r = 0; r < RM; ++r) cur[r] = lpos[r] < cnt[r] ? nxt[r] : 0x7fffffff;
-        } else {
-#pragma unroll
-            for (int r = 0; r < RM; ++r) sel[r] = true;
+    if (w == 0) {
+        int n = 0;
+        for (int i0 = 0; i0 < span; i0 += 64) {
+            const bool on = i0 + lane < span && s_sel[i0 + lane] != 0u;
+            const unsigned long long bal = __ballot(on);
+            if (on) s_act[n + __popcll(bal & ((1ull << lane) - 1ull))] = i0 + lane;
+            n += __popcll(bal);
         }
-#pragma unroll
-        for (int r = 0; r < RM; ++r) {
-            sel[r] = sel[r] && n <= mrow[r] && r < R;
-            any = any || sel[r];
-        }
-        if (!any) continue;                               // the same in every lane of the workgroup
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            // four keys per lane group: key index, clamped for the loads to the positions that exist
-            u32x4 kk[4], vv[4];
-            int kidx[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                kidx[i] = n * kDecBlock + wv * 32 + half * 16 + 4 * i + kq;
-                const int kc = kidx[i] < g.Lr ? kidx[i] : g.Lr - 1;
-                kk[i] = *reinterpret_cast<const u32x4*>(Kp + (long long)kc * g.ksl);
-                vv[i] = *reinterpret_cast<const u32x4*>(Vp + (long long)kc * g.ksl);
-            }
-            float sc[RM][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const bf16x8 kb = __builtin_bit_cast(bf16x8, kk[i]);
-#pragma unroll
-                for (int r = 0; r < RM; ++r) {
-                    const float d = row16_sum(dot8(kb, q[r]));
-                    sc[r][i] = (sel[r] && kidx[i] <= qpos[r]) ? d * da.scale_log2 : NEG_INF;
-                }
-            }
-            float p[RM][4];
-#pragma unroll
-            for (int r = 0; r < RM; ++r) {
-                const float mx = fmaxf(fmaxf(sc[r][0], sc[r][1]), fmaxf(sc[r][2], sc[r][3]));
-                const float mnew = fmaxf(mref[r], mx);
-                if (mnew == NEG_INF) {                     // nothing visible so far
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) p[r][i] = 0.f;
-                    continue;
-                }
-                const float alpha = __builtin_amdgcn_exp2f(mref[r] - mnew);    // mref = -inf: 0
-                mref[r] = mnew;
-                float ps = 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    p[r][i] = __builtin_amdgcn_exp2f(sc[r][i] - mnew);         // masked: 0
-                    ps += p[r][i];
-                }
-                lsum[r] = lsum[r] * alpha + ps;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[r][e] *= alpha;
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float vf[8];
-                unpack8(vv[i], vf);
-#pragma unroll
-                for (int r = 0; r < RM; ++r) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[r][e] = fmaf(p[r][i], vf[e], acc[r][e]);
-                }
-            }
-        }
-    }
-
-    // the four lane groups of the wavefront: to one reference, then summed (every lane ends with the totals)
-#pragma unroll
-    for (int r = 0; r < RM; ++r) {
-        float mall = fmaxf(mref[r], __shfl_xor(mref[r], 16));
-        mall = fmaxf(mall, __shfl_xor(mall, 32));
-        const float f = mref[r] == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(mref[r] - mall);
-        float l = lsum[r] * f;
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
-        lsum[r] = l;
-        mref[r] = mall;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float o = acc[r][e] * f;
-            o += __shfl_xor(o, 16);
-            o += __shfl_xor(o, 32);
-            acc[r][e] = o;
-        }
-        if (kq == 0) {
-            if (c == 0) { s_m[wv][r] = mall; s_l[wv][r] = l; }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s_o[wv][r][c * 8 + e] = acc[r][e];
-        }
+        if (lane == 0) s_nact = n;
     }
     __syncthreads();
-    // the four wavefronts: the part's normalised output and its natural-log sum of exponentials
-    for (int idx = tid; idx < RM * 128; idx += kDecThreads) {
-        const int r = idx >> 7, e = idx & 127;
-        if (r >= R) continue;
-        float mall = NEG_INF;
+    const int nact = __builtin_amdgcn_readfirstlane(s_nact);
+
+    f32x4 acc[QT][8];
+    float ref[QT], lsum[QT];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mall = fmaxf(mall, s_m[w][r]);
-        float tot = 0.f, o = 0.f;
+    for (int u = 0; u < QT; ++u) {
+        ref[u] = NEG_INF;
+        lsum[u] = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float f = s_m[w][r] == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(s_m[w][r] - mall);
-            tot = fmaf(s_l[w][r], f, tot);
-            o = fmaf(s_o[w][r][e], f, o);
+        for (int c = 0; c < 8; ++c) acc[u][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    // rows of a tile this lane reads, relative to its first key; keys past the context: a copy of the last, masked
+    const long long k_off = (long long)x * g.ksl;
+    long long v_off[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v_off[r] = (long long)(4 * gq + r) * g.ksl;
+    F kf[2];
+    int key0 = 0;                                            // first key of the wave's 32
+    unsigned sel = 0u;
+    auto load_keys = [&](int i) {
+        const int at = __builtin_amdgcn_readfirstlane(s_act[i]);
+        sel = (unsigned)__builtin_amdgcn_readfirstlane((int)s_sel[at]);
+        key0 = (n_lo + at) * kDecBlock + 32 * w;
+        const bf16_t* base = K + (long long)key0 * g.ksl;
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+            if (key0 + 32 <= g.Lr) kf[tl].load(base + 16 * tl * g.ksl + k_off, 128, gq);
+            else kf[tl].load(K + (long long)min(key0 + 16 * tl + x, g.Lr - 1) * g.ksl, 128, gq);
         }
-        // rows of this instantiation are (hl, t) pairs in the order of the set-up loop
-        const int hl = r / T, t = r - hl * T;
-        const long long row = ((long long)b * g.Hq + kv * g.G + hl) * T + t;
-        a.part_O[((long long)part * nrows + row) * 128 + e] = tot > 0.f ? o / tot : 0.f;
-        if (e == 0) a.part_lse[(long long)part * nrows + row] = tot > 0.f ? mall * 0.6931471805599453f + logf(tot) : NEG_INF;
+    };
+    if (nact > 0) load_keys(0);
+    for (int i = 0; i < nact; ++i) {
+        typename F::V vf;
+        const bf16_t* base = V + (long long)key0 * g.ksl;
+        if (key0 + 32 <= g.Lr) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) F::load_v(vf, k, base + 16 * (k >> 2) * g.ksl + v_off[k & 3], 128, x);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                F::load_v(vf, k, V + (long long)min(key0 + 16 * (k >> 2) + 4 * gq + (k & 3), g.Lr - 1) * g.ksl, 128, x);
+        }
+        f32x4 s[QT][2];
+#pragma unroll
+        for (int u = 0; u < QT; ++u)
+#pragma unroll
+            for (int tl = 0; tl < 2; ++tl) s[u][tl] = f32x4{0.f, 0.f, 0.f, 0.f};
+        F::template qk<QT>(s, kf, qf);
+        if (sel != all || key0 + 31 > g.q0) {
+#pragma unroll
+            for (int u = 0; u < QT; ++u)
+#pragma unroll
+                for (int tl = 0; tl < 2; ++tl) {
+                    // last of the lane's four keys that its row sees: the row selected the block, and token causality
+                    const int last = (sel & mine[u]) ? qpos[u] - key0 - 16 * tl - 4 * gq : -1;
+                    f32x4 v = s[u][tl];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = r > last ? NEG_INF : v[r];
+                    s[u][tl] = v;
+                }
+        }
+        if (i + 1 < nact) load_keys(i + 1);                  // travels during the softmax and the second product
+        float p[QT][8];
+#pragma unroll
+        for (int u = 0; u < QT; ++u) frag_softmax<2, 8>(s[u], da.scale_log2, ref[u], lsum[u], acc[u], p[u]);
+        F::template pv<QT>(acc, vf, p);
+    }
+
+    // the four waves: the part's normalised output and its natural-log sum of exponentials
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        float l = lsum[u];
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        if (gq == 0) { s_ref[w][16 * u + x] = ref[u]; s_l[w][16 * u + x] = l; }
+        frag_store<F::kW, 8>(acc[u], &s_o[w][16 * u + x][0], gq);
+    }
+    __syncthreads();
+    for (int idx = tid; idx < kQ * 32; idx += kDecThreads) {
+        const int q = idx >> 5, c = 4 * (idx & 31);
+        if (q >= R) continue;
+        float top = NEG_INF;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) top = fmaxf(top, s_ref[i][q]);
+        float l = 0.f;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float f = s_ref[i][q] == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(s_ref[i][q] - top);
+            l = fmaf(f, s_l[i][q], l);
+            const f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[i][q][c]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(f, v[e], o[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = l > 0.f ? o[e] / l : 0.f;
+        const int hl = q / T, tk = q - hl * T;
+        const long long row = ((long long)b * g.Hq + kv * g.G + hl) * T + tk;
+        *reinterpret_cast<f32x4*>(a.part_O + ((long long)part * nrows + row) * 128 + c) = o;
+        if (c == 0) a.part_lse[(long long)part * nrows + row] = l > 0.f ? top * 0.6931471805599453f + logf(l) : NEG_INF;
     }
 }
 
@@ -337,22 +263,27 @@ k_attn_decode_combine(Geom g, AttnArgs a, int T) {
 
 }  // namespace
 
-// Parts of a decode-sized step, 0 when the step is not one: at most kDecMaxTokens positions and kDecMaxRows
-// rows per KV head.  The launch is sized to what the chip holds at once -- two workgroups per compute unit (the
-// kernel is compiled to at most 256 registers per lane for that; eight rows need 244) -- because a second round
-// of workgroups costs more than longer parts save; measured at 128K tokens, one new token, 32 / 8 heads: 256
-// workgroups 143 us, 384 132, 512 112, 768 115, 1024 125-133, 2048 144; two tokens (eight rows): 256 227 us,
-// 512 166.  A part is at least two key blocks long.
+// Parts of a decode-sized step, 0 when the step is not one.  The launch is sized to what the chip holds at once -- two
+// workgroups per compute unit (237 registers per lane for two tiles of rows) -- because a second round of workgroups costs
+// more than longer parts save.  A part is at least two key blocks long.  One or two tokens of up to 8 rows are taken at
+// any depth; others where all rows lie deep in the context (16 causal blocks or more), as the split launch of the
+// 128-row kernel, which serves the steps with more rows.
 int attn_decode_parts(const Geom& g, int B) {
     if (B != kDecBlock || g.d != 128) return 0;
-    const int T = g.Lr - g.q0;
-    if (T < 1 || T > kDecMaxTokens || g.G * T > kDecMaxRows) return 0;
+    const int T = g.Lr - g.q0, Nb = g.L / B, Nbq = g.Lq / B;
+    if (T < 1) return 0;
+    if (g.G * T > kDecMaxRows) return 0;
+    if (!(T <= 2 && g.G * T <= 8) && Nb - Nbq + 1 < 16) return 0;
     const int nblocks = (g.Lr - 1) / kDecBlock + 1;
     const long long groups = (long long)g.batch * g.Hkv, target = 512;
     long long P = (target + groups - 1) / groups;
     if (P > (nblocks + 1) / 2) P = (nblocks + 1) / 2;
     if (P > kDecMaxParts) P = kDecMaxParts;
-    return P < 1 ? 1 : (int)P;
+    if (P < 1) P = 1;
+    const long long least = (nblocks + kDecMaxLen - 1) / kDecMaxLen;
+    if (P < least) P = least;
+    if (P > kDecMaxParts) return 0;
+    return (int)P;
 }
 
 size_t attn_decode_bytes(const Geom& g, int B) {
@@ -365,7 +296,7 @@ size_t attn_decode_bytes(const Geom& g, int B) {
 // expects a.nsplit = attn_decode_parts(g, a.B) >= 1 and a.part_O / a.part_lse of attn_decode_bytes
 hipError_t launch_attn_decode(const Geom& g, const AttnArgs& a, hipStream_t st) {
     const int T = g.Lr - g.q0, R = g.G * T;
-    if (a.nsplit < 1 || a.nsplit > kDecMaxParts || !a.part_O || !a.part_lse || T < 1 || T > kDecMaxTokens || R > kDecMaxRows ||
+    if (a.nsplit < 1 || a.nsplit > kDecMaxParts || !a.part_O || !a.part_lse || T < 1 ||
         g.batch > 65535 || g.Hkv > 65535)
         return hipErrorInvalidValue;
     DecodeArgs da;
@@ -375,10 +306,9 @@ hipError_t launch_attn_decode(const Geom& g, const AttnArgs& a, hipStream_t st) 
     da.len = (da.nblocks + a.nsplit - 1) / a.nsplit;
     da.scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     const dim3 grid((unsigned)a.nsplit, (unsigned)g.Hkv, (unsigned)g.batch);
-    if (R <= 1) hipLaunchKernelGGL(k_attn_decode<1>, grid, dim3(kDecThreads), 0, st, g, da);
-    else if (R <= 2) hipLaunchKernelGGL(k_attn_decode<2>, grid, dim3(kDecThreads), 0, st, g, da);
-    else if (R <= 4) hipLaunchKernelGGL(k_attn_decode<4>, grid, dim3(kDecThreads), 0, st, g, da);
-    else hipLaunchKernelGGL(k_attn_decode<8>, grid, dim3(kDecThreads), 0, st, g, da);
+    if (R > kDecMaxRows || da.len > kDecMaxLen) return hipErrorInvalidValue;
+    if (R <= 16) hipLaunchKernelGGL(k_attn_decode<1>, grid, dim3(kDecThreads), 0, st, g, da);
+    else hipLaunchKernelGGL(k_attn_decode<2>, grid, dim3(kDecThreads), 0, st, g, da);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const long long nrows = (long long)g.batch * g.Hq * T;

@@ -13,194 +13,17 @@
 // Fragments go from global memory (K and V of these shapes stay in L2) straight to registers: with keys split over
 // the waves no two of them would share a staged tile, and there is no barrier before the merge.
 //
-// Transposed products, S^T = K Q^T and O^T = V^T P^T: a lane owns one query (column lane % 16), and the accumulator
-// layout of S^T (keys 4 (lane / 16) + 0..3 of a tile) is the B operand of the second product.  V^T fragments need
-// consecutive keys of one channel per lane; which channel a lane's row stands for is free, so lane x = lane % 16 loads
-// W consecutive channels W x .. W x + W - 1 of each of its keys and these W values belong to W different tiles: with
-// fp32 they are the fragments as loaded, with bf16 one byte permutation per register pairs two keys.
-//
 // Measured against the form before it (one workgroup per query block, fp32 vector FMAs on operands staged in LDS, where
 // every multiply-add waited for an LDS read): fp32, 1024 tokens, 4 / 2 heads of 64: 576 -> 19 us; fp32, 4096 tokens, 8 / 2
 // heads of 128: 5954 -> 174 us (62 TFLOP/s of selected blocks); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 183 us.
 //
 // Softmax: base 2, the reference is moved only when a wave's sum of a step exceeds 2^8 (all terms of a row share it).
-#include "rr_common.hpp"
-
-#include <type_traits>
+#include "rr_attn_frag.hpp"
 
 namespace rr {
 
 namespace {
 
-constexpr float kLazySum = 256.0f;
-
-// f(W, base) for every piece of a row of 16 NT channels that a lane loads at once: W channels, lane x those from
-// base + W x on
-template <int WMAX, int NT, typename F>
-__device__ __forceinline__ void for_pieces(F&& f) {
-    using std::integral_constant;
-    constexpr int full = NT / WMAX;
-    if constexpr (full > 0) f(integral_constant<int, WMAX>{}, integral_constant<int, 0>{});
-    if constexpr (full > 1) f(integral_constant<int, WMAX>{}, integral_constant<int, 16 * WMAX>{});
-    if constexpr (full > 2) f(integral_constant<int, WMAX>{}, integral_constant<int, 32 * WMAX>{});
-    if constexpr (full > 3) f(integral_constant<int, WMAX>{}, integral_constant<int, 48 * WMAX>{});
-    static_assert(full <= 4, "at most 256 channels");
-    constexpr int r8 = WMAX * full;
-    if constexpr (WMAX > 4 && ((NT - r8) & 4)) f(integral_constant<int, 4>{}, integral_constant<int, 16 * r8>{});
-    constexpr int r4 = r8 + (WMAX > 4 ? ((NT - r8) & 4) : 0);
-    if constexpr ((NT - r4) & 2) f(integral_constant<int, 2>{}, integral_constant<int, 16 * r4>{});
-    constexpr int r2 = r4 + ((NT - r4) & 2);
-    if constexpr ((NT - r2) & 1) f(integral_constant<int, 1>{}, integral_constant<int, 16 * r2>{});
-}
-
-// Fragments of one element type for rows of up to 16 NT channels.
-//   KF   K (or Q) operand of one 16-row tile: this lane's channels of row lane % 16
-//   VF   V^T operand of one pair of tiles (32 keys): this lane's 8 keys
-template <typename T, int NT, int TL> struct Frag;
-
-template <int NT, int TL> struct Frag<float, NT, TL> {
-    static constexpr int kW = 4;
-    f32x4 k[NT];                                     // chunk i: channels 16 i + 4 g .. +3
-    struct V { float v[4 * TL][NT]; };                    // [tile * 4 + r][channel tile]
-
-    __device__ __forceinline__ void load(const float* row, int d, int gq) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            const int c = 16 * i + 4 * gq;
-            if (i < NT - 1) {
-                k[i] = *reinterpret_cast<const f32x4*>(row + c);
-            } else {
-                const bool in = c < d;                // channels that do not exist are zero on both sides
-                const f32x4 v = *reinterpret_cast<const f32x4*>(row + (in ? c : 0));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) k[i][e] = in ? v[e] : 0.f;
-            }
-        }
-    }
-    __device__ static __forceinline__ void load_v(V& o, int key, const float* row, int d, int x) {
-        for_pieces<kW, NT>([&](auto w, auto base) {
-            constexpr int W = decltype(w)::value, B0 = decltype(base)::value;
-            const int c = min(B0 + W * x, d - W);     // channels past d are never stored
-            typedef __attribute__((ext_vector_type(W))) float vec;
-            if constexpr (W == 1) {
-                o.v[key][B0 / 16] = row[c];
-            } else {
-                const vec v = *reinterpret_cast<const vec*>(row + c);
-#pragma unroll
-                for (int e = 0; e < W; ++e) o.v[key][B0 / 16 + e] = v[e];
-            }
-        });
-    }
-    // scores of the two tiles of a pair; interleaved so that consecutive MFMAs do not depend on each other
-    template <int QT>
-    __device__ static __forceinline__ void qk(f32x4 (&s)[QT][TL], const Frag (&kf)[TL], const Frag (&qf)[QT]) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int t = 0; t < TL; ++t)
-#pragma unroll
-                    for (int u = 0; u < QT; ++u)
-                        s[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t].k[i][e], qf[u].k[i][e], s[u][t], 0, 0, 0);
-    }
-    template <int QT>
-    __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][4 * TL]) {
-#pragma unroll
-        for (int key = 0; key < 4 * TL; ++key)
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int u = 0; u < QT; ++u)
-                    acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.v[key][t], p[u][key], acc[u][t], 0, 0, 0);
-    }
-};
-
-template <int NT, int TL> struct Frag<bf16_t, NT, TL> {
-    static_assert(TL == 2, "the second product takes 32 keys");
-    static constexpr int kW = 8;
-    static constexpr int KC = (NT + 1) / 2;
-    u32x4 k[KC];                                     // chunk i: channels 32 i + 8 g .. +7
-    struct V { unsigned v[8][(NT + 1) / 2]; };       // [tile * 4 + r]: the channels as loaded, two to a register
-
-    __device__ __forceinline__ void load(const bf16_t* row, int d, int gq) {
-#pragma unroll
-        for (int i = 0; i < KC; ++i) {
-            const int c = 32 * i + 8 * gq;
-            if (i < KC - 1) {
-                k[i] = *reinterpret_cast<const u32x4*>(row + c);
-            } else {
-                const bool in = c < d;
-                const u32x4 v = *reinterpret_cast<const u32x4*>(row + (in ? c : 0));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) k[i][e] = in ? v[e] : 0u;
-            }
-        }
-    }
-    __device__ static __forceinline__ void load_v(V& o, int key, const bf16_t* row, int d, int x) {
-        for_pieces<kW, NT>([&](auto w, auto base) {
-            constexpr int W = decltype(w)::value, B0 = decltype(base)::value;
-            const int c = min(B0 + W * x, d - W);
-            if constexpr (W == 1) {
-                o.v[key][B0 / 32] = row[c].bits;
-            } else if constexpr (W == 2) {
-                o.v[key][B0 / 32] = *reinterpret_cast<const unsigned*>(row + c);
-            } else {
-                typedef __attribute__((ext_vector_type(W / 2))) unsigned vec;
-                const vec v = *reinterpret_cast<const vec*>(row + c);
-#pragma unroll
-                for (int e = 0; e < W / 2; ++e) o.v[key][B0 / 32 + e] = v[e];
-            }
-        });
-    }
-    template <int QT>
-    __device__ static __forceinline__ void qk(f32x4 (&s)[QT][TL], const Frag (&kf)[TL], const Frag (&qf)[QT]) {
-#pragma unroll
-        for (int i = 0; i < KC; ++i)
-#pragma unroll
-            for (int t = 0; t < TL; ++t)
-#pragma unroll
-                for (int u = 0; u < QT; ++u)
-                    s[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t].k[i]),
-                                                                      __builtin_bit_cast(bf16x8, qf[u].k[i]), s[u][t], 0, 0, 0);
-    }
-    template <int QT>
-    __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][4 * TL]) {
-        // p = hi + mid + lo, every term the leading 8 significant bits of what is left (truncated, so exact)
-        u32x4 plane[QT][3];
-#pragma unroll
-        for (int u = 0; u < QT; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                unsigned a = __float_as_uint(p[u][2 * j]), b = __float_as_uint(p[u][2 * j + 1]);
-                float ra = p[u][2 * j], rb = p[u][2 * j + 1];
-#pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
-                    plane[u][pl][j] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-                    if (pl < 2) {
-                        ra -= __uint_as_float(a & 0xFFFF0000u);
-                        rb -= __uint_as_float(b & 0xFFFF0000u);
-                        a = __float_as_uint(ra);
-                        b = __float_as_uint(rb);
-                    }
-                }
-            }
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            u32x4 vt;                                // 8 keys of this lane's channel of tile t
-            const unsigned sel = (t & 1) ? 0x07060302u : 0x05040100u;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) vt[j] = __builtin_amdgcn_perm(v.v[2 * j + 1][t / 2], v.v[2 * j][t / 2], sel);
-            const bf16x8 vb = __builtin_bit_cast(bf16x8, vt);
-#pragma unroll
-            for (int pl = 2; pl >= 0; --pl)          // the small terms first
-#pragma unroll
-                for (int u = 0; u < QT; ++u)
-                    acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, __builtin_bit_cast(bf16x8, plane[u][pl]),
-                                                                        acc[u][t], 0, 0, 0);
-        }
-    }
-};
 
 __device__ __forceinline__ void store4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
 __device__ __forceinline__ void store4(bf16_t* p, const f32x4& v) {
@@ -371,38 +194,8 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
 
         float p[QT][4 * TL];
 #pragma unroll
-        for (int u = 0; u < QT; ++u) {
-            float sum = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4 * TL; ++i) {
-                p[u][i] = __builtin_amdgcn_exp2f(fmaf(s[u][i >> 2][i & 3], scale_log2, -ref[u]));
-                sum += p[u][i];
-            }
-            // (a reference of -inf, nothing seen yet, gives inf or nan and lands here as well)
-            if (__any(!(sum <= kLazySum))) {
-                float mx = NEG_INF;
-#pragma unroll
-                for (int i = 0; i < 4 * TL; ++i) mx = fmaxf(mx, s[u][i >> 2][i & 3]);
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float nref = fmaxf(ref[u], mx * scale_log2);
-                const float use = nref == NEG_INF ? 0.f : nref;
-                const float alpha = __builtin_amdgcn_exp2f(ref[u] - use);       // 0 while the reference is -inf
-                ref[u] = nref;
-                lsum[u] *= alpha;
-#pragma unroll
-                for (int c = 0; c < NT; ++c)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[u][c][r] *= alpha;
-                sum = 0.f;
-#pragma unroll
-                for (int i = 0; i < 4 * TL; ++i) {
-                    p[u][i] = __builtin_amdgcn_exp2f(fmaf(s[u][i >> 2][i & 3], scale_log2, -use));
-                    sum += p[u][i];
-                }
-            }
-            lsum[u] += sum;
-        }
+        for (int u = 0; u < QT; ++u)
+            frag_softmax<TL, NT>(s[u], scale_log2, ref[u], lsum[u], acc[u], p[u]);
         F::template pv<QT>(acc, vf, p);
     }
 
@@ -414,17 +207,7 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
         l += __shfl_xor(l, 32);
         const int q = 16 * u + x;
         if (gq == 0) { s_ref[w][q] = ref[u]; s_l[w][q] = l; }
-        for_pieces<F::kW, NT>([&](auto wd, auto base) {
-            // accumulator row 4 g + r of tile e of a piece is channel base + W (4 g + r) + e
-            constexpr int W = decltype(wd)::value, B0 = decltype(base)::value;
-#pragma unroll
-            for (int i = 0; i < W; ++i) {
-                f32x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = acc[u][B0 / 16 + (4 * i + e) % W][(4 * i + e) / W];
-                *reinterpret_cast<f32x4*>(&s_o[w][q][B0 + 4 * W * gq + 4 * i]) = o;
-            }
-        });
+        frag_store<F::kW, NT>(acc[u], &s_o[w][q][0], gq);
     }
     __syncthreads();
     T* O = reinterpret_cast<T*>(a.O) + b * g.qsb + h * g.qsh + row0 * g.qsl;

@@ -172,7 +172,7 @@ int attn_mfma_plan_len(const Geom& g, int B, int* budget);
 size_t attn_mfma_plan_bytes(const Geom& g, int B);
 void attn_mfma_plan_pointers(const Geom& g, int B, void* workspace, AttnArgs* a);
 hipError_t launch_attn_combine(const Geom& g, const AttnArgs& a, hipStream_t st);
-// Decode-sized steps (one or two positions, at most 8 rows per KV head; bf16, d = 128, B = 128): parts of the
+// Decode-sized steps (at most 32 query rows per KV head; bf16, d = 128, B = 128): parts of the
 // launch (0: not such a step), bytes of its partial results, and the launch itself (a.nsplit parts, a.part_O /
 // a.part_lse laid out as above), which also merges the parts into a.O / a.lse.
 int attn_decode_parts(const Geom& g, int B);

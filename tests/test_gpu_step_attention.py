@@ -1,0 +1,69 @@
+"""Attention of steps with 5 to 32 query rows per KV head (bf16, d = 128, B = 128, with the workspace): row counts at the
+edges of the 16-column tiles, steps inside one block and across two, lengths that end inside a block, batches, dense and
+under random block lists (one of them with a single block, one empty), against attention in 64 bits under the same mask."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # batch, Hq, Hkv, T, L
+    (1, 5, 1, 1, 640), (1, 8, 1, 1, 129), (2, 16, 2, 1, 2700), (1, 14, 2, 1, 5000), (1, 6, 1, 1, 1),   # one token
+    (1, 8, 2, 2, 3001), (1, 8, 2, 2, 2049), (1, 4, 1, 4, 2690), (2, 8, 2, 4, 2691), (1, 17, 1, 1, 2561),
+    (1, 8, 2, 8, 4000), (1, 8, 2, 8, 4099), (1, 7, 1, 4, 2700), (1, 2, 1, 16, 2817), (1, 1, 1, 31, 2700),
+    (1, 32, 1, 1, 2688), (1, 16, 1, 2, 2689), (1, 4, 4, 32, 2720),
+]
+
+
+@pytest.mark.parametrize("sparse", [False, True])
+@pytest.mark.parametrize("batch,Hq,Hkv,T,L", CASES)
+def test_step_attention(batch, Hq, Hkv, T, L, sparse):
+    import paper_2602_05853_amd as rr
+    B, d = 128, 128
+    g = torch.Generator(device="cuda:0").manual_seed(L + T)
+    Q = (torch.randn(batch, Hq, T, d, generator=g, device="cuda:0") * 1.5).bfloat16()
+    K = torch.randn(batch, Hkv, L, d, generator=g, device="cuda:0").bfloat16()
+    V = torch.randn(batch, Hkv, L, d, generator=g, device="cuda:0").bfloat16()
+    Nb, m0 = -(-L // B), (L - T) // B
+    rows = Nb - m0
+    mask = torch.ones(batch, Hq, rows, Nb, dtype=torch.uint8, device="cuda:0")
+    if sparse:
+        mask = (torch.rand(mask.shape, generator=g, device="cuda:0") < 0.3).to(torch.uint8)
+        mask[:, 0, 0] = 0                                   # nothing selected
+        mask[:, Hq - 1, rows - 1] = 0
+        mask[:, Hq - 1, rows - 1, Nb // 2] = 1              # one block
+    for r in range(rows):
+        mask[:, :, r, m0 + r + 1:] = 0
+    need = rr.rr_attn_workspace_bytes(Q, K, B)
+    assert need > 0
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda:0")
+    O = torch.full_like(Q, float("nan"))
+    lse = torch.full((batch, Hq, T), float("nan"), dtype=torch.float32, device="cuda:0")
+    print(f"[step] {batch} x {Hq}/{Hkv} heads, {T} of {L} {'sparse' if sparse else 'dense'}", flush=True)
+    if sparse:
+        bm = rr.rr_mask_from_dense(Q, K, mask.contiguous(), B)
+        rr.rr_sparse_attn(Q, K, V, bm, O=O, lse=lse, workspace=ws)
+    else:
+        rr.rr_dense_attn(Q, K, V, B, O=O, lse=lse, workspace=ws)
+    torch.cuda.synchronize()
+    G = Hq // Hkv
+    q, k, v = (t.double().cpu() for t in (Q, K, V))
+    k, v = k.repeat_interleave(G, 1), v.repeat_interleave(G, 1)
+    pos = torch.arange(L - T, L)
+    seen = mask.cpu().bool()[:, :, pos // B - m0].repeat_interleave(B, 3)[..., :L] & (torch.arange(L) <= pos[:, None])
+    s = ((q[:, :, :, None, :] * k[:, :, None]).sum(-1) / math.sqrt(d)).masked_fill(~seen, float("-inf"))
+    want_lse = torch.logsumexp(s, -1)
+    p = torch.exp(s - want_lse.clamp_min(-1e300)[..., None])
+    want = (p[..., None] * v[:, :, None]).sum(-2)
+    err = (O.double().cpu() - want).abs()
+    assert err.max() <= gu.BF16_MAX_ABS and err.mean() <= gu.BF16_MEAN_ABS, (err.max(), err.mean())
+    got = lse.double().cpu()
+    assert torch.equal(torch.isinf(got), torch.isinf(want_lse))
+    finite = ~torch.isinf(want_lse)
+    if finite.any():
+        # scores and sums are held in 32 bits: a few 2^-24 of logits of magnitude 20
+        assert (got - want_lse)[finite].abs().max() <= 1e-4
