@@ -58,7 +58,22 @@ k_stride_sum_split(Geom g, const unsigned short* __restrict__ K, int S, int Ls, 
     for (int i = 0; i < 8; ++i) acc[i] = 0.f;
     // strides that are not complete within the real length do not exist (Sec. 3.1: floor(L/S) of them): zeros
     const int nkeys = (j + 1) * S <= g.Lr ? S : 0;
-    for (int s = 0; s < nkeys; ++s) {
+    // eight keys requested at once (one at a time, a thread's S loads were a chain: 2048
+    // new positions at 128K 11.4 -> 5.0 us, 8K tokens, all 8 KV heads 8.3 -> 6.1, 128K 68 -> 63)
+    int s = 0;
+    for (; s + 8 <= nkeys; s += 8) {
+        u32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const u32x4*>(src + (s + u) * g.ksl);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc[2 * i] += __uint_as_float(v[u][i] << 16);
+                acc[2 * i + 1] += __uint_as_float(v[u][i] & 0xFFFF0000u);
+            }
+    }
+    for (; s < nkeys; ++s) {
         const u32x4 v = *reinterpret_cast<const u32x4*>(src + s * g.ksl);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {

@@ -29,7 +29,18 @@ k_stride_sum(Geom g, const T* __restrict__ K, int S, int Ls, float* __restrict__
     for (int i = 0; i < V; ++i) acc[i] = 0.f;
     // strides that are not complete within the real length do not exist (Sec. 3.1: floor(L/S) of them): zeros
     const int nkeys = (j + 1) * S <= g.Lr ? S : 0;
-    for (int s = 0; s < nkeys; ++s) {
+    // eight keys requested at once: one at a time, a thread's S loads were a chain of latencies
+    int s = 0;
+    for (; s + 8 <= nkeys; s += 8) {
+        float v[8][V];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) Elem<T>::load16(src + (s + u) * g.ksl, v[u]);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[i] += v[u][i];
+    }
+    for (; s < nkeys; ++s) {
         float v[V];
         Elem<T>::load16(src + s * g.ksl, v);
 #pragma unroll
