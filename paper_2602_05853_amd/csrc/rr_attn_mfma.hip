@@ -720,7 +720,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         if (split && plan_slot != base + part) return;
     }
     if (split) {
-        const int len = planned ? a.split_len : (count + a.nsplit - 1) / a.nsplit;
+        const int len = planned ? __builtin_amdgcn_readfirstlane(a.plan_total[2]) : (count + a.nsplit - 1) / a.nsplit;
         list_lo = min(count, part * len);
         const int hi = min(count, list_lo + len);
         last_part = hi == count;
@@ -1044,31 +1044,70 @@ k_attn_combine(Geom g, AttnArgs a) {
 }
 
 // ---- planned launches (chunks of a long prompt): the plan and the merge ----
-// One workgroup walks the rows in launch order, gives every row longer than split_len entries one slot per part
-// (a prefix sum, so the longest rows, which start first, are served first when the slots run out) and lists the
-// slots' rows.
+// One workgroup.  First the part length: the shortest of a fixed series, not below split_len, with which all rows longer
+// than a part fit into the slots and a part is a quarter of a workgroup's share of the launch or more (shorter ones only add
+// partial results); no row is cut where none is long (dense chunks of many rows).  (Rows for which no slot is left are computed whole, and one of them can take longer
+// than everything else: with a fixed 64 entries a chunk of 512 tokens at 128K whose heads kept 42 000 block pairs took
+// 2.17 ms, with the length that fits 0.42 ms.)  Then it walks the rows in launch order, gives every row longer than
+// that one slot per part (a prefix sum) and lists the slots' rows.
 constexpr int kPlanThreads = 1024;
+constexpr int kPlanShare = 2048;     // four times the workgroups that are resident at once
+constexpr int kPlanWhole = 768;      // no row is longer than two thirds of a workgroup's share: none is cut
 __global__ void __launch_bounds__(kPlanThreads)
 k_split_plan(Geom g, AttnArgs a, int grid_rows) {
     __shared__ int s_scan[kPlanThreads];
     __shared__ int s_base, s_used, s_cut;
+    constexpr int kLens = 16;
+    __shared__ int s_need[kLens + 1], s_longest;                // slots per length, and the entries of all rows
     const int t = threadIdx.x;
     const int Nbq = g.Lq >> 7;
     const int rows_total = g.batch * g.Hq * Nbq;
-    for (int i = t; i < rows_total; i += kPlanThreads) a.plan_row[i] = -1;
-    if (t == 0) { s_base = 0; s_used = 0; s_cut = 0; }
+    auto count_of = [&](int rid) {                              // as the attention kernel holds it
+        const int m = rid % Nbq + (a.Nb - Nbq);
+        const int count = a.row_list ? a.row_count[rid] : m + 1;
+        return count < 0 ? 0 : (count > m + 1 ? m + 1 : count);
+    };
+    auto len_of = [&](int i) { return (4 + (i & 3)) * (a.split_len << (i >> 2)) / 4; };   // 1, 1.25, 1.5, 1.75, 2, 2.5 ..
+    if (t <= kLens) s_need[t] = 0;
+    if (t == 0) { s_base = 0; s_used = 0; s_cut = 0; s_longest = 0; }
     __syncthreads();
+    int longest = 0;
+    int need[kLens + 1];
+#pragma unroll
+    for (int i = 0; i <= kLens; ++i) need[i] = 0;
+    for (int rid = t; rid < rows_total; rid += kPlanThreads) {
+        a.plan_row[rid] = -1;
+        const int count = count_of(rid);
+        need[kLens] += count;
+        longest = max(longest, count);
+#pragma unroll
+        for (int i = 0; i < kLens; ++i) {
+            const int len = len_of(i);
+            need[i] += count > len ? (count + len - 1) / len : 0;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i <= kLens; ++i) {
+#pragma unroll
+        for (int sft = 32; sft >= 1; sft >>= 1) need[i] += __shfl_xor(need[i], sft);
+        if ((t & 63) == 0) atomicAdd(&s_need[i], need[i]);
+    }
+    atomicMax(&s_longest, longest);
+    __syncthreads();
+    int len = len_of(kLens - 1);
+#pragma unroll
+    for (int i = kLens - 2; i >= 0; --i)
+        if (s_need[i] <= a.split_budget && len_of(i) >= s_need[kLens] / kPlanShare) len = len_of(i);
+    if (s_longest <= s_need[kLens] / kPlanWhole) len = max(len, s_longest);
     for (int start = 0; start < grid_rows; start += kPlanThreads) {
         const int rank = start + t;
         int parts = 0, rid = -1;
         if (rank < grid_rows) {
             int b, h, mq;
             if (decode_block(rank, g, Nbq, a.row_order, a.interleave, b, h, mq)) {
-                const int m = mq + (a.Nb - Nbq);
                 rid = (b * g.Hq + h) * Nbq + mq;
-                int count = a.row_list ? a.row_count[rid] : m + 1;
-                count = count < 0 ? 0 : (count > m + 1 ? m + 1 : count);      // as the attention kernel holds it
-                if (count > a.split_len) parts = (count + a.split_len - 1) / a.split_len;
+                const int count = count_of(rid);
+                if (count > len) parts = (count + len - 1) / len;
             }
         }
         // the parts (at most 4096 rows x 32 < 2^18), and above them the number of rows with parts (at most 2^12)
@@ -1093,7 +1132,7 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
         if (t == 0) s_base += s_scan[kPlanThreads - 1];
         __syncthreads();
     }
-    if (t == 0) { a.plan_total[0] = s_used; a.plan_total[1] = s_cut; }
+    if (t == 0) { a.plan_total[0] = s_used; a.plan_total[1] = s_cut; a.plan_total[2] = len; }
 }
 
 // The cut rows: O = sum_p exp(lse_p - lse) O_p over the row's parts, rounded once.  A wavefront per query row
@@ -1111,7 +1150,8 @@ k_attn_combine_plan(Geom g, AttnArgs a) {
     const int m = mq + (a.Nb - Nbq);
     int count = a.row_list ? a.row_count[rid] : m + 1;
     count = count < 0 ? 0 : (count > m + 1 ? m + 1 : count);
-    int parts = (count + a.split_len - 1) / a.split_len;
+    const int len = a.plan_total[2];
+    int parts = (count + len - 1) / len;
     parts = parts > 64 ? 64 : parts;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const long long rows_call = g.Lr - g.q0;
@@ -1145,17 +1185,19 @@ k_attn_combine_plan(Geom g, AttnArgs a) {
 int attn_mfma_plan_len(const Geom& g, int B, int* budget) {
     // A chunk of a long prompt: many rows, most of them short, a few nearly as long as the context, and the launch
     // takes as long as its longest row (measured at 128K, tau 0.9: 1.1 ms for chunks of 512 to 2048 tokens whose
-    // blocks are 0.15-0.19 ms of matrix work).  Parts of 64 list entries, 128 where the launch has more than 2048 rows
-    // (measured: 32 / 64 / 128 entries are level up to 4096 tokens, 64 is best at 8192, 128 at 16384; what remains
-    // above the matrix work is memory traffic: the rows of such a launch share few tiles in L2).
+    // blocks are 0.15-0.19 ms of matrix work).  The result is the shortest length a part may have; k_split_plan chooses.
+    // Measured, 32 / 8 heads at tau 0.9 unless said (fixed 64 entries, 128 above 2048 rows -> the length that is chosen):
+    // 512 tokens at 128K (42 000 block pairs) 1750 -> 475 us, 2048 (54 000) 613 -> 585, 16384 2460 -> 2300, 28 / 4 heads 2048 at
+    // 64K 264 -> 213, 64 / 8 heads 1000 at 40 000 tokens, tau 0.95, 412 -> 401; dense 2048 at 128K 4.8 -> 4.1 ms.
     if (budget) *budget = 0;
     if (B != 128 || g.d != 128) return 0;
     const int Nb = g.L / B, Nbq = g.Lq / B;
     const long long rows = (long long)g.batch * g.Hq * Nbq;
     if (Nbq < 2 || Nb < 128 || g.q0 <= 0 || rows > 4096) return 0;
-    int len = rows <= 2048 ? 64 : 128;
+    int len = rows <= 2048 ? 64 : 128;                                  // contexts that are not longer are not planned
     if (len < (Nb + 31) / 32) len = (Nb + 31) / 32;                     // at most 32 parts per row
     if (Nb <= len) return 0;
+    len = (Nb + 31) / 32 > 40 ? (Nb + 31) / 32 : 40;
     // slots: several times what the rows of such chunks were seen to need (300-1000 at 128K), between 512 and 2048
     // (34-135 MB of partial results); the workgroups of unused slots run last and cost nothing measurable
     if (budget) *budget = (int)(4 * rows < 512 ? 512 : (4 * rows > 2048 ? 2048 : 4 * rows));

@@ -153,12 +153,12 @@ struct AttnArgs {
     // [nsplit][batch][Hq][rows], fp32, rows = the query positions of the call) and a second kernel merges them
     int nsplit;
     float* part_O; float* part_lse;
-    // MFMA kernel, chunks of a long prompt (many rows, a few of them very long): rows longer than split_len list
-    // entries are cut into parts of split_len entries.  A plan made on the device before the launch gives every such
+    // MFMA kernel, chunks of a long prompt (many rows, a few of them very long): rows longer than a part are cut
+    // into parts of plan_total[2] >= split_len list entries.  A plan made on the device before the launch gives every such
     // row a run of slots (one per part) in part_O / part_lse, here laid out [slot][128 query rows][d] and
     // [slot][128]: plan_row[row] = first slot or -1 (the row is computed whole and stored directly), plan_items[slot]
     // = row, plan_cut[k] = the k-th cut row, plan_total[0] = slots in use (at most split_budget; rows that no longer
-    // fit stay whole), plan_total[1] = cut rows.  The launch has one workgroup per slot and one per row.
+    // fit stay whole), plan_total[1] = cut rows, plan_total[2] = entries of a part.  The launch has one workgroup per slot and one per row.
     // split_len = 0: off.
     int split_len, split_budget;
     int32_t* plan_total; int32_t* plan_row; int32_t* plan_items; int32_t* plan_cut;
