@@ -45,7 +45,8 @@ __global__ void __launch_bounds__(kDecThreads, 2)
 k_attn_decode(Geom g, DecodeArgs da) {
     using F = Frag<bf16_t, 8, 2>;
     constexpr int kQ = 16 * QT, kPitch = 132;
-    __shared__ __align__(16) float s_o[4][kQ][kPitch];
+    __shared__ __align__(16) float s_o[4][kQ][kPitch];       // a wave's share: its rows at the end
+    static_assert(kPitch >= 128, "a wave's accumulators fit its share");
     __shared__ float s_ref[4][kQ], s_l[4][kQ];
     __shared__ unsigned s_sel[kDecMaxLen];                  // which lists hold a block of the range
     __shared__ int s_act[kDecMaxLen];                       // the blocks that any does, as offsets into the range
@@ -79,7 +80,9 @@ k_attn_decode(Geom g, DecodeArgs da) {
     const int n_lo = part * da.len;
     const int n_hi = min(n_lo + da.len, da.nblocks), span = max(n_hi - n_lo, 0);
     const unsigned all = lists >= 32 ? 0xFFFFFFFFu : (1u << lists) - 1u;
-    for (int i = tid; i < span; i += kDecThreads) s_sel[i] = a.row_list ? 0u : all;
+    // dense: every block up to a list's own query block (of two query blocks, odd lists are the second's)
+    for (int i = tid; i < span; i += kDecThreads)
+        s_sel[i] = a.row_list ? 0u : (n_lo + i <= m_first ? all : (Nbq == 2 ? all & 0xAAAAAAAAu : 0u));
     __syncthreads();
     if (a.row_list) {
         // every list read whole by the workgroup at once (no search: a chain of dependent loads is longer than that);
@@ -157,6 +160,7 @@ k_attn_decode(Geom g, DecodeArgs da) {
 #pragma unroll
             for (int tl = 0; tl < 2; ++tl) s[u][tl] = f32x4{0.f, 0.f, 0.f, 0.f};
         F::template qk<QT>(s, kf, qf);
+        const unsigned sel_now = sel;
         if (sel != all || key0 + 31 > g.q0) {
 #pragma unroll
             for (int u = 0; u < QT; ++u)
@@ -174,7 +178,33 @@ k_attn_decode(Geom g, DecodeArgs da) {
         float p[QT][8];
 #pragma unroll
         for (int u = 0; u < QT; ++u) frag_softmax<2, 8>(s[u], da.scale_log2, ref[u], lsum[u], acc[u], p[u]);
+        // A row takes nothing from a block it did not select.  Its probabilities there are zero, which is enough unless the
+        // values are not finite: then (rare) the accumulators wait in the wave's share of the merge area meanwhile.
+        bool apart = false;
+        if (sel_now != all) {
+            unsigned bad = 0u;                               // an exponent of all ones carries into the sign's place
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) bad |= (vf.v[k][e] & 0x7F807F80u) + 0x00800080u;
+            apart = __any((bad & 0x80008000u) != 0u);
+        }
+        f32x4* const aside = reinterpret_cast<f32x4*>(&s_o[w][0][0]) + lane;
+        if (apart) {
+#pragma unroll
+            for (int u = 0; u < QT; ++u)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) aside[64 * (8 * u + c)] = acc[u][c];
+        }
         F::template pv<QT>(acc, vf, p);
+        if (apart) {
+#pragma unroll
+            for (int u = 0; u < QT; ++u)
+                if ((sel_now & mine[u]) == 0u) {
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) acc[u][c] = aside[64 * (8 * u + c)];
+                }
+        }
     }
 
     // the four waves: the part's normalised output and its natural-log sum of exponentials

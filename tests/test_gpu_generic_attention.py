@@ -41,7 +41,7 @@ def test_generic_attention_matches_the_oracle(B, d, dtype, Hq, Nb):
     mask[1, 4] = 0                                          # a row with nothing selected
     mask[2, 5], mask[2, 5, 5] = 0, 1                        # the diagonal block alone
     mask[3, 6], mask[3, 6, 2] = 0, 1                        # one block, not the diagonal one
-    t = gu.to_device(x, dtype)
+    t = gu.to_device(x, dtype, layout="blhd" if B % 3 == 0 else "bhld")     # two sets of strides
     print(f"[generic] B={B} d={d} {dtype} L={L}", flush=True)
     O = torch.full_like(t["Q"], float("nan"))
     lse = torch.full(t["Q"].shape[:3], float("nan"), dtype=torch.float32, device="cuda:0")

@@ -28,6 +28,8 @@ def test_step_attention(batch, Hq, Hkv, T, L, sparse):
     Q = (torch.randn(batch, Hq, T, d, generator=g, device="cuda:0") * 1.5).bfloat16()
     K = torch.randn(batch, Hkv, L, d, generator=g, device="cuda:0").bfloat16()
     V = torch.randn(batch, Hkv, L, d, generator=g, device="cuda:0").bfloat16()
+    if T > 1 or batch > 1:                                  # heads inside positions: other strides than the default
+        Q, K, V = (t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for t in (Q, K, V))
     Nb, m0 = -(-L // B), (L - T) // B
     rows = Nb - m0
     mask = torch.ones(batch, Hq, rows, Nb, dtype=torch.uint8, device="cuda:0")
@@ -67,3 +69,40 @@ def test_step_attention(batch, Hq, Hkv, T, L, sparse):
     if finite.any():
         # scores and sums are held in 32 bits: a few 2^-24 of logits of magnitude 20
         assert (got - want_lse)[finite].abs().max() <= 1e-4
+
+
+@pytest.mark.parametrize("T,L", [(1, 2700), (4, 2700), (4, 2690)])
+def test_blocks_a_row_did_not_select_do_not_reach_it(T, L):
+    """Infinite and NaN keys and values in blocks that one head alone selected (and, across two query blocks, in the
+    second one): the rows without them are what they are with ordinary values there, bit for bit."""
+    import paper_2602_05853_amd as rr
+    B, dev = 128, "cuda:0"
+    g = torch.Generator(device=dev).manual_seed(L + T)
+    Q = torch.randn(1, 6, T, 128, generator=g, device=dev).bfloat16()
+    K = torch.randn(1, 1, L, 128, generator=g, device=dev).bfloat16()
+    V = torch.randn(1, 1, L, 128, generator=g, device=dev).bfloat16()
+    Nb, m0 = -(-L // B), (L - T) // B
+    rows = Nb - m0
+    mask = torch.ones(1, 6, rows, Nb, dtype=torch.uint8, device=dev)
+    mask[:, 1:, :, 3] = 0
+    mask[:, 1:, :, 7] = 0
+    for r in range(rows):
+        mask[:, :, r, m0 + r + 1:] = 0
+    bm = rr.rr_mask_from_dense(Q, K, mask.contiguous(), B)
+    ws = torch.empty(rr.rr_attn_workspace_bytes(Q, K, B), dtype=torch.uint8, device=dev)
+    clean = rr.rr_sparse_attn(Q, K, V, bm, workspace=ws).clone()
+    dense_clean = rr.rr_dense_attn(Q, K, V, B, workspace=ws).clone()
+    K2, V2 = K.clone(), V.clone()
+    K2[:, :, 3 * B:4 * B] = float("nan")
+    V2[:, :, 3 * B:4 * B] = float("nan")
+    V2[:, :, 7 * B + 5] = float("inf")
+    got = rr.rr_sparse_attn(Q, K2, V2, bm, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got[:, 1:], clean[:, 1:])
+    if rows == 2:                                           # dense: the second query block's keys are past the first one's rows
+        V3 = V.clone()
+        V3[:, :, (m0 + 1) * B:] = float("nan")
+        first = (m0 + 1) * B - (L - T)
+        got = rr.rr_dense_attn(Q, K, V3, B, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(got[:, :, :first], dense_clean[:, :, :first])
