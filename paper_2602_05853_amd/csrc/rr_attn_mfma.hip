@@ -957,7 +957,14 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // tile copies behind this row's last reads of the staging area.
     if (!have_row) { draw_issue(); draw_publish(); }
     __syncthreads();
-    if (!have_row) { step_rank(); step_row(); step_last(); }
+    if (!have_row) {
+        step_rank();
+        // The next draw may be published before another barrier is met (the next rank may have no row either, or a row
+        // without a block): not until every wave has read this ticket.
+        __syncthreads();
+        step_row();
+        step_last();
+    }
     step_done();                                            // (5)
   }
     if (kPersist && draws) {

@@ -120,3 +120,41 @@ def test_two_tiles_per_block_at_the_edges_of_rows_and_launches(L, Lq):
         ref = torch.softmax(s, 1) @ V[0, h // 4].float()
         assert (O1[0, h].float() - ref).abs().max().item() <= 2.5e-2, h
         assert (l1[0, h] - torch.logsumexp(s, 1)).abs().max().item() <= 2e-2, h
+
+
+def test_queue_launch_over_long_runs_of_ranks_without_work():
+    """Behind the first row of every workgroup come long runs of ranks that name no row, some followed by rows
+    that selected nothing: a workgroup then draws one ticket after the other with little in between, and all its waves
+    must follow each of them.  2048 rows against at most two workgroups per compute unit."""
+    p = rr()
+    L, Hq, Hkv, B = 8192, 32, 8, 128
+    Nb, G = L // B, Hq // Hkv
+    resident = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    assert Hq * Nb >= 2 * resident
+    g = torch.Generator(device="cuda:0").manual_seed(80)
+    Q, K, V = (torch.randn(1, h, L, 128, generator=g, device="cuda:0").bfloat16() for h in (Hq, Hkv, Hkv))
+    dense = torch.zeros(1, Hq, Nb, Nb, dtype=torch.uint8, device="cuda:0")
+    n = torch.arange(Nb, device="cuda:0")
+    dense[0, :, n, n] = 1
+    dense[0, 1::4, n, 0] = 1
+    dense[0, 2::4] = 0                                      # rows without a block
+    mask = p.rr_mask_from_dense(Q, K, dense, B)
+    first = resident // Hkv                                 # order entries that the workgroups start with
+    order = torch.arange(G * Nb, dtype=torch.int32, device="cuda:0").repeat(Hkv, 1)
+    order = order.reshape(Hkv, G, Nb).transpose(1, 2).reshape(Hkv, G * Nb).contiguous()     # empty rows between others
+    order[:, first:first + 40] = -1
+    order[:, first + 41:first + 60] = G * Nb
+    order[:, first + 70:first + 100:2] = -7
+    mask.row_order.copy_(order[None])
+    named = torch.zeros(Hkv, G * Nb, dtype=torch.bool, device="cuda:0")
+    for kv in range(Hkv):
+        ok = order[kv][(order[kv] >= 0) & (order[kv] < G * Nb)]
+        named[kv, ok.long()] = True
+    named = named.reshape(Hq, Nb).repeat_interleave(B, 1)[None, :, :, None]
+    ref = p.rr_sparse_attn(Q, K, V, dataclasses.replace(mask, queue=None, row_order=None))
+    for rep in range(5):
+        O = torch.full_like(Q, 7.0)
+        p.rr_sparse_attn(Q, K, V, mask, O=O)
+        torch.cuda.synchronize()
+        assert int(mask.queue.abs().sum().item()) == 0, rep
+        assert torch.equal(O, torch.where(named, ref, torch.full_like(ref, 7.0))), rep
