@@ -30,8 +30,19 @@
 // MFMA slot.  The softmax itself is pipelined over the slots (scale, exp2, bf16 rounding and row sum of
 // an element sit in four different slots), so that a wave never issues a vector instruction right behind
 // the one that produces its operand.  The running maximum is lazy: P is taken relative to a reference that is only moved
-// (with a rescale of O^T and the denominator) when a new maximum exceeds it by 2^8, which keeps the
-// common path branch-free and exact (all terms of a row share the reference).
+// (with a rescale of O^T and the denominator) when a lane's terms add up to far more than the reference's, which
+// keeps the common path branch-free (all terms of a row share the reference).
+//
+// Precision.  P is rounded to bf16 for the second product, and the denominator sums P as rounded: a row's weights add up
+// to one, and the error of a large weight w weighs 1 - w.  (What rounding took from the diagonal block's terms and
+// from those of a step that moved the reference is kept apart, for the log-sum-exp.)  A weight that the reference was
+// moved to is 1 and exact, so a row is the more precise the less a weight may exceed the reference.  Error against 64 bits,
+// 2-norm, of which the last rounding is 1.667e-3; moved beyond 2^8, 2^6, 2^5 (8 heads of 32):
+//   4096 tokens 1.811e-3, 1.804, 1.796; 65536 tokens 1.841, 1.832, 1.825; dense, 16384 tokens 1.806, 1.801, 1.797
+//   chunks: 1000 tokens at 20480 1.826, 1.810, 1.797; 2048 at 65536 1.853, 1.826, 1.812
+// With two key halves to a row, each with a reference of its own moved beyond 2^8, and the diagonal block's terms summed
+// unrounded, these were 1.816, 1.844, 1.816; 1.804, 1.825.  2^8 is below that for whole prompts, and 2^5 for launches in
+// parts, whose rows lie deep in the context (whole prompts spend 1-3 % more time at 2^5, 2048 tokens at 128K 2 %).
 //
 // Staging.  K and V tiles go global -> LDS directly (global_load_lds, 16 bytes per lane, no
 // staging registers), row-major, double-buffered one key block ahead.  K fragments are plain
@@ -62,8 +73,6 @@ constexpr int kCopies = kRowsPerWave / 4;            // copy instructions per wa
 constexpr int kTileBytes = kTileKeys * 256;          // one 64 x 128 bf16 tile
 constexpr int kLdsBytes = 4 * kTileBytes;            // K and V, two stages each
 constexpr int kOutRowBytes = 264;                    // 128 bf16 + 8 bytes of padding
-constexpr float kLazyLog2 = 8.0f;                    // move the softmax reference when exceeded by 2^8
-constexpr float kLazySum = 256.0f;                   // = 2^kLazyLog2: a lane's 16-term sum above it triggers the move
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
@@ -200,10 +209,13 @@ struct Wave {
     const lds_byte_t* lds;
     int lane, l32, gsel;
     float sl2;                         // log2(e) / sqrt(d)
+    float lazy, lazy_sum;              // how far above the softmax reference a score may lie: in log2 units, and 2^ that
+    bool tight;                        // a constant: no registers for two tiles of O^T outside their place, see move_reference
     bf16x8 qf[8];                      // Q^T operand: 16-wide d chunks
     f32x16 acc[4];                     // O^T: 32-row d tiles
     float mref;                        // softmax reference of the lane's query, log2 units
-    float lsum;                        // this lane's part of the denominator
+    float lsum;                        // this lane's part of the denominator: the sum of P as rounded
+    float lfix;                        // what rounding took from it where that is known, for the log-sum-exp
     // Per-lane LDS byte addresses.  The XOR swizzle makes the chunk part of an address
     // base ^ (32 * kc) for K and base ^ (64 * dt) for V.
     unsigned ka0;                      // K: row lane%32, chunk gsel, swizzled
@@ -269,23 +281,41 @@ __device__ __forceinline__ void pv_step(Wave& w, int buf, int t, const bf16x8 (&
     mfma_settle_acc(w.acc);
 }
 
-// exp2 of the 16 scores of a step against the current reference; fills P, returns sum and maximum.
-__device__ __forceinline__ void exp_all(const Wave& w, const f32x16& s, bf16x8 (&p)[2], float& psum, float& mx) {
-    const float nb = -w.mref;
+// P of a step's 16 scores against a reference: exp2, rounded; the sum of the rounded terms and of what rounding took.
+__device__ __forceinline__ void exp_all(const Wave& w, const f32x16& s, float ref, bf16x8 (&p)[2], float& psum, float& fix) {
+    const float nb = -ref;
+    bf16x2 ones;
+    ones[0] = (__bf16)1.0f;
+    ones[1] = (__bf16)1.0f;
+    float sum = 0.f;
     psum = 0.f;
-    mx = -__builtin_huge_valf();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const float e = __builtin_amdgcn_exp2f(fmaf(s[r], w.sl2, nb));
-        psum += e;
-        mx = fmaxf(mx, s[r]);
-        p[r >> 3][r & 7] = (__bf16)e;
+    for (int r = 0; r < 16; r += 2) {
+        const float e0 = __builtin_amdgcn_exp2f(fmaf(s[r], w.sl2, nb));
+        const float e1 = __builtin_amdgcn_exp2f(fmaf(s[r + 1], w.sl2, nb));
+        sum += e0;
+        sum += e1;
+        bf16x2 pr;
+        pr[0] = (__bf16)e0;
+        pr[1] = (__bf16)e1;
+        p[r >> 3][r & 7] = pr[0];
+        p[r >> 3][(r & 7) + 1] = pr[1];
+        psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, psum, false);
     }
+    fix = sum - psum;
+}
+__device__ __forceinline__ float max_of(const f32x16& s) {
+    float mx = -__builtin_huge_valf();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    return mx;
 }
 
 // Moves the softmax reference of the lane's query up to the new maximum, rescales O^T and the
-// denominator, and recomputes P of the step at hand.  Rare; entered by the whole wave.
-__device__ __forceinline__ void move_reference(Wave& w, const f32x16& s, bf16x8 (&p)[2], float& psum, float mx) {
+// denominator, and recomputes P of the step at hand.  Rare; entered by the whole wave.  (Where registers are short, each
+// tile of O^T is back in place before the next is taken; without that the ragged and persistent forms spill 12 to 25
+// registers: 32K tokens 3357 against 3296 us.  The plain form has room, and is 0.7 % faster without: 64K, 64 heads.)
+__device__ __forceinline__ void move_reference(Wave& w, const f32x16& s, bf16x8 (&p)[2], float& psum, float& fix, float mx) {
     mfma_settle_acc(w.acc);                             // O^T is about to be read by vector instructions
     float top = mx * w.sl2;
     top = fmaxf(top, __shfl_xor(top, 32));
@@ -294,24 +324,25 @@ __device__ __forceinline__ void move_reference(Wave& w, const f32x16& s, bf16x8 
     const float alpha = __builtin_amdgcn_exp2f(w.mref - use);   // 0 while the reference is -inf
     w.mref = nref;
     w.lsum *= alpha;
+    w.lfix *= alpha;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < 4; ++dt) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) w.acc[dt][r] *= alpha;
-    float sum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const float e = __builtin_amdgcn_exp2f(fmaf(s[r], w.sl2, -use));
-        sum += e;
-        p[r >> 3][r & 7] = (__bf16)e;
+        if (w.tight) asm volatile("" : "+a"(w.acc[dt]));
     }
-    psum = sum;
+    exp_all(w, s, use, p, psum, fix);
     mfma_settle_acc(w.acc);                             // ... and was written by them
 }
 
-__device__ __forceinline__ void finish_softmax(Wave& w, const f32x16& s, bf16x8 (&p)[2], float psum, float mx) {
-    if (__any(mx * w.sl2 > w.mref + kLazyLog2)) move_reference(w, s, p, psum, mx);
+// softmax of one 32-key step, nothing overlapped (the diagonal block)
+__device__ __forceinline__ void softmax_step(Wave& w, const f32x16& s, bf16x8 (&p)[2]) {
+    float psum, fix;
+    exp_all(w, s, w.mref, p, psum, fix);
+    const float mx = max_of(s);
+    if (__any(mx * w.sl2 > w.mref + w.lazy)) move_reference(w, s, p, psum, fix, mx);
     w.lsum += psum;
+    w.lfix += fix;
 }
 
 // Global -> LDS copies of one 128 x 128 bf16 tile, kCopies instructions per wave (4 rows each), issued
@@ -471,15 +502,14 @@ __device__ __forceinline__ void phase(Wave& w, const f32x16& scur, f32x16& snext
             SCHED_FENCE();
         }
     }
-    // A score more than 2^8 above the reference makes its term, hence the lane's sum of 16 terms,
+    // A score more than 2^8 (2^5) above the reference makes its term, hence the lane's sum of 16 terms,
     // exceed 2^8 (the first step of a row, whose reference is -inf, gives +inf): the sum is the
     // trigger, the maximum itself is only computed on the rare path.
     if (valid) {
-        if (__any(!(psum <= kLazySum))) {
-            float mx = -__builtin_huge_valf();
-#pragma unroll
-            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, scur[r]);
-            move_reference(w, scur, pcur, psum, mx);
+        if (__any(!(psum <= w.lazy_sum))) {
+            float fix;
+            move_reference(w, scur, pcur, psum, fix, max_of(scur));
+            w.lfix += fix;
         }
         w.lsum += psum;
     }
@@ -497,6 +527,7 @@ struct AttnKernelArgs {
     Geom g;
     AttnArgs a;
     float scale_log2;
+    float lazy_log2, lazy_sum;
 };
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef const __attribute__((address_space(4))) AttnKernelArgs* kernarg_ptr_t;
@@ -686,6 +717,9 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     w.lds = lds;
     w.lane = lane; w.l32 = lane & 31; w.gsel = lane >> 5;
     w.sl2 = scale_log2;
+    w.lazy = kargs->lazy_log2;
+    w.lazy_sum = kargs->lazy_sum;
+    w.tight = kRagged || kPersist;
     w.init_addresses();
     const int l32 = w.l32, gsel = w.gsel;
     const int kv = h / g.G;
@@ -760,6 +794,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         for (int r = 0; r < 16; ++r) w.acc[dt][r] = 0.f;
     w.mref = NEG_INF;
     w.lsum = 0.f;
+    w.lfix = 0.f;
 
     f32x16 sa, sb;
     bf16x8 pa[2], pb[2];
@@ -872,9 +907,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
                 for (int r = 0; r < 16; ++r)
                     if (8 * (r >> 2) + 4 * gsel + (r & 3) > l32) s[r] = NEG_INF;
             }
-            float psum, mx;
-            exp_all(w, s, pa, psum, mx);
-            finish_softmax(w, s, pa, psum, mx);
+            softmax_step(w, s, pa);
             pv_step(w, j >> 1, j & 1, pa);
         };
         diag_step(0, sa);
@@ -899,6 +932,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // ---- normalise, write ----
     {
         const float l = w.lsum + __shfl_xor(w.lsum, 32);
+        const float whole = l + (w.lfix + __shfl_xor(w.lfix, 32));
         const float inv = l > 0.f ? 1.0f / l : 0.f;
         unsigned char* ost = lds_generic + wv * (32 * kOutRowBytes);      // the tile buffers are free
         // row of Q / O of this wave's first query (negative in front of a step that starts inside its first
@@ -912,7 +946,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         float* lse_base = split ? a.part_lse + (long long)part * g.batch * g.Hq * rows_call : a.lse;
         float* lse = lse_base ? lse_base + ((long long)b * g.Hq + h) * rows_call + wrow0 : nullptr;
         if (planned && split) lse = a.part_lse + (long long)plan_slot * 128 + 32 * wv;   // a slot holds a whole tile
-        if (lse && gsel == 0 && l32 < rows_q && l32 >= rows_lo) lse[l32] = l > 0.f ? w.mref * 0.6931471805599453f + logf(l) : NEG_INF;
+        if (lse && gsel == 0 && l32 < rows_q && l32 >= rows_lo) lse[l32] = l > 0.f ? w.mref * 0.6931471805599453f + logf(whole) : NEG_INF;
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -1291,6 +1325,9 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
         if (pe != hipSuccess) return pe;
     }
     if (persist) grid = dim3((unsigned)resident);
+    // How far a weight may exceed the softmax reference before the reference moves up to it, see the head of the file: 2^8, or 2^5
+    // in launches whose rows are computed in parts.
+    const float lazy_log2 = planned || a.nsplit > 1 ? 5.0f : 8.0f;
     const int lds_bytes = kLdsBytes + (persist ? 16 : 0);
     auto launch = [&](auto kernel) -> hipError_t {
         hipError_t e = allow_dynamic_lds((const void*)kernel, lds_bytes);
@@ -1299,6 +1336,8 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
         ka.g = g;
         ka.a = a;
         ka.scale_log2 = scale_log2;
+        ka.lazy_log2 = lazy_log2;
+        ka.lazy_sum = exp2f(lazy_log2);
         hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds_bytes, st, ka);
         return hipGetLastError();
     };

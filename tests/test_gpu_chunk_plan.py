@@ -2,7 +2,9 @@
 parts, or no row is cut), a few long among short ones, none long.  Every output row against the same call without a workspace,
 which walks every row in one piece.  Both round the probabilities to bf16, relative to references that differ between
 them: each by at most 2^-9, so a result moves by at most 2^-8 sum(p |v|) <= 2^-8 max|v| (max|v| taken from the inputs,
-about 5.3) plus its own last rounding, 2^-8 of the value; the log-sum-exp is held in 32 bits."""
+about 5.3) plus its own last rounding, 2^-8 of the value.  The log-sum-exp is the logarithm of the sum of the rounded
+probabilities (unrounded where a step moved the reference), so each form's is off by at most log(1 + 2^-9): 2^-8 between
+the two, and typically far less, since a row sums hundreds of terms rounded either way."""
 import numpy as np
 import pytest
 import torch
@@ -42,6 +44,6 @@ def test_parts_fit_the_slots(Hq, Hkv, L, Lq, rows_kept):
     (a, la), (b, lb) = out
     assert torch.equal(torch.isinf(la), torch.isinf(lb))
     fin = torch.isfinite(la)
-    assert fin.any() and (la - lb)[fin].abs().max() <= 1e-5 * max(1.0, la[fin].abs().max().item())
+    assert fin.any() and (la - lb)[fin].abs().max() <= 2.0 ** -8 and (la - lb)[fin].abs().mean() <= 2.0 ** -12
     top = V.abs().max().float()
     assert ((a - b).abs() <= 2.0 ** -8 * torch.maximum(a.abs(), b.abs()) + 2.0 ** -8 * top).all()
