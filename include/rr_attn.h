@@ -249,6 +249,8 @@ int rr_sparse_attn(const rr_shape* shape, const void* Q, const void* K, const vo
 /*
  * Dense causal attention (the full-attention baseline of the paper's experiments): identical to
  * rr_sparse_attn with every block n <= m listed; B is the tile height used to walk the keys.
+ * (For bf16 / d = 128 / B = 128 the work on a row is split in one of two ways, by the number of rows and of key blocks of
+ * the call: the same row in calls of different sizes may differ by the rounding of the probabilities.)
  */
 int rr_dense_attn(const rr_shape* shape, const void* Q, const void* K, const void* V, int B,
                   void* O, float* lse, void* hip_stream);

@@ -18,9 +18,11 @@
 // of tile buffers and at most 256 registers per lane TWO workgroups share a compute unit, and one's start and end
 // run behind the other's tiles.
 // Measured against one workgroup of 8 waves per compute unit with 128 KB of tile buffers (a wave then owned 32
-// queries and one key half of a 128-key tile; the same MFMAs, LDS reads and copies per block), 32 / 8 heads: estimate
-// + sparse 8K tokens 316 -> 276 us, 128K 35.0 -> 32.8 ms, 64K / 64 heads 25.0 -> 22.8 ms, dense 16K 2.14 -> 2.02 ms,
-// eight packed prompts 1.73 -> 1.51 ms.
+// queries and one key half of a 128-key tile; the same MFMAs, LDS reads and copies per block), 32 / 8 heads, both on one
+// machine: estimate + sparse 8K tokens 317 -> 256 us, 128K 35.6 -> 33.9 ms, 64K / 64 heads 24.9 -> 23.6 ms, dense 16K 2.15
+// -> 2.01 ms, eight packed prompts 1.75 -> 1.49 ms.
+// A launch that takes as long as its longest row is the other way round: it runs the row with both halves side by side
+// (kWide; wide_rows_pay says when), the halves of a query merged in LDS at the end.
 //
 // Software pipeline.  On this chip the vector ALU instructions of a SIMD do not run in the shadow
 // of its MFMAs for more than a few cycles per MFMA (measured: 32 MFMAs + the softmax of 32 scores
@@ -58,6 +60,7 @@
 // position; query rows past the length work on a copy of the last real row and are not stored.
 #include "rr_common.hpp"
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -73,6 +76,7 @@ constexpr int kCopies = kRowsPerWave / 4;            // copy instructions per wa
 constexpr int kTileBytes = kTileKeys * 256;          // one 64 x 128 bf16 tile
 constexpr int kLdsBytes = 4 * kTileBytes;            // K and V, two stages each
 constexpr int kOutRowBytes = 264;                    // 128 bf16 + 8 bytes of padding
+constexpr int kXchgFloats = 67;                      // per lane, of a wide workgroup's second group: O^T, reference, sums
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
@@ -345,7 +349,7 @@ __device__ __forceinline__ void softmax_step(Wave& w, const f32x16& s, bf16x8 (&
     w.lfix += fix;
 }
 
-// Global -> LDS copies of one 128 x 128 bf16 tile, kCopies instructions per wave (4 rows each), issued
+// Global -> LDS copies of one 64 x 128 bf16 tile, kCopies instructions per wave (4 rows each), issued
 // as asm statements: the compiler would otherwise make every later LDS read wait for them (it
 // cannot tell that the reads go to the other buffer), which turns the prefetch into a blocking
 // copy.  The kernel waits for them itself (wait_vm) before the barrier that hands a buffer over.
@@ -547,8 +551,8 @@ __device__ __forceinline__ kernarg_ptr_t kernel_args() {
 #endif
 }
 
-template <bool kRagged, bool kPersist>
-__global__ void __launch_bounds__(kThreads, 2)
+template <bool kRagged, bool kPersist, bool kWide>
+__global__ void __launch_bounds__(kWide ? 2 * kThreads : kThreads, 2)
 k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // kRagged: the real length ends inside the last block (g.Lr < g.L) or the queries start inside their first
     // block (g.qoff > 0): clamped Q rows, a clamped copy of the partial diagonal tile, predicated stores.  Compiled apart so that the plain launch carries none of it
@@ -559,6 +563,10 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // dispatcher gave it) from the counter of its XCD, so that every rank keeps the XCD the order was made for
     // while the compute units of an XCD share its rows dynamically, and the next row is looked up while the
     // current one is merged and stored.
+    //
+    // kWide (launches whose time is that of a row, see launch_attn_mfma_bf16): two groups of four waves to a row, group
+    // hg with the keys 64 hg .. +63 of every block and tile buffers of its own; one workgroup per compute unit
+    // (the persistent form too).
     (void)kernel_arguments;
     extern __shared__ __align__(16) unsigned char lds_generic[];
     lds_byte_t* lds = (lds_byte_t*)lds_generic;
@@ -585,7 +593,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     nx.rank = -1; nx.live = false; nx.order_entry = 0;
     nx.b = nx.h = nx.mq = 0; nx.count_raw = nx.e0 = nx.elast = 0;
     const int xcd = (int)blockIdx.x & 7;
-    volatile lds_int_t* const ticket_slot = (volatile lds_int_t*)(lds + kLdsBytes);
+    volatile lds_int_t* const ticket_slot = (volatile lds_int_t*)(lds + (kWide ? 2 : 1) * kLdsBytes);
     int ticket = 0;                                         // lane 0 of wave 0
     auto draw_issue = [&]() {
         if (draws) ticket = atomicAdd(kernel_args<true>()->a.queue + kQueueStride * xcd, 1);
@@ -652,7 +660,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         step_row(); step_last(); step_done();
     }
 
-  constexpr bool kSplit = kRagged && !kPersist;          // the one instantiation that also serves split launches
+  constexpr bool kSplit = kRagged && !kPersist && !kWide;    // the one instantiation that also serves split launches
   for (;;) {
     // (The persistent form reads its arguments again for every row, and derives everything that depends on the
     // lane from a thread index the compiler takes for a new value each time: hoisted out of the row loop, the
@@ -660,7 +668,8 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     int tid = threadIdx.x;
     if (kPersist) asm volatile("" : "+v"(tid));
     const int lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hg = kWide ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;                  // the wave's group
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6) - 4 * hg;                     // its place in that
     const kernarg_ptr_t kargs = kernel_args<kPersist>();
     const Geom g = kargs->g;
     const AttnArgs a = kargs->a;
@@ -714,7 +723,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     const int m = mq + (a.Nb - Nbq);                    // query block inside the context: causal limit of the row
 
     Wave w;
-    w.lds = lds;
+    w.lds = lds + hg * kLdsBytes;
     w.lane = lane; w.l32 = lane & 31; w.gsel = lane >> 5;
     w.sl2 = scale_log2;
     w.lazy = kargs->lazy_log2;
@@ -729,7 +738,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     st.Kp = reinterpret_cast<const unsigned short*>(a.K) + b * g.ksb + kv * g.ksh;
     st.Vp = reinterpret_cast<const unsigned short*>(a.V) + b * g.ksb + kv * g.ksh;
     st.ksl = g.ksl;
-    st.lds0 = (unsigned)(uintptr_t)lds;
+    st.lds0 = (unsigned)(uintptr_t)w.lds;
     st.wv = wv;
     st.init(lane);
 
@@ -772,6 +781,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     };
     // the entries a row needs before its first tile: the first and the last (the persistent form has them already)
     const int e0_raw = kPersist ? clamp_block(pf_e0) : block_raw(0);
+    const int e1_raw = kWide ? block_raw(1) : 0;
     const int elast_raw = kPersist ? clamp_block(pf_elast) : block_raw(count > 0 ? count - 1 : 0);
     // the diagonal block, if listed, is the last entry; it is taken after the pipelined blocks
     const bool has_diag = last_part && count > 0 && __builtin_amdgcn_readfirstlane(elast_raw) == m;
@@ -808,6 +818,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         // zero P against the K(0) tile, which is there and finite), iteration 2 cnt - 1 finishes the
         // last PV products (its QK products are those of the diagonal block's first half, or of whatever the idle
         // K buffer holds, and are then never used).
+        // A wide workgroup's group walks one tile to a block, its own half: tile tau = i, in buffers tau & 1.
         int n_next = __builtin_amdgcn_readfirstlane(e0_raw);     // block i + 1 of trip i
         // A partial block m is only ever read by the diagonal pass, whose copies stay inside the real length:
         // an entry of a malformed list that names it in the middle of the row is moved to block m - 1.
@@ -815,7 +826,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         // would move the wait for the list load, and with it a stall, into the middle of the iteration.
         auto whole_tile = [&](int n) { return (partial && n == m && m > 0) ? m - 1 : n; };
         n_next = whole_tile(n_next);
-        st.issue_k(n_next, 0, 0);
+        st.issue_k(n_next, hg, 0);
         wait_vm();
         // The Q^T operand must be complete in its registers here.  Its loads may target the accumulation
         // registers directly, and their first reader would then be an MFMA inside the tile loop: the compiler
@@ -838,39 +849,57 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         // thrown away by clearing O^T afterwards.  (The fill must stay an ordinary trip of the one loop: peeled
         // off, the compiler knows O^T to be zero there, builds the accumulator tuples of the asm MFMAs from
         // copies and moves the results right behind each MFMA without the wait states an MFMA result needs.)
-        auto tile = [&](auto half, bool fill, bool more, int nv) {
-            constexpr int HF = decltype(half)::value;
+        auto tile = [&](auto half, bool fill, bool more, int nk, int nv) {
+            constexpr int HF = decltype(half)::value;                  // tau & 1
             constexpr int KO = (HF ^ 1) * kTileBytes;
             constexpr int VO = HF * kTileBytes;
-            // phase 2 tau + 1: softmax | PV(2 tau) QK(2 tau + 2) | fetch K(tau+2) and V(tau+1)
-            phase<true, VO, KO>(w, sb, sa, pa, pb, !fill, st, st.k_src(n_next, HF), st.k_dst(HF),
-                                st.v_src(nv, HF ^ 1), st.v_dst(HF ^ 1));
+            // phase 2 tau + 1: softmax | PV(2 tau) QK(2 tau + 2) | fetch K(tau+2) of block nk and V(tau+1) of block nv
+            phase<true, VO, KO>(w, sb, sa, pa, pb, !fill, st, st.k_src(nk, kWide ? hg : HF), st.k_dst(HF),
+                                st.v_src(nv, kWide ? hg : HF ^ 1), st.v_dst(HF ^ 1));
             // phase 2 tau + 2: softmax | PV(2 tau + 1) QK(2 tau + 3)
             phase<false, VO + 32 * 256, KO + 32 * 256>(w, sa, sb, pb, pa, more, st, nullptr, 0, nullptr, 0);
         };
+        auto clear_acc = [&]() {
+            mfma_settle_acc(w.acc);
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) w.acc[dt][r] = 0.f;
+            mfma_settle_acc(w.acc);
+        };
         using std::integral_constant;
-        for (int i = -1; i < cnt; ++i) {
-            if (i >= 0) {
+        if constexpr (kWide) {
+            int n2 = whole_tile(__builtin_amdgcn_readfirstlane(last_entry >= 1 ? e1_raw : e0_raw));   // block i + 2 of trip i
+            auto iteration = [&](int i, auto parity, bool fill) {
                 __syncthreads();
-                tile(integral_constant<int, 0>{}, false, true, n_cur);
+                const int n3_raw = entry_raw(i + 3);                  // requested in front of the copies, as below
+                tile(parity, fill, i + 1 < cnt, n2, n_next);
+                if (fill) clear_acc();
                 wait_vm();
+                n_next = n2;
+                n2 = whole_tile(__builtin_amdgcn_readfirstlane(n3_raw));
+            };
+            for (int i = -1; i < cnt; i += 2) {
+                iteration(i, integral_constant<int, 1>{}, i < 0);
+                if (i + 1 < cnt) iteration(i + 1, integral_constant<int, 0>{}, false);
             }
-            __syncthreads();
-            // list entry i + 2, wanted at the end of this trip: requested in front of the tile copies, so that it
-            // is back long before the wait for them (loads complete in order)
-            const int n2_raw = entry_raw(i + 2);
-            tile(integral_constant<int, 1>{}, i < 0, i + 1 < cnt, n_next);
-            if (i < 0) {
-                mfma_settle_acc(w.acc);
-#pragma unroll
-                for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) w.acc[dt][r] = 0.f;
-                mfma_settle_acc(w.acc);
+        } else {
+            for (int i = -1; i < cnt; ++i) {
+                if (i >= 0) {
+                    __syncthreads();
+                    tile(integral_constant<int, 0>{}, false, true, n_next, n_cur);
+                    wait_vm();
+                }
+                __syncthreads();
+                // list entry i + 2, wanted at the end of this trip: requested in front of the tile copies, so that it
+                // is back long before the wait for them (loads complete in order)
+                const int n2_raw = entry_raw(i + 2);
+                tile(integral_constant<int, 1>{}, i < 0, i + 1 < cnt, n_next, n_next);
+                if (i < 0) clear_acc();
+                wait_vm();
+                n_cur = n_next;
+                n_next = whole_tile(__builtin_amdgcn_readfirstlane(n2_raw));
             }
-            wait_vm();
-            n_cur = n_next;
-            n_next = whole_tile(__builtin_amdgcn_readfirstlane(n2_raw));
         }
         mfma_settle_acc(w.acc);
         mfma_settle_s(sa);
@@ -883,24 +912,26 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         // the last of them through the mask.  Half hf sits in buffers hf; after the pipeline S of the first half
         // is in sa and sb already, and only the second half of V is still to come. ----
         __syncthreads();                                    // the pipeline is done; its last copies have landed
-        if (ahead) {
-            st.issue_v(m, 1, 1);
-        } else {
+        // buffers of half hf
+        auto buffer_of = [&](int hf) { return kWide ? (ahead ? cnt & 1 : 0) : hf; };
+        if (!ahead) {
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
+            for (int k = 0; k < (kWide ? 1 : 2); ++k) {
+                const int hf = kWide ? hg : k;
                 if (partial) {
-                    st.issue_partial(st.Kp, m, hf, st.k_dst(hf), false, tile_rows, lane);
-                    st.issue_partial(st.Vp, m, hf, st.v_dst(hf), true, tile_rows, lane);
+                    st.issue_partial(st.Kp, m, hf, st.k_dst(buffer_of(hf)), false, tile_rows, lane);
+                    st.issue_partial(st.Vp, m, hf, st.v_dst(buffer_of(hf)), true, tile_rows, lane);
                 } else {
-                    st.issue_k(m, hf, hf);
-                    st.issue_v(m, hf, hf);
+                    st.issue_k(m, hf, buffer_of(hf));
+                    st.issue_v(m, hf, buffer_of(hf));
                 }
             }
             wait_vm();
             __syncthreads();
-            qk_step(w, 0, 0, sa);
-            if (wv >= 1) qk_step(w, 0, 1, sb);
+        } else if (!kWide) {
+            st.issue_v(m, 1, 1);
         }
+        auto scores = [&](int j, f32x16& s) { qk_step(w, buffer_of(j >> 1), j & 1, s); };
         auto diag_step = [&](int j, f32x16& s) {            // 32-key step j of the block
             if (j == wv) {
 #pragma unroll
@@ -908,33 +939,64 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
                     if (8 * (r >> 2) + 4 * gsel + (r & 3) > l32) s[r] = NEG_INF;
             }
             softmax_step(w, s, pa);
-            pv_step(w, j >> 1, j & 1, pa);
+            pv_step(w, buffer_of(j >> 1), j & 1, pa);
         };
-        diag_step(0, sa);
-        if (wv >= 1) diag_step(1, sb);
-        if (ahead) {
-            wait_vm();
-            __syncthreads();
+        // the steps of the first half, or of the group's own one
+        if (!ahead && 2 * hg <= wv) {
+            scores(2 * hg, sa);
+            if (2 * hg + 1 <= wv) scores(2 * hg + 1, sb);
         }
-        if (wv >= 2) {
-            qk_step(w, 1, 0, sa);
-            diag_step(2, sa);
-        }
-        if (wv >= 3) {
-            qk_step(w, 1, 1, sb);
-            diag_step(3, sb);
+        if (2 * hg <= wv) diag_step(2 * hg, sa);
+        if (2 * hg + 1 <= wv) diag_step(2 * hg + 1, sb);
+        if (!kWide) {
+            if (ahead) {
+                wait_vm();
+                __syncthreads();
+            }
+            if (wv >= 2) {
+                scores(2, sa);
+                diag_step(2, sa);
+            }
+            if (wv >= 3) {
+                scores(3, sb);
+                diag_step(3, sb);
+            }
         }
     }
     if (kPersist) draw_publish();
     __syncthreads();
     if (kPersist) step_rank();                              // (2): the order entry arrives during the normalisation
 
-    // ---- normalise, write ----
-    {
-        const float l = w.lsum + __shfl_xor(w.lsum, 32);
-        const float whole = l + (w.lfix + __shfl_xor(w.lfix, 32));
+    // ---- a wide workgroup: the second group hands its half over; normalise, write ----
+    float l = w.lsum + __shfl_xor(w.lsum, 32);
+    float whole = l + (w.lfix + __shfl_xor(w.lfix, 32));
+    float* const xch = reinterpret_cast<float*>(lds_generic) + wv * (kXchgFloats * 64) + lane;     // the tile buffers are free
+    float f0 = 1.f, f1 = 0.f;                               // weights of the two halves
+    if constexpr (kWide) {
+        if (hg == 1) {
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) xch[(dt * 16 + r) * 64] = w.acc[dt][r];
+            xch[64 * 64] = w.mref;
+            xch[65 * 64] = l;
+            xch[66 * 64] = whole;
+        }
+        __syncthreads();
+        if (hg == 0) {
+            const float m0 = w.mref, m1 = xch[64 * 64];
+            const float mm = fmaxf(m0, m1);
+            f0 = m0 == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(m0 - mm);
+            f1 = m1 == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
+            l = l * f0 + xch[65 * 64] * f1;
+            whole = whole * f0 + xch[66 * 64] * f1;
+            w.mref = mm;
+        }
+    }
+    if (hg == 0) {
         const float inv = l > 0.f ? 1.0f / l : 0.f;
-        unsigned char* ost = lds_generic + wv * (32 * kOutRowBytes);      // the tile buffers are free
+        const float w0 = kWide ? f0 * inv : inv, w1 = f1 * inv;
+        unsigned char* ost = lds_generic + (kWide ? kWaves * kXchgFloats * 256 : 0) + wv * (32 * kOutRowBytes);
         // row of Q / O of this wave's first query (negative in front of a step that starts inside its first
         // block), and the rows of the wave that exist: rows_lo <= x < rows_q (may be empty in the ragged form)
         const long long wrow0 = (long long)mq * 128 + 32 * wv - (kRagged ? g.qoff : 0);
@@ -953,7 +1015,10 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
             for (int rg = 0; rg < 4; ++rg) {
                 float v[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = w.acc[dt][4 * rg + e] * inv;
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = w.acc[dt][4 * rg + e] * w0;
+                    if (kWide) v[e] = fmaf(xch[(dt * 16 + 4 * rg + e) * 64], w1, v[e]);
+                }
                 if (split) {
                     // a part's result stays fp32 (the merge rounds once, at the end): straight from the
                     // registers, 16 bytes per lane
@@ -984,6 +1049,9 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
             if (!split && row < rows_q && row >= rows_lo) *reinterpret_cast<u32x4*>(Op + (long long)row * g.qsl + 8 * ch) = o;
         }
         if (kPersist) step_last();                          // (4): count and first entry came in during the stores
+    } else if (kPersist) {
+        step_row();                                         // the waves that only handed their half over: (3), (4)
+        step_last();
     }
    }  // have_row
     if (!kPersist) break;
@@ -1035,16 +1103,15 @@ int interleave_groups(const Geom& g) {
 
 constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens, see launch_attn_mfma_bf16
 
-// workgroups of a persistent launch: two per compute unit, as many as it holds at once, a multiple of 8 so that
-// workgroup i sits on XCD i mod 8
-int persistent_workgroups() {
+// compute units of the present device, a multiple of 8 so that workgroup i of a persistent launch sits on XCD i mod 8
+int compute_units() {
     static std::atomic<int> cached[64];                    // zero-initialised; per device, written once
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
     int n = cached[dev].load(std::memory_order_relaxed);
     if (n == 0) {
         if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        n = 2 * n / 8 * 8;
+        n = n / 8 * 8;
         cached[dev].store(n, std::memory_order_relaxed);
     }
     return n;
@@ -1299,6 +1366,21 @@ hipError_t launch_attn_combine(const Geom& g, const AttnArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
+// Eight waves to a row, four of them per key half, instead of four waves with all keys: a long row takes 1.57 us per block
+// instead of 2.1 (2.6 with a neighbour on the compute unit), but nothing runs behind its start and end.  It pays where a launch
+// takes as long as its longest row: few rows, or sparse calls whose protected last row keeps every block.  The counts are on
+// the device, so the rule goes by the number of rows and the length of the context; and it does not ask whether the call
+// has a list, so that a list of every block gives the dense call's result to the bit.  Measured, us, four waves -> eight:
+//   sparse, tau 0.9 unless said: 2048 tokens 8 / 2 heads (128 rows) 42 -> 39; 3072, 16 / 4 (384) 62 -> 56; 8192, 8 / 2 (512) 148
+//     -> 112, 16 / 4 (1024) 161 -> 127, at tau 0.95 182 -> 166; 65536, 8 / 2 (4096) 2197 -> 1962, at tau 0.95 4634 -> 4873
+//   steps and chunks at 128K without a workspace, 32 / 8: 1 token 2175 -> 1642, 2048 (512 rows) 2654 -> 1649, 8192 (2048) 2735 -> 2056
+//   not taken: 512, 32 / 8 (128) 20.2 -> 21.4; 2048, 32 / 8 (512) 54 -> 52; 4096, 32 / 8 (1024) 93 -> 94, at tau 0.95 101 -> 114; 12000,
+//     16 / 4 (1504) 246 -> 242, at tau 0.95 311 -> 350; 32768, 16 / 4 (4096) 1178 -> 1078, at tau 0.95 2072 -> 2192; 98304, 8 / 2 (6144)
+//     4117 -> 4363
+//   dense: 4096, 8 / 2 (256) 79 -> 69; 8192, 8 / 2 (512) 182 -> 162, 16 / 4 (1024) 280 -> 304; 16384, 4 / 1 (512) 335 -> 283, 8 / 2 (1024)
+//     524 -> 546; 1000 at 20480, 32 / 8 (256) 385 -> 329, 2048 at 128K (512) 3885 -> 3926; not taken: 2048, 32 / 8 (512) 56 -> 69
+bool wide_rows_pay(int Nb, long long rows) { return rows <= std::min<long long>(15ll * Nb + 64, 5000); }
+
 hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_t st) {
     AttnArgs a = a_in;
     a.interleave = interleave_groups(g);
@@ -1309,12 +1391,14 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     const bool ragged = g.Lr != g.L || g.qoff != 0 || a.nsplit > 1 || planned;   // split launches use the ragged instantiation
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     const long long rows = (long long)g.batch * g.Hq * (g.Lq / 128);
-    const int resident = persistent_workgroups();
+    const bool wide = a.nsplit == 1 && !planned && wide_rows_pay(a.Nb, rows);
+    // workgroups the chip holds at once
+    const int resident = (wide ? 1 : 2) * compute_units();
     // Persistent workgroups pay where rows are short, i.e. where the start of a row is a visible share of it, and
     // a workgroup takes several: measured with two workgroups per compute unit, estimate + sparse against one
     // workgroup per row: 280 -> 274 us at 8K tokens (4 rows each), 905 -> 898 us at 18K, level at 32K (and beyond: the
     // launch is limited by power there, not by the gaps between rows); with fewer rows than workgroups the look-ahead only
-    // costs (1139 tokens, 252 rows: 67 against 72 us).
+    // costs (1139 tokens, 252 rows: 67 against 72 us).  Wide rows, attention alone: 2048 tokens, 28 / 4 heads 62 -> 47 us.
     const bool persist = a.row_order != nullptr && a.queue != nullptr && resident >= 8 && a.Nb <= kPersistMaxBlocks &&
                          a.nsplit == 1 && !planned && rows >= resident;
     const unsigned grid_rows = grid_size(g, g.Lq / 128, a.row_order != nullptr);
@@ -1328,7 +1412,7 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     // How far a weight may exceed the softmax reference before the reference moves up to it, see the head of the file: 2^8, or 2^5
     // in launches whose rows are computed in parts.
     const float lazy_log2 = planned || a.nsplit > 1 ? 5.0f : 8.0f;
-    const int lds_bytes = kLdsBytes + (persist ? 16 : 0);
+    const int lds_bytes = (wide ? 2 : 1) * kLdsBytes + (persist ? 16 : 0);
     auto launch = [&](auto kernel) -> hipError_t {
         hipError_t e = allow_dynamic_lds((const void*)kernel, lds_bytes);
         if (e != hipSuccess) return e;
@@ -1338,11 +1422,13 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
         ka.scale_log2 = scale_log2;
         ka.lazy_log2 = lazy_log2;
         ka.lazy_sum = exp2f(lazy_log2);
-        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds_bytes, st, ka);
+        hipLaunchKernelGGL(kernel, grid, dim3((wide ? 2 : 1) * kThreads), lds_bytes, st, ka);
         return hipGetLastError();
     };
-    if (persist) return ragged ? launch(k_attn_mfma_bf16<true, true>) : launch(k_attn_mfma_bf16<false, true>);
-    const hipError_t e = ragged ? launch(k_attn_mfma_bf16<true, false>) : launch(k_attn_mfma_bf16<false, false>);
+    if (wide && persist) return ragged ? launch(k_attn_mfma_bf16<true, true, true>) : launch(k_attn_mfma_bf16<false, true, true>);
+    if (wide) return ragged ? launch(k_attn_mfma_bf16<true, false, true>) : launch(k_attn_mfma_bf16<false, false, true>);
+    if (persist) return ragged ? launch(k_attn_mfma_bf16<true, true, false>) : launch(k_attn_mfma_bf16<false, true, false>);
+    const hipError_t e = ragged ? launch(k_attn_mfma_bf16<true, false, false>) : launch(k_attn_mfma_bf16<false, false, false>);
     if (e != hipSuccess) return e;
     if (planned) {
         const long long rows_total = (long long)g.batch * g.Hq * (g.Lq / 128);

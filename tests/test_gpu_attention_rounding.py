@@ -5,8 +5,8 @@ where a row is that block alone, and, in a chunk of a longer context with the wo
 
 Bound.  The denominator sums the rounded probabilities, so the error of the large weight w leaves delta (1 - w): in the
 first case 1 - w <= 1/17, 2.1e-4.  In the chunk a weight more than 2^5 above the reference becomes the reference and is
-exact; of the other 255 keys the 58 at most that come after it are rounded, by 2^-9: 3.6e-4 of the sum.  A channel's last rounding is at most 2^-9, 0.58 of that in the mean square,
-and the mean of 128 channels of random mantissas is off by 4 x 0.58 x 2^-9 / sqrt(128) = 4e-4 at most.  A weight that is
+exact; of the other 255 keys the 58 at most that come after it are rounded, by 2^-9: 3.6e-4 of the sum.  A channel's last
+rounding is at most 2^-8, 0.58 of that in the mean square, and the mean of 128 channels of random mantissas is off by 4 x 0.58 x 2^-8 / sqrt(128) = 8e-4 at most.  A weight that is
 rounded in the numerator alone is off by 3e-3, one that stays 2^6 or 2^7 above the reference by 2.3e-3."""
 import math
 
@@ -81,6 +81,6 @@ def test_large_weights_are_not_rounded_alone(case, k, form):
     off = (O[0][:, seen].double() / (math.exp(score) / total * V[0, 0, int(at[0])].double())).mean(-1) - 1
     lse_off = (lse[0][:, seen].double() - math.log(total)).abs().max().item()
     print(f"[rounding] {case} 2^{k} {form}: mean error {off.abs().max().item():.2e}, lse {lse_off:.1e}", flush=True)
-    assert off.abs().max().item() <= (2.1e-4 if case == "diagonal" else 3.6e-4) + 4e-4
+    assert off.abs().max().item() <= (2.1e-4 if case == "diagonal" else 3.6e-4) + 8e-4
     # the diagonal block's terms are known unrounded: fp32 sums and exponentials of scores of magnitude 5
     assert lse_off <= (1e-5 if case == "diagonal" else 3.6e-4)

@@ -1,10 +1,10 @@
 """Planned chunk launches whose rows need parts of different lengths: all rows long (the slots hold them only with longer
 parts, or no row is cut), a few long among short ones, none long.  Every output row against the same call without a workspace,
 which walks every row in one piece.  Both round the probabilities to bf16, relative to references that differ between
-them: each by at most 2^-9, so a result moves by at most 2^-8 sum(p |v|) <= 2^-8 max|v| (max|v| taken from the inputs,
-about 5.3) plus its own last rounding, 2^-8 of the value.  The log-sum-exp is the logarithm of the sum of the rounded
-probabilities (unrounded where a step moved the reference), so each form's is off by at most log(1 + 2^-9): 2^-8 between
-the two, and typically far less, since a row sums hundreds of terms rounded either way."""
+them: each by at most 2^-8, and by half of that and less where hundreds of terms are rounded either way, so a result moves
+by at most 2^-8 sum(p |v|) <= 2^-8 max|v| (max|v| taken from the inputs, about 5.3) plus its own last rounding, 2^-8 of the value.  The log-sum-exp is the logarithm of the sum of the rounded
+probabilities (unrounded where a step moved the reference), so likewise 2^-8 between the two
+forms, and far less in the mean."""
 import numpy as np
 import pytest
 import torch
