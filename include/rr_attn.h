@@ -242,6 +242,9 @@ int rr_estimate_static(const rr_shape* shape, const void* Q, const void* K, int 
  *   O    [batch, Hq, L, d] in the layout and dtype of Q.
  *   lse  optional [batch, Hq, L] fp32 contiguous: log of the softmax denominator (natural log,
  *        logits already scaled by 1/sqrt(d)); NULL = not written.
+ * An infinite element of V makes its channel infinite in every row that attends its key (NaN where infinities of both
+ * signs meet); blocks that a row did not select do not reach it.  A row of the key's own query block in front of the
+ * key, whose probability of it is zero, gets NaN in that channel, as zero times infinity does in the plain formula.
  */
 int rr_sparse_attn(const rr_shape* shape, const void* Q, const void* K, const void* V,
                    const rr_mask* mask, void* O, float* lse, void* hip_stream);

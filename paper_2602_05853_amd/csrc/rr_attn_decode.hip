@@ -116,13 +116,6 @@ k_attn_decode(Geom g, DecodeArgs da) {
 
     f32x4 acc[QT][8];
     float ref[QT], lsum[QT];
-#pragma unroll
-    for (int u = 0; u < QT; ++u) {
-        ref[u] = NEG_INF;
-        lsum[u] = 0.f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[u][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
     // rows of a tile this lane reads, relative to its first key; keys past the context: a copy of the last, masked
     const long long k_off = (long long)x * g.ksl;
     long long v_off[4];
@@ -142,6 +135,14 @@ k_attn_decode(Geom g, DecodeArgs da) {
             else kf[tl].load(K + (long long)min(key0 + 16 * tl + x, g.Lr - 1) * g.ksl, 128, gq);
         }
     };
+    auto walk = [&](auto careful) {
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        ref[u] = NEG_INF;
+        lsum[u] = 0.f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[u][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     if (nact > 0) load_keys(0);
     for (int i = 0; i < nact; ++i) {
         typename F::V vf;
@@ -161,6 +162,7 @@ k_attn_decode(Geom g, DecodeArgs da) {
             for (int tl = 0; tl < 2; ++tl) s[u][tl] = f32x4{0.f, 0.f, 0.f, 0.f};
         F::template qk<QT>(s, kf, qf);
         const unsigned sel_now = sel;
+        const int key_now = key0;
         if (sel != all || key0 + 31 > g.q0) {
 #pragma unroll
             for (int u = 0; u < QT; ++u)
@@ -174,38 +176,36 @@ k_attn_decode(Geom g, DecodeArgs da) {
                     s[u][tl] = v;
                 }
         }
-        if (i + 1 < nact) load_keys(i + 1);                  // travels during the softmax and the second product
+        // travels during the softmax and the second product (the careful walk has no registers for it)
+        if (!decltype(careful)::value && i + 1 < nact) load_keys(i + 1);
         float p[QT][8];
 #pragma unroll
         for (int u = 0; u < QT; ++u) frag_softmax<2, 8>(s[u], da.scale_log2, ref[u], lsum[u], acc[u], p[u]);
-        // A row takes nothing from a block it did not select.  Its probabilities there are zero, which is enough unless the
-        // values are not finite: then (rare) the accumulators wait in the wave's share of the merge area meanwhile.
-        bool apart = false;
-        if (sel_now != all) {
-            unsigned bad = 0u;                               // an exponent of all ones carries into the sign's place
+        if constexpr (!decltype(careful)::value) {
+            F::template pv<QT, false>(acc, vf, p);
+        } else {
+            // The values of keys past the context are left out, and a row takes nothing from a block it did not select: its
+            // accumulators wait in the wave's share of the merge area meanwhile.
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) bad |= (vf.v[k][e] & 0x7F807F80u) + 0x00800080u;
-            apart = __any((bad & 0x80008000u) != 0u);
-        }
-        f32x4* const aside = reinterpret_cast<f32x4*>(&s_o[w][0][0]) + lane;
-        if (apart) {
+            for (int k = 0; k < 8; ++k) F::drop(vf, k, key_now + 16 * (k >> 2) + 4 * gq + (k & 3) >= g.Lr);
+            f32x4* const aside = reinterpret_cast<f32x4*>(&s_o[w][0][0]) + lane;
 #pragma unroll
             for (int u = 0; u < QT; ++u)
 #pragma unroll
                 for (int c = 0; c < 8; ++c) aside[64 * (8 * u + c)] = acc[u][c];
-        }
-        F::template pv<QT>(acc, vf, p);
-        if (apart) {
+            F::template pv<QT, true>(acc, vf, p);
 #pragma unroll
             for (int u = 0; u < QT; ++u)
                 if ((sel_now & mine[u]) == 0u) {
 #pragma unroll
                     for (int c = 0; c < 8; ++c) acc[u][c] = aside[64 * (8 * u + c)];
                 }
+            if (i + 1 < nact) load_keys(i + 1);
         }
     }
+    };
+    walk(std::false_type{});
+    if (has_nan(acc)) walk(std::true_type{});
 
     // the four waves: the part's normalised output and its natural-log sum of exponentials
 #pragma unroll

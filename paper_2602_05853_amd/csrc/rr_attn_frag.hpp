@@ -6,6 +6,11 @@
 // consecutive keys of one channel per lane; which channel a lane's row stands for is free, so lane x = lane % 16 loads
 // W consecutive channels W x .. W x + W - 1 of each of its keys and these W values belong to W different tiles: with
 // fp32 they are the fragments as loaded, with bf16 one byte permutation per register pairs two keys.
+//
+// Values that are not finite.  A product of tiles also multiplies what a row does not take: probabilities of zero (keys
+// behind the end of a block, blocks of another row's list) and the zero terms of a split probability.  Zero times
+// infinity is not a number, and sums keep that, so a wave that finds one in its result (has_nan) takes its keys once more with
+// such values left out (kCareful).  Checking every value as it is loaded was vector work on every key.
 #pragma once
 #include "rr_common.hpp"
 
@@ -87,7 +92,12 @@ template <int NT, int TL> struct Frag<float, NT, TL> {
                     for (int u = 0; u < QT; ++u)
                         s[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t].k[i][e], qf[u].k[i][e], s[u][t], 0, 0, 0);
     }
-    template <int QT>
+    // the values of key slot `key` where `gone`: zero
+    __device__ static __forceinline__ void drop(V& v, int key, bool gone) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) v.v[key][t] = gone ? 0.f : v.v[key][t];
+    }
+    template <int QT, bool kCareful>
     __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][4 * TL]) {
 #pragma unroll
         for (int key = 0; key < 4 * TL; ++key)
@@ -147,7 +157,12 @@ template <int NT, int TL> struct Frag<bf16_t, NT, TL> {
                     s[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t].k[i]),
                                                                       __builtin_bit_cast(bf16x8, qf[u].k[i]), s[u][t], 0, 0, 0);
     }
-    template <int QT>
+    __device__ static __forceinline__ void drop(V& v, int key, bool gone) {
+#pragma unroll
+        for (int i = 0; i < (NT + 1) / 2; ++i) v.v[key][i] = gone ? 0u : v.v[key][i];
+    }
+    // kCareful: the lower two terms, which may be zero where the probability is not, take finite values only
+    template <int QT, bool kCareful>
     __device__ static __forceinline__ void pv(f32x4 (&acc)[QT][NT], const V& v, const float (&p)[QT][4 * TL]) {
         // p = hi + mid + lo, every term the leading 8 significant bits of what is left (truncated, so exact)
         u32x4 plane[QT][3];
@@ -174,13 +189,20 @@ template <int NT, int TL> struct Frag<bf16_t, NT, TL> {
             const unsigned sel = (t & 1) ? 0x07060302u : 0x05040100u;
 #pragma unroll
             for (int j = 0; j < 4; ++j) vt[j] = __builtin_amdgcn_perm(v.v[2 * j + 1][t / 2], v.v[2 * j][t / 2], sel);
-            const bf16x8 vb = __builtin_bit_cast(bf16x8, vt);
+            u32x4 vf = vt;
+            if (kCareful) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {        // an exponent of all ones carries into the sign's place
+                    const unsigned bad = ((vt[j] & 0x7F807F80u) + 0x00800080u) & 0x80008000u;
+                    vf[j] = vt[j] & ~(bad | (bad - (bad >> 15)));
+                }
+            }
 #pragma unroll
             for (int pl = 2; pl >= 0; --pl)          // the small terms first
 #pragma unroll
                 for (int u = 0; u < QT; ++u)
-                    acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, __builtin_bit_cast(bf16x8, plane[u][pl]),
-                                                                        acc[u][t], 0, 0, 0);
+                    acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pl > 0 ? vf : vt),
+                                                                        __builtin_bit_cast(bf16x8, plane[u][pl]), acc[u][t], 0, 0, 0);
         }
     }
 };
@@ -221,6 +243,20 @@ __device__ __forceinline__ void frag_softmax(const f32x4 (&s)[TL], float scale_l
         }
     }
     lsum += sum;
+}
+
+// Is any of the wave's accumulators not a number?  (Or its sum not one, which infinities of both signs also give.)
+template <int QT, int NT>
+__device__ __forceinline__ bool has_nan(const f32x4 (&acc)[QT][NT]) {
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < QT; ++u)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[r] += acc[u][t][r];
+    const float all = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    return __any(all != all);
 }
 
 // The lane's accumulators of one query tile to a row of floats: accumulator row 4 g + r of tile e of a piece is channel

@@ -98,17 +98,9 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
     if (count > 0 && clamp_block(entry(count - 1)) == m) tiles -= TB - 1 - (y_last >> 4);
     const int steps = (tiles + TL - 1) / TL;
     const int step_it = (TL * KW) / TB, step_sub = TL * KW - step_it * TB;   // KW steps on
-    int it = (TL * w) / TB, ts = TL * w - it * TB;               // first tile of the step: entry `it`, tile `ts` of it
-
+    int it, ts;                                                  // first tile of the step: entry `it`, tile `ts` of it
     f32x4 acc[QT][NT];
     float ref[QT], lsum[QT];
-#pragma unroll
-    for (int u = 0; u < QT; ++u) {
-        ref[u] = NEG_INF;
-        lsum[u] = 0.f;
-#pragma unroll
-        for (int c = 0; c < NT; ++c) acc[u][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
 
     // Rows of a tile this lane reads, relative to its first key: row x of K, rows 4 g .. +3 of V.  Keys past the end of
     // the block or of the context are read as a copy of its last one, and masked.
@@ -139,6 +131,16 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
             kf[tl].load(base + off, d, gq);
         }
     };
+    auto walk = [&](auto careful) {
+    it = (TL * w) / TB;
+    ts = TL * w - it * TB;
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        ref[u] = NEG_INF;
+        lsum[u] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NT; ++c) acc[u][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     if (w < steps) {
         request();
         load_keys();
@@ -166,10 +168,11 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
 #pragma unroll
             for (int tl = 0; tl < TL; ++tl) s[u][tl] = f32x4{0.f, 0.f, 0.f, 0.f};
         F::template qk<QT>(s, kf, qf);
-
+        int last_v[TL];                                          // keys behind it are copies that no row takes
 #pragma unroll
         for (int tl = 0; tl < TL; ++tl) {
             const bool diag = n[tl] == m, none = TL * st + tl >= tiles;      // (a tile past the last one)
+            last_v[tl] = none ? -1 : last_key(tl);
             if (diag || kk[tl] + 16 > B || none) {
 #pragma unroll
                 for (int u = 0; u < QT; ++u) {
@@ -196,8 +199,18 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
 #pragma unroll
         for (int u = 0; u < QT; ++u)
             frag_softmax<TL, NT>(s[u], scale_log2, ref[u], lsum[u], acc[u], p[u]);
-        F::template pv<QT>(acc, vf, p);
+#pragma unroll
+        for (int tl = 0; tl < TL; ++tl)
+            if (last_v[tl] < 15) {                               // the same in every lane, and rare
+#pragma unroll
+                for (int r = 0; r < 4; ++r) F::drop(vf, 4 * tl + r, 4 * gq + r > last_v[tl]);
+            }
+        F::template pv<QT, decltype(careful)::value>(acc, vf, p);
     }
+    };
+    walk(std::false_type{});
+    if constexpr (std::is_same<T, bf16_t>::value)
+        if (has_nan(acc)) walk(std::true_type{});
 
     // ---- the waves' shares, brought to one reference ----
 #pragma unroll
