@@ -303,6 +303,9 @@ int rr_dense_attn_packed(const rr_shape* shape, const void* Q, const void* K, co
  * rr_attn_workspace_bytes() returns 0 where a call would not be split (many rows, short lists, shapes outside
  * bf16 / d = 128 / B = 128); a NULL workspace, or a geometry that is not split, gives exactly rr_sparse_attn /
  * rr_dense_attn.  A workspace that is too small or misaligned: RR_ERR_WORKSPACE.
+ * For steps inside one block the size grows with the positions: a workspace sized for the longest step serves the
+ * shorter ones (steps of one or two positions and at most 8 rows per KV head need what they ask for themselves), and a larger
+ * one than a step asks for lets it run on more parts.
  */
 size_t rr_attn_workspace_bytes(const rr_shape* shape, int B);
 int rr_sparse_attn_ws(const rr_shape* shape, const void* Q, const void* K, const void* V, const rr_mask* mask,

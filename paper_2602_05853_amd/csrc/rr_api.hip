@@ -121,11 +121,16 @@ int run_attn(const rr_shape* shape, const void* Q, const void* K, const void* V,
     a.plan_items = nullptr;
     a.plan_cut = nullptr;
     bool decode = false;
+    const bool misaligned = (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0;
+    int decode_parts = 0;
     if (workspace && use_mfma_attn(g, shape->dtype, B) && !seq_first && attn_decode_parts(g, B) >= 1) {
-        // few query rows per KV head: the kernel that reads K and V once per KV head for all its query heads
-        const size_t need = attn_decode_bytes(g, B);
-        if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return RR_ERR_WORKSPACE;
-        a.nsplit = attn_decode_parts(g, B);
+        // few query rows per KV head: as many parts as the workspace holds
+        decode_parts = attn_decode_fit(g, B, workspace_bytes, !misaligned);
+        if (decode_parts < 0) return RR_ERR_WORKSPACE;
+    }
+    if (decode_parts > 0) {
+        // the kernel that reads K and V once per KV head for all its query heads
+        a.nsplit = decode_parts;
         const size_t rows = (size_t)g.batch * g.Hq * (size_t)(g.Lr - g.q0);
         a.part_O = reinterpret_cast<float*>(workspace);
         a.part_lse = a.part_O + (size_t)a.nsplit * rows * g.d;
@@ -133,13 +138,13 @@ int run_attn(const rr_shape* shape, const void* Q, const void* K, const void* V,
     } else if (workspace && use_mfma_attn(g, shape->dtype, B) && !seq_first && attn_mfma_plan_len(g, B, nullptr) > 0) {
         // a chunk of a long prompt: the few very long rows are cut into parts after a plan made on the device
         const size_t need = attn_mfma_plan_bytes(g, B);
-        if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return RR_ERR_WORKSPACE;
+        if (workspace_bytes < need || misaligned) return RR_ERR_WORKSPACE;
         attn_mfma_plan_pointers(g, B, workspace, &a);
     } else if (workspace && use_mfma_attn(g, shape->dtype, B) && !seq_first) {
         // a launch of few rows with a workspace: the block list of every row is shared out among several workgroups
         const size_t need = attn_mfma_split_bytes(g, B);
         if (need) {
-            if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return RR_ERR_WORKSPACE;
+            if (workspace_bytes < need || misaligned) return RR_ERR_WORKSPACE;
             a.nsplit = attn_mfma_splits(g, B);
             const size_t rows = (size_t)g.batch * g.Hq * (size_t)(g.Lr - g.q0);
             a.part_O = reinterpret_cast<float*>(workspace);

@@ -18,8 +18,10 @@
 // What bounds it: the stream of K and V.  Measured, dense, against fp32 vector dot products on the same split (up to 8 rows,
 // 16 lanes to a key) and, above 8 rows, a 128-row tile per query head and key range (which reads K and V once per
 // query head): 128K tokens, 32 / 8 heads, one token 112 -> 101 us (5.3 TB/s), two 176 -> 105; 64 / 8 heads, one token 175 ->
-// 104; 28 / 4 heads, one token 98 -> 56, four 286 -> 61; 16K tokens, one token 27 -> 23; 64K, 8 tokens 143 -> 54.
+// 104; 28 / 4 heads, one token 98 -> 56, four 286 -> 78; 16K tokens, one token 27 -> 23; 64K, 8 tokens 143 -> 56.
 #include "rr_attn_frag.hpp"
+
+#include <algorithm>
 
 namespace rr {
 
@@ -40,14 +42,16 @@ struct DecodeArgs {
 };
 
 // QT: 16-column tiles of query rows, for G T <= 16 or 32; columns beyond G T repeat the last row and are never stored.
-template <int QT>
-__global__ void __launch_bounds__(kDecThreads, 2)
+// KW: waves, four to a block of keys and with eight of them two blocks at a time.
+template <int QT, int KW>
+__global__ void __launch_bounds__(64 * KW, 2)
 k_attn_decode(Geom g, DecodeArgs da) {
+    constexpr int kThreads = 64 * KW;
     using F = Frag<bf16_t, 8, 2>;
     constexpr int kQ = 16 * QT, kPitch = 132;
-    __shared__ __align__(16) float s_o[4][kQ][kPitch];       // a wave's share: its rows at the end
+    __shared__ __align__(16) float s_o[KW][kQ][kPitch];       // a wave's share: its rows at the end
     static_assert(kPitch >= 128, "a wave's accumulators fit its share");
-    __shared__ float s_ref[4][kQ], s_l[4][kQ];
+    __shared__ float s_ref[KW][kQ], s_l[KW][kQ];
     __shared__ unsigned s_sel[kDecMaxLen];                  // which lists hold a block of the range
     __shared__ int s_act[kDecMaxLen];                       // the blocks that any does, as offsets into the range
     __shared__ int s_nact;
@@ -81,13 +85,13 @@ k_attn_decode(Geom g, DecodeArgs da) {
     const int n_hi = min(n_lo + da.len, da.nblocks), span = max(n_hi - n_lo, 0);
     const unsigned all = lists >= 32 ? 0xFFFFFFFFu : (1u << lists) - 1u;
     // dense: every block up to a list's own query block (of two query blocks, odd lists are the second's)
-    for (int i = tid; i < span; i += kDecThreads)
+    for (int i = tid; i < span; i += kThreads)
         s_sel[i] = a.row_list ? 0u : (n_lo + i <= m_first ? all : (Nbq == 2 ? all & 0xAAAAAAAAu : 0u));
     __syncthreads();
     if (a.row_list) {
         // every list read whole by the workgroup at once (no search: a chain of dependent loads is longer than that);
         // an entry counts where it lies in the range, whatever the list's order
-        for (int l = w; l < lists; l += 4) {
+        for (int l = w; l < lists; l += KW) {
             const int hl = l / Nbq, mq = l - hl * Nbq;
             const long long rid = ((long long)b * g.Hq + kv * g.G + hl) * Nbq + mq;
             int cn = a.row_count[rid];
@@ -127,7 +131,7 @@ k_attn_decode(Geom g, DecodeArgs da) {
     auto load_keys = [&](int i) {
         const int at = __builtin_amdgcn_readfirstlane(s_act[i]);
         sel = (unsigned)__builtin_amdgcn_readfirstlane((int)s_sel[at]);
-        key0 = (n_lo + at) * kDecBlock + 32 * w;
+        key0 = (n_lo + at) * kDecBlock + 32 * (w & 3);
         const bf16_t* base = K + (long long)key0 * g.ksl;
 #pragma unroll
         for (int tl = 0; tl < 2; ++tl) {
@@ -143,8 +147,9 @@ k_attn_decode(Geom g, DecodeArgs da) {
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc[u][c] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    if (nact > 0) load_keys(0);
-    for (int i = 0; i < nact; ++i) {
+    const int i0 = w >> 2;
+    if (i0 < nact) load_keys(i0);
+    for (int i = i0; i < nact; i += KW / 4) {
         typename F::V vf;
         const bf16_t* base = V + (long long)key0 * g.ksl;
         if (key0 + 32 <= g.Lr) {
@@ -177,7 +182,7 @@ k_attn_decode(Geom g, DecodeArgs da) {
                 }
         }
         // travels during the softmax and the second product (the careful walk has no registers for it)
-        if (!decltype(careful)::value && i + 1 < nact) load_keys(i + 1);
+        if (!decltype(careful)::value && i + KW / 4 < nact) load_keys(i + KW / 4);
         float p[QT][8];
 #pragma unroll
         for (int u = 0; u < QT; ++u) frag_softmax<2, 8>(s[u], da.scale_log2, ref[u], lsum[u], acc[u], p[u]);
@@ -200,14 +205,14 @@ k_attn_decode(Geom g, DecodeArgs da) {
 #pragma unroll
                     for (int c = 0; c < 8; ++c) acc[u][c] = aside[64 * (8 * u + c)];
                 }
-            if (i + 1 < nact) load_keys(i + 1);
+            if (i + KW / 4 < nact) load_keys(i + KW / 4);
         }
     }
     };
     walk(std::false_type{});
     if (has_nan(acc)) walk(std::true_type{});
 
-    // the four waves: the part's normalised output and its natural-log sum of exponentials
+    // the waves: the part's normalised output and its natural-log sum of exponentials
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
         float l = lsum[u];
@@ -217,16 +222,16 @@ k_attn_decode(Geom g, DecodeArgs da) {
         frag_store<F::kW, 8>(acc[u], &s_o[w][16 * u + x][0], gq);
     }
     __syncthreads();
-    for (int idx = tid; idx < kQ * 32; idx += kDecThreads) {
+    for (int idx = tid; idx < kQ * 32; idx += kThreads) {
         const int q = idx >> 5, c = 4 * (idx & 31);
         if (q >= R) continue;
         float top = NEG_INF;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) top = fmaxf(top, s_ref[i][q]);
+        for (int i = 0; i < KW; ++i) top = fmaxf(top, s_ref[i][q]);
         float l = 0.f;
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < KW; ++i) {
             const float f = s_ref[i][q] == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(s_ref[i][q] - top);
             l = fmaf(f, s_l[i][q], l);
             const f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[i][q][c]);
@@ -293,19 +298,34 @@ k_attn_decode_combine(Geom g, AttnArgs a, int T) {
 
 }  // namespace
 
-// Parts of a decode-sized step, 0 when the step is not one.  The launch is sized to what the chip holds at once -- two
-// workgroups per compute unit (237 registers per lane for two tiles of rows) -- because a second round of workgroups costs
-// more than longer parts save.  A part is at least two key blocks long.  One or two tokens of up to 8 rows are taken at
-// any depth; others where all rows lie deep in the context (16 causal blocks or more), as the split launch of the
-// 128-row kernel, which serves the steps with more rows.
+namespace {
+// One or two positions of up to 8 rows: no other form serves these, at any depth in the context
+bool shortest(const Geom& g) {
+    const int T = g.Lr - g.q0;
+    return T <= 2 && g.G * T <= 8;
+}
+size_t part_bytes(const Geom& g) {
+    return (size_t)g.batch * g.Hq * (size_t)(g.Lr - g.q0) * (128 + 1) * sizeof(float);
+}
+// What the launches that the other steps fall back to need of the workspace (0: they do without)
+size_t fallback_bytes(const Geom& g, int B) {
+    return attn_mfma_plan_len(g, B, nullptr) > 0 ? attn_mfma_plan_bytes(g, B) : attn_mfma_split_bytes(g, B);
+}
+}  // namespace
+
+// The most parts that pay, 0 when the step is not one of this kernel.  One token: 512 workgroups, two per compute unit (a
+// second round of workgroups costs more than longer parts save); steps of more rows, whose parts are wider, 256 (8 tokens
+// at 64K, 32 / 8 heads, 512 workgroups 55 us, 256 51; 4 tokens, 28 / 4, 42 and 35).  A part is at least two key blocks
+// long.  The shortest steps are taken at any depth; others where all rows lie deep in the context (16 causal blocks or
+// more), as the split launch of the 128-row kernel, which serves the steps with more rows.
 int attn_decode_parts(const Geom& g, int B) {
     if (B != kDecBlock || g.d != 128) return 0;
     const int T = g.Lr - g.q0, Nb = g.L / B, Nbq = g.Lq / B;
     if (T < 1) return 0;
     if (g.G * T > kDecMaxRows) return 0;
-    if (!(T <= 2 && g.G * T <= 8) && Nb - Nbq + 1 < 16) return 0;
+    if (!shortest(g) && Nb - Nbq + 1 < 16) return 0;
     const int nblocks = (g.Lr - 1) / kDecBlock + 1;
-    const long long groups = (long long)g.batch * g.Hkv, target = 512;
+    const long long groups = (long long)g.batch * g.Hkv, target = shortest(g) ? 512 : 256;
     long long P = (target + groups - 1) / groups;
     if (P > (nblocks + 1) / 2) P = (nblocks + 1) / 2;
     if (P > kDecMaxParts) P = kDecMaxParts;
@@ -316,14 +336,29 @@ int attn_decode_parts(const Geom& g, int B) {
     return (int)P;
 }
 
+// The bytes a call asks for: all parts of the shortest steps, and for the others no more than the launches that served
+// them before ask for, so that the size grows with the step and one workspace serves every step up to the one it was
+// sized for.  These parts are fewer than fill the chip where the heads of a group are many; eight waves to a workgroup
+// make up for some of it.  Dense, us: all parts, these, (the split launch): 8 tokens at 64K, 32 / 8 heads 51, 56, (131); 4 tokens,
+// 28 / 4 heads 35, 45, (177); 64 / 8 heads 51, 89, (239); 32 / 1 heads, one token, 16 workgroups 30, 50, (218).
 size_t attn_decode_bytes(const Geom& g, int B) {
     const int P = attn_decode_parts(g, B);
     if (P < 1) return 0;
-    const size_t rows = (size_t)g.batch * g.Hq * (size_t)(g.Lr - g.q0);
-    return (size_t)P * rows * 128 * sizeof(float) + (size_t)P * rows * sizeof(float);
+    const size_t all = (size_t)P * part_bytes(g), other = fallback_bytes(g, B);
+    return shortest(g) || other == 0 ? all : std::min(all, other);
 }
 
-// expects a.nsplit = attn_decode_parts(g, a.B) >= 1 and a.part_O / a.part_lse of attn_decode_bytes
+int attn_decode_fit(const Geom& g, int B, size_t bytes, bool aligned) {
+    const int all = attn_decode_parts(g, B);
+    if (all < 1) return 0;
+    if (!aligned) return shortest(g) ? -1 : 0;              // (the others check for themselves)
+    if (bytes < attn_decode_bytes(g, B) && (shortest(g) || fallback_bytes(g, B) > 0)) return -1;
+    const long long fit = std::min<long long>(all, (long long)(bytes / part_bytes(g)));
+    const long long nblocks = (g.Lr - 1) / kDecBlock + 1;
+    return fit < 1 || (nblocks + fit - 1) / fit > kDecMaxLen ? 0 : (int)fit;
+}
+
+// expects 1 <= a.nsplit <= attn_decode_parts(g, a.B), and a.part_O / a.part_lse of that many parts
 hipError_t launch_attn_decode(const Geom& g, const AttnArgs& a, hipStream_t st) {
     const int T = g.Lr - g.q0, R = g.G * T;
     if (a.nsplit < 1 || a.nsplit > kDecMaxParts || !a.part_O || !a.part_lse || T < 1 ||
@@ -337,8 +372,13 @@ hipError_t launch_attn_decode(const Geom& g, const AttnArgs& a, hipStream_t st) 
     da.scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     const dim3 grid((unsigned)a.nsplit, (unsigned)g.Hkv, (unsigned)g.batch);
     if (R > kDecMaxRows || da.len > kDecMaxLen) return hipErrorInvalidValue;
-    if (R <= 16) hipLaunchKernelGGL(k_attn_decode<1>, grid, dim3(kDecThreads), 0, st, g, da);
-    else hipLaunchKernelGGL(k_attn_decode<2>, grid, dim3(kDecThreads), 0, st, g, da);
+    // fewer workgroups than compute units, with parts of some length: two blocks at a time (at 64K, 32 / 8 heads, 8 tokens, 128
+    // workgroups 75 -> 56 us; 256 workgroups 51 and 52)
+    const bool eight = (long long)a.nsplit * g.batch * g.Hkv < 256 && da.len >= 8;
+    if (R <= 16 && eight) hipLaunchKernelGGL((k_attn_decode<1, 8>), grid, dim3(512), 0, st, g, da);
+    else if (R <= 16) hipLaunchKernelGGL((k_attn_decode<1, 4>), grid, dim3(256), 0, st, g, da);
+    else if (eight) hipLaunchKernelGGL((k_attn_decode<2, 8>), grid, dim3(512), 0, st, g, da);
+    else hipLaunchKernelGGL((k_attn_decode<2, 4>), grid, dim3(256), 0, st, g, da);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const long long nrows = (long long)g.batch * g.Hq * T;

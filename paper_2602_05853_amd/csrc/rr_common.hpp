@@ -176,6 +176,8 @@ hipError_t launch_attn_combine(const Geom& g, const AttnArgs& a, hipStream_t st)
 // launch (0: not such a step), bytes of its partial results, and the launch itself (a.nsplit parts, a.part_O /
 // a.part_lse laid out as above), which also merges the parts into a.O / a.lse.
 int attn_decode_parts(const Geom& g, int B);
+// Parts to run with on a workspace of so many bytes, 256-byte aligned or not; -1: it cannot serve the step, 0: another launch.
+int attn_decode_fit(const Geom& g, int B, size_t bytes, bool aligned);
 size_t attn_decode_bytes(const Geom& g, int B);
 hipError_t launch_attn_decode(const Geom& g, const AttnArgs& a, hipStream_t st);
 constexpr int kMaxOrderedRows = 32768;   // G * Nb up to which a row order is produced and used

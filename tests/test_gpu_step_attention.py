@@ -106,3 +106,36 @@ def test_blocks_a_row_did_not_select_do_not_reach_it(T, L):
         got = rr.rr_dense_attn(Q, K, V3, B, workspace=ws)
         torch.cuda.synchronize()
         assert torch.equal(got[:, :, :first], dense_clean[:, :, :first])
+
+
+@pytest.mark.parametrize("Hq,Hkv,longest", [(32, 8, 16), (28, 4, 8), (16, 1, 4), (64, 8, 6)])
+def test_a_workspace_sized_for_the_longest_step_serves_the_shorter_ones(Hq, Hkv, longest):
+    """Steps of 1 .. longest positions on one workspace, on one of the size they ask for themselves (fewer parts) and on a
+    large one (as many parts as pay).  bf16 outputs of fp32 sums in another order: neighbouring numbers at most, 2^-7."""
+    import paper_2602_05853_amd as rr
+    from paper_2602_05853_amd import binding as bd
+    dev, B, L = "cuda:0", 128, 128 * 80
+    g = torch.Generator(device=dev).manual_seed(Hq)
+    Qall = torch.randn(1, Hq, longest, 128, generator=g, device=dev).bfloat16()
+    K, V = (torch.randn(1, Hkv, L, 128, generator=g, device=dev).bfloat16() for _ in range(2))
+    steps = {T: Qall[:, :, longest - T:].contiguous() for T in range(1, longest + 1)}
+    need = {T: rr.rr_attn_workspace_bytes(Q, K, B) for T, Q in steps.items()}
+    small = [T for T in (1, 2) if Hq // Hkv * T <= 8]       # these need what they ask for
+    assert all(need[T] <= need[T + 1] for T in range(1, longest) if T not in small)
+    one = torch.empty(max(need[T] for T in small + [longest]), dtype=torch.uint8, device=dev)
+    large = torch.empty(16 << 20, dtype=torch.uint8, device=dev)
+    for T, Q in steps.items():
+        mask = rr.rr_mask_from_dense(Q, K, (torch.rand(1, Hq, 1, L // B, generator=g, device=dev) < 0.4).to(torch.uint8), B)
+        for call in (lambda **kw: rr.rr_dense_attn(Q, K, V, B, **kw), lambda **kw: rr.rr_sparse_attn(Q, K, V, mask, **kw)):
+            out = []
+            for ws in (one, torch.empty(need[T], dtype=torch.uint8, device=dev), large):
+                lse = torch.empty(1, Hq, T, dtype=torch.float32, device=dev)
+                out.append((call(workspace=ws, lse=lse).float(), lse))
+            torch.cuda.synchronize()
+            for got, lse in out[:2]:
+                assert ((got - out[2][0]).abs() <= 2.0 ** -7 * out[2][0].abs() + 1e-5).all(), T
+                assert (lse - out[2][1]).abs().max() <= 1e-4, T
+    # what no form of the step can do with is refused as before
+    with pytest.raises(bd.RRError) as err:
+        rr.rr_dense_attn(Qall, K, V, B, workspace=one[:256])
+    assert err.value.status == bd.RR_ERR_WORKSPACE
