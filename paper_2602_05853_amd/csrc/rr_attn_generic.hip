@@ -32,6 +32,8 @@ __device__ __forceinline__ void store4(bf16_t* p, const f32x4& v) {
     *reinterpret_cast<u32x2*>(p) = o;
 }
 
+constexpr unsigned kMaxGridY = 65535;
+
 template <int NT> constexpr int out_pitch() { return 16 * NT + 4; }
 
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -54,9 +56,17 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
     const int Nbq = g.Lq / B;                         // rows of the launch (chunked prefill: the last query blocks)
     // heaviest rows first (blockIdx.y), heads fastest, and of those the KV head: the XCDs, which take consecutive
     // workgroups in turn, then each keep the keys of few KV heads in L2
-    const int m = Nb - 1 - (int)blockIdx.y;
+    // (more query blocks than the y axis holds: the rest in further turns of the x axis)
+    int bx = (int)blockIdx.x, rank = (int)blockIdx.y;
+    if (Nbq > (int)kMaxGridY) {
+        const int per_row = g.Hq * ((B + kQ - 1) / kQ), turn = bx / per_row;
+        bx -= turn * per_row;
+        if (rank >= Nbq - turn * (int)kMaxGridY) return;
+        rank += turn * (int)kMaxGridY;
+    }
+    const int m = Nb - 1 - rank;
     const int mq = m - (Nb - Nbq);
-    const int sub = (int)blockIdx.x / g.Hq, hx = (int)blockIdx.x - sub * g.Hq;
+    const int sub = bx / g.Hq, hx = bx - sub * g.Hq;
     const int hl = hx / g.Hkv, kv = hx - hl * g.Hkv;
     const int h = kv * g.G + hl, b = blockIdx.z;
     const long long row_id = ((long long)b * g.Hq + h) * Nbq + mq;
@@ -131,6 +141,8 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
             kf[tl].load(base + off, d, gq);
         }
     };
+    // bf16, whose probabilities are split: all keys a second time where the first met zero times infinity
+    constexpr bool kTwoWalks = std::is_same<T, bf16_t>::value;
     auto walk = [&](auto careful) {
     it = (TL * w) / TB;
     ts = TL * w - it * TB;
@@ -199,17 +211,20 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
 #pragma unroll
         for (int u = 0; u < QT; ++u)
             frag_softmax<TL, NT>(s[u], scale_log2, ref[u], lsum[u], acc[u], p[u]);
+        constexpr bool kCareful = decltype(careful)::value;
+        if constexpr (kCareful || !kTwoWalks) {
 #pragma unroll
-        for (int tl = 0; tl < TL; ++tl)
-            if (last_v[tl] < 15) {                               // the same in every lane, and rare
+            for (int tl = 0; tl < TL; ++tl)
+                if (last_v[tl] < 15) {                           // the same in every lane, and rare
 #pragma unroll
-                for (int r = 0; r < 4; ++r) F::drop(vf, 4 * tl + r, 4 * gq + r > last_v[tl]);
-            }
-        F::template pv<QT, decltype(careful)::value>(acc, vf, p);
+                    for (int r = 0; r < 4; ++r) F::drop(vf, 4 * tl + r, 4 * gq + r > last_v[tl]);
+                }
+        }
+        F::template pv<QT, kCareful>(acc, vf, p);
     }
     };
     walk(std::false_type{});
-    if constexpr (std::is_same<T, bf16_t>::value)
+    if constexpr (kTwoWalks)
         if (has_nan(acc)) walk(std::true_type{});
 
     // ---- the waves' shares, brought to one reference ----
@@ -252,7 +267,8 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
 
 }  // namespace
 
-// Shapes the entry points accept on this path: B (4 d + 19) fp32 words within 150 KB.
+// Shapes the entry points accept on this path: B (4 d + 19) fp32 words within 150 KB.  A bound of the interface (a caller pads
+// or picks B by it); this kernel holds its operands in registers and would take any B up to 128 with any d up to 256.
 bool attn_generic_fits(int B, int d) {
     return sizeof(float) * ((size_t)B * (4 * (size_t)d + 19)) <= 150 * 1024;
 }
@@ -261,7 +277,9 @@ hipError_t launch_attn_generic(const Geom& g, int dtype, const AttnArgs& a, hipS
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     auto launch = [&](auto kernel, int queries, int waves) -> hipError_t {
         const unsigned subs = (unsigned)((a.B + queries - 1) / queries);
-        dim3 grid((unsigned)g.Hq * subs, g.Lq / a.B, g.batch);
+        const unsigned Nbq = (unsigned)(g.Lq / a.B), turns = (Nbq + kMaxGridY - 1) / kMaxGridY;
+        if ((unsigned long long)g.Hq * subs * turns * 64 * waves > 0xFFFFFFFFull) return hipErrorInvalidValue;
+        dim3 grid((unsigned)g.Hq * subs * turns, Nbq < kMaxGridY ? Nbq : kMaxGridY, g.batch);
         hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, st, g, a, scale_log2);
         return hipGetLastError();
     };

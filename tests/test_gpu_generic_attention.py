@@ -59,3 +59,27 @@ def test_generic_attention_matches_the_oracle(B, d, dtype, Hq, Nb):
         assert worst <= gu.F32_MAX_ABS
     # the scores and their sum are formed in 32 bits for both types
     assert lse_err <= gu.F32_MAX_ABS
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_more_query_blocks_than_a_grid_axis_holds(dtype):
+    """Blocks of one position, 66 000 of them, dense: rows around the 65 535th from either end and a sample of others
+    against attention in 64 bits (weights of thousands of keys: the output is a mean, of magnitude 0.01 and more)."""
+    import paper_2602_05853_amd as rr
+    dev, L, d = "cuda:0", 66000, 8
+    g = torch.Generator(device=dev).manual_seed(3)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Q, K, V = (torch.randn(1, 1, L, d, generator=g, device=dev).to(tdt) for _ in range(3))
+    print(f"[generic] {L} blocks of one position, {dtype}", flush=True)
+    O = torch.full_like(Q, float("nan"))
+    lse = torch.full((1, 1, L), float("nan"), device=dev)
+    rr.rr_dense_attn(Q, K, V, 1, O=O, lse=lse)
+    torch.cuda.synchronize()
+    assert torch.isfinite(O.float()).all() and torch.isfinite(lse).all()
+    rows = sorted({0, 1, 463, 464, 465, 466, 65534, 65535, 65536, L - 1} | set(range(777, L, 4999)))
+    for r in rows:
+        s = K[0, 0, :r + 1].double() @ Q[0, 0, r].double() / d ** 0.5
+        want = torch.softmax(s, 0) @ V[0, 0, :r + 1].double()
+        off = (O[0, 0, r].double() - want).abs()
+        assert (off <= (2.0 ** -8 if dtype == "bf16" else 0.0) * want.abs() + gu.F32_MAX_ABS).all(), r
+        assert (lse[0, 0, r].double() - torch.logsumexp(s, 0)).abs() <= gu.F32_MAX_ABS, r
