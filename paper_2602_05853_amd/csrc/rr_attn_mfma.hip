@@ -1302,10 +1302,9 @@ int attn_mfma_plan_len(const Geom& g, int B, int* budget) {
     const int Nb = g.L / B, Nbq = g.Lq / B;
     const long long rows = (long long)g.batch * g.Hq * Nbq;
     if (Nbq < 2 || Nb < 128 || g.q0 <= 0 || rows > 4096) return 0;
-    int len = rows <= 2048 ? 64 : 128;                                  // contexts that are not longer are not planned
-    if (len < (Nb + 31) / 32) len = (Nb + 31) / 32;                     // at most 32 parts per row
-    if (Nb <= len) return 0;
-    len = (Nb + 31) / 32 > 40 ? (Nb + 31) / 32 : 40;
+    const int at_most_32 = (Nb + 31) / 32;                              // parts per row
+    if (Nb <= std::max(rows <= 2048 ? 64 : 128, at_most_32)) return 0;  // contexts that are not longer are not planned
+    const int len = std::max(at_most_32, 40);
     // slots: several times what the rows of such chunks were seen to need (300-1000 at 128K), between 512 and 2048
     // (34-135 MB of partial results); the workgroups of unused slots run last and cost nothing measurable
     if (budget) *budget = (int)(4 * rows < 512 ? 512 : (4 * rows > 2048 ? 2048 : 4 * rows));
