@@ -41,10 +41,11 @@
 // moved to is 1 and exact, so a row is the more precise the less a weight may exceed the reference.  Error against 64 bits,
 // 2-norm, of which the last rounding is 1.667e-3; moved beyond 2^8, 2^6, 2^5 (8 heads of 32):
 //   4096 tokens 1.811e-3, 1.804, 1.796; 65536 tokens 1.841, 1.832, 1.825; dense, 16384 tokens 1.806, 1.801, 1.797
-//   chunks: 1000 tokens at 20480 1.826, 1.810, 1.797; 2048 at 65536 1.853, 1.826, 1.812
+//   chunks: 1000 tokens at 20480 1.826, 1.810, 1.797; 2048 at 65536 1.853, 1.827, 1.812; 300 at 32768 1.890, 1.865, 1.844
+//   64 tokens at 65536 1.805, 1.796, 1.792; ten chunks and steps 1.842, 1.825, 1.811 in the mean
 // With two key halves to a row, each with a reference of its own moved beyond 2^8, and the diagonal block's terms summed
-// unrounded, these were 1.816, 1.844, 1.816; 1.804, 1.825.  2^8 is below that for whole prompts, and 2^5 for launches in
-// parts, whose rows lie deep in the context (whole prompts spend 1-3 % more time at 2^5, 2048 tokens at 128K 2 %).
+// unrounded: 1.816, 1.844, 1.816; 1.804, 1.825, 1.890; 1.805, 1.833.  2^8 stays below that for whole prompts and steps and 2^6
+// for chunks, whose rows lie deep in the context.  A move is dear: 2^6 costs a chunk 1-2 %, 2^5 4-9 % and a prompt 1-3 %.
 //
 // Staging.  K and V tiles go global -> LDS directly (global_load_lds, 16 bytes per lane, no
 // staging registers), row-major, double-buffered one key block ahead.  K fragments are plain
@@ -59,6 +60,7 @@
 // tile: it is read by the diagonal pass alone, through copies whose source rows stop at the last real
 // position; query rows past the length work on a copy of the last real row and are not stored.
 #include "rr_common.hpp"
+#include "rr_select.hpp"
 
 #include <algorithm>
 #include <atomic>
@@ -506,7 +508,7 @@ __device__ __forceinline__ void phase(Wave& w, const f32x16& scur, f32x16& snext
             SCHED_FENCE();
         }
     }
-    // A score more than 2^8 (2^5) above the reference makes its term, hence the lane's sum of 16 terms,
+    // A score more than 2^8 (2^6) above the reference makes its term, hence the lane's sum of 16 terms,
     // exceed 2^8 (the first step of a row, whose reference is -inf, gives +inf): the sum is the
     // trigger, the maximum itself is only computed on the rare path.
     if (valid) {
@@ -1183,24 +1185,25 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
     int need[kLens + 1];
 #pragma unroll
     for (int i = 0; i <= kLens; ++i) need[i] = 0;
+    // parts of a row of `count` entries, exact: a row has at most 33, so the quotient is off by less than 2^-16, and from
+    // the next whole number it is 1 / (2 len) > 2^-13 away.  (Integer divisions and sums through LDS: 18.0 us; so 13.2, of which the scan below is 6.)
+    auto parts_of = [](int count, int len, float inv) { return count > len ? (int)(((float)(count + len - 1) + 0.5f) * inv) : 0; };
     for (int rid = t; rid < rows_total; rid += kPlanThreads) {
         a.plan_row[rid] = -1;
         const int count = count_of(rid);
         need[kLens] += count;
         longest = max(longest, count);
 #pragma unroll
-        for (int i = 0; i < kLens; ++i) {
-            const int len = len_of(i);
-            need[i] += count > len ? (count + len - 1) / len : 0;
-        }
+        for (int i = 0; i < kLens; ++i) need[i] += parts_of(count, len_of(i), 1.0f / (float)len_of(i));
     }
 #pragma unroll
     for (int i = 0; i <= kLens; ++i) {
-#pragma unroll
-        for (int sft = 32; sft >= 1; sft >>= 1) need[i] += __shfl_xor(need[i], sft);
-        if ((t & 63) == 0) atomicAdd(&s_need[i], need[i]);
+        const float sum = wave_sum_fixed((float)need[i]);       // whole numbers below 2^24: exact
+        if ((t & 63) == 0) atomicAdd(&s_need[i], (int)sum);
     }
-    atomicMax(&s_longest, longest);
+#pragma unroll
+    for (int sft = 32; sft >= 1; sft >>= 1) longest = max(longest, __shfl_xor(longest, sft));
+    if ((t & 63) == 0) atomicMax(&s_longest, longest);
     __syncthreads();
     int len = len_of(kLens - 1);
 #pragma unroll
@@ -1408,9 +1411,9 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
         if (pe != hipSuccess) return pe;
     }
     if (persist) grid = dim3((unsigned)resident);
-    // How far a weight may exceed the softmax reference before the reference moves up to it, see the head of the file: 2^8, or 2^5
-    // in launches whose rows are computed in parts.
-    const float lazy_log2 = planned || a.nsplit > 1 ? 5.0f : 8.0f;
+    // How far a weight may exceed the softmax reference before the reference moves up to it, see the head of the file: 2^8, or 2^6
+    // in planned launches.
+    const float lazy_log2 = planned ? 6.0f : 8.0f;
     const int lds_bytes = (wide ? 2 : 1) * kLdsBytes + (persist ? 16 : 0);
     auto launch = [&](auto kernel) -> hipError_t {
         hipError_t e = allow_dynamic_lds((const void*)kernel, lds_bytes);

@@ -4,10 +4,10 @@ average out over the rows.  The key comes after a step of keys that set the soft
 where a row is that block alone, and, in a chunk of a longer context with the workspace, in a block of the pipeline.
 
 Bound.  The denominator sums the rounded probabilities, so the error of the large weight w leaves delta (1 - w): in the
-first case 1 - w <= 1/17, 2.1e-4.  In the chunk a weight more than 2^5 above the reference becomes the reference and is
+first case 1 - w <= 1/17, 2.1e-4.  In the chunk a weight more than 2^6 above the reference becomes the reference and is
 exact; of the other 255 keys the 58 at most that come after it are rounded, by 2^-9: 3.6e-4 of the sum.  A channel's last
 rounding is at most 2^-8, 0.58 of that in the mean square, and the mean of 128 channels of random mantissas is off by 4 x 0.58 x 2^-8 / sqrt(128) = 8e-4 at most.  A weight that is
-rounded in the numerator alone is off by 3e-3, one that stays 2^6 or 2^7 above the reference by 2.3e-3."""
+rounded in the numerator alone is off by 3e-3, one that stays as far above the reference by 2.3e-3."""
 import math
 
 import pytest
