@@ -383,8 +383,12 @@ struct Stager {
                      :: "v"(off[i]), "s"(wave_src), "s"(wave_dst + 4 * i * 256) : "memory");
     }
     // this wave's rows of half `hf` (64 keys) of key block n
-    __device__ __forceinline__ const unsigned short* k_src(int n, int hf) const { return Kp + ((long long)n * 128 + kTileKeys * hf + kRowsPerWave * wv) * ksl; }
-    __device__ __forceinline__ const unsigned short* v_src(int n, int hf) const { return Vp + ((long long)n * 128 + kTileKeys * hf + kRowsPerWave * wv) * ksl; }
+    __device__ __forceinline__ const unsigned short* k_src(int n, int hf) const {
+        return Kp + ((long long)n * 128 + kTileKeys * hf + kRowsPerWave * wv) * ksl;
+    }
+    __device__ __forceinline__ const unsigned short* v_src(int n, int hf) const {
+        return Vp + ((long long)n * 128 + kTileKeys * hf + kRowsPerWave * wv) * ksl;
+    }
     __device__ __forceinline__ unsigned k_dst(int buf) const { return lds0 + buf * kTileBytes + kRowsPerWave * wv * 256; }
     __device__ __forceinline__ unsigned v_dst(int buf) const { return lds0 + (2 + buf) * kTileBytes + kRowsPerWave * wv * 256; }
     // Half `hf` of a block whose last rows lie past the real length (`rows` real rows, 1 <= rows < 128): those LDS
@@ -1010,7 +1014,8 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         float* lse_base = split ? a.part_lse + (long long)part * g.batch * g.Hq * rows_call : a.lse;
         float* lse = lse_base ? lse_base + ((long long)b * g.Hq + h) * rows_call + wrow0 : nullptr;
         if (planned && split) lse = a.part_lse + (long long)plan_slot * 128 + 32 * wv;   // a slot holds a whole tile
-        if (lse && gsel == 0 && l32 < rows_q && l32 >= rows_lo) lse[l32] = l > 0.f ? w.mref * 0.6931471805599453f + logf(whole) : NEG_INF;
+        if (lse && gsel == 0 && l32 < rows_q && l32 >= rows_lo)
+            lse[l32] = l > 0.f ? w.mref * 0.6931471805599453f + logf(whole) : NEG_INF;
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -1156,20 +1161,24 @@ k_attn_combine(Geom g, AttnArgs a) {
 // ---- planned launches (chunks of a long prompt): the plan and the merge ----
 // One workgroup.  First the part length: the shortest of a fixed series, not below split_len, with which all rows longer
 // than a part fit into the slots and a part is a quarter of a workgroup's share of the launch or more (shorter ones only add
-// partial results); no row is cut where none is long (dense chunks of many rows).  (Rows for which no slot is left are computed whole, and one of them can take longer
-// than everything else: with a fixed 64 entries a chunk of 512 tokens at 128K whose heads kept 42 000 block pairs took
-// 2.17 ms, with the length that fits 0.42 ms.)  Then it walks the rows in launch order, gives every row longer than
-// that one slot per part (a prefix sum) and lists the slots' rows.
+// partial results); no row is cut where none is long (dense chunks of many rows).  (Rows for which no slot is left are
+// computed whole, and one of them can take longer than everything else: with a fixed 64 entries a chunk of 512 tokens at
+// 128K whose heads kept 42 000 block pairs took 2.17 ms, with the length that fits 0.42 ms.)  Lengths down to half of split_len
+// are taken where all parts and rows then run at once, so that the launch takes as long as one part: tau 0.8, 300 tokens at
+// 30000, 32 / 8 heads 147 -> 131 us, 300 at 20000, 16 / 4 115 -> 78, 600 at 40000, 8 / 2 111 -> 70, 1000 at 65536, 8 / 2 123 -> 86.
+// Then it walks the rows in launch order, gives every row longer than that one slot per part (a prefix sum) and lists the
+// slots' rows.
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanShare = 2048;     // four times the workgroups that are resident at once
+constexpr int kPlanResident = 512;   // workgroups that run at once
+constexpr int kPlanShare = 4 * kPlanResident;
 constexpr int kPlanWhole = 768;      // no row is longer than two thirds of a workgroup's share: none is cut
 __global__ void __launch_bounds__(kPlanThreads)
 k_split_plan(Geom g, AttnArgs a, int grid_rows) {
-    __shared__ int s_scan[kPlanThreads];
-    __shared__ int s_base, s_used, s_cut;
-    constexpr int kLens = 16;
+    __shared__ int s_wave[kPlanThreads / 64];
+    __shared__ int s_used, s_cut;
+    constexpr int kShort = 4, kLens = kShort + 16;              // below split_len, in all
     __shared__ int s_need[kLens + 1], s_longest;                // slots per length, and the entries of all rows
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int Nbq = g.Lq >> 7;
     const int rows_total = g.batch * g.Hq * Nbq;
     auto count_of = [&](int rid) {                              // as the attention kernel holds it
@@ -1177,17 +1186,20 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
         const int count = a.row_list ? a.row_count[rid] : m + 1;
         return count < 0 ? 0 : (count > m + 1 ? m + 1 : count);
     };
-    auto len_of = [&](int i) { return (4 + (i & 3)) * (a.split_len << (i >> 2)) / 4; };   // 1, 1.25, 1.5, 1.75, 2, 2.5 ..
+    auto len_of = [&](int i) { return (4 + (i & 3)) * (a.split_len << (i >> 2)) / 8; };   // of split_len: 1/2, 5/8 .. 1, 5/4 ..
     if (t <= kLens) s_need[t] = 0;
-    if (t == 0) { s_base = 0; s_used = 0; s_cut = 0; s_longest = 0; }
+    if (t == 0) { s_used = 0; s_cut = 0; s_longest = 0; }
     __syncthreads();
     int longest = 0;
     int need[kLens + 1];
 #pragma unroll
     for (int i = 0; i <= kLens; ++i) need[i] = 0;
-    // parts of a row of `count` entries, exact: a row has at most 33, so the quotient is off by less than 2^-16, and from
-    // the next whole number it is 1 / (2 len) > 2^-13 away.  (Integer divisions and sums through LDS: 18.0 us; so 13.2, of which the scan below is 6.)
-    auto parts_of = [](int count, int len, float inv) { return count > len ? (int)(((float)(count + len - 1) + 0.5f) * inv) : 0; };
+    // parts of a row of `count` entries, exact where the length may be taken: at most 33 then, so the quotient is off by less
+    // than 2^-16, and from the next whole number it is 1 / (2 len) > 2^-13 away.  (Integer divisions, sums and scan through
+    // LDS: 18.0 us; so 11.4.)
+    auto parts_of = [](int count, int len, float inv) {
+        return count > len ? (int)(((float)(count + len - 1) + 0.5f) * inv) : 0;
+    };
     for (int rid = t; rid < rows_total; rid += kPlanThreads) {
         a.plan_row[rid] = -1;
         const int count = count_of(rid);
@@ -1196,20 +1208,27 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
 #pragma unroll
         for (int i = 0; i < kLens; ++i) need[i] += parts_of(count, len_of(i), 1.0f / (float)len_of(i));
     }
+    if (64 * wave < rows_total) {
+        int mine = 0;                                           // lane i: sum i
 #pragma unroll
-    for (int i = 0; i <= kLens; ++i) {
-        const float sum = wave_sum_fixed((float)need[i]);       // whole numbers below 2^24: exact
-        if ((t & 63) == 0) atomicAdd(&s_need[i], (int)sum);
+        for (int i = 0; i <= kLens; ++i) {
+            const int sum = (int)wave_sum_fixed((float)need[i]);    // whole numbers below 2^24: exact
+            mine = lane == i ? sum : mine;
+        }
+        if (lane <= kLens) atomicAdd(&s_need[lane], mine);
+#pragma unroll
+        for (int sft = 32; sft >= 1; sft >>= 1) longest = max(longest, __shfl_xor(longest, sft));
+        if (lane == 0) atomicMax(&s_longest, longest);
     }
-#pragma unroll
-    for (int sft = 32; sft >= 1; sft >>= 1) longest = max(longest, __shfl_xor(longest, sft));
-    if ((t & 63) == 0) atomicMax(&s_longest, longest);
     __syncthreads();
     int len = len_of(kLens - 1);
 #pragma unroll
-    for (int i = kLens - 2; i >= 0; --i)
-        if (s_need[i] <= a.split_budget && len_of(i) >= s_need[kLens] / kPlanShare) len = len_of(i);
+    for (int i = kLens - 2; i >= 0; --i) {
+        const bool fits = s_need[i] <= a.split_budget && len_of(i) >= s_need[kLens] / kPlanShare;
+        if (fits && (i >= kShort || (s_need[i] + rows_total <= kPlanResident && 32 * len_of(i) >= a.Nb))) len = len_of(i);
+    }
     if (s_longest <= s_need[kLens] / kPlanWhole) len = max(len, s_longest);
+    int base = 0;                                               // what the rows of earlier trips take
     for (int start = 0; start < grid_rows; start += kPlanThreads) {
         const int rank = start + t;
         int parts = 0, rid = -1;
@@ -1222,15 +1241,23 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
             }
         }
         // the parts (at most 4096 rows x 32 < 2^18), and above them the number of rows with parts (at most 2^12)
-        s_scan[t] = parts | (parts > 0 ? 1 << 18 : 0);
-        __syncthreads();
-        for (int off = 1; off < kPlanThreads; off <<= 1) {
-            const int v = t >= off ? s_scan[t - off] : 0;
-            __syncthreads();
-            s_scan[t] += v;
-            __syncthreads();
+        const int mine = parts | (parts > 0 ? 1 << 18 : 0);
+        int incl = mine;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            if (lane >= off) incl += v;
         }
-        const int incl = s_base + s_scan[t];
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        int before = base;
+#pragma unroll
+        for (int i = 0; i < kPlanThreads / 64; ++i) {
+            const int v = s_wave[i];
+            before += i < wave ? v : 0;
+            base += v;
+        }
+        incl += before;
         const int first = (incl & 0x3FFFF) - parts, nth = (incl >> 18) - 1;      // slots and cut rows in front of this row
         if (parts > 0 && first + parts <= a.split_budget) {
             a.plan_row[rid] = first;
@@ -1239,9 +1266,7 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
             atomicMax(&s_used, first + parts);
             atomicMax(&s_cut, nth + 1);
         }
-        __syncthreads();
-        if (t == 0) s_base += s_scan[kPlanThreads - 1];
-        __syncthreads();
+        __syncthreads();                                       // s_wave is read, s_used and s_cut are whole
     }
     if (t == 0) { a.plan_total[0] = s_used; a.plan_total[1] = s_cut; a.plan_total[2] = len; }
 }

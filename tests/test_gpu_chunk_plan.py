@@ -1,10 +1,10 @@
 """Planned chunk launches whose rows need parts of different lengths: all rows long (the slots hold them only with longer
-parts, or no row is cut), a few long among short ones, none long.  Every output row against the same call without a workspace,
-which walks every row in one piece.  Both round the probabilities to bf16, relative to references that differ between
-them: each by at most 2^-8, and by half of that and less where hundreds of terms are rounded either way, so a result moves
-by at most 2^-8 sum(p |v|) <= 2^-8 max|v| (max|v| taken from the inputs, about 5.3) plus its own last rounding, 2^-8 of the value.  The log-sum-exp is the logarithm of the sum of the rounded
-probabilities (unrounded where a step moved the reference), so likewise 2^-8 between the two
-forms, and far less in the mean."""
+parts, or no row is cut), a few long among short ones, none long.  Every output row against the same call without a
+workspace, which walks every row in one piece.  Both round the probabilities to bf16, relative to references that differ
+between them: each by at most 2^-8, and by half of that and less where hundreds of terms are rounded either way, so a
+result moves by at most 2^-8 sum(p |v|) <= 2^-8 max|v| (max|v| taken from the inputs, about 5.3) plus its own last rounding,
+2^-8 of the value.  The log-sum-exp is the logarithm of the sum of the rounded probabilities (unrounded where a step moved
+the reference), so likewise 2^-8 between the two forms, and far less in the mean."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows_kept", ["all", "none_long", "some", "half"])
-@pytest.mark.parametrize("Hq,Hkv,L,Lq", [(4, 1, 128 * 200, 600), (16, 4, 128 * 700 - 41, 512), (32, 8, 128 * 170, 2048)])
+@pytest.mark.parametrize("Hq,Hkv,L,Lq", [(4, 1, 128 * 200, 600), (16, 4, 128 * 700 - 41, 512), (32, 8, 128 * 170, 2048),
+                                          (32, 8, 128 * 160, 5000)])   # more rows than the plan takes at once
 def test_parts_fit_the_slots(Hq, Hkv, L, Lq, rows_kept):
     import paper_2602_05853_amd as rr
     B, dev = 128, "cuda:0"
