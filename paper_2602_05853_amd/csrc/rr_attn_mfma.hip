@@ -666,7 +666,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         step_row(); step_last(); step_done();
     }
 
-  constexpr bool kSplit = kRagged && !kPersist && !kWide;    // the one instantiation that also serves split launches
+  constexpr bool kSplit = kRagged && !kPersist;              // the instantiations that also serve launches in parts
   for (;;) {
     // (The persistent form reads its arguments again for every row, and derives everything that depends on the
     // lane from a thread index the compiler takes for a new value each time: hoisted out of the row loop, the
@@ -1418,7 +1418,11 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     const bool ragged = g.Lr != g.L || g.qoff != 0 || a.nsplit > 1 || planned;   // split launches use the ragged instantiation
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     const long long rows = (long long)g.batch * g.Hq * (g.Lq / 128);
-    const bool wide = a.nsplit == 1 && !planned && wide_rows_pay(a.Nb, rows);
+    // Launches split into equal parts that are no more than the compute units (few heads, where the parts are at most 32): the
+    // longest part counts there as well.  128 tokens at 128K, 8 / 2 heads, dense 142 -> 109 us, 16 / 4 179 -> 174; 100 at 65536,
+    // 8 / 2, 94 -> 77; 32 / 8 heads fill the chip with rows of four waves (64 at 65536: 151 us, wide 164).  Planned launches stay
+    // on four waves: the plan makes more parts than there are compute units.
+    const bool wide = !planned && (a.nsplit == 1 ? wide_rows_pay(a.Nb, rows) : rows * a.nsplit <= compute_units());
     // workgroups the chip holds at once
     const int resident = (wide ? 1 : 2) * compute_units();
     // Persistent workgroups pay where rows are short, i.e. where the start of a row is a visible share of it, and
@@ -1453,7 +1457,10 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
         return hipGetLastError();
     };
     if (wide && persist) return ragged ? launch(k_attn_mfma_bf16<true, true, true>) : launch(k_attn_mfma_bf16<false, true, true>);
-    if (wide) return ragged ? launch(k_attn_mfma_bf16<true, false, true>) : launch(k_attn_mfma_bf16<false, false, true>);
+    if (wide) {
+        const hipError_t e = ragged ? launch(k_attn_mfma_bf16<true, false, true>) : launch(k_attn_mfma_bf16<false, false, true>);
+        return e != hipSuccess || a.nsplit == 1 ? e : launch_attn_combine(g, a, st);
+    }
     if (persist) return ragged ? launch(k_attn_mfma_bf16<true, true, false>) : launch(k_attn_mfma_bf16<false, true, false>);
     const hipError_t e = ragged ? launch(k_attn_mfma_bf16<true, false, false>) : launch(k_attn_mfma_bf16<false, false, false>);
     if (e != hipSuccess) return e;

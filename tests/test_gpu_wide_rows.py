@@ -65,3 +65,50 @@ def test_rows_of_four_and_of_eight_waves(Hq, Hkv, L, Lq):
             assert torch.equal(torch.isneginf(lse[0, h]), empty) and not O[0, h][empty].any()
             off = (lse[0, h] - want_lse)[~empty].abs()
             assert off.numel() == 0 or off.max().item() <= 2.0 ** -8 + 1e-5, (what, h)
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,Lq", [(8, 2, 128 * 34 - 20, 60), (8, 8, 128 * 300, 100), (9, 9, 128 * 300 - 7, 100),
+                                         (2, 1, 128 * 17, 128), (3, 1, 128 * 60 - 50, 40)])
+def test_equal_parts_of_four_and_of_eight_waves(Hq, Hkv, L, Lq):
+    """Split launches of up to 256 parts (eight waves) and of more (288, four): rows of no entry, of the diagonal block
+    alone, of fewer entries than parts, without the diagonal block, and of every block.  The parts are merged in fp32 from
+    sums that round P as above; the log-sum-exp of each is off by log(1 + 2^-8) at most."""
+    import paper_2602_05853_amd as rr
+    dev, B = "cuda:0", 128
+    g = torch.Generator(device=dev).manual_seed(L + Hq)
+    Q, K, V = (torch.randn(1, h, n, 128, generator=g, device=dev).bfloat16() for h, n in ((Hq, Lq), (Hkv, L), (Hkv, L)))
+    Q = Q * 1.5
+    Nb, q0 = -(-L // B), L - Lq
+    rows = Nb - q0 // B
+    assert rows == 1 and Hq // Hkv * Lq > 32                # neither a planned launch nor the decode kernel
+    m = Nb - 1
+    dense = (torch.rand(1, Hq, rows, Nb, generator=g, device=dev) < 0.3).to(torch.uint8)
+    for h, cols in enumerate(([], [m], [0, m], [1, 5], range(Nb), [m - 1], range(0, Nb - 1), [0])[:Hq]):
+        dense[0, h] = 0
+        dense[0, h, 0, list(cols)] = 1
+    mask = rr.rr_mask_from_dense(Q, K, dense, B)
+    ws = torch.full((rr.rr_attn_workspace_bytes(Q, K, B),), 0xFF, dtype=torch.uint8, device=dev)
+    assert ws.numel() > 0
+    kpos = torch.arange(L, device=dev)
+    causal = kpos[None] <= torch.arange(q0, L, device=dev)[:, None]
+    bound = 2.0 ** -7 * V.abs().max().item() + 1e-5
+    print(f"[parts] {Hq}/{Hkv} heads, {Lq} of {L}", flush=True)
+    for what in ("sparse", "dense"):
+        O = torch.full_like(Q, float("nan"))
+        lse = torch.full(Q.shape[:3], float("nan"), dtype=torch.float32, device=dev)
+        if what == "dense":
+            rr.rr_dense_attn(Q, K, V, B, O=O, lse=lse, workspace=ws)
+        else:
+            rr.rr_sparse_attn(Q, K, V, mask, O=O, lse=lse, workspace=ws)
+        torch.cuda.synchronize()
+        for h in range(Hq):
+            keep = causal
+            if what == "sparse":
+                keep = causal & dense[0, h, 0].bool().repeat_interleave(B)[:L][None]
+            want, want_lse = _attention(Q[0, h], K[0, h // (Hq // Hkv)], V[0, h // (Hq // Hkv)], keep)
+            empty = torch.isinf(want_lse)
+            assert torch.equal(torch.isinf(lse[0, h]), empty), (what, h)
+            assert not empty.any() or O[0, h][empty].abs().max() == 0
+            if (~empty).any():
+                assert (O[0, h].float() - want)[~empty].abs().max() <= bound, (what, h)
+                assert (lse[0, h] - want_lse)[~empty].abs().max() <= 2.0 ** -8, (what, h)
