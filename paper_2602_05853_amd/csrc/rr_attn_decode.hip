@@ -28,7 +28,7 @@ namespace rr {
 namespace {
 
 constexpr int kDecThreads = 256;
-constexpr int kDecMaxRows = 32;         // G * T
+constexpr int kDecMaxRows = 32;         // G * T: two tiles of 16 rows take 254 registers a lane, a third does not fit two waves a SIMD
 constexpr int kDecMaxLen = 1024;        // key blocks a part may have
 constexpr int kDecMaxParts = 256;
 constexpr int kDecBlock = 128;
@@ -317,7 +317,7 @@ size_t fallback_bytes(const Geom& g, int B) {
 // second round of workgroups costs more than longer parts save); steps of more rows, whose parts are wider, 256 (8 tokens
 // at 64K, 32 / 8 heads, 512 workgroups 55 us, 256 51; 4 tokens, 28 / 4, 42 and 35).  A part is at least two key blocks
 // long.  The shortest steps are taken at any depth; others where all rows lie deep in the context (16 causal blocks or
-// more), as the split launch of the 128-row kernel, which serves the steps with more rows.
+// more): the limit of the split launch of the 128-row kernel, kept so that the same calls go without a workspace.
 int attn_decode_parts(const Geom& g, int B) {
     if (B != kDecBlock || g.d != 128) return 0;
     const int T = g.Lr - g.q0, Nb = g.L / B, Nbq = g.Lq / B;

@@ -15,7 +15,7 @@
 //
 // Measured against the form before it (one workgroup per query block, fp32 vector FMAs on operands staged in LDS, where
 // every multiply-add waited for an LDS read): fp32, 1024 tokens, 4 / 2 heads of 64: 576 -> 19 us; fp32, 4096 tokens, 8 / 2
-// heads of 128: 5954 -> 174 us (62 TFLOP/s of selected blocks); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 183 us.
+// heads of 128: 5954 -> 175 us (62 TFLOP/s of selected blocks); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 186 us.
 //
 // Softmax: base 2, the reference is moved only when a wave's sum of a step exceeds 2^8 (all terms of a row share it).
 #include "rr_attn_frag.hpp"

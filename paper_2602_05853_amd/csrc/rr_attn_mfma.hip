@@ -561,8 +561,8 @@ template <bool kRagged, bool kPersist, bool kWide>
 __global__ void __launch_bounds__(kWide ? 2 * kThreads : kThreads, 2)
 k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // kRagged: the real length ends inside the last block (g.Lr < g.L) or the queries start inside their first
-    // block (g.qoff > 0): clamped Q rows, a clamped copy of the partial diagonal tile, predicated stores.  Compiled apart so that the plain launch carries none of it
-    // (both forms run at the same rate).
+    // block (g.qoff > 0): clamped Q rows, a clamped copy of the partial diagonal tile, predicated stores.  Compiled apart so
+    // that the plain launch carries none of it (both forms run at the same rate).
     //
     // kPersist (sparse launches with a row order and a queue): two workgroups per compute unit that take row after
     // row.  Workgroup i starts with launch rank i and then draws ranks x + 8 t (x = i mod 8, the XCD the
@@ -1272,8 +1272,8 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
 }
 
 // The cut rows: O = sum_p exp(lse_p - lse) O_p over the row's parts, rounded once.  A wavefront per query row
-// (blockIdx.x: which cut row, blockIdx.y picks four of its tile's 128), a lane two channels; the parts' lse values are read by one lane each, so
-// that nothing in the merge is a chain of dependent loads.  At most 64 parts per row.
+// (blockIdx.x: which cut row, blockIdx.y picks four of its tile's 128), a lane two channels; the parts' lse values are
+// read by one lane each, so that nothing in the merge is a chain of dependent loads.  At most 64 parts per row.
 __global__ void __launch_bounds__(256)
 k_attn_combine_plan(Geom g, AttnArgs a) {
     const int Nbq = g.Lq >> 7;
