@@ -1091,24 +1091,34 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
 
 }  // namespace
 
-// KV groups launched interleaved: the largest divisor of the number of groups that keeps K and V of the set
-// within 32 MB, the L2 capacity of the chip (8 XCDs x 4 MB).  Measured on the 128K-token workload's generator at
-// other lengths: 8 groups at 8K tokens (32 MB) +24 %, 4 at 16K +7 %, 2 at 32K +5 %; sets of 64 MB and 128 MB
-// lose 2-6 % at 32K-128K (their rows no longer find each other's tiles in L2), so 64K tokens and more keep
-// one group at a time.
-#ifndef RR_INTERLEAVE_BYTES
-#define RR_INTERLEAVE_BYTES (32ll << 20)
-#endif
-int interleave_groups(const Geom& g) {
+constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens, see launch_attn_mfma_bf16
+
+// KV groups launched interleaved (decode_block, order_entry_of): one set of them after the other, and a set ends with light rows
+// while the next one's heavy rows have not started.  A set should therefore hold several rows for each of the 512
+// workgroups that run at once -- the smallest divisor of the number of groups that makes it 3000 rows -- but its
+// rows find each other's tiles in L2 (32 MB) only so long.  Sets of more K and V than that lose less than the tails cost up to
+// 96 MB, on contexts longer than 32K tokens, one workgroup per row, up to 76 MB, and there only where at least three
+// of four tails go.  Measured, attention alone, tau 0.9, us, sets of 1 / 2 / 4 / 8 groups:
+//   32 / 8 heads: 9000 tokens 297, 295, 267, 203; 16384 780, 722, 632, 542; 24000 1481, 1363, 1211, 1186; 28000 1737, 1769, 1546, 1584; 32768
+//     2613, 2379, 2122, 2221; 40000 3247, 3103, 3075, 3120; 50000 4901, 4712, 4868, 4972; 65536 8368, 7893, 8055, 8395 (weaker
+//     structure 14315, 14482, 14995, 15723); 98304 18245, 18973, 19982, 20243; 131072 31951, 32166, 34074, 36301
+//   64 / 8: 8192 491, 420, 351, 326; 12000 916, 806, 682, 693; 20000 1985, 1760, 1626, 1703; 40000 6284, 6049, 6075, 6441; 65536 15912, 16012
+//   28 / 4: 20000 907, 811, 734; 32768 2361, 2057, 2035; 40000 2659, 2788, 2828; 50000 4304, 4180, 4414; 65536 6973, 7229, 7419
+//   8 / 2: 32768 694, 585; 50000 1224, 1259; 65536 2260, 2306
+// (Sets within 32 MB, whatever their rows: 20000 1033 us, 16384 628, 32768 2613.)  Launches in parts, whose long rows are cut,
+// and those without a row order keep to 32 MB: for the first no size of set is better throughout, and dense ones are level (4096
+// tokens 186, 183, 163, 162, taken with 32 MB as well; 16384 2012 with two groups, 2032 with eight).
+int interleave_groups(const Geom& g, bool by_size) {
     const long long per_group = 2ll * g.L * g.d * 2;               // K and V of one KV head, bf16
-    const int NG = g.batch * g.Hkv;
+    const int NG = g.batch * g.Hkv, Nb = g.L / 128;
+    const long long rows = (long long)g.G * (g.Lq / 128);          // of a group
+    const bool far = Nb > kPersistMaxBlocks;
+    const long long most = (by_size ? 32ll : far ? 76ll : 96ll) << 20;
     int gi = 1;
-    for (int c = 1; c <= NG && c <= 64; ++c)
-        if (NG % c == 0 && c * per_group <= RR_INTERLEAVE_BYTES) gi = c;
+    for (int c = 2; c <= NG && c <= 64 && (by_size || gi * rows < 3000); ++c)
+        if (NG % c == 0 && c * per_group <= most && (by_size || !far || 4 * c <= NG)) gi = c;
     return gi;
 }
-
-constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens, see launch_attn_mfma_bf16
 
 // compute units of the present device, a multiple of 8 so that workgroup i of a persistent launch sits on XCD i mod 8
 int compute_units() {
@@ -1410,11 +1420,11 @@ bool wide_rows_pay(int Nb, long long rows) { return rows <= std::min<long long>(
 
 hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_t st) {
     AttnArgs a = a_in;
-    a.interleave = interleave_groups(g);
     if (a.nsplit < 1 || !a.part_O || !a.part_lse) a.nsplit = 1;
     const bool planned = a.split_len > 0 && a.split_budget > 0 && a.plan_total && a.plan_row && a.plan_items && a.plan_cut &&
                          a.part_O && a.part_lse;
     if (!planned) { a.split_len = 0; a.split_budget = 0; } else a.nsplit = 1;
+    a.interleave = interleave_groups(g, planned || a.nsplit > 1 || !a.row_order);
     const bool ragged = g.Lr != g.L || g.qoff != 0 || a.nsplit > 1 || planned;   // split launches use the ragged instantiation
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     const long long rows = (long long)g.batch * g.Hq * (g.Lq / 128);
