@@ -105,23 +105,27 @@ __device__ __forceinline__ int v_swz(int key, int chunk) { return key * 256 + ((
 // Ordered launches: the entry of the caller-supplied row order (rows of each KV group, heaviest first) that
 // launch rank `bid` stands for, with the batch index and the first query head of its KV group.  Sets of gi
 // groups, rank by rank inside a set, the group's position rotating with the rank.
-__device__ __forceinline__ int order_entry_of(int bid, const Geom& g, int Nb, const int32_t* order, int gi,
+__device__ __forceinline__ int order_entry_of(int bid, const Geom& g, int Nb, const int32_t* order, int gi, int hoist,
                                               int& b, int& h0) {
-    const int N = g.G * Nb;
-    const int set = bid / (gi * N), r = bid - set * (gi * N);
-    const int rank = r / gi;
-    const int grp = set * gi + (r - rank * gi + rank) % gi;
+    const int N = g.G * Nb, NG = g.batch * g.Hkv;
+    const bool first = bid < NG * hoist;                   // the `hoist` heaviest rows of every group, then the sets
+    const int n = first ? NG : gi, rows = first ? hoist : N - hoist;
+    const int at = first ? bid : bid - NG * hoist;
+    const int set = at / (n * rows), r = at - set * (n * rows);
+    const int q = r / n;
+    const int rank = first ? q : hoist + q;
+    const int grp = set * n + (r - q * n + rank) % n;
     b = grp / g.Hkv;
     h0 = (grp - b * g.Hkv) * g.G;
     return order[(long long)grp * N + rank];
 }
 
-__device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, const int32_t* order, int a_interleave,
+__device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, const int32_t* order, int a_interleave, int hoist,
                                              int& b, int& h, int& m) {
     const int NG = g.batch * g.Hkv, G = g.G;
     int mr, grp, hl;
     if (order) {
-        const int v = order_entry_of(bid, g, Nb, order, a_interleave, b, h);
+        const int v = order_entry_of(bid, g, Nb, order, a_interleave, hoist, b, h);
         if ((unsigned)v >= (unsigned)(G * Nb)) return false;
         hl = v / Nb;
         m = v - hl * Nb;
@@ -616,7 +620,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         if (rank >= 0 && rank < (long long)g.batch * g.Hq * Nbq) {
             int pb, ph;
             nx.rank = (int)rank;
-            nx.order_entry = order_entry_of((int)rank, g, Nbq, ka->a.row_order, ka->a.interleave, pb, ph);
+            nx.order_entry = order_entry_of((int)rank, g, Nbq, ka->a.row_order, ka->a.interleave, ka->a.hoist, pb, ph);
             nx.b = __builtin_amdgcn_readfirstlane(pb);
             nx.h = __builtin_amdgcn_readfirstlane(ph);
         } else {
@@ -716,7 +720,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         } else {
             const int rank = (int)blockIdx.x - used;
             if (planned && rank >= grid_rows) return;
-            have_row = decode_block(kSplit && !planned ? rank / a.nsplit : rank, g, Nbq, a.row_order, a.interleave, b, h, mq);
+            have_row = decode_block(kSplit && !planned ? rank / a.nsplit : rank, g, Nbq, a.row_order, a.interleave, a.hoist, b, h, mq);
             if (planned) part = 0;
         }
         if (!have_row) return;
@@ -1093,31 +1097,32 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
 
 constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens, see launch_attn_mfma_bf16
 
-// KV groups launched interleaved (decode_block, order_entry_of): one set of them after the other, and a set ends with light rows
-// while the next one's heavy rows have not started.  A set should therefore hold several rows for each of the 512
-// workgroups that run at once -- the smallest divisor of the number of groups that makes it 3000 rows -- but its
-// rows find each other's tiles in L2 (32 MB) only so long.  Sets of more K and V than that lose less than the tails cost up to
-// 96 MB, on contexts longer than 32K tokens, one workgroup per row, up to 76 MB, and there only where at least three
-// of four tails go.  Measured, attention alone, tau 0.9, us, sets of 1 / 2 / 4 / 8 groups:
-//   32 / 8 heads: 9000 tokens 297, 295, 267, 203; 16384 780, 722, 632, 542; 24000 1481, 1363, 1211, 1186; 28000 1737, 1769, 1546, 1584; 32768
-//     2613, 2379, 2122, 2221; 40000 3247, 3103, 3075, 3120; 50000 4901, 4712, 4868, 4972; 65536 8368, 7893, 8055, 8395 (weaker
-//     structure 14315, 14482, 14995, 15723); 98304 18245, 18973, 19982, 20243; 131072 31951, 32166, 34074, 36301
-//   64 / 8: 8192 491, 420, 351, 326; 12000 916, 806, 682, 693; 20000 1985, 1760, 1626, 1703; 40000 6284, 6049, 6075, 6441; 65536 15912, 16012
-//   28 / 4: 20000 907, 811, 734; 32768 2361, 2057, 2035; 40000 2659, 2788, 2828; 50000 4304, 4180, 4414; 65536 6973, 7229, 7419
-//   8 / 2: 32768 694, 585; 50000 1224, 1259; 65536 2260, 2306
-// (Sets within 32 MB, whatever their rows: 20000 1033 us, 16384 628, 32768 2613.)  Launches in parts, whose long rows are cut,
-// and those without a row order keep to 32 MB: for the first no size of set is better throughout, and dense ones are level (4096
-// tokens 186, 183, 163, 162, taken with 32 MB as well; 16384 2012 with two groups, 2032 with eight).
-int interleave_groups(const Geom& g, bool by_size) {
+// KV groups launched interleaved (decode_block, order_entry_of): the largest divisor of the number of groups that keeps K and V of
+// the set within 38 MB.  More groups to a set find less of each other's tiles in L2 (8 x 4 MB), fewer put more of a
+// launch's heavy rows late.  And what starts late counts: the longest row (the protected one keeps every block) of the last set took as
+// long as that whole set, so sparse launches first take the heaviest rows of ALL groups, one run of the row order (8 G
+// rows, which one XCD each was chosen for), and then the sets.  Sets of 4096 rows and more (eight to each of the 512 workgroups that
+// run at once) go without: 128K, estimate and attention 32.4 ms, 32.7 with it; and contexts of more than 256 blocks with fewer
+// than eight groups: the last set is a large part of the launch there, and the mixed rows cost what they save.
+// Measured, attention alone, tau 0.9, us; sets of 32 MB without the first run / sets of 1, 2, 4 groups with it:
+//   32 / 8 heads: 9000 tokens 265 / 208, 206, 206; 16384 628 / 580, 555, 541; 24000 1330 / 1217, 1171, 1158; 28000 1730 / 1580, 1532,
+//     1545; 36000 3020 / 2699, 2643, 2736; 50000 4950 / 4637, 4617, 4731; 65536 8350 / 7906, 7704, 8065 (weaker structure 14349 / 14201,
+//     14321, 15066); 98304 18126 / 18141, 18479, 19748; 131072 32503 / 32249, 32013, 33814
+//   64 / 8: 12000 685 / 706, 694, 689; 20000 1704 / 1692, 1633, 1664; 65536 (S = 8) 20671 / 20342, 20365, 21409
+//   28 / 4: 20000 806 / 773, 731, 739; 8 / 2: 20000 272 / 260, 271; not taken: 28 / 4 40000 2715 / 2672; 8 / 2 50000 1204 / 1226; 28 / 4, eight
+//     packed prompts (311 blocks) 1371 / 1385
+int interleave_groups(const Geom& g) {
     const long long per_group = 2ll * g.L * g.d * 2;               // K and V of one KV head, bf16
-    const int NG = g.batch * g.Hkv, Nb = g.L / 128;
-    const long long rows = (long long)g.G * (g.Lq / 128);          // of a group
-    const bool far = Nb > kPersistMaxBlocks;
-    const long long most = (by_size ? 32ll : far ? 76ll : 96ll) << 20;
+    const int NG = g.batch * g.Hkv;
     int gi = 1;
-    for (int c = 2; c <= NG && c <= 64 && (by_size || gi * rows < 3000); ++c)
-        if (NG % c == 0 && c * per_group <= most && (by_size || !far || 4 * c <= NG)) gi = c;
+    for (int c = 1; c <= NG && c <= 64; ++c)
+        if (NG % c == 0 && c * per_group <= 38ll << 20) gi = c;
     return gi;
+}
+int hoisted_rows(const Geom& g, int interleave) {
+    const int NG = g.batch * g.Hkv, rows = g.G * (g.Lq / 128);
+    if (interleave == NG || interleave * rows >= 4096 || 8 * g.G >= rows || (g.L / 128 > kPersistMaxBlocks && NG < 8)) return 0;
+    return 8 * g.G;
 }
 
 // compute units of the present device, a multiple of 8 so that workgroup i of a persistent launch sits on XCD i mod 8
@@ -1244,7 +1249,7 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
         int parts = 0, rid = -1;
         if (rank < grid_rows) {
             int b, h, mq;
-            if (decode_block(rank, g, Nbq, a.row_order, a.interleave, b, h, mq)) {
+            if (decode_block(rank, g, Nbq, a.row_order, a.interleave, a.hoist, b, h, mq)) {
                 rid = (b * g.Hq + h) * Nbq + mq;
                 const int count = count_of(rid);
                 if (count > len) parts = (count + len - 1) / len;
@@ -1424,7 +1429,8 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     const bool planned = a.split_len > 0 && a.split_budget > 0 && a.plan_total && a.plan_row && a.plan_items && a.plan_cut &&
                          a.part_O && a.part_lse;
     if (!planned) { a.split_len = 0; a.split_budget = 0; } else a.nsplit = 1;
-    a.interleave = interleave_groups(g, planned || a.nsplit > 1 || !a.row_order);
+    a.interleave = interleave_groups(g);
+    a.hoist = planned || a.nsplit > 1 || !a.row_order ? 0 : hoisted_rows(g, a.interleave);
     const bool ragged = g.Lr != g.L || g.qoff != 0 || a.nsplit > 1 || planned;   // split launches use the ragged instantiation
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     const long long rows = (long long)g.batch * g.Hq * (g.Lq / 128);
