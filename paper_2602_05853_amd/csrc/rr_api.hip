@@ -300,10 +300,9 @@ RR_API int rr_estimate_ex(const rr_shape* shape, const void* Q, const void* K, i
         float* mass = reinterpret_cast<float*>(wsb + planes);
         float2* stats = reinterpret_cast<float2*>(reinterpret_cast<unsigned char*>(mass) +
                                                   align_up(estimate_mfma_mass_bytes(g, B), 256));
-        if (launch_stride_mass_mfma(g, Q, K, S, B, off_hmul, off_add, diag_token, opts->seq_first, ksplit, ls_cap,
-                                    ls_valid, mass, estimate_mfma_stats_bytes(g, S, B) ? stats : nullptr, st) != hipSuccess)
+        if (launch_estimate_mfma(g, a, ksplit, ls_cap, ls_valid, mass, estimate_mfma_stats_bytes(g, S, B) ? stats : nullptr, st) !=
+            hipSuccess)
             return RR_ERR_LAUNCH;
-        if (launch_select_rows(g, a, mass, st) != hipSuccess) return RR_ERR_LAUNCH;
     } else {
         float* Ksum = reinterpret_cast<float*>(wsb);
         if (launch_stride_sum(g, shape->dtype, K, S, Ksum, st) != hipSuccess) return RR_ERR_LAUNCH;

@@ -110,16 +110,15 @@ bool estimate_generic_fits(const Geom& g, int S, int B);   // LDS plan within th
 bool attn_generic_fits(int B, int d);
 hipError_t launch_estimate_generic(const Geom& g, int dtype, const EstimateArgs& a, hipStream_t st);
 
-// (2') MFMA form for bf16, d = 128, B/S in {4,8,16,32}: split stride sums, then scores -> stride softmax ->
-// block mass [batch*Hq*Nbq][Nb] in two sweeps; launch_select_rows then does Top-tau on those rows
-// (only a's selection parameters and output arrays are read).
+// (2') MFMA form for bf16, d = 128, B/S in {4,8,16,32}: split stride sums; then scores -> stride softmax -> block mass -> Top-tau
+// in one launch (short contexts), or block masses [batch*Hq*Nbq][Nb] in two sweeps and launch_select_rows, Top-tau on those rows
+// (which reads only a's selection parameters and output arrays).
 bool estimate_mfma_supported(const Geom& g, int dtype, int S, int B);
 size_t estimate_mfma_ksplit_bytes(const Geom& g, int S);
 size_t estimate_mfma_mass_bytes(const Geom& g, int B);
 size_t estimate_mfma_stats_bytes(const Geom& g, int S, int B);   // per-chunk softmax states of the key split; 0 without one
-hipError_t launch_stride_mass_mfma(const Geom& g, const void* Q, const void* K, int S, int B, int off_hmul,
-                                   int off_add, int diag_token, const int32_t* seq_first, unsigned short* ksplit,
-                                   int ls_cap, int ls_valid, float* mass, float2* stats, hipStream_t st);
+hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& a, unsigned short* ksplit, int ls_cap, int ls_valid,
+                                float* mass, float2* stats, hipStream_t st);
 // (ksplit holds rows of ls_cap >= L / S strides per (batch, KV head); the first ls_valid strides are kept as they are)
 hipError_t launch_select_rows(const Geom& g, const EstimateArgs& a, const float* mass, hipStream_t st);
 

@@ -392,53 +392,13 @@ k_select_rows(Geom g, EstimateArgs a, const float* __restrict__ mass, long long 
     const int mq = Nbq - 1 - (int)(slot % Nbq);
     const long long bh = slot / Nbq;
     const long long row_id = bh * Nbq + mq;
-    const int m = mq + (Nb - Nbq);
-    int nlo = seq_first ? seq_first[m] : 0;
-    nlo = nlo < 0 ? 0 : (nlo > m ? m : nlo);
-    const bool last_of_seq = (m == Nb - 1) || (seq_first && seq_first[m + 1] == m + 1);
-    const float* src = mass + row_id * Nb;
-    // a row without a sampled query (a last block without one complete stride, a decode step that holds none of
-    // its block's sampled positions) has no estimate, and nothing was written to its row of the workspace
     bool has_strides;
-    {
-        const int h = (int)(bh % g.Hq);
-        const int off = a.S - 1 - ((a.off_hmul * h + a.off_add) % a.S);
-        int r_hi = g.Lr / a.S - m * a.R;                       // strides of the block complete within the length
-        r_hi = r_hi > a.R ? a.R : r_hi;
-        int r_lo = g.q0 - off - m * a.R * a.S;                 // sampled positions not in front of the step
-        r_lo = r_lo <= 0 ? 0 : (r_lo + a.S - 1) / a.S;
-        has_strides = r_lo < r_hi;
-    }
-    SelectRow r;
-    r.nlo = nlo; r.m = m; r.Nb = Nb;
-    r.tau = a.tau;
-    r.keep_all = (a.tau >= 1.0f) || (a.protect_last && last_of_seq);
-    r.sink_blocks = a.sink_blocks; r.recent_blocks = a.recent_blocks;
-    r.dense = a.dense ? a.dense + row_id * Nb : nullptr;
-    r.list = a.row_list + row_id * Nb;
-    r.count = a.row_count + row_id;
+    SelectRow r = select_row_of(g, a, seq_first, bh, mq, has_strides);
+    const int nlo = r.nlo, m = r.m;
+    const float* src = mass + row_id * Nb;
     float* bm = a.block_mass ? a.block_mass + row_id * Nb : nullptr;
     if (NCH > 0) {
-        // the row fits in registers: 64 * NCH >= Nb
-        RowInRegs<(NCH > 0 ? NCH : 1)> row;
-        row.c0 = __builtin_amdgcn_readfirstlane(nlo) >> 6;
-        row.c1 = (__builtin_amdgcn_readfirstlane(m) >> 6) + 1;
-        float part = 0.f;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int n = 64 * c + lane;
-            row.v[c] = (has_strides && n >= nlo && n <= m) ? src[n] : 0.f;
-            part += row.v[c];
-        }
-        const float total = wave_sum_fixed(part);
-        const bool estimated = total > 0.f;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            row.v[c] = estimated ? row.v[c] / total : 0.f;
-            if (bm && 64 * c + lane < Nb) bm[64 * c + lane] = row.v[c];
-        }
-        r.keep_all = r.keep_all || !estimated;
-        select_row_wave(row, r, lane);
+        select_row_in_regs<(NCH > 0 ? NCH : 1)>(r, has_strides, src, bm, lane);
     } else {
         float* frac = reinterpret_cast<float*>(lds) + (size_t)w * ((Nb + 63) / 64 * 64);
         float part = 0.f;

@@ -26,6 +26,9 @@
 // block).  The matrix work doubles; the traffic to memory drops by 2 R and the per-row selection
 // (k_select_rows) reads R times less.
 #include "rr_common.hpp"
+#include "rr_select.hpp"
+
+#include <type_traits>
 
 namespace rr {
 
@@ -493,6 +496,178 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
     }
 }
 
+
+// ---- short contexts: scores, softmax, block mass and selection in one launch ----
+// Up to 1024 key strides the scores of 64 sampled queries against ALL of them fit the registers of one workgroup: eight
+// waves, each TPW tiles of 32 strides (tile w + 8 i) by two column tiles of queries.  The matrix work is then done once
+// instead of twice, the softmax needs no second sweep (the waves exchange maxima and sums through LDS), nothing is
+// left for another launch, and the workgroup selects its own 64 / R rows, whose masses meet in LDS.  A workgroup takes
+// 64 / R consecutive (query block, head) pairs of a KV head, so the heads of a query block share the stride sums it
+// reads, which go from L2 straight to the operand registers (every wave has tiles of its own: nothing to share in LDS).
+// What bounds it: the chain launch, queries, stride sums, softmax, selection of one row, each waiting for the one before; 8192
+// tokens, 32 / 8 heads: 15 us where two sweeps and the selection took 21 + 19 + 7.
+constexpr int kRowWaves = 8, kRowCols = 64;
+constexpr int kRowTiles = 4 * kRowWaves;                           // the most tiles of key strides it takes
+template <int R, int TPW>
+__global__ void __launch_bounds__(64 * kRowWaves, 2)
+k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
+    constexpr int P = kRowCols / R;                                // (query block, head) pairs of a workgroup
+    constexpr int kMaxNb = kTileStrides * kRowWaves * TPW / R;     // key blocks its tiles cover
+    __shared__ float s_red[2][kRowWaves][kRowCols];
+    __shared__ float s_mass[P][kMaxNb];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, gsel = lane >> 5;
+    const int Nbq = g.Lq / (R * a.S), mfirst = a.Nb - Nbq;
+    const int npairs = Nbq * g.G, ngroups = (npairs + P - 1) / P;
+    // the last query blocks (the most tiles) first, the KV head fastest, as in k_stride_mass_mfma
+    const int kvs = g.Hkv * g.batch;
+    const int rank = (int)blockIdx.x / kvs, pr = (int)blockIdx.x - rank * kvs;
+    const int p0 = (ngroups - 1 - rank) * P;
+    const int b = pr / g.Hkv, kv = pr - b * g.Hkv;
+    const int m_last = mfirst + (min(p0 + P, npairs) - 1) / g.G;   // of the workgroup's pairs
+    const int ntiles = ((m_last + 1) * R - 1) / kTileStrides + 1;
+    const int sure = (mfirst + p0 / g.G) * R;                      // every sampled query here sees the strides up to this one
+
+    bf16x8 qf[2][8];
+    int qi_stride[2];                 // query stride index m R + r, or -1: no such sampled query
+    int q_m[2];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+        const int q = 32 * nt + l32, pi = p0 + q / R, r = q & (R - 1);
+        const bool in_group = pi < npairs;
+        const int ml = in_group ? pi / g.G : 0;
+        const int h = kv * g.G + (in_group ? pi - ml * g.G : 0), m = mfirst + ml;
+        const long long pos = (long long)(m * R + r) * a.S + (a.S - 1 - ((a.off_hmul * h + a.off_add) % a.S)) - g.q0;   // Sec. 3.1
+        const bool valid = in_group && (m * R + r + 1) * a.S <= g.Lr && pos >= 0;
+        qi_stride[nt] = valid ? m * R + r : -1;
+        q_m[nt] = in_group ? m : -1;
+        const unsigned short* qp = a.Q + b * g.qsb + h * g.qsh + pos * g.qsl + 8 * gsel;
+#pragma unroll
+        for (int kc = 0; kc < 8; ++kc) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (valid) v = *reinterpret_cast<const u32x4*>(qp + 16 * kc);
+            qf[nt][kc] = __builtin_bit_cast(bf16x8, v);
+        }
+    }
+    const long long plane = (long long)g.batch * g.Hkv * a.LsCap * g.d;
+    const unsigned short* kbase = a.Ksp + ((long long)(b * g.Hkv + kv) * a.LsCap) * g.d + 8 * gsel;
+    const float NEG_INF = -__builtin_huge_valf();
+
+    f32x16 s[TPW][2];
+    float mx[2] = {NEG_INF, NEG_INF};
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+        const int jt = w + kRowWaves * i, j0 = jt * kTileStrides;
+        if (jt < ntiles) {
+            const unsigned short* kp = kbase + (long long)min(j0 + l32, a.Ls - 1) * g.d;
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) s[i][nt][e] = 0.f;
+#pragma unroll
+            for (int kc = 0; kc < 8; ++kc)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kp + p * plane + 16 * kc);
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt)
+                        s[i][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[nt][kc], s[i][nt], 0, 0, 0);
+                }
+            const bool need_mask = j0 + kTileStrides - 1 > sure;
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const int iq = qi_stride[nt];
+                f32x16 v = s[i][nt];
+                if (need_mask) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) v[e] = j0 + 8 * (e >> 2) + 4 * gsel + (e & 3) > iq ? NEG_INF : v[e];
+                    s[i][nt] = v;
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) mx[nt] = fmaxf(mx[nt], v[e]);
+            }
+        }
+    }
+    // the softmax over all key strides: maximum, then sum, of the lane's strides, of the two lanes of a query, of the waves
+    float nb[2], sum[2] = {0.f, 0.f}, invZ[2];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+        mx[nt] = fmaxf(mx[nt], lane_xor32(mx[nt], gsel != 0));
+        if (gsel == 0) s_red[0][w][32 * nt + l32] = mx[nt];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+        float top = NEG_INF;
+#pragma unroll
+        for (int i = 0; i < kRowWaves; ++i) top = fmaxf(top, s_red[0][i][32 * nt + l32]);
+        nb[nt] = top == NEG_INF ? 0.f : -(top * a.scale_log2);
+    }
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+        if (w + kRowWaves * i < ntiles) {
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    s[i][nt][e] = __builtin_amdgcn_exp2f(fmaf(s[i][nt][e], a.scale_log2, nb[nt]));
+                    sum[nt] += s[i][nt][e];
+                }
+        }
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+        sum[nt] += lane_xor32(sum[nt], gsel != 0);
+        if (gsel == 0) s_red[1][w][32 * nt + l32] = sum[nt];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+        float z = 0.f;
+#pragma unroll
+        for (int i = 0; i < kRowWaves; ++i) z += s_red[1][i][32 * nt + l32];
+        invZ[nt] = (qi_stride[nt] >= 0 && z > 0.f) ? 1.0f / z : 0.f;
+    }
+    // block masses, as in the second sweep of k_stride_mass_mfma
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+        const int jt = w + kRowWaves * i;
+        if (jt < ntiles) {
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                constexpr int NBL = (R == 4) ? 4 : kTileStrides / R;
+                constexpr int RPB = 16 / NBL;
+                const int r = l32 & (R - 1);
+                float out = 0.f;
+#pragma unroll
+                for (int k = 0; k < NBL; ++k) {
+                    float t = 0.f;
+#pragma unroll
+                    for (int e = 0; e < RPB; ++e) t += s[i][nt][k * RPB + e];
+                    if (R != 4) t += lane_xor32(t, gsel != 0);
+                    const float tot = group_sum<R>(t * invZ[nt]);
+                    if (r == k) out = tot;
+                }
+                const int n = (R == 4) ? jt * 8 + 2 * r + gsel : jt * NBL + r;
+                const bool writer = (R == 4) ? true : (gsel == 0 && r < NBL);
+                if (writer && n <= q_m[nt]) s_mass[(32 * nt + l32) / R][n] = out;
+            }
+        }
+    }
+    __syncthreads();
+    // the rows, one to a wave
+    for (int j = w; j < P; j += kRowWaves) {
+        const int pi = p0 + j;
+        if (pi >= npairs) break;
+        const int mq = pi / g.G;
+        const long long bh = (long long)b * g.Hq + kv * g.G + (pi - mq * g.G);
+        bool has_strides;
+        const SelectRow row = select_row_of(g, ea, nullptr, bh, mq, has_strides);
+        float* bm = ea.block_mass ? ea.block_mass + (bh * Nbq + mq) * a.Nb : nullptr;
+        select_row_in_regs<(kMaxNb + 63) / 64>(row, has_strides, s_mass[j], bm, lane);
+    }
+}
+
 }  // namespace
 
 size_t estimate_mfma_ksplit_bytes(const Geom& g, int S) {
@@ -533,40 +708,68 @@ bool estimate_mfma_supported(const Geom& g, int dtype, int S, int B) {
     return dtype == RR_BF16 && g.d == 128 && (R == 4 || R == 8 || R == 16 || R == 32) && g.G * R <= 256;
 }
 
-hipError_t launch_stride_mass_mfma(const Geom& g, const void* Q, const void* K, int S, int B, int off_hmul,
-                                   int off_add, int diag_token, const int32_t* seq_first, unsigned short* ksplit,
-                                   int ls_cap, int ls_valid, float* mass, float2* stats, hipStream_t st) {
-    const int Ls = g.L / S, R = B / S, Nb = g.L / B;
+hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned short* ksplit, int ls_cap, int ls_valid,
+                                float* mass, float2* stats, hipStream_t st) {
+    const int S = ea.S, B = ea.B, Ls = g.L / S, R = B / S, Nb = g.L / B, Nbq = g.Lq / B;
     if (ls_cap < Ls || ls_valid < 0) return hipErrorInvalidValue;
     const int j0 = ls_valid < Ls ? ls_valid : Ls;
     if (j0 < Ls) {
         const long long total = (long long)g.batch * g.Hkv * (Ls - j0) * (g.d / 8);
         hipLaunchKernelGGL(k_stride_sum_split, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, g,
-                           (const unsigned short*)K, S, Ls, j0, ls_cap, ksplit);
+                           (const unsigned short*)ea.K, S, Ls, j0, ls_cap, ksplit);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     ScoreArgs a;
-    a.Q = (const unsigned short*)Q;
+    a.Q = (const unsigned short*)ea.Q;
     a.Ksp = ksplit;
     a.LsCap = ls_cap;
     a.mass = mass;
-    a.off_hmul = off_hmul;
-    a.off_add = off_add;
-    a.seq_first = seq_first;
-    a.K = (const unsigned short*)K;
-    a.diag_token = diag_token;
+    a.off_hmul = ea.off_hmul;
+    a.off_add = ea.off_add;
+    a.seq_first = ea.seq_first;
+    a.K = (const unsigned short*)ea.K;
+    a.diag_token = ea.diag_token;
     a.S = S; a.R = R; a.Nb = Nb; a.Ls = Ls;
     a.MB = 256 / (g.G * R);
-    const int Nbq = g.Lq / B;
     if (a.MB > Nbq) a.MB = Nbq;
     const double sc = 1.0 / ((double)S * sqrt((double)g.d));
     a.scale_log2 = (float)(sc * 1.4426950408889634);
+    const bool ext = ea.seq_first != nullptr || ea.diag_token != 0;
+    const int tiles = (Ls + kTileStrides - 1) / kTileStrides, P = kRowCols / R;
+    const long long row_wgs = (long long)((Nbq * g.G + P - 1) / P) * g.Hkv * g.batch;
+    // One launch where its workgroups, which fill a compute unit each and do not overlap one's loads with another's products,
+    // are less than three to a compute unit.  The whole estimate, us, two sweeps and selection / one launch, with its workgroups:
+    // 32 / 8 heads, S = 16: 2048 tokens (64) 33 / 20, 8192 (256) 57 / 33, 16384 (512) 73 / 64; two prompts of 8192 (512) 63 / 48, four
+    // (1024) 83 / 86; 64 / 8: 10000 (632) 71 / 63, 12000 (752) 75 / 74, 16384 (1024) 98 / 111; S = 8, 8192 (1024) 90 / 98; S = 32, 16384 (512)
+    // 69 / 56; eight prompts of 2048 (1024) 45 / 49.
+    if (!ext && tiles <= kRowTiles && row_wgs <= 700) {
+        a.nsplit = 1;
+        a.mode = 0;
+        a.stats = nullptr;
+        const dim3 grid((unsigned)row_wgs);
+        auto launch = [&](auto kernel) -> hipError_t {
+            hipLaunchKernelGGL(kernel, grid, dim3(64 * kRowWaves), 0, st, g, a, ea);
+            return hipGetLastError();
+        };
+        auto pick = [&](auto r) -> hipError_t {
+            constexpr int RV = decltype(r)::value;
+            if (tiles <= kRowWaves) return launch(k_estimate_rows<RV, 1>);
+            if (tiles <= 2 * kRowWaves) return launch(k_estimate_rows<RV, 2>);
+            return launch(k_estimate_rows<RV, 4>);
+        };
+        switch (R) {
+            case 4: return pick(std::integral_constant<int, 4>{});
+            case 8: return pick(std::integral_constant<int, 8>{});
+            case 16: return pick(std::integral_constant<int, 16>{});
+            case 32: return pick(std::integral_constant<int, 32>{});
+            default: return hipErrorInvalidValue;
+        }
+    }
     const int ngroups = (Nbq + a.MB - 1) / a.MB;
     a.nsplit = stats ? estimate_mfma_splits(g, S, B) : 1;
     a.stats = a.nsplit > 1 ? stats : nullptr;
     dim3 grid((unsigned)ngroups * g.Hkv * g.batch * a.nsplit);
-    const bool ext = seq_first != nullptr || diag_token != 0;
 #define RR_LAUNCH_MASS(RV)                                                                          \
     do {                                                                                            \
         if (ext) hipLaunchKernelGGL((k_stride_mass_mfma<RV, true>), grid, dim3(kThreads), kLdsBytes, st, g, a);  \
@@ -586,7 +789,7 @@ hipError_t launch_stride_mass_mfma(const Geom& g, const void* Q, const void* K, 
         if (e != hipSuccess) return e;
     }
 #undef RR_LAUNCH_MASS
-    return hipSuccess;
+    return launch_select_rows(g, ea, mass, st);
 }
 
 }  // namespace rr

@@ -157,4 +157,58 @@ __device__ __forceinline__ void select_row_wave(const Row& row, const SelectRow&
     }
 }
 
+// The selection of mask row mq of head h of batch bh / Hq (bh = b Hq + h), but for its masses.  has_strides: a row
+// without a sampled query (a last block without one complete stride, a decode step that holds none of its block's sampled
+// positions) has no estimate and no masses.
+__device__ __forceinline__ SelectRow select_row_of(const Geom& g, const EstimateArgs& a, const int32_t* seq_first, long long bh,
+                                                   int mq, bool& has_strides) {
+    const int Nb = a.Nb, Nbq = g.Lq / a.B;
+    const long long row_id = bh * Nbq + mq;
+    const int m = mq + (Nb - Nbq);
+    int nlo = seq_first ? seq_first[m] : 0;
+    nlo = nlo < 0 ? 0 : (nlo > m ? m : nlo);
+    const bool last_of_seq = (m == Nb - 1) || (seq_first && seq_first[m + 1] == m + 1);
+    const int h = (int)(bh % g.Hq);
+    const int off = a.S - 1 - ((a.off_hmul * h + a.off_add) % a.S);
+    int r_hi = g.Lr / a.S - m * a.R;                       // strides of the block complete within the length
+    r_hi = r_hi > a.R ? a.R : r_hi;
+    int r_lo = g.q0 - off - m * a.R * a.S;                 // sampled positions not in front of the step
+    r_lo = r_lo <= 0 ? 0 : (r_lo + a.S - 1) / a.S;
+    has_strides = r_lo < r_hi;
+    SelectRow r;
+    r.nlo = nlo; r.m = m; r.Nb = Nb;
+    r.tau = a.tau;
+    r.keep_all = (a.tau >= 1.0f) || (a.protect_last && last_of_seq);
+    r.sink_blocks = a.sink_blocks; r.recent_blocks = a.recent_blocks;
+    r.dense = a.dense ? a.dense + row_id * Nb : nullptr;
+    r.list = a.row_list + row_id * Nb;
+    r.count = a.row_count + row_id;
+    return r;
+}
+
+// Selection of a row of up to 64 NCH blocks held in registers; mass: its masses (readable for nlo <= n <= m), bm: where its
+// fractions go as well, or nullptr.  Called by all 64 lanes of one wavefront.
+template <int NCH>
+__device__ __forceinline__ void select_row_in_regs(SelectRow r, bool has_strides, const float* mass, float* bm, int lane) {
+    RowInRegs<NCH> row;
+    row.c0 = __builtin_amdgcn_readfirstlane(r.nlo) >> 6;
+    row.c1 = (__builtin_amdgcn_readfirstlane(r.m) >> 6) + 1;
+    float part = 0.f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const int n = 64 * c + lane;
+        row.v[c] = (has_strides && n >= r.nlo && n <= r.m) ? mass[n] : 0.f;
+        part += row.v[c];
+    }
+    const float total = wave_sum_fixed(part);
+    const bool estimated = total > 0.f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        row.v[c] = estimated ? row.v[c] / total : 0.f;
+        if (bm && 64 * c + lane < r.Nb) bm[64 * c + lane] = row.v[c];
+    }
+    r.keep_all = r.keep_all || !estimated;
+    select_row_wave(row, r, lane);
+}
+
 }  // namespace rr
