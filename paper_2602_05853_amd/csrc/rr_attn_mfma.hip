@@ -773,9 +773,24 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         if (split && plan_slot != base + part) return;
     }
     if (split) {
-        const int len = planned ? __builtin_amdgcn_readfirstlane(a.plan_total[2]) : (count + a.nsplit - 1) / a.nsplit;
-        list_lo = min(count, part * len);
-        const int hi = min(count, list_lo + len);
+        int hi;
+        if (planned) {
+            const int len = __builtin_amdgcn_readfirstlane(a.plan_total[2]), parts = (count + len - 1) / len;
+            if (part < (parts & ~7)) {
+                // The heads of a KV group whose last query block keeps every block, two thirds of such a launch, walk the same
+                // ranges of keys: part p goes to the XCD p mod 8 in every row, where the tiles of the others may still be in L2.
+                // 2048 tokens at 128K: L2 hit rate 17 -> 42 %, estimate and attention 621 -> 590 us.
+                const int taken = (part & ~7) + ((int)blockIdx.x & 7);
+                plan_slot += taken - part;
+                part = taken;
+            }
+            list_lo = count * part / parts;                 // equal parts: dense, 2048 tokens at 128K 4.36 -> 3.82 ms
+            hi = count * (part + 1) / parts;
+        } else {
+            const int len = (count + a.nsplit - 1) / a.nsplit;
+            list_lo = min(count, part * len);
+            hi = min(count, list_lo + len);
+        }
         last_part = hi == count;
         count = hi - list_lo;
     }
@@ -1286,51 +1301,61 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
     if (t == 0) { a.plan_total[0] = s_used; a.plan_total[1] = s_cut; a.plan_total[2] = len; }
 }
 
-// The cut rows: O = sum_p exp(lse_p - lse) O_p over the row's parts, rounded once.  A wavefront per query row
-// (blockIdx.x: which cut row, blockIdx.y picks four of its tile's 128), a lane two channels; the parts' lse values are
-// read by one lane each, so that nothing in the merge is a chain of dependent loads.  At most 64 parts per row.
+// The cut rows: O = sum_p exp(lse_p - lse) O_p over the row's parts, rounded once.  Four query rows of a cut row's 128 to a
+// workgroup at a time, a wavefront each; the parts' lse values are read by one lane each, so that nothing in the merge is a chain
+// of dependent loads, and the two halves of the wavefront take every other part, a lane four channels.  At most 64 parts per row.
+// The number of cut rows is on the device: a fixed grid takes them in turns (one workgroup for each that might be there, and
+// whole wavefronts per part: 37 us, so 20; 2048 tokens at 128K, 1329 parts of 70 rows).
+constexpr int kMergeGroups = 2048;
 __global__ void __launch_bounds__(256)
 k_attn_combine_plan(Geom g, AttnArgs a) {
     const int Nbq = g.Lq >> 7;
-    if ((int)blockIdx.x >= a.plan_total[1]) return;                      // blockIdx.x: which of the cut rows
-    const int rid = a.plan_cut[blockIdx.x];
-    if ((unsigned)rid >= (unsigned)(g.batch * g.Hq * Nbq)) return;
-    const int base = a.plan_row[rid];
-    if (base < 0) return;
-    const int mq = rid % Nbq, bh = rid / Nbq, h = bh % g.Hq, b = bh / g.Hq;
-    const int m = mq + (a.Nb - Nbq);
-    int count = a.row_list ? a.row_count[rid] : m + 1;
-    count = count < 0 ? 0 : (count > m + 1 ? m + 1 : count);
-    const int len = a.plan_total[2];
-    int parts = (count + len - 1) / len;
-    parts = parts > 64 ? 64 : parts;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, half = lane >> 5;
     const long long rows_call = g.Lr - g.q0;
     const float NEG_INF = -__builtin_huge_valf();
-    const int x = 4 * (int)blockIdx.y + wv;                              // query row of the tile
-    const long long r = (long long)mq * 128 + x - g.qoff;               // row of Q / O
-    if (r < 0 || r >= rows_call) return;
-    const float l = lane < parts ? a.part_lse[(long long)(base + lane) * 128 + x] : NEG_INF;
-    float mx = l;
+    const int len = a.plan_total[2];
+    const int items = 32 * a.plan_total[1];                              // four query rows of a cut row each
+    for (int item = blockIdx.x; item < items; item += gridDim.x) {
+        const int rid = a.plan_cut[item >> 5];
+        if ((unsigned)rid >= (unsigned)(g.batch * g.Hq * Nbq)) continue;
+        const int base = a.plan_row[rid];
+        if (base < 0) continue;
+        const int mq = rid % Nbq, bh = rid / Nbq, h = bh % g.Hq, b = bh / g.Hq;
+        const int m = mq + (a.Nb - Nbq);
+        const int x = 4 * (item & 31) + wv;                              // query row of the tile
+        const long long r = (long long)mq * 128 + x - g.qoff;           // row of Q / O
+        if (r < 0 || r >= rows_call) continue;
+        int count = a.row_list ? a.row_count[rid] : m + 1;
+        count = count < 0 ? 0 : (count > m + 1 ? m + 1 : count);
+        int parts = (count + len - 1) / len;
+        parts = parts > 64 ? 64 : parts;
+        const float l = lane < parts ? a.part_lse[(long long)(base + lane) * 128 + x] : NEG_INF;
+        float mx = l;
 #pragma unroll
-    for (int sft = 32; sft >= 1; sft >>= 1) mx = fmaxf(mx, __shfl_xor(mx, sft));
-    const float wgt = (lane < parts && l != NEG_INF) ? expf(l - mx) : 0.f;
-    float den = wgt;
-#pragma unroll
-    for (int sft = 32; sft >= 1; sft >>= 1) den += __shfl_xor(den, sft);
-    float o0 = 0.f, o1 = 0.f;
-    const float* src = a.part_O + ((long long)base * 128 + x) * g.d + 2 * lane;
+        for (int sft = 32; sft >= 1; sft >>= 1) mx = fmaxf(mx, __shfl_xor(mx, sft));
+        const float wgt = l != NEG_INF ? expf(l - mx) : 0.f;
+        const float den = wave_sum_fixed(wgt);
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        const float* src = a.part_O + ((long long)base * 128 + x) * g.d + 4 * (lane & 31);
 #pragma unroll 4
-    for (int p = 0; p < parts; ++p) {
-        const float wp = __shfl(wgt, p);
-        const float2 v = *reinterpret_cast<const float2*>(src + (long long)p * 128 * g.d);
-        o0 = fmaf(wp, v.x, o0);
-        o1 = fmaf(wp, v.y, o1);
+        for (int p0 = 0; p0 < parts; p0 += 2) {
+            const int p = p0 + half;
+            const float wp = __shfl(wgt, p);
+            if (p < parts) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(src + (long long)p * 128 * g.d);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = fmaf(wp, v[e], o[e]);
+            }
+        }
+        const float inv = den > 0.f ? 1.0f / den : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (o[e] + __shfl_xor(o[e], 32)) * inv;
+        unsigned short* O = reinterpret_cast<unsigned short*>(a.O) + b * g.qsb + h * g.qsh + r * g.qsl;
+        if (half == 0)
+            *reinterpret_cast<u32x2*>(O + 4 * (lane & 31)) = u32x2{f32_to_bf16_bits(o[0]) | (f32_to_bf16_bits(o[1]) << 16),
+                                                                   f32_to_bf16_bits(o[2]) | (f32_to_bf16_bits(o[3]) << 16)};
+        if (a.lse && lane == 0) a.lse[((long long)b * g.Hq + h) * rows_call + r] = den > 0.f ? mx + logf(den) : NEG_INF;
     }
-    const float inv = den > 0.f ? 1.0f / den : 0.f;
-    unsigned short* O = reinterpret_cast<unsigned short*>(a.O) + b * g.qsb + h * g.qsh + r * g.qsl;
-    *reinterpret_cast<unsigned*>(O + 2 * lane) = f32_to_bf16_bits(o0 * inv) | (f32_to_bf16_bits(o1 * inv) << 16);
-    if (a.lse && lane == 0) a.lse[((long long)b * g.Hq + h) * rows_call + r] = den > 0.f ? mx + logf(den) : NEG_INF;
 }
 
 int attn_mfma_plan_len(const Geom& g, int B, int* budget) {
@@ -1481,9 +1506,9 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     const hipError_t e = ragged ? launch(k_attn_mfma_bf16<true, false, false>) : launch(k_attn_mfma_bf16<false, false, false>);
     if (e != hipSuccess) return e;
     if (planned) {
-        const long long rows_total = (long long)g.batch * g.Hq * (g.Lq / 128);
-        const long long cut_max = rows_total < a.split_budget / 2 ? rows_total : a.split_budget / 2;
-        hipLaunchKernelGGL(k_attn_combine_plan, dim3((unsigned)cut_max, 32), dim3(256), 0, st, g, a);
+        const long long cut_max = rows < a.split_budget / 2 ? rows : a.split_budget / 2;
+        const long long groups = 32 * cut_max < kMergeGroups ? 32 * cut_max : kMergeGroups;
+        hipLaunchKernelGGL(k_attn_combine_plan, dim3((unsigned)groups), dim3(256), 0, st, g, a);
         return hipGetLastError();
     }
     if (a.nsplit == 1) return e;

@@ -158,7 +158,7 @@ struct AttnArgs {
     // row a run of slots (one per part) in part_O / part_lse, here laid out [slot][128 query rows][d] and
     // [slot][128]: plan_row[row] = first slot or -1 (the row is computed whole and stored directly), plan_items[slot]
     // = row, plan_cut[k] = the k-th cut row, plan_total[0] = slots in use (at most split_budget; rows that no longer
-    // fit stay whole), plan_total[1] = cut rows, plan_total[2] = entries of a part.  The launch has one workgroup per slot and one per row.
+    // fit stay whole), plan_total[1] = cut rows, plan_total[2] = entries of a part at most (a row's parts are equal).  The launch has one workgroup per slot and one per row.
     // split_len = 0: off.
     int split_len, split_budget;
     int32_t* plan_total; int32_t* plan_row; int32_t* plan_items; int32_t* plan_cut;
