@@ -9,13 +9,14 @@
 // tiles of 16 keys (which may belong to different blocks, so that a block of 48 keys wastes nothing), wave w the
 // steps w, w + KW, ..., each with an online softmax of its own, and meet once, in LDS, at the end.  What bounds this
 // path is the length of the longest row (the protected last one keeps every block) on the few hundred query blocks
-// of such a call, and the traffic between L2 and the compute units (launch_attn_generic chooses QT for both).
+// of such a call, and the traffic between L2 and the compute units (launch_attn_generic chooses QT for both, and 16
+// queries to a workgroup for that row).
 // Fragments go from global memory (K and V of these shapes stay in L2) straight to registers: with keys split over
 // the waves no two of them would share a staged tile, and there is no barrier before the merge.
 //
 // Measured against the form before it (one workgroup per query block, fp32 vector FMAs on operands staged in LDS, where
 // every multiply-add waited for an LDS read): fp32, 1024 tokens, 4 / 2 heads of 64: 576 -> 19 us; fp32, 4096 tokens, 8 / 2
-// heads of 128: 5954 -> 175 us (62 TFLOP/s of selected blocks); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 186 us.
+// heads of 128: 5954 -> 175 us (145 with the last block on small tiles); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 186 us.
 //
 // Softmax: base 2, the reference is moved only when a wave's sum of a step exceeds 2^8 (all terms of a row share it).
 #include "rr_attn_frag.hpp"
@@ -23,7 +24,6 @@
 namespace rr {
 
 namespace {
-
 
 __device__ __forceinline__ void store4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
 __device__ __forceinline__ void store4(bf16_t* p, const f32x4& v) {
@@ -42,33 +42,23 @@ typedef const __attribute__((address_space(4))) int32_t* scalar_list_t;   // rea
 typedef const int32_t* scalar_list_t;                                    // the host pass only parses the kernel
 #endif
 
-template <typename T, int NT, int QT, int TL, int KW, int OCC>
-__global__ void __launch_bounds__(64 * KW, OCC)
-k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
+// The 16 QT queries from 16 QT sub on of query block m of head h, by the KW waves of a workgroup.
+template <typename T, int NT, int QT, int TL, int KW>
+__device__ __forceinline__ void attend(const Geom& g, const AttnArgs& a, float scale_log2, int b, int h, int m, int sub,
+                                       float* lds_o, float* lds_ref, float* lds_l) {
     using F = Frag<T, NT, TL>;
     constexpr int kQ = 16 * QT, kPitch = out_pitch<NT>(), kThreads = 64 * KW;
-    __shared__ __align__(16) float s_o[KW][kQ][kPitch];
-    __shared__ float s_ref[KW][kQ], s_l[KW][kQ];
+    typedef float (*rows_t)[kQ][kPitch];
+    typedef float (*sums_t)[kQ];
+    const rows_t s_o = reinterpret_cast<rows_t>(lds_o);
+    const sums_t s_ref = reinterpret_cast<sums_t>(lds_ref), s_l = reinterpret_cast<sums_t>(lds_l);
 
     const int B = a.B, d = g.d, Nb = a.Nb;
     const int t = threadIdx.x, lane = t & 63, x = lane & 15, gq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int Nbq = g.Lq / B;                         // rows of the launch (chunked prefill: the last query blocks)
-    // heaviest rows first (blockIdx.y), heads fastest, and of those the KV head: the XCDs, which take consecutive
-    // workgroups in turn, then each keep the keys of few KV heads in L2
-    // (more query blocks than the y axis holds: the rest in further turns of the x axis)
-    int bx = (int)blockIdx.x, rank = (int)blockIdx.y;
-    if (Nbq > (int)kMaxGridY) {
-        const int per_row = g.Hq * ((B + kQ - 1) / kQ), turn = bx / per_row;
-        bx -= turn * per_row;
-        if (rank >= Nbq - turn * (int)kMaxGridY) return;
-        rank += turn * (int)kMaxGridY;
-    }
-    const int m = Nb - 1 - rank;
     const int mq = m - (Nb - Nbq);
-    const int sub = bx / g.Hq, hx = bx - sub * g.Hq;
-    const int hl = hx / g.Hkv, kv = hx - hl * g.Hkv;
-    const int h = kv * g.G + hl, b = blockIdx.z;
+    const int kv = h / g.G;
     const long long row_id = ((long long)b * g.Hq + h) * Nbq + mq;
     // row y of the block (position m B + y) is row mq B + y - qoff of Q and O: a step that starts inside its
     // first block has no rows for the first qoff positions of that block
@@ -265,6 +255,38 @@ k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
     }
 }
 
+// QS < QT: the last query block is taken 16 QS queries to a workgroup, by QT / QS times as many (rows of the grid's second axis)
+template <typename T, int NT, int QT, int QS, int TL, int KW, int OCC>
+__global__ void __launch_bounds__(64 * KW, OCC)
+k_attn_generic(Geom g, AttnArgs a, float scale_log2) {
+    constexpr int kQ = 16 * QT;
+    __shared__ __align__(16) float s_o[KW * kQ * out_pitch<NT>()];
+    __shared__ float s_ref[KW * kQ], s_l[KW * kQ];
+    const int Nbq = g.Lq / a.B;
+    // heaviest rows first (blockIdx.y), heads fastest, and of those the KV head: the XCDs, which take consecutive
+    // workgroups in turn, then each keep the keys of few KV heads in L2
+    // (more query blocks than the y axis holds: the rest in further turns of the x axis)
+    int bx = (int)blockIdx.x, rank = (int)blockIdx.y;
+    if (Nbq > (int)kMaxGridY) {
+        const int per_row = g.Hq * ((a.B + kQ - 1) / kQ), turn = bx / per_row;
+        bx -= turn * per_row;
+        if (rank >= Nbq - turn * (int)kMaxGridY) return;
+        rank += turn * (int)kMaxGridY;
+    }
+    int sub = bx / g.Hq;
+    const int hx = bx - sub * g.Hq, hl = hx / g.Hkv, kv = hx - hl * g.Hkv;
+    const int h = kv * g.G + hl;
+    if constexpr (QS < QT) {
+        constexpr int kSplit = QT / QS;
+        if (rank < kSplit) {
+            attend<T, NT, QS, TL, KW>(g, a, scale_log2, blockIdx.z, h, a.Nb - 1, kSplit * sub + rank, s_o, s_ref, s_l);
+            return;
+        }
+        rank -= kSplit - 1;
+    }
+    attend<T, NT, QT, TL, KW>(g, a, scale_log2, blockIdx.z, h, a.Nb - 1 - rank, sub, s_o, s_ref, s_l);
+}
+
 }  // namespace
 
 // Shapes the entry points accept on this path: B (4 d + 19) fp32 words within 150 KB.  A bound of the interface (a caller pads
@@ -275,11 +297,12 @@ bool attn_generic_fits(int B, int d) {
 
 hipError_t launch_attn_generic(const Geom& g, int dtype, const AttnArgs& a, hipStream_t st) {
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
-    auto launch = [&](auto kernel, int queries, int waves) -> hipError_t {
+    auto launch = [&](auto kernel, int queries, int waves, int split) -> hipError_t {
         const unsigned subs = (unsigned)((a.B + queries - 1) / queries);
         const unsigned Nbq = (unsigned)(g.Lq / a.B), turns = (Nbq + kMaxGridY - 1) / kMaxGridY;
         if ((unsigned long long)g.Hq * subs * turns * 64 * waves > 0xFFFFFFFFull) return hipErrorInvalidValue;
-        dim3 grid((unsigned)g.Hq * subs * turns, Nbq < kMaxGridY ? Nbq : kMaxGridY, g.batch);
+        const unsigned ranks = Nbq + (split - 1);
+        dim3 grid((unsigned)g.Hq * subs * turns, ranks < kMaxGridY ? ranks : kMaxGridY, g.batch);
         hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, st, g, a, scale_log2);
         return hipGetLastError();
     };
@@ -292,19 +315,33 @@ hipError_t launch_attn_generic(const Geom& g, int dtype, const AttnArgs& a, hipS
     // 64 queries 182 us (dense 439 and 358 us; wider heads have no registers for 64).
     const long long rows = (long long)g.batch * g.Hq * (g.Lq / a.B);
     auto blocks = [&](int queries) { return rows * ((a.B + queries - 1) / queries); };
+    // The last query block 16 queries to a workgroup.  A sparse launch of so few workgroups takes as long as its longest row, and
+    // that is the protected last one (attention alone, us; this row alone, the rest alone, both before, now: fp32, 4096 tokens, 8 heads
+    // of 128: 166, 134, 168, 145; 2048 tokens 89, 58, 91, 60; bf16, 8000 tokens, 8 heads of 64: 114, 90, 121, 89; 4096 tokens, 16
+    // heads 63, 49, 67, 49).  Not where the rest takes longer (2000 workgroups and more; 8153 tokens, 16 heads: 126, 141, 146 and with it
+    // 146), not for dense calls, whose rows get shorter one by one, and not for further blocks (the last sixteenth of them: 8153 tokens
+    // 162, the first case 146).
+    auto short_last = [&](int queries) {
+        return a.row_list && a.B > 16 && blocks(queries) <= 1536 && g.Lq / a.B + queries / 16 <= (int)kMaxGridY;
+    };
     auto pick = [&](auto tiles) -> hipError_t {
         constexpr int N = decltype(tiles)::value;
         if constexpr (N > 8) {
-            return dtype == RR_BF16 ? launch(k_attn_generic<bf16_t, N, 1, 2, 4, 1>, 16, 4)
-                                    : launch(k_attn_generic<float, N, 1, 1, 4, 1>, 16, 4);
+            return dtype == RR_BF16 ? launch(k_attn_generic<bf16_t, N, 1, 1, 2, 4, 1>, 16, 4, 1)
+                                    : launch(k_attn_generic<float, N, 1, 1, 1, 4, 1>, 16, 4, 1);
         } else {
             if (dtype == RR_BF16) {
                 if constexpr (N <= 4)
-                    if (a.B > 32 && blocks(64) >= 512) return launch(k_attn_generic<bf16_t, N, 4, 2, 4, 2>, 64, 4);
-                return launch(k_attn_generic<bf16_t, N, 2, 2, 4, 2>, 32, 4);
+                    if (a.B > 32 && blocks(64) >= 512)
+                        return short_last(64) ? launch(k_attn_generic<bf16_t, N, 4, 1, 2, 4, 2>, 64, 4, 4)
+                                              : launch(k_attn_generic<bf16_t, N, 4, 4, 2, 4, 2>, 64, 4, 1);
+                return short_last(32) ? launch(k_attn_generic<bf16_t, N, 2, 1, 2, 4, 2>, 32, 4, 2)
+                                      : launch(k_attn_generic<bf16_t, N, 2, 2, 2, 4, 2>, 32, 4, 1);
             }
-            if (a.B > 16 && blocks(32) >= 512) return launch(k_attn_generic<float, N, 2, 1, 8, 2>, 32, 8);
-            return launch(k_attn_generic<float, N, 1, 1, 8, 2>, 16, 8);
+            if (a.B > 16 && blocks(32) >= 512)
+                return short_last(32) ? launch(k_attn_generic<float, N, 2, 1, 1, 8, 2>, 32, 8, 2)
+                                      : launch(k_attn_generic<float, N, 2, 2, 1, 8, 2>, 32, 8, 1);
+            return launch(k_attn_generic<float, N, 1, 1, 1, 8, 2>, 16, 8, 1);
         }
     };
     using std::integral_constant;
