@@ -294,6 +294,9 @@ RR_API int rr_estimate_ex(const rr_shape* shape, const void* Q, const void* K, i
     a.block_mass = out->block_mass;
     a.Ksum = nullptr;
     a.state_ws = nullptr;
+    const bool order = out->row_order && (long long)g.G * (g.Lq / B) <= kMaxOrderedRows;
+    a.row_order = order ? out->row_order : nullptr;
+    a.queue = order ? out->queue : nullptr;
     if (mfma) {
         // split stride sums -> block masses in the workspace (two sweeps on the matrix cores) -> Top-tau per row
         unsigned short* ksplit = reinterpret_cast<unsigned short*>(wsb);
@@ -310,7 +313,7 @@ RR_API int rr_estimate_ex(const rr_shape* shape, const void* Q, const void* K, i
         a.state_ws = estimate_generic_state_bytes(g, S, B) ? reinterpret_cast<float2*>(wsb + ksum_bytes(g, S)) : nullptr;
         if (launch_estimate_generic(g, shape->dtype, a, st) != hipSuccess) return RR_ERR_LAUNCH;
     }
-    if (out->row_order && (long long)g.G * (g.Lq / B) <= kMaxOrderedRows)
+    if (order && !(mfma && estimate_mfma_is_step(g, a)))
         if (launch_row_order(g, a.Nb, out->row_count, out->row_order, out->queue, st) != hipSuccess) return RR_ERR_LAUNCH;
     return RR_OK;
 }

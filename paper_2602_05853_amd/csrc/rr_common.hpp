@@ -104,6 +104,10 @@ struct EstimateArgs {
     int32_t* row_count;
     int32_t* row_list;
     float* block_mass;
+    // where the order of the rows goes and the queue that is zeroed with it (launch_row_order), or nullptr: written by the estimate of a
+    // short step, which selects all rows of a KV head in one workgroup
+    int32_t* row_order;
+    int32_t* queue;
 };
 size_t estimate_generic_state_bytes(const Geom& g, int S, int B);   // 0 when LDS suffices
 bool estimate_generic_fits(const Geom& g, int S, int B);   // LDS plan within the CU's 160 KB
@@ -120,10 +124,14 @@ size_t estimate_mfma_stats_bytes(const Geom& g, int S, int B);   // per-chunk so
 hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& a, unsigned short* ksplit, int ls_cap, int ls_valid,
                                 float* mass, float2* stats, hipStream_t st);
 // (ksplit holds rows of ls_cap >= L / S strides per (batch, KV head); the first ls_valid strides are kept as they are)
+// A step of so few sampled queries that their unnormalised block sums fit the places of masses and states: one sweep, and one
+// more launch for softmax, masses, selection and row order.  (By the shape alone, like every other path of the estimate.)
+bool estimate_mfma_is_step(const Geom& g, const EstimateArgs& a);
 hipError_t launch_select_rows(const Geom& g, const EstimateArgs& a, const float* mass, hipStream_t st);
 
 // (2'') rows of every KV head sorted by descending row_count: order[b][kv][rank] = hl * Nb + m.  A queue
 // (rr_mask.queue, RR_QUEUE_WORDS words) given with it is zeroed.
+int row_order_shift(int Nb);      // rows whose counts agree but for this many low bits form one class
 hipError_t launch_row_order(const Geom& g, int Nb, const int32_t* row_count, int32_t* row_order, int32_t* queue,
                             hipStream_t st);
 

@@ -668,6 +668,142 @@ k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
     }
 }
 
+// ---- short steps: one sweep, then softmax, block masses, selection and row order in one launch ----
+// A step of a few tokens has a handful of sampled queries to a KV head, nst strides of each of its G heads, against all key strides: a
+// wavefront takes 32 key strides and all queries, 32 at a time, and leaves for each query the sum of 2^(score - reference) over
+// each key block and the tile's reference (its largest score).  The second launch, one workgroup to a KV head and one wavefront
+// to a row, brings the references together.  What bounds it: the chain of launches and, in each, of its loads; 8 tokens behind
+// 64512, 32 / 8 heads: 8 + 10 us where the two sweeps, the selection and the row order took 20 + 20 + 9 + 5.
+struct StepArgs {
+    float* sums;                      // [pair][query][tiles * blocks of a tile]
+    float* refs;                      // [pair][query][tiles], log2 units
+    int nst, s0;                      // query strides of the step, the first of them
+    int tiles;
+    int order_shift;
+};
+constexpr int kStepWaves = 4;
+template <int R>
+__global__ void __launch_bounds__(64 * kStepWaves)
+k_step_scores(Geom g, ScoreArgs a, StepArgs sa) {
+    constexpr int NB = kTileStrides / R;                           // key blocks of a tile
+    const int lane = threadIdx.x & 63, l32 = lane & 31, gsel = lane >> 5;
+    const int jt = (int)blockIdx.x * kStepWaves + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (jt >= sa.tiles) return;
+    const int pr = blockIdx.y, b = pr / g.Hkv, kv = pr - b * g.Hkv, j0 = jt * kTileStrides;
+    const long long plane = (long long)g.batch * g.Hkv * a.LsCap * g.d;
+    const unsigned short* kp = a.Ksp + ((long long)pr * a.LsCap + min(j0 + l32, a.Ls - 1)) * g.d + 8 * gsel;
+    bf16x8 kf[8][3];
+#pragma unroll
+    for (int kc = 0; kc < 8; ++kc)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) kf[kc][p] = *reinterpret_cast<const bf16x8*>(kp + p * plane + 16 * kc);
+    const float NEG_INF = -__builtin_huge_valf();
+    const int nq = g.G * sa.nst;
+    for (int q0 = 0; q0 < nq; q0 += 32) {
+        const int q = q0 + l32, hl = q / sa.nst, i = sa.s0 + (q - hl * sa.nst);
+        const int h = kv * g.G + hl;
+        const long long pos = (long long)i * a.S + (a.S - 1 - ((a.off_hmul * h + a.off_add) % a.S)) - g.q0;   // Sec. 3.1
+        const bool in = q < nq;
+        const int iq = in && pos >= 0 ? i : -1;                    // (every stride of the step is complete)
+        const unsigned short* qp = a.Q + b * g.qsb + h * g.qsh + pos * g.qsl + 8 * gsel;
+        bf16x8 qf[8];
+#pragma unroll
+        for (int kc = 0; kc < 8; ++kc) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (iq >= 0) v = *reinterpret_cast<const u32x4*>(qp + 16 * kc);
+            qf[kc] = __builtin_bit_cast(bf16x8, v);
+        }
+        f32x16 s;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int kc = 0; kc < 8; ++kc)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kc][p], qf[kc], s, 0, 0, 0);
+        if (j0 + kTileStrides - 1 > sa.s0 || iq < 0) {
+            f32x16 v = s;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = j0 + 8 * (e >> 2) + 4 * gsel + (e & 3) > iq ? NEG_INF : v[e];
+            s = v;
+        }
+        float mx = NEG_INF;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
+        mx = fmaxf(mx, lane_xor32(mx, gsel != 0)) * a.scale_log2;
+        const float nb = mx == NEG_INF ? 0.f : -mx;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], a.scale_log2, nb));
+        constexpr int NBL = R == 4 ? 4 : NB, RPB = 16 / NBL;
+        float* const out = sa.sums + ((long long)pr * nq + q) * (sa.tiles * NB) + jt * NB;
+#pragma unroll
+        for (int k = 0; k < NBL; ++k) {
+            float t = 0.f;
+#pragma unroll
+            for (int e = 0; e < RPB; ++e) t += s[k * RPB + e];
+            if (R != 4) t += lane_xor32(t, gsel != 0);
+            if (in && (R == 4 || gsel == 0)) out[R == 4 ? 2 * k + gsel : k] = t;
+        }
+        if (in && gsel == 0) sa.refs[((long long)pr * nq + q) * sa.tiles + jt] = mx;
+    }
+}
+
+constexpr int kStepRows = 16;                                      // rows of a KV head
+template <int R, int NCH>
+__global__ void __launch_bounds__(64 * kStepRows)
+k_step_select(Geom g, EstimateArgs ea, StepArgs sa) {
+    constexpr int NB = kTileStrides / R;
+    __shared__ int s_class[kStepRows];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int kv = blockIdx.x, b = blockIdx.y, pr = b * g.Hkv + kv;
+    const int Nbq = g.Lq / ea.B, N = g.G * Nbq, nq = g.G * sa.nst;   // N waves
+    const int mr = w / g.G, hl = w - mr * g.G, mq = Nbq - 1 - mr;    // descending block, then head: the order inside a class
+    const long long bh = (long long)b * g.Hq + kv * g.G + hl;
+    bool has_strides;                                               // (or no query below, no mass, and every block is kept)
+    const SelectRow row = select_row_of(g, ea, nullptr, bh, mq, has_strides);
+    RowInRegs<NCH> masses;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) masses.v[c] = 0.f;
+    const int i_lo = max(sa.s0, row.m * R), i_hi = min(sa.s0 + sa.nst, (row.m + 1) * R);
+    const float NEG_INF = -__builtin_huge_valf();
+    for (int i = i_lo; i < i_hi; ++i) {
+        const long long q = (long long)pr * nq + hl * sa.nst + (i - sa.s0);
+        const float* const e = sa.sums + q * (sa.tiles * NB);
+        const float* const u = sa.refs + q * sa.tiles;
+        float ev[NCH], uv[NCH], top = NEG_INF, z = 0.f;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int n = 64 * c + lane;
+            const bool in = n <= row.m;
+            ev[c] = in ? e[n] : 0.f;
+            uv[c] = in ? u[n / NB] : NEG_INF;
+            top = fmaxf(top, uv[c]);
+        }
+        top = wave_max(top);
+        if (top == NEG_INF) continue;                               // the sampled position lies in front of the step
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            ev[c] *= __builtin_amdgcn_exp2f(uv[c] - top);
+            z += ev[c];
+        }
+        const float inv = 1.0f / wave_sum_fixed(z);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) masses.v[c] = fmaf(ev[c], inv, masses.v[c]);
+    }
+    float* bm = ea.block_mass ? ea.block_mass + (bh * Nbq + mq) * ea.Nb : nullptr;
+    select_row_of_masses(row, masses, bm, lane);
+    if (!ea.row_order) return;
+    // the order k_row_order would give: fewer than 8 G rows are not transposed
+    if (ea.queue && pr == 0)
+        for (int i = threadIdx.x; i < RR_QUEUE_WORDS; i += 64 * N) ea.queue[i] = 0;
+    if (lane == 0) s_class[w] = (ea.Nb - *row.count) >> sa.order_shift;
+    __syncthreads();
+    if (lane == 0) {
+        int rank = 0;
+        for (int f = 0; f < N; ++f) rank += s_class[f] < s_class[w] || (s_class[f] == s_class[w] && f < w);
+        ea.row_order[(long long)pr * N + rank] = hl * Nbq + mq;
+    }
+}
+
 }  // namespace
 
 size_t estimate_mfma_ksplit_bytes(const Geom& g, int S) {
@@ -706,6 +842,20 @@ size_t estimate_mfma_mass_bytes(const Geom& g, int B) {
 bool estimate_mfma_supported(const Geom& g, int dtype, int S, int B) {
     const int R = B / S;
     return dtype == RR_BF16 && g.d == 128 && (R == 4 || R == 8 || R == 16 || R == 32) && g.G * R <= 256;
+}
+
+// Estimate and attention, two sweeps, selection and row order / this form, tau 0.9, us: 32 / 8 heads, 8 tokens of 64512 122 / 89, 1 of
+// 98304 141 / 114, 16 of 30000 107 / 75, 40 of 65000 158 / 126; 64 / 8, S = 8, 3 of 90000 212 / 179; 8 / 2, 12 of 20000 83 / 52.  The limit is the
+// space: what a workspace of this shape always had for masses and states holds four strides or so of sampled queries, and no
+// call may need more than before.
+bool estimate_mfma_is_step(const Geom& g, const EstimateArgs& ea) {
+    const int S = ea.S, B = ea.B, R = B / S, Nb = g.L / B, Nbq = g.Lq / B;
+    const int tiles = (g.L / S + kTileStrides - 1) / kTileStrides;
+    const size_t queries = (size_t)g.batch * g.Hq * (g.Lr / S - g.q0 / S);
+    const size_t need = queries * (tiles * (kTileStrides / R) + tiles) * sizeof(float);
+    return g.q0 > 0 && !ea.seq_first && !ea.diag_token && tiles > kRowTiles && Nb <= 1024 && g.G * Nbq <= kStepRows && Nbq < 8 &&
+           g.batch <= 65535 && g.batch * g.Hkv <= 65535 &&
+           need <= estimate_mfma_mass_bytes(g, B) + estimate_mfma_stats_bytes(g, S, B);
 }
 
 hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned short* ksplit, int ls_cap, int ls_valid,
@@ -763,6 +913,39 @@ hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned 
             case 8: return pick(std::integral_constant<int, 8>{});
             case 16: return pick(std::integral_constant<int, 16>{});
             case 32: return pick(std::integral_constant<int, 32>{});
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (estimate_mfma_is_step(g, ea)) {
+        a.nsplit = 1;
+        a.mode = 0;
+        a.stats = nullptr;
+        StepArgs sa;
+        sa.s0 = g.q0 / S;
+        sa.nst = g.Lr / S - sa.s0;
+        sa.tiles = tiles;
+        sa.sums = mass;
+        sa.refs = mass + (size_t)g.batch * g.Hq * sa.nst * (tiles * (kTileStrides / R));
+        sa.order_shift = row_order_shift(Nb);
+        auto launch = [&](auto r) -> hipError_t {
+            constexpr int RV = decltype(r)::value;
+            if (sa.nst > 0) {
+                hipLaunchKernelGGL(k_step_scores<RV>, dim3((unsigned)((tiles + kStepWaves - 1) / kStepWaves), (unsigned)(g.Hkv * g.batch)),
+                                   dim3(64 * kStepWaves), 0, st, g, a, sa);
+                const hipError_t e = hipGetLastError();
+                if (e != hipSuccess) return e;
+            }
+            const dim3 rows(64 * g.G * Nbq), heads(g.Hkv, g.batch);
+            if (Nb <= 256) hipLaunchKernelGGL((k_step_select<RV, 4>), heads, rows, 0, st, g, ea, sa);
+            else if (Nb <= 512) hipLaunchKernelGGL((k_step_select<RV, 8>), heads, rows, 0, st, g, ea, sa);
+            else hipLaunchKernelGGL((k_step_select<RV, 16>), heads, rows, 0, st, g, ea, sa);
+            return hipGetLastError();
+        };
+        switch (R) {
+            case 4: return launch(std::integral_constant<int, 4>{});
+            case 8: return launch(std::integral_constant<int, 8>{});
+            case 16: return launch(std::integral_constant<int, 16>{});
+            case 32: return launch(std::integral_constant<int, 32>{});
             default: return hipErrorInvalidValue;
         }
     }

@@ -132,13 +132,17 @@ hipError_t launch_mask_from_dense(const Geom& g, int Nb, const uint8_t* dense, i
     return hipGetLastError();
 }
 
+int row_order_shift(int Nb) {
+    int shift = kCountShift;
+    while ((Nb >> shift) + 1 > kMaxClasses) ++shift;
+    return shift;
+}
+
 hipError_t launch_row_order(const Geom& g, int Nb, const int32_t* row_count, int32_t* row_order, int32_t* queue,
                             hipStream_t st) {
     const int N = g.G * (g.Lq / (g.L / Nb));
     if (N > kMaxOrderedRows) return hipErrorInvalidValue;
-    int shift = kCountShift;
-    while ((Nb >> shift) + 1 > kMaxClasses) ++shift;
-    hipLaunchKernelGGL(k_row_order, dim3(g.Hkv, g.batch), dim3(kSortThreads), 0, st, g, Nb, shift, row_count, row_order, queue);
+    hipLaunchKernelGGL(k_row_order, dim3(g.Hkv, g.batch), dim3(kSortThreads), 0, st, g, Nb, row_order_shift(Nb), row_count, row_order, queue);
     return hipGetLastError();
 }
 

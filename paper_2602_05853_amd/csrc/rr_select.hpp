@@ -186,20 +186,15 @@ __device__ __forceinline__ SelectRow select_row_of(const Geom& g, const Estimate
     return r;
 }
 
-// Selection of a row of up to 64 NCH blocks held in registers; mass: its masses (readable for nlo <= n <= m), bm: where its
-// fractions go as well, or nullptr.  Called by all 64 lanes of one wavefront.
+// Selection of a row of up to 64 NCH blocks whose masses are in registers, lane l of chunk c holding block 64 c + l and 0 for what
+// is no candidate; bm: where its fractions go as well, or nullptr.  Called by all 64 lanes of one wavefront.
 template <int NCH>
-__device__ __forceinline__ void select_row_in_regs(SelectRow r, bool has_strides, const float* mass, float* bm, int lane) {
-    RowInRegs<NCH> row;
+__device__ __forceinline__ void select_row_of_masses(SelectRow r, RowInRegs<NCH>& row, float* bm, int lane) {
     row.c0 = __builtin_amdgcn_readfirstlane(r.nlo) >> 6;
     row.c1 = (__builtin_amdgcn_readfirstlane(r.m) >> 6) + 1;
     float part = 0.f;
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int n = 64 * c + lane;
-        row.v[c] = (has_strides && n >= r.nlo && n <= r.m) ? mass[n] : 0.f;
-        part += row.v[c];
-    }
+    for (int c = 0; c < NCH; ++c) part += row.v[c];
     const float total = wave_sum_fixed(part);
     const bool estimated = total > 0.f;
 #pragma unroll
@@ -209,6 +204,17 @@ __device__ __forceinline__ void select_row_in_regs(SelectRow r, bool has_strides
     }
     r.keep_all = r.keep_all || !estimated;
     select_row_wave(row, r, lane);
+}
+// The same with the masses in memory (readable for nlo <= n <= m).
+template <int NCH>
+__device__ __forceinline__ void select_row_in_regs(SelectRow r, bool has_strides, const float* mass, float* bm, int lane) {
+    RowInRegs<NCH> row;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const int n = 64 * c + lane;
+        row.v[c] = (has_strides && n >= r.nlo && n <= r.m) ? mass[n] : 0.f;
+    }
+    select_row_of_masses(r, row, bm, lane);
 }
 
 }  // namespace rr
