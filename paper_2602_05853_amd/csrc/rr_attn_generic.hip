@@ -16,7 +16,7 @@
 //
 // Measured against the form before it (one workgroup per query block, fp32 vector FMAs on operands staged in LDS, where
 // every multiply-add waited for an LDS read): fp32, 1024 tokens, 4 / 2 heads of 64: 576 -> 19 us; fp32, 4096 tokens, 8 / 2
-// heads of 128: 5954 -> 175 us (145 with the last block on small tiles); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 186 us.
+// heads of 128: 5954 -> 175 us (62 TFLOP/s of selected blocks); bf16, 8153 tokens, 16 / 4 heads of 64: 9853 -> 186 us.
 //
 // Softmax: base 2, the reference is moved only when a wave's sum of a step exceeds 2^8 (all terms of a row share it).
 #include "rr_attn_frag.hpp"
@@ -318,9 +318,9 @@ hipError_t launch_attn_generic(const Geom& g, int dtype, const AttnArgs& a, hipS
     // The last query block 16 queries to a workgroup.  A sparse launch of so few workgroups takes as long as its longest row, and
     // that is the protected last one (attention alone, us; this row alone, the rest alone, both before, now: fp32, 4096 tokens, 8 heads
     // of 128: 166, 134, 168, 145; 2048 tokens 89, 58, 91, 60; bf16, 8000 tokens, 8 heads of 64: 114, 90, 121, 89; 4096 tokens, 16
-    // heads 63, 49, 67, 49).  Not where the rest takes longer (2000 workgroups and more; 8153 tokens, 16 heads: 126, 141, 146 and with it
-    // 146), not for dense calls, whose rows get shorter one by one, and not for further blocks (the last sixteenth of them: 8153 tokens
-    // 162, the first case 146).
+    // heads 63, 49, 67, 49; where other rows are nearly as long, less: the first case on other inputs 184, now 179).  Not where the rest
+    // takes longer (2000 workgroups and more; 8153 tokens, 16 heads: 126, 141, 146 and with it 146), not for dense calls, whose rows get
+    // shorter one by one, and not for further blocks (the last sixteenth of them: 8153 tokens 162, the first case 146).
     auto short_last = [&](int queries) {
         return a.row_list && a.B > 16 && blocks(queries) <= 1536 && g.Lq / a.B + queries / 16 <= (int)kMaxGridY;
     };
