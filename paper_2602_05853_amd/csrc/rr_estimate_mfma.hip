@@ -765,7 +765,9 @@ k_step_select(Geom g, EstimateArgs ea, StepArgs sa) {
     for (int c = 0; c < NCH; ++c) masses.v[c] = 0.f;
     const int i_lo = max(sa.s0, row.m * R), i_hi = min(sa.s0 + sa.nst, (row.m + 1) * R);
     const float NEG_INF = -__builtin_huge_valf();
+    const int off = ea.S - 1 - ((ea.off_hmul * (kv * g.G + hl) + ea.off_add) % ea.S);
     for (int i = i_lo; i < i_hi; ++i) {
+        if (i * ea.S + off < g.q0) continue;                        // the sampled position lies in front of the step
         const long long q = (long long)pr * nq + hl * sa.nst + (i - sa.s0);
         const float* const e = sa.sums + q * (sa.tiles * NB);
         const float* const u = sa.refs + q * sa.tiles;
@@ -778,14 +780,17 @@ k_step_select(Geom g, EstimateArgs ea, StepArgs sa) {
             uv[c] = in ? u[n / NB] : NEG_INF;
             top = fmaxf(top, uv[c]);
         }
+        // A query whose scores are no numbers has no largest one, but sums that are no numbers: as in the sweeps they have to reach the
+        // row, which then has no estimate and keeps every block.
         top = wave_max(top);
-        if (top == NEG_INF) continue;                               // the sampled position lies in front of the step
+        const float ref = top == NEG_INF ? 0.f : top;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            ev[c] *= __builtin_amdgcn_exp2f(uv[c] - top);
+            ev[c] *= __builtin_amdgcn_exp2f(uv[c] - ref);
             z += ev[c];
         }
-        const float inv = 1.0f / wave_sum_fixed(z);
+        z = wave_sum_fixed(z);
+        const float inv = z > 0.f ? 1.0f / z : 0.f;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) masses.v[c] = fmaf(ev[c], inv, masses.v[c]);
     }

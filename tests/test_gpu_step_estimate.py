@@ -9,6 +9,33 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
+B = 128
+
+
+def _context(batch, Hq, Hkv, L, Lq, seed):
+    g = torch.Generator(device="cuda:0").manual_seed(seed)
+    K = torch.randn(batch, Hkv, L, 128, generator=g, device="cuda:0")
+    K = (K + 2.0 * torch.randn(batch, Hkv, -(-L // 512), 128, generator=g, device="cuda:0").repeat_interleave(512, 2)[:, :, :L]).bfloat16()
+    return (2.0 * torch.randn(batch, Hq, Lq, 128, generator=g, device="cuda:0")).bfloat16(), K
+
+
+def _dirty(Q, K, S, batch, Hq, Hkv, L, Lq):
+    """a workspace of set bytes and a mask whose every array holds garbage"""
+    import paper_2602_05853_amd as rr
+    ws = torch.full((rr.rr_workspace_bytes(Q, K, S, B),), 0xFF, dtype=torch.uint8, device=Q.device)
+    Nb = -(-L // B)
+    out = rr.BlockMask.allocate(batch, Hq, Nb, B, Q.device, block_mass=True, Hkv=Hkv, rows=Nb - (L - Lq) // B)
+    for t in (out.row_count, out.row_list, out.row_order, out.queue):
+        t.fill_(0x7A7A7A7A)
+    out.dense.fill_(0x7A)
+    out.block_mass.fill_(float("nan"))
+    return ws, out
+
+
+def _one_sweep(ws):
+    """two sweeps leave the softmax states of their last key chunk in the last 2 KB, the forms of short steps and contexts nothing"""
+    return bool((ws[-2048:] == 0xFF).all())
+
 
 def _masses(Q, K, S, B, q0):
     """[Hq, rows, Nb] in 64 bits: fractions of a row; rows without a sampled query are 0"""
@@ -58,3 +85,34 @@ def test_step_estimate(Hq, Hkv, L, Lq, S, tau):
         assert torch.equal(mask.row_list[0, h, r, :n].long(), kept[h, r].nonzero().flatten())
     again = rr.rr_mask_from_dense(Q, K, mask.dense, B)
     assert torch.equal(again.row_order, mask.row_order) and not mask.queue.any()
+
+
+# A block that holds several sampled queries of a head, one of them not finite: the row's mass is unknown, so it keeps every block, in
+# every form of the estimate (`sweeps`: False for the short steps of this file and for a short context in one launch); rows of
+# other heads and blocks are what they are without it.
+@pytest.mark.parametrize("Hq,Hkv,L,Lq,S,sweeps", [(8, 2, 128 * 1024, 12, 4, False), (16, 8, 128 * 700 + 64, 80, 16, False),
+                                                  (8, 2, 128 * 300 + 24, 24, 8, False), (8, 2, 128 * 513, 64, 32, False),
+                                                  (8, 2, 128 * 60, 130, 16, False), (8, 2, 128 * 140, 300, 16, True)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_row_with_a_query_that_is_not_finite_keeps_every_block(Hq, Hkv, L, Lq, S, sweeps, value):
+    import paper_2602_05853_amd as rr
+    Q, K = _context(1, Hq, Hkv, L, Lq, L + Lq)
+    q0, m0, h = L - Lq, (L - Lq) // B, Hq - 2
+    clean = rr.rr_estimate(Q, K, S, B, 0.9, flags=0, block_mass=True)
+    position = lambda i: i * S + S - 1 - h % S - q0                                 # of the sampled query of stride i, in the step
+    held = [i for i in range(q0 // S, L // S) if position(i) >= 0]
+    row = lambda i: i * S // B - m0
+    r = row(held[-1])
+    assert sum(row(i) == r for i in held) >= 2 and int(clean.row_count[0, h, r]) < m0 + r + 1
+    Q[0, h, position(held[-1]), 17] = value
+    ws, mask = _dirty(Q, K, S, 1, Hq, Hkv, L, Lq)
+    print(f"[step] {Hq}/{Hkv} heads, {Lq} of {L}, S {S}: query {value} in row {r} of head {h}", flush=True)
+    rr.rr_estimate(Q, K, S, B, 0.9, flags=0, out=mask, workspace=ws)
+    torch.cuda.synchronize()
+    assert _one_sweep(ws) != sweeps
+    n = torch.arange(mask.Nb, device="cuda:0")
+    assert torch.equal(mask.dense[0, h, r].bool(), n <= m0 + r) and int(mask.row_count[0, h, r]) == m0 + r + 1
+    others = torch.ones(mask.row_count.shape, dtype=torch.bool, device="cuda:0")
+    others[0, h, r] = False
+    for a, b in ((mask.dense, clean.dense), (mask.row_count, clean.row_count), (mask.block_mass, clean.block_mass)):
+        assert torch.equal(a[others], b[others])
