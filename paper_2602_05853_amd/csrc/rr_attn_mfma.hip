@@ -1113,27 +1113,39 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
 constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens, see launch_attn_mfma_bf16
 
 // KV groups launched interleaved (decode_block, order_entry_of): the largest divisor of the number of groups that keeps K and V of
-// the set within 38 MB.  More groups to a set find less of each other's tiles in L2 (8 x 4 MB), fewer put more of a
-// launch's heavy rows late.  And what starts late counts: the longest row (the protected one keeps every block) of the last set took as
-// long as that whole set, so sparse launches first take the heaviest rows of ALL groups, one run of the row order (8 G
-// rows, which one XCD each was chosen for), and then the sets.  Sets of 4096 rows and more (eight to each of the 512 workgroups that
-// run at once) go without: 128K, estimate and attention 32.4 ms, 32.7 with it; and contexts of more than 256 blocks with fewer
-// than eight groups: the last set is a large part of the launch there, and the mixed rows cost what they save.
+// the set within 32 MB, the L2 capacity of the chip (8 x 4 MB), or within 38 MB for the row order of a whole prompt whose sets are at
+// most 3000 rows long.  More groups to a set find less of each other's tiles in L2, fewer put more of a launch's heavy
+// rows late, which counts where a set is over soon.  Measured, estimate and attention or dense call, us, 38 MB / 32 MB, gain of the
+// inputs 3 and tau 0.9 unless said:
+//   sets of up to 3000 rows: 32 / 8 heads, 18000 tokens 752 / 772, 37000 2772 / 2848; 16 / 4, 37000 1552 / 1736, tau 0.95 2168 / 2318; 8 / 2, 36000
+//     810 / 873, 38900 883 / 931 (weaker structure, tau 0.95, 38500 1709 / 1670; three packed prompts of 300 blocks 715 / 706)
+//   longer ones (32 MB): 64 / 8, 9000 538 / 520, 18000 1747 / 1725, 35000 5092 / 4881, 38500 7564 / 7389; 28 / 4, 17000 708 / 699, 18500 647 / 653,
+//     35000 2631 / 2587, 38000 3116 / 3056, packed prompts of 290 blocks 1286 / 1257
+//   no row order or not a whole prompt (32 MB): dense, 32 / 8, 38900 11363 / 11119, 8900 to 36000 level; planned chunks, 1000 of 35000, 64 / 8
+//     heads, 415 / 402 and 424 / 412, 1500 of 18500, 32 / 8, 209 / 203 and 200 / 203; sparse without a row order level
+int interleave_groups(const Geom& g, bool ordered) {
+    const long long per_group = 2ll * g.L * g.d * 2;               // K and V of one KV head, bf16
+    const int NG = g.batch * g.Hkv, rows = g.G * (g.Lq / 128);
+    int gi = 1;
+    for (int c = 1; c <= NG && c <= 64; ++c) {
+        const bool more = ordered && g.q0 == 0 && c * rows <= 3000;
+        if (NG % c == 0 && c * per_group <= (more ? 38ll : 32ll) << 20) gi = c;
+    }
+    return gi;
+}
+// What starts late counts: the longest row (the protected one keeps every block) of the last set took as long as that whole
+// set, so sparse launches first take the heaviest rows of ALL groups, one run of the row order (8 G rows, which one XCD each was
+// chosen for), and then the sets.  Not taken by sets of 4096 rows and more (eight to each of the 512 workgroups that run at
+// once), where it is even: 131072 tokens, 32 / 8 heads, with it 0.2 and 0.4 % slower in two runs, at weaker structure 0.4 and 1.1 %, at tau 0.95
+// 0.7 and 0.6 %; 65536, 64 / 8, S = 8, 1.2 and 1.1 % faster, 65500, tau 0.95, 0.6 and 0.9 %.  And not by contexts of more than 256 blocks
+// with fewer than eight groups: the last set is a large part of the launch there, and the mixed rows cost what they save.
 // Measured, attention alone, tau 0.9, us; sets of 32 MB without the first run / sets of 1, 2, 4 groups with it:
 //   32 / 8 heads: 9000 tokens 265 / 208, 206, 206; 16384 628 / 580, 555, 541; 24000 1330 / 1217, 1171, 1158; 28000 1730 / 1580, 1532,
 //     1545; 36000 3020 / 2699, 2643, 2736; 50000 4950 / 4637, 4617, 4731; 65536 8350 / 7906, 7704, 8065 (weaker structure 14349 / 14201,
-//     14321, 15066); 98304 18126 / 18141, 18479, 19748; 131072 32503 / 32249, 32013, 33814
-//   64 / 8: 12000 685 / 706, 694, 689; 20000 1704 / 1692, 1633, 1664; 65536 (S = 8) 20671 / 20342, 20365, 21409
+//     14321, 15066); 98304 18126 / 18141, 18479, 19748
+//   64 / 8: 12000 685 / 706, 694, 689; 20000 1704 / 1692, 1633, 1664
 //   28 / 4: 20000 806 / 773, 731, 739; 8 / 2: 20000 272 / 260, 271; not taken: 28 / 4 40000 2715 / 2672; 8 / 2 50000 1204 / 1226; 28 / 4, eight
 //     packed prompts (311 blocks) 1371 / 1385
-int interleave_groups(const Geom& g) {
-    const long long per_group = 2ll * g.L * g.d * 2;               // K and V of one KV head, bf16
-    const int NG = g.batch * g.Hkv;
-    int gi = 1;
-    for (int c = 1; c <= NG && c <= 64; ++c)
-        if (NG % c == 0 && c * per_group <= 38ll << 20) gi = c;
-    return gi;
-}
 int hoisted_rows(const Geom& g, int interleave) {
     const int NG = g.batch * g.Hkv, rows = g.G * (g.Lq / 128);
     if (interleave == NG || interleave * rows >= 4096 || 8 * g.G >= rows || (g.L / 128 > kPersistMaxBlocks && NG < 8)) return 0;
@@ -1454,8 +1466,9 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     const bool planned = a.split_len > 0 && a.split_budget > 0 && a.plan_total && a.plan_row && a.plan_items && a.plan_cut &&
                          a.part_O && a.part_lse;
     if (!planned) { a.split_len = 0; a.split_budget = 0; } else a.nsplit = 1;
-    a.interleave = interleave_groups(g);
-    a.hoist = planned || a.nsplit > 1 || !a.row_order ? 0 : hoisted_rows(g, a.interleave);
+    const bool ordered = a.row_order && !planned && a.nsplit == 1;
+    a.interleave = interleave_groups(g, ordered);
+    a.hoist = ordered ? hoisted_rows(g, a.interleave) : 0;
     const bool ragged = g.Lr != g.L || g.qoff != 0 || a.nsplit > 1 || planned;   // split launches use the ragged instantiation
     const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     const long long rows = (long long)g.batch * g.Hq * (g.Lq / 128);
