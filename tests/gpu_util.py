@@ -86,3 +86,20 @@ def blockmask_from_dense(dense_np: np.ndarray, B: int):
     return BlockMask(B=B, Nb=Nb, row_count=torch.from_numpy(count)[None].to(dev),
                      row_list=torch.from_numpy(lst)[None].to(dev),
                      dense=torch.from_numpy(dense_np.astype(np.uint8))[None].to(dev))
+
+
+def stride_masses(q, k, S: int, B: int, q0: int, phase: int):
+    """Block masses of one head in 64 bits, on the device: q [Lq, d], the queries of the positions from q0 on, k [L, d]; the sampled
+    position of a stride is S - 1 - (phase mod S).  [rows, Nb], a row as fractions of its sum; rows without a sampled query are 0."""
+    L, d = k.shape
+    Ls, R, Nb, m0 = L // S, B // S, -(-L // B), q0 // B
+    sums = k[:Ls * S].double().reshape(Ls, S, d).sum(1)
+    out = torch.zeros(Nb - m0, Nb, dtype=torch.float64, device=k.device)
+    block = torch.arange(Ls, device=k.device) // R
+    for i in range(q0 // S, Ls):
+        p = i * S + S - 1 - phase % S - q0
+        if p < 0:
+            continue
+        w = torch.softmax(sums[:i + 1] @ q[p].double() / (S * d ** 0.5), 0)
+        out[i // R - m0].index_add_(0, block[:i + 1], w)
+    return out / out.sum(1, keepdim=True).clamp_min(1e-300)

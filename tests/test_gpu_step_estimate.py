@@ -1,11 +1,15 @@
 """Estimate of short steps deep in a context (one sweep over the key strides, softmax and selection in a second launch): block masses
 against the method in 64 bits, the selection against those masses, the row order against the one made from the finished mask.
 Masses are sums of at most some thousand fp32 terms of exact products: 2^-24 times the logits' spread (below 64) and the
-additions' depth, within 1e-5 of the row."""
-import math
+additions' depth, within 1e-5 of the row.
 
+Which form a call takes is a rule on its shape.  The two sweeps leave the softmax states of their key chunks at the end of the
+workspace, and the last chunk of the last KV head writes its 2 KB whatever it holds; the sums of the one sweep end before
+them in every shape here.  So bytes set beforehand tell the two apart, and each test says which one it is about."""
 import pytest
 import torch
+
+import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
@@ -33,56 +37,69 @@ def _dirty(Q, K, S, batch, Hq, Hkv, L, Lq):
 
 
 def _one_sweep(ws):
-    """two sweeps leave the softmax states of their last key chunk in the last 2 KB, the forms of short steps and contexts nothing"""
     return bool((ws[-2048:] == 0xFF).all())
 
 
-def _masses(Q, K, S, B, q0):
-    """[Hq, rows, Nb] in 64 bits: fractions of a row; rows without a sampled query are 0"""
-    _, Hq, Lq, d = Q.shape
-    Hkv, L = K.shape[1], K.shape[2]
-    Ls, R, Nb = L // S, B // S, -(-L // B)
-    m0 = q0 // B
-    sums = K[0, :, :Ls * S].double().reshape(Hkv, Ls, S, d).sum(2)
-    out = torch.zeros(Hq, Nb - m0, Nb, dtype=torch.float64, device=Q.device)
-    for h in range(Hq):
-        for i in range(q0 // S, Ls):
-            p = i * S + S - 1 - h % S - q0
-            if p < 0:
-                continue
-            w = torch.softmax(sums[h // (Hq // Hkv), :i + 1] @ Q[0, h, p].double() / (S * math.sqrt(d)), 0)
-            out[h, i // R - m0].index_add_(0, torch.arange(i + 1, device=Q.device) // R, w)
-    return out / out.sum(2, keepdim=True).clamp_min(1e-300)
+PLAIN, HYBRID = {}, dict(offset_mode="hybrid", layer=5, sink_blocks=2, recent_blocks=3)
 
 
-@pytest.mark.parametrize("Hq,Hkv,L,Lq,S", [(8, 2, 128 * 300, 8, 16), (4, 4, 128 * 257 - 19, 1, 16), (8, 1, 128 * 1024, 3, 16),
-                                           (14, 2, 128 * 600 + 3, 30, 16), (8, 2, 128 * 130 + 40, 50, 8), (32, 8, 128 * 66 + 1, 5, 4),
-                                           (8, 2, 128 * 512, 100, 32), (4, 1, 128 * 400 + 20, 16, 16), (4, 1, 128 * 400 + 20, 4, 16)])
-@pytest.mark.parametrize("tau", [0.9])
-def test_step_estimate(Hq, Hkv, L, Lq, S, tau):
+# batch, Hq, Hkv, L, Lq, S: every R = 128 / S; one row and two, up to 64 tiles of key strides to 1024 blocks; the last two hold no
+# sampled query at all
+@pytest.mark.parametrize("batch,Hq,Hkv,L,Lq,S,more",
+                         [(1, 8, 2, 128 * 300, 8, 16, PLAIN), (1, 8, 1, 128 * 1024, 3, 16, PLAIN), (1, 14, 2, 128 * 600 + 3, 30, 16, PLAIN),
+                          (2, 4, 2, 128 * 300 + 16, 16, 16, HYBRID), (1, 8, 2, 128 * 700 + 30, 60, 16, PLAIN),
+                          (1, 16, 8, 128 * 700 + 64, 80, 16, HYBRID),
+                          (1, 8, 2, 128 * 130 + 40, 9, 8, PLAIN), (1, 8, 2, 128 * 300 + 8, 24, 8, HYBRID), (2, 8, 2, 128 * 600 + 5, 17, 8, PLAIN),
+                          (1, 8, 2, 128 * 512, 32, 32, PLAIN), (1, 8, 2, 128 * 512 + 32, 64, 32, HYBRID), (2, 8, 2, 128 * 260, 33, 32, PLAIN),
+                          (1, 32, 8, 128 * 66 + 1, 5, 4, PLAIN), (2, 8, 2, 128 * 140 + 2, 9, 4, HYBRID), (1, 8, 2, 128 * 1024, 12, 4, PLAIN),
+                          (1, 4, 1, 128 * 400 + 20, 16, 16, PLAIN), (1, 4, 4, 128 * 257 - 19, 1, 16, PLAIN), (1, 4, 1, 128 * 400 + 20, 4, 16, PLAIN)])
+@pytest.mark.parametrize("tau", [0.9, 1.0])
+def test_step_estimate(batch, Hq, Hkv, L, Lq, S, more, tau):
     import paper_2602_05853_amd as rr
-    B, dev = 128, "cuda:0"
-    g = torch.Generator(device=dev).manual_seed(L + Lq)
-    K = torch.randn(1, Hkv, L, 128, generator=g, device=dev)
-    K = (K + 2.0 * torch.randn(1, Hkv, -(-L // 512), 128, generator=g, device=dev).repeat_interleave(512, 2)[:, :, :L]).bfloat16()
-    Q = (2.0 * torch.randn(1, Hq, Lq, 128, generator=g, device=dev)).bfloat16()
-    print(f"[step] {Hq}/{Hkv} heads, {Lq} of {L}, S {S}", flush=True)
-    mask = rr.rr_estimate(Q, K, S, B, tau, flags=0, block_mass=True)
+    q0, G, Nb = L - Lq, Hq // Hkv, -(-L // B)
+    m0 = q0 // B
+    rows = Nb - m0
+    Q, K = _context(batch, Hq, Hkv, L, Lq, L + Lq)
+    ws, mask = _dirty(Q, K, S, batch, Hq, Hkv, L, Lq)
+    print(f"[step] {batch} x {Hq}/{Hkv} heads, {Lq} of {L}, S {S}, tau {tau}, {more}", flush=True)
+    rr.rr_estimate(Q, K, S, B, tau, flags=0, out=mask, workspace=ws, **more)
     torch.cuda.synchronize()
-    ref, q0 = _masses(Q, K, S, B, L - Lq), L - Lq
-    got = mask.block_mass[0].double()
+    assert _one_sweep(ws)
+    ref = torch.stack([torch.stack([gu.stride_masses(Q[b, h], K[b, h // G], S, B, q0,
+                                                     (h + 5 if more else h)) for h in range(Hq)]) for b in range(batch)])
+    got = mask.block_mass.double()
     assert (got - ref).abs().max() <= 1e-5
-    sampled = ref.sum(2) > 0.5
-    rows = ref.shape[1]
-    causal = torch.arange(ref.shape[2], device=dev)[None] <= (q0 // B + torch.arange(rows, device=dev))[:, None]
-    kept = mask.dense[0].bool()
+    sampled = ref.sum(-1) > 0.5
+    n = torch.arange(Nb, device="cuda:0")
+    m = m0 + torch.arange(rows, device="cuda:0")[:, None]
+    causal = n[None] <= m
+    forced = causal & ((n[None] < more.get("sink_blocks", 0)) | (n[None] > m - more.get("recent_blocks", 0)))
+    assert int(mask.dense.max()) <= 1
+    kept = mask.dense.bool()
     assert not (kept & ~causal).any()
-    assert torch.equal(kept[~sampled], causal.expand(Hq, -1, -1)[~sampled])
-    for h, r in sampled.nonzero().tolist():
-        a, b = got[h, r][kept[h, r]], got[h, r][~kept[h, r]]
-        assert a.sum() >= tau - 1e-5 and (a.sum() - a.min() < tau + 1e-5) and (b.numel() == 0 or b.max() <= a.min())
-        n = int(mask.row_count[0, h, r])
-        assert torch.equal(mask.row_list[0, h, r, :n].long(), kept[h, r].nonzero().flatten())
+    all_rows = causal.expand(batch, Hq, -1, -1)
+    if tau == 1.0:
+        assert torch.equal(kept, all_rows)
+    assert torch.equal(kept[~sampled], all_rows[~sampled])
+    assert (kept | ~forced).all()
+    for b, h, r in (sampled.nonzero().tolist() if tau < 1.0 else []):
+        mass, k = got[b, h, r], kept[b, h, r]
+        if not more:
+            a, rest = mass[k], mass[~k]
+            assert a.sum() >= tau - 1e-5 and (a.sum() - a.min() < tau + 1e-5) and (rest.numel() == 0 or rest.max() <= a.min())
+        else:
+            # the shortest prefix by mass reaches tau, and the forced blocks come on top
+            top, at = mass.sort(descending=True, stable=True)
+            cum = top.cumsum(0)
+            size = int((cum < tau).sum()) + 1
+            base = torch.zeros_like(k)
+            base[at[:size]] = True
+            off = (k != (base | forced[r])).nonzero().flatten()
+            assert off.numel() == 0 or (cum - tau).abs().min() < 1e-5, (b, h, r, off.tolist())
+    count = mask.row_count
+    assert torch.equal(count, mask.dense.sum(-1).int())
+    for b, h, r in (count >= 0).nonzero().tolist():
+        assert torch.equal(mask.row_list[b, h, r, :int(count[b, h, r])].long(), kept[b, h, r].nonzero().flatten())
     again = rr.rr_mask_from_dense(Q, K, mask.dense, B)
     assert torch.equal(again.row_order, mask.row_order) and not mask.queue.any()
 
