@@ -298,7 +298,7 @@ RR_API int rr_estimate_ex(const rr_shape* shape, const void* Q, const void* K, i
     a.row_order = order ? out->row_order : nullptr;
     a.queue = order ? out->queue : nullptr;
     if (mfma) {
-        // split stride sums -> block masses in the workspace (two sweeps on the matrix cores) -> Top-tau per row
+        // split stride sums -> scores on the matrix cores, block masses, Top-tau per row, in the form for this shape
         unsigned short* ksplit = reinterpret_cast<unsigned short*>(wsb);
         float* mass = reinterpret_cast<float*>(wsb + planes);
         float2* stats = reinterpret_cast<float2*>(reinterpret_cast<unsigned char*>(mass) +

@@ -316,11 +316,16 @@ hipError_t launch_attn_generic(const Geom& g, int dtype, const AttnArgs& a, hipS
     const long long rows = (long long)g.batch * g.Hq * (g.Lq / a.B);
     auto blocks = [&](int queries) { return rows * ((a.B + queries - 1) / queries); };
     // The last query block 16 queries to a workgroup.  A sparse launch of so few workgroups takes as long as its longest row, and
-    // that is the protected last one (attention alone, us; this row alone, the rest alone, both before, now: fp32, 4096 tokens, 8 heads
-    // of 128: 166, 134, 168, 145; 2048 tokens 89, 58, 91, 60; bf16, 8000 tokens, 8 heads of 64: 114, 90, 121, 89; 4096 tokens, 16
-    // heads 63, 49, 67, 49; where other rows are nearly as long, less: the first case on other inputs 184, now 179).  Not where the rest
-    // takes longer (2000 workgroups and more; 8153 tokens, 16 heads: 126, 141, 146 and with it 146), not for dense calls, whose rows get
-    // shorter one by one, and not for further blocks (the last sixteenth of them: 8153 tokens 162, the first case 146).
+    // that is the protected last one (attention alone, us; this row alone, the rest alone, both before, now: fp32, 2048 tokens, 8 heads
+    // of 128: 89, 58, 91, 60; 4096 tokens, one set of inputs, 166, 134, 168, 145; bf16, 8000 tokens, 8 heads of 64: 114, 90, 121, 89; 4096 tokens,
+    // 16 heads 63, 49, 67, 49).  What is gained goes down with the number of workgroups, as other rows come to be nearly as long; the limit
+    // lies between the largest that gained (1032) and the smallest that did not (2000).  Estimate and attention, fresh inputs, without / with it, and its workgroups, two runs each:
+    //   fp32, 32 queries: 2048 tokens, 8 / 2 heads of 128 (512) 111 / 81; 3000 (752) 147 / 126; 4096 (1024) 192 / 185; 4096, 8 / 2 of 64 (1024) 105 / 99
+    //   bf16, 32 or 64 queries: 1500, 8 / 2 of 64, B 32 (376) 42 / 38; 4096, 6 / 3 of 80 (1032) 77 / 69; 4096, 16 / 4 of 64 (1024) 90 / 75;
+    //     8000, 8 / 2 of 64 (1000) 152 / 118; 8192, 8 / 2 of 40 (1024) 135 / 104
+    // Not where the rest takes longer (2000 workgroups and more: 8153 tokens, 16 heads, attention alone: 126, 141, 146 and with it
+    // 146), not for dense calls, whose rows get shorter one by one, and not for further blocks (the last sixteenth of them: 8153
+    // tokens 162).
     auto short_last = [&](int queries) {
         return a.row_list && a.B > 16 && blocks(queries) <= 1536 && g.Lq / a.B + queries / 16 <= (int)kMaxGridY;
     };

@@ -1,7 +1,12 @@
 // Kernel group (2), MFMA form of the estimation (importance equation, causal stride softmax and block
 // mass, Sec. 3.2-3.3) for bf16 tensors with d = 128 and B/S in {4,8,16,32}.
 //
-// Exactness.  The stride sums of K are fp32 and must not be rounded to bf16 (that would move
+// Three forms, by the shape of the call (launch_estimate_mfma), behind one launch that forms the stride sums: contexts of up to
+// 1024 key strides in one launch (k_estimate_rows); short steps deep in a longer one in two (k_step_scores, k_step_select);
+// everything else, packed sequences and cut diagonal strides of any length among it, in two sweeps (k_stride_mass_mfma) and a
+// selection (k_select_rows), which the following describes.
+//
+// Exactness (of all three).  The stride sums of K are fp32 and must not be rounded to bf16 (that would move
 // logits by ~1e-2 and flip far more blocks than the parity margin excuses).  Each fp32 sum is
 // instead split exactly into three bf16 terms hi + mid + lo (3 x 8 mantissa bits); Q is bf16
 // already, so three bf16 MFMAs with fp32 accumulation reproduce the fp32 products exactly and only
@@ -505,7 +510,8 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
 // 64 / R consecutive (query block, head) pairs of a KV head, so the heads of a query block share the stride sums it
 // reads, which go from L2 straight to the operand registers (every wave has tiles of its own: nothing to share in LDS).
 // What bounds it: the chain launch, queries, stride sums, softmax, selection of one row, each waiting for the one before; 8192
-// tokens, 32 / 8 heads: 15 us where two sweeps and the selection took 21 + 19 + 7.
+// tokens, 32 / 8 heads: 22-23 us on one set of inputs again and again (26 among other launches) where two sweeps and the selection
+// took 21 + 19 + 7.
 constexpr int kRowWaves = 8, kRowCols = 64;
 constexpr int kRowTiles = 4 * kRowWaves;                           // the most tiles of key strides it takes
 template <int R, int TPW>
