@@ -5,6 +5,8 @@ heads that do not divide a workgroup's rows, lengths that end inside a block and
 import pytest
 import torch
 
+import gpu_util as gu
+
 pytestmark = pytest.mark.gpu
 
 # R = 128 / S, L, Hq, Hkv, batch: one tile, eight tiles and one more, sixteen and one more, the most; a block and less
@@ -52,3 +54,39 @@ def test_one_launch_agrees_with_two_sweeps(R, L, Hq, Hkv, batch):
             near = (cum - tau).abs().min() < 2.0 ** -15
             tied = k < Nb and float(row[k - 1] - row[k]) <= 2.0 ** -15 * float(row[k - 1])
             assert near or tied, (i.tolist(), cum[k - 1].item())
+
+
+# steps whose heads hold a sampled query only in part, or not at all (those that complete no stride): workgroups of 64 / R rows without a
+# single one skip the scores, with others that do not
+@pytest.mark.parametrize("R,L,Lq,Hq,Hkv,batch", [(4, 32000 + 3, 3, 32, 8, 1), (4, 32000, 9, 64, 2, 1), (8, 16007, 1, 8, 2, 2), (8, 16000, 3, 32, 2, 1),
+                                                 (16, 8003, 2, 8, 1, 1), (16, 4000, 1, 16, 2, 1), (32, 4002, 1, 8, 2, 1), (32, 2004, 2, 8, 1, 3)])
+def test_steps_with_few_sampled_queries(R, L, Lq, Hq, Hkv, batch):
+    import paper_2602_05853_amd as rr
+    dev, B, tau = "cuda:0", 128, 0.9
+    S, Nb, q0, G = B // R, -(-L // B), L - Lq, Hq // Hkv
+    g = torch.Generator(device=dev).manual_seed(L + Lq)
+    Q = (2.0 * torch.randn(batch, Hq, Lq, 128, generator=g, device=dev)).bfloat16()
+    K = (torch.randn(batch, Hkv, L, 128, generator=g, device=dev) + 2.0 * (torch.arange(L, device=dev) < L // 5)[:, None]).bfloat16()
+    rows = Nb - q0 // B
+    mask = rr.BlockMask.allocate(batch, Hq, Nb, B, dev, block_mass=True, Hkv=Hkv, rows=rows)
+    mask.block_mass.fill_(float("nan"))
+    mask.dense.fill_(7)
+    print(f"[short step] R={R} {Lq} of {L} {Hq}/{Hkv} x {batch}", flush=True)
+    rr.rr_estimate(Q, K, S, B, tau, flags=0, out=mask)
+    torch.cuda.synchronize()
+    n = torch.arange(Nb, device=dev)
+    held = 0
+    for b in range(batch):
+        for h in range(Hq):
+            ref = gu.stride_masses(Q[b, h], K[b, h // G], S, B, q0, h)
+            assert ((mask.block_mass[b, h].double() - ref).abs() <= 2.0 ** -16 * ref + 2.0 ** -24).all()
+            for r in range(rows):
+                kept, m = mask.dense[b, h, r], q0 // B + r
+                if not bool(ref[r].any()):
+                    assert torch.equal(kept.bool(), n <= m) and int(kept.max()) == 1
+                    continue
+                held += 1
+                a, rest = ref[r][kept.bool()], ref[r][~kept.bool()]
+                assert a.sum() >= tau - 1e-5 and a.sum() - a.min() < tau + 1e-5 and (rest <= a.min() * (1 + 2.0 ** -15)).all()
+    sampled = sum(i * S + S - 1 - h % S >= q0 for h in range(Hq) for i in range(q0 // S, L // S))
+    assert (held > 0) == (sampled > 0)
