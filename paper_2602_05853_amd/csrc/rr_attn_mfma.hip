@@ -1112,15 +1112,32 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
 
 constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens, see launch_attn_mfma_bf16
 
+// Whether the heaviest rows of all KV groups, one run of each group's row order (8 G rows, which one XCD each was chosen for),
+// may go in front of the sets: up to 64 heads in all, whose runs are no more than the 512 workgroups that run at once, or up to 128
+// heads of long prompts, whose runs are at most a sixteenth of the rows, unless the rows of a group are many.  More of them are a
+// visible share of the launch, mixed rows of many groups find less in L2, and the last set of a launch of many sets is a small
+// part of it.  Estimate and attention with the runs in front / without, us, gain of the inputs 3, tau 0.9:
+//   not taken: 64 / 8 heads, four prompts of 5000 tokens 902 / 857, of 12000 3674 / 3503, two of 9200 1130 / 1112, of 14000 2347 / 2290, of 30000
+//     9290 / 9213 (on another box 9657 / 9741), of 40000 16271 / 15879 (17025 / 17221); 32 / 8, four of 3000 229 / 221, of 9000 1153 / 1115, of 16000 3016 / 2976, eight of 6000 1251 / 1205,
+//     of 20000 9342 / 9221; 28 / 4, four of 10000 1196 / 1167, three of 36000 8677 / 8430; 8 / 2, sixteen of 8000 1016 / 979
+//   taken: 32 / 8, four of 18500 3743 / 3964, 24000 6298 / 6509, 33000 11314 / 11824, 45000 21541 / 21344 (22369 / 22346); 64 / 8, two of 20000 4379 / 4393, 26000 7102 /
+//     7167; 28 / 4, four of 20000 3899 / 3794, 25000 5704 / 5862; 16 / 4, eight of 24000 6298 / 6480; 8 / 2, sixteen of 20000 4631 / 4772
+bool first_runs_pay(const Geom& g) {
+    const long long heads = (long long)g.batch * g.Hq;
+    const int Nbq = g.Lq / 128;
+    return heads <= 64 || (heads <= 128 && Nbq >= 128 && g.G * Nbq <= 1750);
+}
+
 // KV groups launched interleaved (decode_block, order_entry_of): the largest divisor of the number of groups that keeps K and V of
-// the set within 32 MB, the L2 capacity of the chip (8 x 4 MB), or within 38 MB for the row order of a whole prompt whose sets are at
-// most 3000 rows long.  More groups to a set find less of each other's tiles in L2, fewer put more of a launch's heavy
-// rows late, which counts where a set is over soon.  Measured, estimate and attention or dense call, us, 38 MB / 32 MB, gain of the
-// inputs 3 and tau 0.9 unless said:
+// the set within 32 MB, the L2 capacity of the chip (8 x 4 MB), or within 38 MB for the row order of whole prompts where the first runs
+// pay and sets are at most 3000 rows long.  More groups to a set find less of each other's tiles in L2, fewer put more of a
+// launch's heavy rows late, which counts where there are few sets and they are over soon.  Measured, estimate and attention or dense
+// call, us, 38 MB / 32 MB, gain of the inputs 3 and tau 0.9 unless said:
 //   sets of up to 3000 rows: 32 / 8 heads, 18000 tokens 752 / 772, 37000 2772 / 2848; 16 / 4, 37000 1552 / 1736, tau 0.95 2168 / 2318; 8 / 2, 36000
 //     810 / 873, 38900 883 / 931 (weaker structure, tau 0.95, 38500 1709 / 1670; three packed prompts of 300 blocks 715 / 706)
 //   longer ones (32 MB): 64 / 8, 9000 538 / 520, 18000 1747 / 1725, 35000 5092 / 4881, 38500 7564 / 7389; 28 / 4, 17000 708 / 699, 18500 647 / 653,
 //     35000 2631 / 2587, 38000 3116 / 3056, packed prompts of 290 blocks 1286 / 1257
+//   many short prompts (32 MB): 32 / 8, three of 12000 1402 / 1368, four of 9000 1118 / 1109
 //   no row order or not a whole prompt (32 MB): dense, 32 / 8, 38900 11363 / 11119, 8900 to 36000 level; planned chunks, 1000 of 35000, 64 / 8
 //     heads, 415 / 402 and 424 / 412, 1500 of 18500, 32 / 8, 209 / 203 and 200 / 203; sparse without a row order level
 int interleave_groups(const Geom& g, bool ordered) {
@@ -1128,17 +1145,20 @@ int interleave_groups(const Geom& g, bool ordered) {
     const int NG = g.batch * g.Hkv, rows = g.G * (g.Lq / 128);
     int gi = 1;
     for (int c = 1; c <= NG && c <= 64; ++c) {
-        const bool more = ordered && g.q0 == 0 && c * rows <= 3000;
+        const bool more = ordered && g.q0 == 0 && first_runs_pay(g) && c * rows <= 3000;
         if (NG % c == 0 && c * per_group <= (more ? 38ll : 32ll) << 20) gi = c;
     }
     return gi;
 }
 // What starts late counts: the longest row (the protected one keeps every block) of the last set took as long as that whole
-// set, so sparse launches first take the heaviest rows of ALL groups, one run of the row order (8 G rows, which one XCD each was
-// chosen for), and then the sets.  Not taken by sets of 4096 rows and more (eight to each of the 512 workgroups that run at
-// once), where it is even: 131072 tokens, 32 / 8 heads, with it 0.2 and 0.4 % slower in two runs, at weaker structure 0.4 and 1.1 %, at tau 0.95
-// 0.7 and 0.6 %; 65536, 64 / 8, S = 8, 1.2 and 1.1 % faster, 65500, tau 0.95, 0.6 and 0.9 %.  And not by contexts of more than 256 blocks
-// with fewer than eight groups: the last set is a large part of the launch there, and the mixed rows cost what they save.
+// set, so sparse launches first take the heaviest rows of ALL groups, one run of the row order, and then the sets.
+// Not taken where
+// - first_runs_pay says no
+// - sets have 4096 rows and more (eight to each of the 512 workgroups that run at once), where it is even: 131072 tokens, 32 / 8
+//   heads, with it 0.2 and 0.4 % slower in two runs, at weaker structure 0.4 and 1.1 %, at tau 0.95 0.7 and 0.6 %; 65536, 64 / 8, S = 8, 1.2 and 1.1 %
+//   faster, 65500, tau 0.95, 0.6 and 0.9 %
+// - contexts of more than 256 blocks have fewer than eight groups: the last set is a large part of the launch there, and the mixed
+//   rows cost what they save.
 // Measured, attention alone, tau 0.9, us; sets of 32 MB without the first run / sets of 1, 2, 4 groups with it:
 //   32 / 8 heads: 9000 tokens 265 / 208, 206, 206; 16384 628 / 580, 555, 541; 24000 1330 / 1217, 1171, 1158; 28000 1730 / 1580, 1532,
 //     1545; 36000 3020 / 2699, 2643, 2736; 50000 4950 / 4637, 4617, 4731; 65536 8350 / 7906, 7704, 8065 (weaker structure 14349 / 14201,
@@ -1148,7 +1168,9 @@ int interleave_groups(const Geom& g, bool ordered) {
 //     packed prompts (311 blocks) 1371 / 1385
 int hoisted_rows(const Geom& g, int interleave) {
     const int NG = g.batch * g.Hkv, rows = g.G * (g.Lq / 128);
-    if (interleave == NG || interleave * rows >= 4096 || 8 * g.G >= rows || (g.L / 128 > kPersistMaxBlocks && NG < 8)) return 0;
+    if (!first_runs_pay(g) || interleave == NG || interleave * rows >= 4096 || 8 * g.G >= rows ||
+        (g.L / 128 > kPersistMaxBlocks && NG < 8))
+        return 0;
     return 8 * g.G;
 }
 

@@ -10,8 +10,11 @@ pytestmark = pytest.mark.gpu
 
 
 # batch, L, Hq, Hkv: 16 groups of 2.6 MB of K and V (sets of 8), 15 groups (sets of 5 and 5 and 5), 4 groups of 10 MB, groups
-# of 7 heads, and 40 groups whose first run is half of their rows
-@pytest.mark.parametrize("batch,L,Hq,Hkv", [(2, 5120, 16, 8), (5, 5100, 6, 3), (4, 20480, 2, 1), (3, 9000, 28, 4), (40, 2048, 2, 1)])
+# of 7 heads, and 30 groups whose first run is half of their rows; 64 heads, the most whose first runs go in front of short prompts, 84, 80
+# and 65 without, 66 heads of 128 blocks with them and of 127 without
+@pytest.mark.parametrize("batch,L,Hq,Hkv", [(2, 5120, 16, 8), (5, 5100, 6, 3), (4, 20480, 2, 1), (3, 9000, 28, 4), (40, 2048, 2, 1),
+                                            (2, 9000, 28, 4), (30, 2048, 2, 1), (1, 5000, 64, 16), (13, 3000, 5, 1), (33, 16300, 2, 1),
+                                            (33, 16250, 2, 1)])
 @pytest.mark.parametrize("queue", [True, False])
 def test_sets_of_groups_compute_every_row(batch, L, Hq, Hkv, queue):
     import paper_2602_05853_amd as rr
