@@ -512,6 +512,11 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
 // What bounds it: the chain launch, queries, stride sums, softmax, selection of one row, each waiting for the one before; 8192
 // tokens, 32 / 8 heads: 22-23 us on one set of inputs again and again (26 among other launches) where two sweeps and the selection
 // took 21 + 19 + 7.
+// A score's exponent is one fma, score scale - round(largest score scale): that rounding is a factor that all strides of a query share, and it
+// goes with the sum.  Not where it is itself too large to be an exponent: beyond this reference (log2 units, rounded to at most
+// 1) the largest score is subtracted first, which leaves its own stride exactly 2^0.  (Without, one key of 1e12 made queries drop out of
+// their row, or the row have no estimate.)
+constexpr float kFarReference = 16777216.f;
 constexpr int kRowWaves = 8, kRowCols = 64;
 constexpr int kRowTiles = 4 * kRowWaves;                           // the most tiles of key strides it takes
 template <int R, int TPW>
@@ -613,6 +618,16 @@ k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
 #pragma unroll
         for (int i = 0; i < kRowWaves; ++i) top = fmaxf(top, s_red[0][i][32 * nt + l32]);
         nb[nt] = top == NEG_INF ? 0.f : -(top * a.scale_log2);
+        if (__any(fabsf(nb[nt]) > kFarReference)) {
+            const float far = top == NEG_INF ? 0.f : top;
+#pragma unroll
+            for (int i = 0; i < TPW; ++i)
+                if (w + kRowWaves * i < ntiles) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) s[i][nt][e] -= far;
+                }
+            nb[nt] = 0.f;
+        }
     }
 #pragma unroll
     for (int i = 0; i < TPW; ++i)
@@ -739,8 +754,15 @@ k_step_scores(Geom g, ScoreArgs a, StepArgs sa) {
         float mx = NEG_INF;
 #pragma unroll
         for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
-        mx = fmaxf(mx, lane_xor32(mx, gsel != 0)) * a.scale_log2;
-        const float nb = mx == NEG_INF ? 0.f : -mx;
+        mx = fmaxf(mx, lane_xor32(mx, gsel != 0));
+        const float far = mx == NEG_INF ? 0.f : mx;
+        mx *= a.scale_log2;
+        float nb = mx == NEG_INF ? 0.f : -mx;
+        if (__any(fabsf(nb) > kFarReference)) {                    // see there
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[e] -= far;
+            nb = 0.f;
+        }
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], a.scale_log2, nb));
         constexpr int NBL = R == 4 ? 4 : NB, RPB = 16 / NBL;
