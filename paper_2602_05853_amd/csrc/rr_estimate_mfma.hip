@@ -515,7 +515,7 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
 // A score's exponent is one fma, score scale - round(largest score scale): that rounding is a factor that all strides of a query share, and it
 // goes with the sum.  Not where it is itself too large to be an exponent: beyond this reference (log2 units, rounded to at most
 // 1) the largest score is subtracted first, which leaves its own stride exactly 2^0.  (Without, one key of 1e12 made queries drop out of
-// their row, or the row have no estimate.  17 layers and steps with the test for it: 0.985 to 1.010 of the time without.)
+// their row, or the row have no estimate.  17 layers and steps with the test for it: 0.986 to 1.015 of the time without, twice without 0.992 to 1.008.)
 constexpr float kFarReference = 16777216.f;
 constexpr int kRowWaves = 8, kRowCols = 64;
 constexpr int kRowTiles = 4 * kRowWaves;                           // the most tiles of key strides it takes
@@ -618,15 +618,16 @@ k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
 #pragma unroll
         for (int i = 0; i < kRowWaves; ++i) top = fmaxf(top, s_red[0][i][32 * nt + l32]);
         nb[nt] = top == NEG_INF ? 0.f : -(top * a.scale_log2);
-        if (__any(fabsf(nb[nt]) > kFarReference)) {
-            const float far = top == NEG_INF ? 0.f : top;
+        const bool is_far = fabsf(nb[nt]) > kFarReference;
+        if (__any(is_far)) {
+            const float far = is_far ? top : 0.f;                  // (other queries of the wavefront stay what they are)
 #pragma unroll
             for (int i = 0; i < TPW; ++i)
                 if (w + kRowWaves * i < ntiles) {
 #pragma unroll
                     for (int e = 0; e < 16; ++e) s[i][nt][e] -= far;
                 }
-            nb[nt] = 0.f;
+            nb[nt] = is_far ? 0.f : nb[nt];
         }
     }
 #pragma unroll
@@ -755,13 +756,14 @@ k_step_scores(Geom g, ScoreArgs a, StepArgs sa) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
         mx = fmaxf(mx, lane_xor32(mx, gsel != 0));
-        const float far = mx == NEG_INF ? 0.f : mx;
+        const float top = mx;
         mx *= a.scale_log2;
         float nb = mx == NEG_INF ? 0.f : -mx;
-        if (__any(fabsf(nb) > kFarReference)) {                    // see there
+        const bool is_far = fabsf(nb) > kFarReference;
+        if (__any(is_far)) {                                       // see there
 #pragma unroll
-            for (int e = 0; e < 16; ++e) s[e] -= far;
-            nb = 0.f;
+            for (int e = 0; e < 16; ++e) s[e] -= is_far ? top : 0.f;
+            nb = is_far ? 0.f : nb;
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], a.scale_log2, nb));
