@@ -112,6 +112,7 @@ int run_attn(const rr_shape* shape, const void* Q, const void* K, const void* V,
     a.queue = a.row_order ? queue : nullptr;
     a.interleave = 1;
     a.hoist = 0;
+    a.by_group = 0;
     a.nsplit = 1;
     a.part_O = nullptr;
     a.part_lse = nullptr;

@@ -92,7 +92,14 @@ __device__ __forceinline__ int k_swz(int key, int chunk) { return key * 256 + ((
 __device__ __forceinline__ int v_swz(int key, int chunk) { return key * 256 + ((chunk ^ ((key & 7) << 1)) << 4); }
 
 // workgroup id -> (batch, head, query block).  Workgroups are dealt to the 8 XCDs round-robin
-// (id % 8 picks the XCD) and start in id order.  When Nb is a multiple of 8 the KV groups are
+// (id % 8 picks the XCD) and start in id order.
+// Dense calls (by_group) where the groups divide into the XCDs or the XCDs into the groups: every XCD takes
+// KV groups of its own, so that the rows that run on it, which walk their blocks in the same order, find each other's tiles in its
+// L2.  All groups cost the same there.  Against sets of groups over all XCDs (below; the order before where Nb is a multiple of 8, elsewhere
+// level with what was), dense, us: 32 / 8 heads, 4096 tokens 157 / 147, 8192 533 / 512, 16384 2002 / 1946, 32768 7817 / 7506, 98304 67445 / 67180;
+// four prompts of 16384 8014 / 7575, sixteen of 2048 686 / 623 (group after group; rank by rank of all an XCD's groups 7704, 635); 28 / 4
+// heads, 16384 1709 / 1680.
+// Elsewhere, when Nb is a multiple of 8 the KV groups are
 // taken `gi` at a time GPU-wide, so that the keys and values in use stay cache resident and L2 misses of
 // the sparse walk stay off HBM (gi = 1 at 128K tokens, where one group's K and V are 64 MB);
 // XCD x takes the rows with rank = x (mod 8), the query heads of a group back to back, rows heaviest
@@ -121,7 +128,7 @@ __device__ __forceinline__ int order_entry_of(int bid, const Geom& g, int Nb, co
 }
 
 __device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, const int32_t* order, int a_interleave, int hoist,
-                                             int& b, int& h, int& m) {
+                                             int by_group, int& b, int& h, int& m) {
     const int NG = g.batch * g.Hkv, G = g.G;
     int mr, grp, hl;
     if (order) {
@@ -132,7 +139,14 @@ __device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, con
         h += hl;
         return true;
     }
-    if ((Nb & 7) == 0) {
+    if (by_group && (NG & 7) == 0) {
+        // XCD x: groups x, x + 8, .. one after the other, rows by descending m, the heads of a query block together
+        const int x = bid & 7, s = bid >> 3, per = Nb * G;
+        grp = x + 8 * (s / per);
+        const int r = s % per;
+        mr = r / G;
+        hl = r - mr * G;
+    } else if ((Nb & 7) == 0 && !by_group) {
         // one KV group after the other GPU-wide (its keys and values then fit the memory-side
         // cache); XCD x takes the rows with rank = x mod 8, the heads of a group back to back
         const int x = bid & 7, s = bid >> 3;
@@ -542,6 +556,7 @@ struct AttnKernelArgs {
     AttnArgs a;
     float scale_log2;
     float lazy_log2, lazy_sum;
+    unsigned starts;                   // persistent form, nibble q: of eight workgroups in a row, those that start with queue q
 };
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef const __attribute__((address_space(4))) AttnKernelArgs* kernarg_ptr_t;
@@ -569,10 +584,11 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // that the plain launch carries none of it (both forms run at the same rate).
     //
     // kPersist (sparse launches with a row order and a queue): two workgroups per compute unit that take row after
-    // row.  Workgroup i starts with launch rank i and then draws ranks x + 8 t (x = i mod 8, the XCD the
-    // dispatcher gave it) from the counter of its XCD, so that every rank keeps the XCD the order was made for
-    // while the compute units of an XCD share its rows dynamically, and the next row is looked up while the
-    // current one is merged and stored.
+    // row.  A workgroup takes rows of one queue: by_group, its XCD's (x = workgroup mod 8, the XCD the dispatcher gave
+    // it) share of the KV groups, queue x mod NQ of NQ = min(groups, 8), with groups q, q + NQ, ..; or the launch ranks x + 8 t, so that every rank keeps
+    // the XCD the order was made for.  The first rows go by workgroup index, the others are drawn from the queue's
+    // counter, and the next row is looked up while the current one is merged and stored.  by_group, a workgroup whose queue is empty goes on
+    // with the one that has the most rows left (groups differ in what they keep).
     //
     // kWide (launches whose time is that of a row, see launch_attn_mfma_bf16): two groups of four waves to a row, group
     // hg with the keys 64 hg .. +63 of every block and tile buffers of its own; one workgroup per compute unit
@@ -585,8 +601,8 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
 
     // ---- the next row of a persistent workgroup ----
     // Fetched in five steps, each needing what the one before it loaded: (1) a ticket from the XCD's counter,
-    // published to the other waves through LDS, (2) the rank it stands for and that rank's entry of the row
-    // order, (3) the row, its count and its first list entry, (4) its last list entry, (5) done.  They are
+    // published to the other waves through LDS, (2) the entry of the row order that it stands for,
+    // (3) the row, its count and its first list entry, (4) its last list entry, (5) done.  They are
     // placed in the tail of the current row: the ticket travels during the diagonal pass, the order entry during
     // the merge, count and first entry during the output stores; only the last entry is waited for.  The ticket
     // is deliberately NOT drawn earlier (say, at the
@@ -594,7 +610,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     // ahead starts it out of step with the rows queued around it, which were ordered to walk the same key
     // blocks at the same time on one XCD; measured, the early draw cost 2-3 % at 32K-128K tokens.
     struct NextRow {
-        int rank;           // launch rank, or -1 when the queue is empty
+        int rank;           // its place in the queue, or -1 when there is none
         int order_entry;    // as loaded
         bool live;          // the order entry names a row
         int b, h, mq;
@@ -602,34 +618,90 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
     } nx;
     nx.rank = -1; nx.live = false; nx.order_entry = 0;
     nx.b = nx.h = nx.mq = 0; nx.count_raw = nx.e0 = nx.elast = 0;
-    const int xcd = (int)blockIdx.x & 7;
-    volatile lds_int_t* const ticket_slot = (volatile lds_int_t*)(lds + (kWide ? 2 : 1) * kLdsBytes);
-    int ticket = 0;                                         // lane 0 of wave 0
+    volatile lds_int_t* const ticket_slot = (volatile lds_int_t*)(lds + (kWide ? 2 : 1) * kLdsBytes);   // queue, place in it
+    int queue_id = 0, ticket = 0;                           // lane 0 of wave 0
+    auto groups_of = [&](const Geom& g, int q) {
+        const int NG = g.batch * g.Hkv;
+        return NG >= 8 ? (NG - q + 7) >> 3 : 1;
+    };
+    auto rows_of = [&](kernarg_ptr_t ka, const Geom& g, int q) {
+        const int Nbq = g.Lq >> 7;
+        return ka->a.by_group ? groups_of(g, q) * g.G * Nbq : (g.batch * g.Hq * Nbq - q + 7) >> 3;
+    };
+    auto first_of = [&](kernarg_ptr_t ka, int q) { return ((int)gridDim.x >> 3) * (int)((ka->starts >> (4 * q)) & 15u); };
     auto draw_issue = [&]() {
-        if (draws) ticket = atomicAdd(kernel_args<true>()->a.queue + kQueueStride * xcd, 1);
+        if (draws) ticket = atomicAdd(kernel_args<true>()->a.queue + kQueueStride * queue_id, 1);
     };
     auto draw_publish = [&]() {                             // readable after the next workgroup barrier
-        if (draws) *ticket_slot = ticket;
+        if (!draws) return;
+        const kernarg_ptr_t ka = kernel_args<true>();
+        const Geom g = ka->g;
+        int at = first_of(ka, queue_id) + ticket;
+        while (at >= rows_of(ka, g, queue_id)) {
+            at = -1;
+            if (!ka->a.by_group) break;
+            // the queue with the most rows left (counters only grow: this ends)
+            const int NQ = min(g.batch * g.Hkv, 8);
+            int drawn[8], most = 0, from = -1;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                drawn[q] = q < NQ ? __hip_atomic_load(ka->a.queue + kQueueStride * q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int left = q < NQ ? rows_of(ka, g, q) - first_of(ka, q) - drawn[q] : 0;
+                if (left > most) { most = left; from = q; }
+            }
+            if (from < 0) break;
+            queue_id = from;
+            at = first_of(ka, from) + atomicAdd(ka->a.queue + kQueueStride * from, 1);
+        }
+        ticket_slot[0] = queue_id;
+        ticket_slot[1] = at;
     };
-    auto step_order = [&](long long rank) {                 // (2); rank = workgroup index for the first row
+    auto step_order = [&](int q, int at) {                  // (2)
         const kernarg_ptr_t ka = kernel_args<true>();
         const Geom g = ka->g;
         const int Nbq = g.Lq >> 7;
         nx.live = false;
-        // (a queue that did not start from zero can only make the launch skip rows: a rank outside the launch ends it)
-        if (rank >= 0 && rank < (long long)g.batch * g.Hq * Nbq) {
-            int pb, ph;
-            nx.rank = (int)rank;
-            nx.order_entry = order_entry_of((int)rank, g, Nbq, ka->a.row_order, ka->a.interleave, ka->a.hoist, pb, ph);
-            nx.b = __builtin_amdgcn_readfirstlane(pb);
-            nx.h = __builtin_amdgcn_readfirstlane(ph);
+        nx.rank = -1;
+        if (at < 0) return;
+        nx.rank = at;
+        int pb, ph;
+        if (ka->a.by_group) {
+            int grp = q, i = at;
+            if (g.batch * g.Hkv > 8) {
+                // the heaviest rows of all groups of the queue, then group by group
+                const int n = groups_of(g, q), N = g.G * Nbq, hoist = ka->a.hoist;
+                int gi;
+                if (at < n * hoist) {
+                    i = at / n;
+                    gi = at - i * n;
+                } else {
+                    const int r = at - n * hoist;
+                    gi = r / (N - hoist);
+                    i = hoist + (r - gi * (N - hoist));
+                }
+                grp = q + 8 * gi;
+            }
+            pb = grp / g.Hkv;
+            ph = (grp - pb * g.Hkv) * g.G;
+            // The order is transposed inside runs of 8 G rows, for XCDs that take every eighth: here the rows as they were sorted,
+            // the heads of a query block together (32 / 8 heads, 50000 tokens 7866 -> 7785 us; packed prompts of 311 blocks, 28 / 4, 1395 -> 1382).
+            const int C = g.G, run = 8 * C;
+            if (C > 1 && i < g.G * Nbq / run * run) {
+                const int base = i / run * run, w = i - base;
+                i = base + 8 * (w % C) + w / C;
+            }
+            nx.order_entry = ka->a.row_order[(long long)grp * (g.G * Nbq) + i];
         } else {
-            nx.rank = -1;
+            nx.order_entry = order_entry_of(8 * at + q, g, Nbq, ka->a.row_order, ka->a.interleave, ka->a.hoist, pb, ph);
         }
+        nx.b = __builtin_amdgcn_readfirstlane(pb);
+        nx.h = __builtin_amdgcn_readfirstlane(ph);
     };
     auto step_rank = [&]() {
-        const int t = __builtin_amdgcn_readfirstlane(*ticket_slot);
-        step_order(((long long)((int)gridDim.x >> 3) + t) * 8 + xcd);
+        const int q = __builtin_amdgcn_readfirstlane(ticket_slot[0]), at = __builtin_amdgcn_readfirstlane(ticket_slot[1]);
+        step_order(q, at);
     };
     auto step_row = [&]() {                                 // (3)
         if (nx.rank < 0) return;
@@ -665,8 +737,12 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         if (nx.rank >= 0 && nx.live) nx.elast = __builtin_amdgcn_readfirstlane(nx.elast);
     };
     if (kPersist) {
-        // the first row: rank = workgroup index, the same steps, each waiting for its loads
-        step_order((long long)blockIdx.x);
+        // the first row, by workgroup index: the same steps, each waiting for its loads
+        const kernarg_ptr_t ka = kernel_args<false>();
+        const int x = (int)blockIdx.x & 7, NQ = ka->a.by_group ? min(ka->g.batch * ka->g.Hkv, 8) : 8;
+        queue_id = x % NQ;
+        const int at = ((int)blockIdx.x >> 3) * (int)((ka->starts >> (4 * queue_id)) & 15u) + x / NQ;
+        step_order(queue_id, at < rows_of(ka, ka->g, queue_id) ? at : -1);
         step_row(); step_last(); step_done();
     }
 
@@ -720,7 +796,7 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         } else {
             const int rank = (int)blockIdx.x - used;
             if (planned && rank >= grid_rows) return;
-            have_row = decode_block(kSplit && !planned ? rank / a.nsplit : rank, g, Nbq, a.row_order, a.interleave, a.hoist, b, h, mq);
+            have_row = decode_block(kSplit && !planned ? rank / a.nsplit : rank, g, Nbq, a.row_order, a.interleave, a.hoist, a.by_group, b, h, mq);
             if (planned) part = 0;
         }
         if (!have_row) return;
@@ -1298,7 +1374,7 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
         int parts = 0, rid = -1;
         if (rank < grid_rows) {
             int b, h, mq;
-            if (decode_block(rank, g, Nbq, a.row_order, a.interleave, a.hoist, b, h, mq)) {
+            if (decode_block(rank, g, Nbq, a.row_order, a.interleave, a.hoist, 0, b, h, mq)) {
                 rid = (b * g.Hq + h) * Nbq + mq;
                 const int count = count_of(rid);
                 if (count > len) parts = (count + len - 1) / len;
@@ -1506,8 +1582,21 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     // workgroup per row: 280 -> 274 us at 8K tokens (4 rows each), 905 -> 898 us at 18K, level at 32K (and beyond: the
     // launch is limited by power there, not by the gaps between rows); with fewer rows than workgroups the look-ahead only
     // costs (1139 tokens, 252 rows: 67 against 72 us).  Wide rows, attention alone: 2048 tokens, 28 / 4 heads 62 -> 47 us.
-    const bool persist = a.row_order != nullptr && a.queue != nullptr && resident >= 8 && a.Nb <= kPersistMaxBlocks &&
-                         a.nsplit == 1 && !planned && rows >= resident;
+    const int NG = g.batch * g.Hkv;
+    const bool queued = a.row_order != nullptr && a.queue != nullptr && resident >= 8 && a.nsplit == 1 && !planned && rows < 1 << 30;
+    // Rows drawn by KV group: at least eight to a workgroup, four where a queue has several groups (below that the groups' different
+    // lengths cost what the L2 hits give), and as long as the keys and values of the groups in flight fit the memory-side cache of
+    // 256 MB.  Estimate and attention, gain of the inputs 3, tau 0.9, us, rows in rank order over all XCDs / by group:
+    //   32 / 8 heads: 16384 tokens 708 / 681, 24000 1518 / 1430, 31907 3142 / 3034, 40000 4068 / 3864, 50000, weaker structure, 8088 / 7776; 64 / 8:
+    //     9000 533 / 521, 20000 2124 / 2040, 60000 17788 / 17407; 28 / 4: 20000 911 / 902, 32000 2247 / 2176, 50000 5442 / 5221; 16 / 4: 60000 4537 /
+    //     4312, 90000 10911 / 10725; 8 / 2: 40000 1087 / 1068; batches: four of 2000, 32 / 8, 162 / 152, sixteen 585 / 554, three of 12000 1360 / 1260, two of 45000 10346 /
+    //     9835, eight of 3000, 28 / 4, 357 / 342; packed prompts of 311 blocks, 28 / 4, 1452 / 1382, forty of 6 blocks, 32 / 8, 403 / 373
+    //   not taken: 2500, 32 / 8, (1.3 rows to a workgroup) 76 / 82, 6500 (3.2) 172 / 180, 8192 (4) level, 12000 (5.9) level; 28 / 4, 8000 (3.4) 217 / 229; 16 / 4,
+    //     16384 (4) 411 / 428; 65536, 64 / 8, 21131 / 21141, 98304, 32 / 8, 25889 / 25944, 131072 31994 / 32199
+    const bool by_group = queued && rows >= (NG > 8 ? 4ll : 8ll) * resident && std::min(NG, 8) * 4ll * g.L * g.d < 256ll << 20;
+    const bool persist = by_group || (queued && a.Nb <= kPersistMaxBlocks && rows >= resident);
+    // (a list without an order: its heavy rows, the last of every head, would meet on few XCDs)
+    a.by_group = by_group || (!a.row_list && a.nsplit == 1 && !planned && ((NG & 7) == 0 || 8 % NG == 0));
     const unsigned grid_rows = grid_size(g, g.Lq / 128, a.row_order != nullptr);
     dim3 grid(grid_rows * (unsigned)a.nsplit + (planned ? (unsigned)a.split_budget : 0u));
     if (planned) {
@@ -1515,7 +1604,13 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
         const hipError_t pe = hipGetLastError();
         if (pe != hipSuccess) return pe;
     }
+    unsigned starts = 0x11111111u;
     if (persist) grid = dim3((unsigned)resident);
+    if (by_group) {
+        starts = 0;
+        for (int x = 0; x < 8; ++x) starts += 1u << (4 * (x % std::min(NG, 8)));
+        a.hoist = 8 * g.G < g.G * (g.Lq / 128) ? 8 * g.G : 0;
+    }
     // How far a weight may exceed the softmax reference before the reference moves up to it, see the head of the file: 2^8, or 2^6
     // in planned launches.
     const float lazy_log2 = planned ? 6.0f : 8.0f;
@@ -1529,6 +1624,7 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
         ka.scale_log2 = scale_log2;
         ka.lazy_log2 = lazy_log2;
         ka.lazy_sum = exp2f(lazy_log2);
+        ka.starts = starts;
         hipLaunchKernelGGL(kernel, grid, dim3((wide ? 2 : 1) * kThreads), lds_bytes, st, ka);
         return hipGetLastError();
     };
