@@ -191,6 +191,47 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
     const int GR = g.G * R;
     const int NR = mb * GR;                                        // rows of this workgroup
 
+    // ---- second launch of a key split: the softmax state of a query over ALL key strides, its states in the chunks brought to one
+    // reference.  A lane takes one of the wave's 64 queries and up to 32 chunks at once.  (Both lanes of a query for each of two
+    // queries, eight chunks at a time and twice, took 12.7 of the 43 us of such a workgroup for 2048 tokens at 128K, 32 chunks; so 3.5.
+    // 32K tokens, three chunks, 4.4 -> 2.4.)
+    const float NEG_INF = -__builtin_huge_valf();
+    float2* const my_stats = a.stats ? a.stats + (((long long)pr * ngroups + mg) * a.nsplit) * 256 : nullptr;
+    float state_um = NEG_INF, state_z = 0.f;
+    if (a.nsplit > 1 && a.mode == 2) {
+        const float2* const sq = my_stats + tid;
+        constexpr int kAtOnce = 32;
+        float2 part[kAtOnce];
+        auto read = [&](int c0) {
+#pragma unroll
+            for (int u0 = 0; u0 < kAtOnce; u0 += 8) {
+                if (c0 + u0 < a.nsplit) {
+#pragma unroll
+                    for (int u = u0; u < u0 + 8; ++u) part[u] = sq[min(c0 + u, a.nsplit - 1) * 256];
+                } else {
+#pragma unroll
+                    for (int u = u0; u < u0 + 8; ++u) part[u] = make_float2(0.f, 0.f);
+                }
+            }
+        };
+        for (int c0 = 0; c0 < a.nsplit; c0 += kAtOnce) {
+            read(c0);
+#pragma unroll
+            for (int u = 0; u < kAtOnce; ++u)                       // (the last chunk again: no new maximum)
+                if (part[u].y > 0.f) state_um = fmaxf(state_um, part[u].x);
+        }
+        for (int c0 = 0; c0 < a.nsplit; c0 += kAtOnce) {
+            if (a.nsplit > kAtOnce) read(c0);
+#pragma unroll
+            for (int u0 = 0; u0 < kAtOnce; u0 += 8) {
+                if (c0 + u0 >= a.nsplit) break;
+#pragma unroll
+                for (int u = u0; u < u0 + 8; ++u)
+                    if (c0 + u < a.nsplit && part[u].y > 0.f) state_z += part[u].y * __builtin_amdgcn_exp2f(part[u].x - state_um);
+            }
+        }
+    }
+
     // ---- this lane's two sampled queries (one per column tile) ----
     bf16x8 qf[2][8];
     int qi_stride[2];                 // query stride index m*R + r, or -1 for a padding row
@@ -324,7 +365,6 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
         if (a.mode == 2 && t_begin >= t_end) return;               // no key block of these rows is in this chunk
     }
     auto tile_of = [&](int t) { return tile0 + (t >= span ? t - span : t); };
-    float2* const my_stats = a.stats ? a.stats + (((long long)pr * ngroups + mg) * a.nsplit) * 256 : nullptr;
 
     if (t_begin < t_end) issue_tile(tile_of(t_begin), t_begin & 1);
     // The sampled queries must be complete in their registers before the tile loop: the compiler's waits for
@@ -336,7 +376,6 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
     wait_copies();
     __syncthreads();
 
-    const float NEG_INF = -__builtin_huge_valf();
     // Softmax state of this lane's share (the strides 8k + 4 gsel .. +3 of every tile) of its two queries, in
     // log2 units: reference U (lazily moved) and sum of 2^(score - U).  Rows that do not exist score 0
     // everywhere (zero query): a finite reference keeps them off the slow path.
@@ -345,30 +384,10 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
     for (int nt = 0; nt < 2; ++nt) U[nt] = qi_stride[nt] >= 0 ? NEG_INF : 0.f;
 
     if (a.nsplit > 1 && a.mode == 2) {
-        // the softmax state of a query over ALL key strides: its states in the chunks, brought to one reference
+        // lanes l and l + 32 of the wave hold the states of its queries in the column tiles 0 and 1
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-            // eight chunks at a time: read one after the other, their latencies were a third of a launch of 32 chunks
-            // (2048 tokens behind 128K: 61 -> 39 us; 8 tokens behind 64K 19 -> 9.5 us)
-            const float2* sq = my_stats + 64 * wv + 32 * nt + l32;
-            float um = NEG_INF;
-            for (int c0 = 0; c0 < a.nsplit; c0 += 8) {
-                float2 s8[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) s8[u] = sq[min(c0 + u, a.nsplit - 1) * 256];   // (the last one again: no new maximum)
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (s8[u].y > 0.f) um = fmaxf(um, s8[u].x);
-            }
-            float z = 0.f;
-            for (int c0 = 0; c0 < a.nsplit; c0 += 8) {
-                float2 s8[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) s8[u] = sq[min(c0 + u, a.nsplit - 1) * 256];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (c0 + u < a.nsplit && s8[u].y > 0.f) z += s8[u].y * __builtin_amdgcn_exp2f(s8[u].x - um);
-            }
+            const float um = __shfl(state_um, 32 * nt + l32), z = __shfl(state_z, 32 * nt + l32);
             nbq[nt] = (um == NEG_INF) ? 0.f : -um;
             invZ[nt] = (qi_stride[nt] >= 0 && z > 0.f) ? 1.0f / z : 0.f;
         }

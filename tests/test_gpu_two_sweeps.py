@@ -93,3 +93,22 @@ def test_kept_stride_sums_deep_in_a_context(Hq, Hkv, S, batch):
         live = torch.arange(plain.Nb, device="cuda:0") < plain.row_count[..., None]
         assert torch.equal(torch.where(live, kept.row_list, -1), torch.where(live, plain.row_list, -1))
     assert sum(one for one, _ in forms) >= 3 and sum(not one for one, _ in forms) >= 2
+
+
+# key strides shared out among 7, 8, 9, 31, 33 and 39 workgroups, whose softmax states the second launch reads 8 to 32 at a time
+@pytest.mark.parametrize("S,L,parts", [(16, 30000, 7), (16, 128 * 256, 8), (16, 37000, 9), (4, 31800, 31), (4, 33900, 33), (4, 40000, 39)])
+def test_states_of_many_parts(S, L, parts):
+    import paper_2602_05853_amd as rr
+    Hq, Hkv, Lq, Nb = 4, 2, 600, -(-L // B)
+    Q, K = _context(1, Hq, Hkv, L, Lq, L + S)
+    rows = Nb - (L - Lq) // B
+    ws = torch.full((rr.rr_workspace_bytes(Q, K, S, B),), 0xFF, dtype=torch.uint8, device="cuda:0")
+    print(f"[states] S {S}, {L} tokens", flush=True)
+    mask = rr.rr_estimate(Q, K, S, B, 0.9, workspace=ws, block_mass=True)
+    torch.cuda.synchronize()
+    planes, masses = _parts(1, Hq, Hkv, L, rows, S)
+    groups = -(-rows // min(rows, 256 // (Hq // Hkv * (B // S))))
+    assert ws.numel() - planes - masses >= Hkv * groups * parts * 256 * 8 > ws.numel() - planes - masses - 2048
+    for h in range(Hq):
+        ref = gu.stride_masses(Q[0, h], K[0, h // (Hq // Hkv)], S, B, L - Lq, h)
+        assert ((mask.block_mass[0, h].double() - ref).abs() <= 2.0 ** -16 * ref + 2.0 ** -24).all(), h      # as above
