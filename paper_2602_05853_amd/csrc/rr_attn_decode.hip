@@ -268,15 +268,23 @@ k_attn_decode_combine(Geom g, AttnArgs a, int T) {
     const float w = (tid < P && l != NEG_INF) ? expf(l - mx) : 0.f;
     if (tid < kDecMaxParts) s_w[tid] = w;
     __syncthreads();
-    // wavefront wv takes the parts p = wv, wv + 4, ..; a lane two channels
+    // wavefront wv takes the parts p = wv, wv + 4, ..; a lane two channels, eight parts requested at once (one at a time, a part
+    // of weight zero skipped, their latencies were the kernel: one token of 128K, 64 parts, 8.8 us, so 4.2; 16384 tokens, the whole call 22.1 -> 17.8)
+    constexpr int kAtOnce = 8;
     float den = 0.f, o0 = 0.f, o1 = 0.f;
-    for (int p = wv; p < P; p += 4) {
-        const float wp = s_w[p];
-        if (wp == 0.f) continue;
-        const float2 v = *reinterpret_cast<const float2*>(a.part_O + ((long long)p * nrows + row) * 128 + 2 * lane);
-        den += wp;
-        o0 = fmaf(wp, v.x, o0);
-        o1 = fmaf(wp, v.y, o1);
+    for (int p0 = wv; p0 < P; p0 += 4 * kAtOnce) {
+        float2 v[kAtOnce];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u)
+            v[u] = *reinterpret_cast<const float2*>(a.part_O + ((long long)min(p0 + 4 * u, P - 1) * nrows + row) * 128 + 2 * lane);
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            const float wp = p0 + 4 * u < P ? s_w[p0 + 4 * u] : 0.f;
+            if (wp == 0.f) continue;                          // (whatever it holds)
+            den += wp;
+            o0 = fmaf(wp, v[u].x, o0);
+            o1 = fmaf(wp, v[u].y, o1);
+        }
     }
     __syncthreads();
     if (lane == 0) s_red[wv] = den;
