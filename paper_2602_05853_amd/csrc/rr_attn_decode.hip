@@ -38,10 +38,12 @@ struct DecodeArgs {
     int T;              // query positions of the step
     int nblocks;        // key blocks 0 .. nblocks-1 reach the last query
     int len;            // key blocks per part
+    int halves;         // 2: a workgroup takes 16 of the rows (QT = 1)
     float scale_log2;   // log2(e) / sqrt(d)
 };
 
-// QT: 16-column tiles of query rows, for G T <= 16 or 32; columns beyond G T repeat the last row and are never stored.
+// QT: 16-column tiles of query rows, for G T <= 16 or 32; columns beyond G T repeat the last row and are never stored.  (QT = 1 also takes 32
+// rows in two workgroups to a part.)
 // KW: waves, four to a block of keys and with eight of them two blocks at a time.
 template <int QT, int KW>
 __global__ void __launch_bounds__(64 * KW, 2)
@@ -56,7 +58,25 @@ k_attn_decode(Geom g, DecodeArgs da) {
     __shared__ int s_act[kDecMaxLen];                       // the blocks that any does, as offsets into the range
     __shared__ int s_nact;
     const AttnArgs& a = da.a;
-    const int part = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
+    int part = blockIdx.x, kv = blockIdx.y, b = blockIdx.z, half = 0;
+    if (QT == 1 && da.halves == 2) {
+        // a grid of one axis: the two workgroups of a part are eight apart, on one XCD, where the second finds the keys in L2 (but for up to
+        // seven parts at the end)
+        const int items = (int)gridDim.x >> 1, full = items & ~7;
+        int item = (int)blockIdx.x;
+        if (item < 2 * full) {
+            half = (item >> 3) & 1;
+            item = 8 * (item >> 4) + (item & 7);
+        } else {
+            item -= full;
+            half = item >= items;
+            item -= half ? items - full : 0;
+        }
+        const int pair = item / a.nsplit;
+        part = item - pair * a.nsplit;
+        b = pair / g.Hkv;
+        kv = pair - b * g.Hkv;
+    }
     const int tid = threadIdx.x, lane = tid & 63, x = lane & 15, gq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T = da.T, R = g.G * T;
@@ -75,7 +95,7 @@ k_attn_decode(Geom g, DecodeArgs da) {
     unsigned mine[QT];                                       // the row's bit in s_sel
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
-        const int rr = min(16 * u + x, R - 1), hl = rr / T, tk = rr - hl * T;
+        const int rr = min(16 * (half + u) + x, R - 1), hl = rr / T, tk = rr - hl * T;
         qf[u].load(Q + (kv * g.G + hl) * g.qsh + (long long)tk * g.qsl, 128, gq);
         qpos[u] = g.q0 + tk;
         mine[u] = 1u << (hl * Nbq + qpos[u] / kDecBlock - m_first);
@@ -83,7 +103,12 @@ k_attn_decode(Geom g, DecodeArgs da) {
 
     const int n_lo = part * da.len;
     const int n_hi = min(n_lo + da.len, da.nblocks), span = max(n_hi - n_lo, 0);
-    const unsigned all = lists >= 32 ? 0xFFFFFFFFu : (1u << lists) - 1u;
+    // the lists of this workgroup's rows
+    unsigned all = lists >= 32 ? 0xFFFFFFFFu : (1u << lists) - 1u;
+    if (QT == 1 && da.halves == 2) {
+        const int hl_lo = 16 * half / T, hl_hi = min(16 * half + 15, R - 1) / T;
+        all &= (unsigned)((1ull << ((hl_hi + 1) * Nbq)) - 1ull) & ~((1u << (hl_lo * Nbq)) - 1u);
+    }
     // dense: every block up to a list's own query block (of two query blocks, odd lists are the second's)
     for (int i = tid; i < span; i += kThreads)
         s_sel[i] = a.row_list ? 0u : (n_lo + i <= m_first ? all : (Nbq == 2 ? all & 0xAAAAAAAAu : 0u));
@@ -92,6 +117,7 @@ k_attn_decode(Geom g, DecodeArgs da) {
         // every list read whole by the workgroup at once (no search: a chain of dependent loads is longer than that);
         // an entry counts where it lies in the range, whatever the list's order
         for (int l = w; l < lists; l += KW) {
+            if (!((all >> l) & 1u)) continue;
             const int hl = l / Nbq, mq = l - hl * Nbq;
             const long long rid = ((long long)b * g.Hq + kv * g.G + hl) * Nbq + mq;
             int cn = a.row_count[rid];
@@ -223,8 +249,8 @@ k_attn_decode(Geom g, DecodeArgs da) {
     }
     __syncthreads();
     for (int idx = tid; idx < kQ * 32; idx += kThreads) {
-        const int q = idx >> 5, c = 4 * (idx & 31);
-        if (q >= R) continue;
+        const int q = idx >> 5, c = 4 * (idx & 31), rr = 16 * half + q;
+        if (rr >= R) continue;
         float top = NEG_INF;
 #pragma unroll
         for (int i = 0; i < KW; ++i) top = fmaxf(top, s_ref[i][q]);
@@ -240,7 +266,7 @@ k_attn_decode(Geom g, DecodeArgs da) {
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = l > 0.f ? o[e] / l : 0.f;
-        const int hl = q / T, tk = q - hl * T;
+        const int hl = rr / T, tk = rr - hl * T;
         const long long row = ((long long)b * g.Hq + kv * g.G + hl) * T + tk;
         *reinterpret_cast<f32x4*>(a.part_O + ((long long)part * nrows + row) * 128 + c) = o;
         if (c == 0) a.part_lse[(long long)part * nrows + row] = l > 0.f ? top * 0.6931471805599453f + logf(l) : NEG_INF;
@@ -347,7 +373,7 @@ int attn_decode_parts(const Geom& g, int B) {
 // The bytes a call asks for: all parts of the shortest steps, and for the others no more than the launches that served
 // them before ask for, so that the size grows with the step and one workspace serves every step up to the one it was
 // sized for.  These parts are fewer than fill the chip where the heads of a group are many; eight waves to a workgroup
-// make up for some of it.  Dense, us: all parts, these, (the split launch): 8 tokens at 64K, 32 / 8 heads 51, 56, (131); 4 tokens,
+// make up for some of it, and two workgroups to a part for more.  Dense, us, before the latter: all parts, these, (the split launch): 8 tokens at 64K, 32 / 8 heads 51, 56, (131); 4 tokens,
 // 28 / 4 heads 35, 45, (177); 64 / 8 heads 51, 89, (239); 32 / 1 heads, one token, 16 workgroups 30, 50, (218).
 size_t attn_decode_bytes(const Geom& g, int B) {
     const int P = attn_decode_parts(g, B);
@@ -378,15 +404,22 @@ hipError_t launch_attn_decode(const Geom& g, const AttnArgs& a, hipStream_t st) 
     da.nblocks = (g.Lr - 1) / kDecBlock + 1;
     da.len = (da.nblocks + a.nsplit - 1) / a.nsplit;
     da.scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
-    const dim3 grid((unsigned)a.nsplit, (unsigned)g.Hkv, (unsigned)g.batch);
     if (R > kDecMaxRows || da.len > kDecMaxLen) return hipErrorInvalidValue;
     // fewer workgroups than compute units, with parts of some length: two blocks at a time (at 64K, 32 / 8 heads, 8 tokens, 128
     // workgroups 75 -> 56 us; 256 workgroups 51 and 52)
     const bool eight = (long long)a.nsplit * g.batch * g.Hkv < 256 && da.len >= 8;
-    if (R <= 16 && eight) hipLaunchKernelGGL((k_attn_decode<1, 8>), grid, dim3(512), 0, st, g, da);
-    else if (R <= 16) hipLaunchKernelGGL((k_attn_decode<1, 4>), grid, dim3(256), 0, st, g, da);
-    else if (eight) hipLaunchKernelGGL((k_attn_decode<2, 8>), grid, dim3(512), 0, st, g, da);
-    else hipLaunchKernelGGL((k_attn_decode<2, 4>), grid, dim3(256), 0, st, g, da);
+    // Of more than 16 rows: two workgroups to such a part, with 16 rows each, also where parts are short and both fit the compute units at
+    // once.  Both read the part's keys, the second from L2, and use the matrix and vector units of twice as many compute units; sparse, each walks the
+    // blocks of its own rows only.  Estimate and attention, or dense call, us, 32 rows in eight waves / this: 8 tokens of 64512, 32 / 8 heads, 90.2 / 84.4, of
+    // 30000 51.3 / 47.1, of 4000 (four waves) 40.8 / 38.2, of 90000, 8 / 2, 65.6 / 57.7; dense, 4 tokens of 131072, 28 / 4 90.4 / 83.8, 64 / 8 193.5 / 181.7, eight
+    // sequences of 5000, 28 / 4, 28.1 / 26.1 (31 with the two on different XCDs).  (The values of the next keys requested with these, which one tile of rows has registers
+    // for: 86.2 instead of 83.7, one token of 128K 97.3 instead of 95.9.)
+    da.halves = R > 16 && (eight || 2ll * a.nsplit * g.batch * g.Hkv <= 256) ? 2 : 1;
+    const unsigned parts = (unsigned)a.nsplit;
+    const dim3 grid = da.halves == 2 ? dim3(2 * parts * (unsigned)g.Hkv * (unsigned)g.batch) : dim3(parts, (unsigned)g.Hkv, (unsigned)g.batch);
+    if (R > 16 && da.halves == 1) hipLaunchKernelGGL((k_attn_decode<2, 4>), grid, dim3(256), 0, st, g, da);
+    else if (eight) hipLaunchKernelGGL((k_attn_decode<1, 8>), grid, dim3(512), 0, st, g, da);
+    else hipLaunchKernelGGL((k_attn_decode<1, 4>), grid, dim3(256), 0, st, g, da);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const long long nrows = (long long)g.batch * g.Hq * T;
