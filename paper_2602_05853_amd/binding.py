@@ -7,7 +7,6 @@ module raises.
 from __future__ import annotations
 
 import ctypes as C
-import math
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -129,18 +128,21 @@ def _dtype_code(t: torch.Tensor) -> int:
 def make_shape(Q: torch.Tensor, K: torch.Tensor) -> rr_shape:
     """Q [batch, Hq, Lq, d], K [batch, Hkv, L, d] (any strides with the last dimension contiguous).
     Lq < L is chunked prefill: Q holds the last Lq positions of the L-token context."""
-    if Q.dim() != 4 or K.dim() != 4 or Q.stride(3) != 1 or K.stride(3) != 1:
+    q, k = Q.stride(), K.stride()
+    if len(q) != 4 or len(k) != 4 or q[3] != 1 or k[3] != 1:
         raise RRError(RR_ERR_SHAPE)
     b, Hq, Lq, d = Q.shape
-    L = K.shape[2]
-    if K.shape[0] != b or K.shape[3] != d or Lq > L:
+    kb, Hkv, L, kd = K.shape
+    if kb != b or kd != d or Lq > L:
         raise RRError(RR_ERR_SHAPE)
-    return rr_shape(b, L, Hq, K.shape[1], d, _dtype_code(Q),
-                    Q.stride(0), Q.stride(1), Q.stride(2), K.stride(0), K.stride(1), K.stride(2), Lq)
+    return rr_shape(b, L, Hq, Hkv, d, _dtype_code(Q), q[0], q[1], q[2], k[0], k[1], k[2], Lq)
 
 
 def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
-    return (stream or torch.cuda.current_stream()).cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # the handle of torch.cuda.current_stream(), without an object for it (2.9 -> 0.6 us)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 @dataclass
@@ -170,36 +172,47 @@ class BlockMask:
         rows = number of query blocks (Lq / B), Nb by default."""
         Nq = Nb if rows is None else rows
         i32, f32, u8 = torch.int32, torch.float32, torch.uint8
-        want = {"row_count": ((batch, Hq, Nq), i32), "row_list": ((batch, Hq, Nq, Nb), i32)}
+        n_rows = batch * Hq * Nq
+        n = n_rows * Nb
+        G = Hq // Hkv if Hkv else 0
+        n_order = batch * Hkv * G * Nq if Hkv else 0
+        queue = RR_QUEUE_WORDS if Hkv else 0
+        per_row, per_block, of_rows, of_order = (batch, Hq, Nq), (batch, Hq, Nq, Nb), (Hq * Nq, Nq, 1), (batch, Hkv, G * Nq)
+        out = BlockMask(B, Nb, None, None)
+        if 4 * (n_rows + n + (n if block_mass else 0) + n_order + queue) + (n if dense else 0) > _ONE_BUFFER_BYTES:
+            out.row_count = torch.zeros(per_row, dtype=i32, device=device)
+            out.row_list = torch.zeros(per_block, dtype=i32, device=device)
+            if dense:
+                out.dense = torch.zeros(per_block, dtype=u8, device=device)
+            if block_mass:
+                out.block_mass = torch.zeros(per_block, dtype=f32, device=device)
+            if Hkv:
+                out.row_order = torch.zeros(of_order, dtype=i32, device=device)
+                out.queue = torch.zeros((queue,), dtype=i32, device=device)
+            return out
+        # one cleared buffer, every array at a multiple of 256 bytes (64 words) in it
+        of_blocks = (Hq * Nq * Nb, Nq * Nb, Nb, 1)
+        at_list = (n_rows + 63) & ~63
+        at_dense = at_list + ((n + 63) & ~63)
+        at_mass = at_dense + ((n + 255) // 256 * 64 if dense else 0)
+        at_order = at_mass + ((n + 63) & ~63 if block_mass else 0)
+        at_queue = at_order + ((n_order + 63) & ~63)
+        buf = torch.zeros(at_queue + queue, dtype=i32, device=device)
+        out.row_count = buf.as_strided(per_row, of_rows, 0)
+        out.row_list = buf.as_strided(per_block, of_blocks, at_list)
         if dense:
-            want["dense"] = ((batch, Hq, Nq, Nb), u8)
+            out.dense = buf.view(u8).as_strided(per_block, of_blocks, 4 * at_dense)
         if block_mass:
-            want["block_mass"] = ((batch, Hq, Nq, Nb), f32)
+            out.block_mass = buf.view(f32).as_strided(per_block, of_blocks, at_mass)
         if Hkv:
-            want["row_order"] = ((batch, Hkv, (Hq // Hkv) * Nq), i32)
-            want["queue"] = ((RR_QUEUE_WORDS,), i32)
-        size = {k: math.prod(shape) * (1 if dt is u8 else 4) for k, (shape, dt) in want.items()}
-        if sum(size.values()) > _ONE_BUFFER_BYTES:
-            return BlockMask(B=B, Nb=Nb, **{k: torch.zeros(shape, dtype=dt, device=device) for k, (shape, dt) in want.items()})
-        # one cleared buffer, every array at a multiple of 256 bytes in it
-        at, off = {}, 0
-        for k in want:
-            at[k] = off
-            off += (size[k] + 255) // 256 * 256
-        buf = torch.zeros(off // 4, dtype=i32, device=device)
-        views = {i32: buf, u8: buf.view(u8) if dense else None, f32: buf.view(f32) if block_mass else None}
-        out = {}
-        for k, (shape, dt) in want.items():
-            stride, strides = 1, []
-            for n in reversed(shape):
-                strides.append(stride)
-                stride *= n
-            out[k] = views[dt].as_strided(shape, strides[::-1], at[k] // (1 if dt is u8 else 4))
-        return BlockMask(B=B, Nb=Nb, **out)
+            out.row_order = buf.as_strided(of_order, (Hkv * G * Nq, G * Nq, 1), at_order)
+            out.queue = buf.as_strided((queue,), (1,), at_queue)
+        return out
 
 
 # Masks up to this size are views of one buffer: five allocations and fills were 10-20 us of a call that makes its own mask
-# (estimate + sparse, fp32, 1024 tokens 68 -> 56 us; bf16, 8K tokens, 32 heads 273 -> 259).  Larger ones are separate tensors, so that keeping one of them does not keep the others' memory.
+# (estimate + sparse, fp32, 1024 tokens 68 -> 56 us; bf16, 8K tokens, 32 heads 273 -> 259; with offsets worked out in plain statements and the
+# stream by its handle 57.8 -> 43.2).  Larger ones are separate tensors, so that keeping one of them does not keep the others' memory.
 _ONE_BUFFER_BYTES = 4 << 20
 
 
@@ -269,7 +282,7 @@ def rr_sparse_attn(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, mask: Bloc
     if V.stride() != K.stride() or V.shape != K.shape:
         raise RRError(RR_ERR_SHAPE)
     if O is None:
-        O = torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
+        O = _output_like(Q)
     cm = mask.c_struct()
     if workspace is not None:
         _check(lib.rr_sparse_attn_ws(C.byref(shp), Q.data_ptr(), K.data_ptr(), V.data_ptr(), C.byref(cm),
@@ -291,7 +304,7 @@ def rr_dense_attn(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, B: int,
     if V.stride() != K.stride() or V.shape != K.shape:
         raise RRError(RR_ERR_SHAPE)
     if O is None:
-        O = torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
+        O = _output_like(Q)
     if workspace is not None:
         _check(lib.rr_dense_attn_ws(C.byref(shp), Q.data_ptr(), K.data_ptr(), V.data_ptr(), B,
                                     O.data_ptr(), lse.data_ptr() if lse is not None else None,
@@ -302,6 +315,11 @@ def rr_dense_attn(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, B: int,
                              O.data_ptr(), lse.data_ptr() if lse is not None else None,
                              _stream_ptr(stream)))
     return O
+
+
+def _output_like(Q: torch.Tensor) -> torch.Tensor:
+    """Uninitialised, with Q's strides."""
+    return torch.empty_like(Q) if Q.is_contiguous() else torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
 
 
 def _blocks(length: int, B: int) -> int:
@@ -338,7 +356,7 @@ def rr_dense_attn_packed(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, B: i
         raise RRError(RR_ERR_SHAPE)
     _check_seq_first(seq_first, _blocks(shp.L, B), Q.device)
     if O is None:
-        O = torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
+        O = _output_like(Q)
     _check(lib.rr_dense_attn_packed(C.byref(shp), Q.data_ptr(), K.data_ptr(), V.data_ptr(), B, seq_first.data_ptr(),
                                     O.data_ptr(), lse.data_ptr() if lse is not None else None,
                                     _stream_ptr(stream)))
