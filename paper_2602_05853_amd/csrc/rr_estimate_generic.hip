@@ -22,6 +22,8 @@
 #include "rr_common.hpp"
 #include "rr_select.hpp"
 
+#include <type_traits>
+
 namespace rr {
 
 namespace {
@@ -134,9 +136,11 @@ __device__ __forceinline__ float with_lane32(float v, F&& f) {
 // RF: B / S where it is 4, 8, 16 or 32 and kExt is false.  The strides of a key block then sit in whole lanes of a score
 // tile and are reduced where they are: nothing goes through LDS but the state, and the waves need no barrier between
 // their tiles.  RF = 0: any B / S, the scores of a chunk of strides through LDS.
-template <typename T, bool kExt, int RF>
-__global__ void __launch_bounds__(kThreads)
+// W: waves of the workgroup.
+template <typename T, bool kExt, int RF, int W>
+__global__ void __launch_bounds__(64 * W)
 k_estimate_generic(Geom g, EstimateArgs a, EstPlan p, float scale_log2) {
+    constexpr int kThreads = 64 * W;
     extern __shared__ __align__(16) unsigned char lds[];
     const int32_t* const seq_first = kExt ? a.seq_first : nullptr;
     const bool diag_token = kExt && a.diag_token != 0;
@@ -331,7 +335,7 @@ k_estimate_generic(Geom g, EstimateArgs a, EstPlan p, float scale_log2) {
             part += mass;
         }
         part = wave_sum_fixed(part);
-        if (lane == 0) scanbuf[4 * hh + wv] = part;
+        if (lane == 0 && wv < 4) scanbuf[4 * hh + wv] = part;         // (W > 4: up to 256 blocks, nothing behind them)
     }
     __syncthreads();
 
@@ -443,21 +447,33 @@ hipError_t launch_estimate_generic(const Geom& g, int dtype, const EstimateArgs&
         }
     const float scale_log2 = (float)(1.4426950408889634 / ((double)a.S * sqrt((double)g.d)));
     dim3 grid(g.Hq / p.HP, g.Lq / a.B, g.batch);
-    auto launch = [&](auto kernel) -> hipError_t {
+    auto launch = [&](auto kernel, int waves) -> hipError_t {
         hipError_t e = allow_dynamic_lds((const void*)kernel, p.total);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), p.total, st, g, a, p, scale_log2);
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), p.total, st, g, a, p, scale_log2);
         return hipGetLastError();
+    };
+    // Eight waves where the launch has two workgroups to a compute unit at most: what bounds it then is the chain of score tiles of
+    // a wave (11 of the 21 us of the last row's workgroup for 4096 tokens, fp32).  Up to 256 blocks, whose masses the first four waves sum in the
+    // same order.  Estimate and attention, four waves / eight, us, with the workgroups: fp32, 4096 tokens, 8 / 2 heads of 128 (256) 192.2 / 188.7, 2048
+    // (128) 82.8 / 79.9, 3000, 6 / 3 of 80 (282) 73.6 / 70.2; bf16, 6000, 6 / 3 of 96 (282) 93.0 / 89.7, 8000, 8 / 2 of 64 (500) 114.8 / 113.5, 4096, 16 / 4 of
+    // 64 (512) 81.4 / 80.4; not taken: 8153, 16 / 4 of 64 (1024) 180.6 / 185.4; sixteen waves the same as eight.
+    const bool eight = a.Nb <= 256 && (long long)grid.x * grid.y * grid.z <= 512;
+    auto launch_waves = [&](auto type, auto r) -> hipError_t {
+        using T = decltype(type);
+        constexpr int RF = decltype(r)::value;
+        return eight ? launch(k_estimate_generic<T, false, RF, 8>, 8) : launch(k_estimate_generic<T, false, RF, 4>, 4);
     };
     auto launch_type = [&](auto type) -> hipError_t {
         using T = decltype(type);
-        if (ext) return launch(k_estimate_generic<T, true, 0>);
+        using std::integral_constant;
+        if (ext) return launch(k_estimate_generic<T, true, 0, 4>, 4);
         switch (a.R) {
-            case 4: return launch(k_estimate_generic<T, false, 4>);
-            case 8: return launch(k_estimate_generic<T, false, 8>);
-            case 16: return launch(k_estimate_generic<T, false, 16>);
-            case 32: return launch(k_estimate_generic<T, false, 32>);
-            default: return launch(k_estimate_generic<T, false, 0>);
+            case 4: return launch_waves(T{}, integral_constant<int, 4>{});
+            case 8: return launch_waves(T{}, integral_constant<int, 8>{});
+            case 16: return launch_waves(T{}, integral_constant<int, 16>{});
+            case 32: return launch_waves(T{}, integral_constant<int, 32>{});
+            default: return launch(k_estimate_generic<T, false, 0, 4>, 4);
         }
     };
     return dtype == RR_BF16 ? launch_type(bf16_t{}) : launch_type(float{});

@@ -53,3 +53,20 @@ def test_generic_estimate_matches_the_oracle(B, S, d, Hq, Hkv, L, dtype):
     rep = gu.compare_estimate(mask, ref_mask, ref_frac, ref_margin, 0.9)
     # fractions of a row are at most 1 and come from 32-bit logits of magnitude below 4: a few 2^-24 each
     assert rep["failed"] == 0 and rep["mass_max_abs_err"] <= 1e-6, rep
+
+
+# blocks of 32 keys, a batch of more than 512 workgroups (four waves each) and its prompts alone (eight, up to 256 blocks)
+@pytest.mark.parametrize("S,batch,Nb", [(8, 130, 5), (4, 40, 16), (2, 9, 64), (1, 3, 200), (8, 5, 256), (4, 5, 257)])
+def test_workgroups_of_four_and_of_eight_waves(S, batch, Nb):
+    import paper_2602_05853_amd as rr
+    B, d, Hq, Hkv, L = 32, 40, 4, 4, 32 * Nb - 3
+    assert batch * Hq * Nb > 512
+    g = torch.Generator(device="cuda:0").manual_seed(Nb)
+    Q, K = (2.0 * torch.randn(batch, h, L, d, generator=g, device="cuda:0") for h in (Hq, Hkv))
+    print(f"[waves] S {S}: {batch} prompts of {Nb} blocks", flush=True)
+    whole = rr.rr_estimate(Q, K, S, B, 0.8, block_mass=True)
+    for b in (0, batch - 1):
+        one = rr.rr_estimate(Q[b:b + 1], K[b:b + 1], S, B, 0.8, block_mass=True)
+        torch.cuda.synchronize()
+        for name in ("row_count", "dense", "block_mass", "row_order"):
+            assert torch.equal(getattr(one, name)[0], getattr(whole, name)[b]), (name, b)
