@@ -46,6 +46,45 @@ constexpr int kTileBytes = 3 * kPlaneBytes;            // hi, mid, lo
 constexpr int kLdsBytes = 2 * kTileBytes;              // double buffered
 
 // ---- stride sums, split into three bf16 planes: Ksp[p][b][kv][j][c], j < LsCap ----
+// Eight channels of `nkeys` keys from src on, summed in fp32 in the order of the keys and split.  kAtOnce keys requested at once, eight
+// or sixteen (one at a time, a thread's S loads were a chain: 2048 new positions at 128K 11.4 -> 5.0 us, 8K tokens, all 8 KV heads
+// 8.3 -> 6.1, 128K 68 -> 63).
+template <int kAtOnce>
+__device__ __forceinline__ void stride_sum_parts(const Geom& g, const unsigned short* src, int nkeys, u32x4 (&part)[3]) {
+    float acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+    int s = 0;
+    auto take = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        for (; s + N <= nkeys; s += N) {
+            u32x4 v[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) v[u] = *reinterpret_cast<const u32x4*>(src + (s + u) * g.ksl);
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    acc[2 * i] += __uint_as_float(v[u][i] << 16);
+                    acc[2 * i + 1] += __uint_as_float(v[u][i] & 0xFFFF0000u);
+                }
+        }
+    };
+    if constexpr (kAtOnce > 8) take(std::integral_constant<int, kAtOnce>{});
+    take(std::integral_constant<int, 8>{});
+    take(std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float x = acc[2 * i], y = acc[2 * i + 1];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const unsigned lo = f32_to_bf16_bits(x), hi = f32_to_bf16_bits(y);
+            part[p][i] = lo | (hi << 16);
+            x -= __uint_as_float(lo << 16);                // exact: the remainder has fewer bits
+            y -= __uint_as_float(hi << 16);
+        }
+    }
+}
 __global__ void __launch_bounds__(256)
 k_stride_sum_split(Geom g, const unsigned short* __restrict__ K, int S, int Ls, int j0, int LsCap,
                    unsigned short* __restrict__ Ksp) {
@@ -60,55 +99,13 @@ k_stride_sum_split(Geom g, const unsigned short* __restrict__ K, int S, int Ls, 
     r /= span;
     const int kv = (int)(r % g.Hkv);
     const int b = (int)(r / g.Hkv);
-    const unsigned short* src = K + b * g.ksb + kv * g.ksh + (long long)j * S * g.ksl + c * 8;
-    float acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
     // strides that are not complete within the real length do not exist (Sec. 3.1: floor(L/S) of them): zeros
-    const int nkeys = (j + 1) * S <= g.Lr ? S : 0;
-    // eight keys requested at once (one at a time, a thread's S loads were a chain: 2048
-    // new positions at 128K 11.4 -> 5.0 us, 8K tokens, all 8 KV heads 8.3 -> 6.1, 128K 68 -> 63)
-    int s = 0;
-    for (; s + 8 <= nkeys; s += 8) {
-        u32x4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const u32x4*>(src + (s + u) * g.ksl);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                acc[2 * i] += __uint_as_float(v[u][i] << 16);
-                acc[2 * i + 1] += __uint_as_float(v[u][i] & 0xFFFF0000u);
-            }
-    }
-    for (; s < nkeys; ++s) {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(src + s * g.ksl);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc[2 * i] += __uint_as_float(v[i] << 16);
-            acc[2 * i + 1] += __uint_as_float(v[i] & 0xFFFF0000u);
-        }
-    }
+    u32x4 part[3];
+    stride_sum_parts<8>(g, K + b * g.ksb + kv * g.ksh + (long long)j * S * g.ksl + c * 8, (j + 1) * S <= g.Lr ? S : 0, part);
     const long long plane = (long long)g.batch * g.Hkv * LsCap * g.d;
     const long long at = (((long long)(b * g.Hkv + kv) * LsCap + j) * g.d + c * 8);
-    unsigned int part[3][8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        float x = acc[i];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            const unsigned int bits = f32_to_bf16_bits(x);
-            part[p][i] = bits;
-            x -= __uint_as_float(bits << 16);              // exact: the remainder has fewer bits
-        }
-    }
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        u32x4 o;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = part[p][2 * i] | (part[p][2 * i + 1] << 16);
-        *reinterpret_cast<u32x4*>(Ksp + p * plane + at) = o;
-    }
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(Ksp + p * plane + at) = part[p];
 }
 
 // The value lane ^ 32 holds, through the vector ALU (v_permlane32_swap: the upper half of one operand and
@@ -718,13 +715,15 @@ k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
 // wavefront takes 32 key strides and all queries, 32 at a time, and leaves for each query the sum of 2^(score - reference) over
 // each key block and the tile's reference (its largest score).  The second launch, one workgroup to a KV head and one wavefront
 // to a row, brings the references together.  What bounds it: the chain of launches and, in each, of its loads; 8 tokens behind
-// 64512, 32 / 8 heads: 8 + 10 us where the two sweeps, the selection and the row order took 20 + 20 + 9 + 5.
+// 64512, 32 / 8 heads: 8 + 10 us, the sums of the new strides among them, where those, the two sweeps, the selection and the row order took 5 + 20 + 20 + 9 + 5.
 struct StepArgs {
     float* sums;                      // [pair][query][tiles * blocks of a tile]
     float* refs;                      // [pair][query][tiles], log2 units
     int nst, s0;                      // query strides of the step, the first of them
     int tiles;
     int order_shift;
+    int j_new;                        // strides from here on have no sums yet: their wavefronts form and keep them
+    unsigned short* Ksp;
 };
 constexpr int kStepWaves = 4;
 template <int R>
@@ -736,12 +735,39 @@ k_step_scores(Geom g, ScoreArgs a, StepArgs sa) {
     if (jt >= sa.tiles) return;
     const int pr = blockIdx.y, b = pr / g.Hkv, kv = pr - b * g.Hkv, j0 = jt * kTileStrides;
     const long long plane = (long long)g.batch * g.Hkv * a.LsCap * g.d;
-    const unsigned short* kp = a.Ksp + ((long long)pr * a.LsCap + min(j0 + l32, a.Ls - 1)) * g.d + 8 * gsel;
+    __shared__ u32x4 s_new[2][3][kTileStrides][16];                // new strides lie in two tiles at most
+    // (rows that have no sums, or do not exist: one that has)
+    const unsigned short* kp = a.Ksp + ((long long)pr * a.LsCap + min(j0 + l32, min(a.Ls, sa.j_new) - 1)) * g.d + 8 * gsel;
     bf16x8 kf[8][3];
 #pragma unroll
     for (int kc = 0; kc < 8; ++kc)
 #pragma unroll
         for (int p = 0; p < 3; ++p) kf[kc][p] = *reinterpret_cast<const bf16x8*>(kp + p * plane + 16 * kc);
+    const int j_end = min(j0 + kTileStrides, a.Ls);
+    if (j_end > sa.j_new) {
+        // strides without sums: four at a time, 16 lanes to a stride, kept for the calls to come
+        for (int r = max(j0, sa.j_new); r < j_end; r += 4) {
+            const int j = r + (lane >> 4), c = lane & 15;
+            if (j < j_end) {
+                u32x4 part[3];
+                stride_sum_parts<16>(g, a.K + b * g.ksb + kv * g.ksh + (long long)j * a.S * g.ksl + 8 * c, (j + 1) * a.S <= g.Lr ? a.S : 0, part);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    *reinterpret_cast<u32x4*>(sa.Ksp + p * plane + ((long long)pr * a.LsCap + j) * g.d + 8 * c) = part[p];
+                    s_new[jt & 1][p][j - j0][c] = part[p];
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (j0 + l32 >= sa.j_new && j0 + l32 < j_end) {
+#pragma unroll
+            for (int kc = 0; kc < 8; ++kc)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) kf[kc][p] = __builtin_bit_cast(bf16x8, s_new[jt & 1][p][l32][2 * kc + gsel]);
+        }
+    }
     const float NEG_INF = -__builtin_huge_valf();
     const int nq = g.G * sa.nst;
     for (int q0 = 0; q0 < nq; q0 += 32) {
@@ -916,12 +942,29 @@ bool estimate_mfma_is_step(const Geom& g, const EstimateArgs& ea) {
            need <= estimate_mfma_mass_bytes(g, B) + estimate_mfma_stats_bytes(g, S, B);
 }
 
+// k_estimate_rows takes the call.
+// One launch where its workgroups, which fill a compute unit each and do not overlap one's loads with another's products,
+// are less than three to a compute unit.  The whole estimate, us, two sweeps and selection / one launch, with its workgroups:
+// 32 / 8 heads, S = 16: 2048 tokens (64) 33 / 20, 8192 (256) 57 / 33, 16384 (512) 73 / 64; two prompts of 8192 (512) 63 / 48, four
+// (1024) 83 / 86; 64 / 8: 10000 (632) 71 / 63, 12000 (752) 75 / 74, 16384 (1024) 98 / 111; S = 8, 8192 (1024) 90 / 98; S = 32, 16384 (512)
+// 69 / 56; eight prompts of 2048 (1024) 45 / 49.
+bool short_context(const Geom& g, const EstimateArgs& ea) {
+    const int R = ea.B / ea.S, Nbq = g.Lq / ea.B, P = kRowCols / R;
+    const int tiles = (g.L / ea.S + kTileStrides - 1) / kTileStrides;
+    const long long row_wgs = (long long)((Nbq * g.G + P - 1) / P) * g.Hkv * g.batch;
+    return !ea.seq_first && !ea.diag_token && tiles <= kRowTiles && row_wgs <= 700;
+}
+
 hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned short* ksplit, int ls_cap, int ls_valid,
                                 float* mass, float2* stats, hipStream_t st) {
     const int S = ea.S, B = ea.B, Ls = g.L / S, R = B / S, Nb = g.L / B, Nbq = g.Lq / B;
     if (ls_cap < Ls || ls_valid < 0) return hipErrorInvalidValue;
     const int j0 = ls_valid < Ls ? ls_valid : Ls;
-    if (j0 < Ls) {
+    // A short step's few new strides are left to the wavefronts that score them: a launch of 5 us less.  Estimate and attention, us: 8 tokens
+    // of 64512, 32 / 8 heads, 85.2 -> 81.2, of 30000 47.8 -> 43.4, 1 of 50000 66.8 -> 62.5, 100 of 65000 level.
+    const bool step = !short_context(g, ea) && estimate_mfma_is_step(g, ea);
+    const bool sums_in_scores = step && j0 > 0 && Ls - j0 <= kTileStrides && g.Lr / S > g.q0 / S;
+    if (j0 < Ls && !sums_in_scores) {
         const long long total = (long long)g.batch * g.Hkv * (Ls - j0) * (g.d / 8);
         hipLaunchKernelGGL(k_stride_sum_split, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, g,
                            (const unsigned short*)ea.K, S, Ls, j0, ls_cap, ksplit);
@@ -946,12 +989,7 @@ hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned 
     const bool ext = ea.seq_first != nullptr || ea.diag_token != 0;
     const int tiles = (Ls + kTileStrides - 1) / kTileStrides, P = kRowCols / R;
     const long long row_wgs = (long long)((Nbq * g.G + P - 1) / P) * g.Hkv * g.batch;
-    // One launch where its workgroups, which fill a compute unit each and do not overlap one's loads with another's products,
-    // are less than three to a compute unit.  The whole estimate, us, two sweeps and selection / one launch, with its workgroups:
-    // 32 / 8 heads, S = 16: 2048 tokens (64) 33 / 20, 8192 (256) 57 / 33, 16384 (512) 73 / 64; two prompts of 8192 (512) 63 / 48, four
-    // (1024) 83 / 86; 64 / 8: 10000 (632) 71 / 63, 12000 (752) 75 / 74, 16384 (1024) 98 / 111; S = 8, 8192 (1024) 90 / 98; S = 32, 16384 (512)
-    // 69 / 56; eight prompts of 2048 (1024) 45 / 49.
-    if (!ext && tiles <= kRowTiles && row_wgs <= 700) {
+    if (short_context(g, ea)) {
         a.nsplit = 1;
         a.mode = 0;
         a.stats = nullptr;
@@ -974,7 +1012,7 @@ hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned 
             default: return hipErrorInvalidValue;
         }
     }
-    if (estimate_mfma_is_step(g, ea)) {
+    if (step) {
         a.nsplit = 1;
         a.mode = 0;
         a.stats = nullptr;
@@ -985,6 +1023,8 @@ hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned 
         sa.sums = mass;
         sa.refs = mass + (size_t)g.batch * g.Hq * sa.nst * (tiles * (kTileStrides / R));
         sa.order_shift = row_order_shift(Nb);
+        sa.j_new = sums_in_scores ? j0 : Ls;
+        sa.Ksp = ksplit;
         auto launch = [&](auto r) -> hipError_t {
             constexpr int RV = decltype(r)::value;
             if (sa.nst > 0) {

@@ -133,3 +133,36 @@ def test_row_with_a_query_that_is_not_finite_keeps_every_block(Hq, Hkv, L, Lq, S
     others[0, h, r] = False
     for a, b in ((mask.dense, clean.dense), (mask.row_count, clean.row_count), (mask.block_mass, clean.block_mass)):
         assert torch.equal(a[others], b[others])
+
+
+# new strides of a step, formed where they are scored up to 32 of them: within a tile of 32 strides, over two, from its first or last row on; a
+# context that ends inside a stride; S of one batch of keys, of two, and of fewer than a batch
+@pytest.mark.parametrize("S", [4, 8, 16, 32])
+@pytest.mark.parametrize("first,new,more", [(0, 1, 0), (31, 1, 2), (31, 2, 0), (17, 31, 1), (1, 32, 0), (0, 32, 3), (20, 33, 0)])
+def test_new_strides_of_a_step(S, first, new, more):
+    """The stride sums are known up to stride `first` of a tile; the step brings `new` more and `more` tokens of the next one.  As the call that forms all
+    sums itself, and what it left is what the next call takes."""
+    import paper_2602_05853_amd as rr
+    Hq, Hkv, B = 4, 2, 128
+    known = (34 * 32 + first) * S
+    L = known + new * S + min(more, S - 1)
+    Lq = min(L - known, 2 * S + 1)
+    cap = -(-(L + B) // 4096) * 4096
+    g = torch.Generator(device="cuda:0").manual_seed(known + new)
+    Q = torch.randn(1, Hq, Lq, 128, generator=g, device="cuda:0").bfloat16()
+    K = torch.randn(1, Hkv, L + 1, 128, generator=g, device="cuda:0").bfloat16()
+    room = K.new_empty((1, Hkv, cap, 128), device="meta")
+    ws = torch.full((rr.rr_workspace_bytes(Q.new_empty((1, Hq, L, 128), device="meta"), room, S, B),), 0xFF, dtype=torch.uint8, device="cuda:0")
+    print(f"[new strides] S {S}: {new} behind {known // S}, {Lq} of {L}", flush=True)
+    rr.rr_estimate(Q[:, :, :1], K[:, :, :known], S, B, 0.9, flags=0, workspace=ws, ksum_capacity=cap)
+    for end in (L, L + 1):
+        queries, keys = Q if end == L else Q[:, :, :1], K[:, :, :end]
+        kept = rr.rr_estimate(queries, keys, S, B, 0.9, flags=0, workspace=ws, block_mass=True, ksum_capacity=cap, ksum_valid=known if end == L else L)
+        plain = rr.rr_estimate(queries, keys, S, B, 0.9, flags=0, block_mass=True)
+        torch.cuda.synchronize()
+        for name in ("row_count", "dense", "block_mass", "row_order"):
+            assert torch.equal(getattr(kept, name), getattr(plain, name)), (name, end)
+    sums = ws[:3 * Hkv * (cap // S) * 128 * 2].view(torch.bfloat16).view(3, Hkv, cap // S, 128)[:, :, :L // S].double().sum(0)
+    ref = K[0, :, :L // S * S].double().view(Hkv, L // S, S, 128).sum(2)
+    # three terms of 8 bits hold the 32-bit sum of up to 32 values exactly: its rounding
+    assert ((sums - ref).abs() <= 2.0 ** -20 * K[0].double().abs().max() * S).all()
