@@ -524,22 +524,26 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
 // instead of twice, the softmax needs no second sweep (the waves exchange maxima and sums through LDS), nothing is
 // left for another launch, and the workgroup selects its own 64 / R rows, whose masses meet in LDS.  A workgroup takes
 // 64 / R consecutive (query block, head) pairs of a KV head, so the heads of a query block share the stride sums it
-// reads, which go from L2 straight to the operand registers (every wave has tiles of its own: nothing to share in LDS).
-// What bounds it: the chain launch, queries, stride sums, softmax, selection of one row, each waiting for the one before; 8192
-// tokens, 32 / 8 heads: 22-23 us on one set of inputs again and again (26 among other launches) where two sweeps and the selection
-// took 21 + 19 + 7.
+// reads; every wave has tiles of its own, copied through LDS of its own (see there).
+// What bounds it: the chain launch, queries, stride sums, softmax, selection of one row, each waiting for the one before.  Estimate and attention, us,
+// fragments straight from L2 to registers / through LDS: 32 / 8 heads, 2048 tokens 67.9 / 65.3, 8192 231.0 / 223.8, 16384 694.7 / 683.0; 8 / 2, 12000 195.9 / 187.0; 8
+// tokens of 12000 54.0 / 46.1, 700 of 16000 184.5 / 172.7; launches of two workgroups to a compute unit before, which LDS for one now excludes: three prompts of 3000, 64 / 8
+// heads, 293.3 / 294.0, four of 4000, 32 / 8, 324.3 / 323.7.
 // A score's exponent is one fma, score scale - round(largest score scale): that rounding is a factor that all strides of a query share, and it
 // goes with the sum.  Not where it is itself too large to be an exponent: beyond this reference (log2 units, rounded to at most
 // 1) the largest score is subtracted first, which leaves its own stride exactly 2^0.  (Without, one key of 1e12 made queries drop out of
 // their row, or the row have no estimate.  17 layers and steps with the test for it: 0.986 to 1.015 of the time without, twice without 0.992 to 1.008.)
 constexpr float kFarReference = 16777216.f;
 constexpr int kRowWaves = 8, kRowCols = 64;
+constexpr int kQuarterBytes = 3 * kTileStrides * 64;              // 32 channels of a tile's three planes
+constexpr int kRowStageBytes = kRowWaves * 2 * kQuarterBytes;
 constexpr int kRowTiles = 4 * kRowWaves;                           // the most tiles of key strides it takes
 template <int R, int TPW>
 __global__ void __launch_bounds__(64 * kRowWaves, 2)
 k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
     constexpr int P = kRowCols / R;                                // (query block, head) pairs of a workgroup
     constexpr int kMaxNb = kTileStrides * kRowWaves * TPW / R;     // key blocks its tiles cover
+    extern __shared__ __align__(16) unsigned char lds_stage[];
     __shared__ float s_red[2][kRowWaves][kRowCols];
     __shared__ float s_mass[P][kMaxNb];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -582,29 +586,76 @@ k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
     // 71 us with two sweeps, 84 with the scores here, 51 without; 1 of 16007, S = 16, 47, 58, 39.
     if (!__any(qi_stride[0] >= 0 || qi_stride[1] >= 0)) ntiles = 0;
     const long long plane = (long long)g.batch * g.Hkv * a.LsCap * g.d;
-    const unsigned short* kbase = a.Ksp + ((long long)(b * g.Hkv + kv) * a.LsCap) * g.d + 8 * gsel;
+    const unsigned short* kbase = a.Ksp + ((long long)(b * g.Hkv + kv) * a.LsCap) * g.d;
     const float NEG_INF = -__builtin_huge_valf();
 
+    // A wave's tiles, a quarter (32 channels, 3 planes, 6 KB) at a time through LDS of its own, the next quarter on its way meanwhile.
+    // The rows of a tile lie 256 bytes apart, so fragments loaded straight to registers took 32 bytes of a line with each of its visits
+    // (one a cycle and compute unit): 12 us for the longest workgroup at 8192 tokens; a copy takes 64.  LDS rows of 64 bytes, chunk c of row r
+    // in place c ^ (r / 4 mod 4): conflict-free reads.  (Waves read what they copied themselves: no barrier.)
+    const unsigned stage = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_stage + (unsigned)(w * 2 * kQuarterBytes);
+    const int copy_row = lane >> 2, copy_chunk = (lane & 3) ^ ((lane >> 4) & 3);
+    auto issue_quarter = [&](int i, int q) {
+        const int j0 = (w + kRowWaves * i) * kTileStrides, lim = a.Ls - 1 - j0;   // rows past the last stride: a copy of it, masked
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const unsigned long long srcv = (unsigned long long)(kbase + p * plane + (long long)j0 * g.d + 32 * q);
+            const unsigned src_hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(srcv >> 32));
+            const unsigned src_lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)srcv);
+            const unsigned short* src =
+                reinterpret_cast<const unsigned short*>(((unsigned long long)src_hi << 32) | (unsigned long long)src_lo);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const unsigned off = (unsigned)(min(copy_row + 16 * half, lim) * 256 + copy_chunk * 16);
+                const unsigned dst = stage + (unsigned)((q & 1) * kQuarterBytes + p * 2048 + half * 1024);
+                asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+                             :: "v"(off), "s"(src), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
+            }
+        }
+    };
+    typedef __attribute__((address_space(3))) bf16x8 lds_frag_t;
+    auto fragment = [&](int q, int p, int k) {
+        return *(const lds_frag_t*)(uintptr_t)(stage + (unsigned)((q & 1) * kQuarterBytes + p * 2048 + l32 * 64 + (((2 * k + gsel) ^ ((l32 >> 2) & 3)) << 4)));
+    };
+    // the queries are complete in their registers here: the waits below count the copies alone
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int kc = 0; kc < 8; ++kc) asm volatile("" : "+v"(qf[nt][kc]));
     f32x16 s[TPW][2];
     float mx[2] = {NEG_INF, NEG_INF};
+    if (w < ntiles) issue_quarter(0, 0);
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
         const int jt = w + kRowWaves * i, j0 = jt * kTileStrides;
         if (jt < ntiles) {
-            const unsigned short* kp = kbase + (long long)min(j0 + l32, a.Ls - 1) * g.d;
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) s[i][nt][e] = 0.f;
 #pragma unroll
-            for (int kc = 0; kc < 8; ++kc)
-#pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kp + p * plane + 16 * kc);
-#pragma unroll
-                    for (int nt = 0; nt < 2; ++nt)
-                        s[i][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[nt][kc], s[i][nt], 0, 0, 0);
+            for (int q = 0; q < 4; ++q) {
+                // the buffer's fragments of two quarters ago have been read
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if (q < 3 || (i + 1 < TPW && jt + kRowWaves < ntiles)) {
+                    issue_quarter(q < 3 ? i : i + 1, (q + 1) & 3);
+                    asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+                } else {
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 }
+                bf16x8 kf[2][3];
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) kf[k][p] = fragment(q, p, k);
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+#pragma unroll
+                        for (int nt = 0; nt < 2; ++nt)
+                            s[i][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[k][p], qf[nt][2 * q + k], s[i][nt], 0, 0, 0);
+            }
             const bool need_mask = j0 + kTileStrides - 1 > sure;
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
@@ -944,7 +995,7 @@ bool estimate_mfma_is_step(const Geom& g, const EstimateArgs& ea) {
 
 // k_estimate_rows takes the call.
 // One launch where its workgroups, which fill a compute unit each and do not overlap one's loads with another's products,
-// are less than three to a compute unit.  The whole estimate, us, two sweeps and selection / one launch, with its workgroups:
+// are less than three to a compute unit.  The whole estimate, us, two sweeps and selection / one launch (before its tiles went through LDS), with its workgroups:
 // 32 / 8 heads, S = 16: 2048 tokens (64) 33 / 20, 8192 (256) 57 / 33, 16384 (512) 73 / 64; two prompts of 8192 (512) 63 / 48, four
 // (1024) 83 / 86; 64 / 8: 10000 (632) 71 / 63, 12000 (752) 75 / 74, 16384 (1024) 98 / 111; S = 8, 8192 (1024) 90 / 98; S = 32, 16384 (512)
 // 69 / 56; eight prompts of 2048 (1024) 45 / 49.
@@ -995,7 +1046,9 @@ hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned 
         a.stats = nullptr;
         const dim3 grid((unsigned)row_wgs);
         auto launch = [&](auto kernel) -> hipError_t {
-            hipLaunchKernelGGL(kernel, grid, dim3(64 * kRowWaves), 0, st, g, a, ea);
+            const hipError_t e = allow_dynamic_lds((const void*)kernel, kRowStageBytes);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(kernel, grid, dim3(64 * kRowWaves), kRowStageBytes, st, g, a, ea);
             return hipGetLastError();
         };
         auto pick = [&](auto r) -> hipError_t {
