@@ -22,10 +22,10 @@ namespace rr {
 
 namespace {
 
-constexpr int kSortThreads = 1024;
 constexpr int kCountShift = 3;      // rows whose counts differ by less than 8 blocks form one class
 constexpr int kMaxClasses = 4096;   // (beyond 32K blocks classes are wider)
 
+template <int kSortThreads>                         // at least RR_QUEUE_WORDS
 __global__ void __launch_bounds__(kSortThreads)
 k_row_order(Geom g, int Nb, int shift, const int32_t* __restrict__ row_count, int32_t* __restrict__ row_order,
             int32_t* __restrict__ queue) {
@@ -142,7 +142,16 @@ hipError_t launch_row_order(const Geom& g, int Nb, const int32_t* row_count, int
                             hipStream_t st) {
     const int N = g.G * (g.Lq / (g.L / Nb));
     if (N > kMaxOrderedRows) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_row_order, dim3(g.Hkv, g.batch), dim3(kSortThreads), 0, st, g, Nb, row_order_shift(Nb), row_count, row_order, queue);
+    const dim3 grid(g.Hkv, g.batch);
+    const int shift = row_order_shift(Nb);
+    // No more wavefronts than rows fill: they wait for each other at every barrier.  Estimate and attention with 1024 threads / these, us: fp32, 4096
+    // tokens, 8 / 2 heads (256 rows) 188.9 / 187.0, bf16, 2048, 32 / 8 (64) 65.5 / 64.8, 8153, 16 / 4 of 64 (512) 181.3 / 180.0.
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, g, Nb, shift, row_count, row_order, queue);
+    };
+    if (N <= 256) launch(k_row_order<256>, 256);
+    else if (N <= 512) launch(k_row_order<512>, 512);
+    else launch(k_row_order<1024>, 1024);
     return hipGetLastError();
 }
 

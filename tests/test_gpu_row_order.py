@@ -41,3 +41,10 @@ def test_row_order_follows_its_rule(G, Nb, equal):
                 rank = base + 8 * (w % G) + w // G
             want[rank] = hl * Nb + m
         assert np.array_equal(got[kv], want)
+
+
+@pytest.mark.parametrize("equal", [False, True])
+@pytest.mark.parametrize("G,Nb", [(1, 255), (1, 256), (1, 257), (8, 64), (1, 513), (2, 512)])
+def test_row_order_at_the_largest_sizes_of_its_workgroups(G, Nb, equal):
+    """256, 512 and 1024 threads."""
+    test_row_order_follows_its_rule(G, Nb, equal)
