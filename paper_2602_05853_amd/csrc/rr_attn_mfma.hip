@@ -60,6 +60,7 @@
 // tile: it is read by the diagonal pass alone, through copies whose source rows stop at the last real
 // position; query rows past the length work on a copy of the last real row and are not stored.
 #include "rr_common.hpp"
+#include "rr_attn_rows.hpp"
 #include "rr_select.hpp"
 
 #include <algorithm>
@@ -93,12 +94,12 @@ __device__ __forceinline__ int v_swz(int key, int chunk) { return key * 256 + ((
 
 // workgroup id -> (batch, head, query block).  Workgroups are dealt to the 8 XCDs round-robin
 // (id % 8 picks the XCD) and start in id order.
-// Dense calls (by_group) where the groups divide into the XCDs or the XCDs into the groups: every XCD takes
-// KV groups of its own, so that the rows that run on it, which walk their blocks in the same order, find each other's tiles in its
-// L2.  All groups cost the same there.  Against sets of groups over all XCDs (below; the order before where Nb is a multiple of 8, elsewhere
-// level with what was), dense, us: 32 / 8 heads, 4096 tokens 157 / 147, 8192 533 / 512, 16384 2002 / 1946, 32768 7817 / 7506, 98304 67445 / 67180;
-// four prompts of 16384 8014 / 7575, sixteen of 2048 686 / 623 (group after group; rank by rank of all an XCD's groups 7704, 635); 28 / 4
-// heads, 16384 1709 / 1680.
+// Dense calls (by_group) where the groups divide into the XCDs or the XCDs into the groups: every XCD takes KV groups of its
+// own (rr_attn_rows.hpp), so that the rows that run on it, which walk their blocks in the same order, find each other's tiles in
+// its L2.  All groups cost the same there; XCDs that share a group take its rows in turn.  Against sets of groups over all XCDs
+// (below; the order before where Nb is a multiple of 8, elsewhere level with what was), dense, us: 32 / 8 heads, 4096 tokens
+// 157 / 147, 8192 533 / 512, 16384 2002 / 1946, 32768 7817 / 7506, 98304 67445 / 67180; four prompts of 16384 8014 / 7575, sixteen of
+// 2048 686 / 623 (group after group; rank by rank of all an XCD's groups 7704, 635).
 // Elsewhere, when Nb is a multiple of 8 the KV groups are
 // taken `gi` at a time GPU-wide, so that the keys and values in use stay cache resident and L2 misses of
 // the sparse walk stay off HBM (gi = 1 at 128K tokens, where one group's K and V are 64 MB);
@@ -140,12 +141,8 @@ __device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, con
         return true;
     }
     if (by_group && (NG & 7) == 0) {
-        // XCD x: groups x, x + 8, .. one after the other, rows by descending m, the heads of a query block together
-        const int x = bid & 7, s = bid >> 3, per = Nb * G;
-        grp = x + 8 * (s / per);
-        const int r = s % per;
-        mr = r / G;
-        hl = r - mr * G;
+        const RowPlace p = row_of_whole_groups(bid, G, Nb);
+        grp = p.grp; hl = p.hl; mr = p.mr;
     } else if ((Nb & 7) == 0 && !by_group) {
         // one KV group after the other GPU-wide (its keys and values then fit the memory-side
         // cache); XCD x takes the rows with rank = x mod 8, the heads of a group back to back
@@ -165,11 +162,8 @@ __device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, con
         grp = x + 8 * (r / G);
         hl = r % G;
     } else if (8 % NG == 0) {
-        const int k = 8 / NG, x = bid & 7, s = bid >> 3;
-        grp = x % NG;
-        const int q = s / G;
-        hl = s - q * G;
-        mr = q * k + x / NG;
+        const RowPlace p = row_of_shared_group(bid, NG, G, Nb);
+        grp = p.grp; hl = p.hl; mr = p.mr;
     } else {
         mr = bid / (NG * G);
         const int r = bid - mr * NG * G;

@@ -1,0 +1,68 @@
+"""Dense launches whose XCDs take KV groups of their own (csrc/rr_attn_rows.hpp), on the host: every row is taken once, no XCD takes groups
+of another, and none has more work than its share but for what the last rows leave.  A row's work is its number of key blocks."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2602_05853_amd", "csrc")
+
+PROGRAM = r'''
+#include <cstdio>
+#include <cstdlib>
+#include "rr_attn_rows.hpp"
+int main(int argc, char** argv) {
+    for (int a = 1; a + 2 < argc; a += 3) {
+        const int NG = atoi(argv[a]), G = atoi(argv[a + 1]), Nb = atoi(argv[a + 2]);
+        const int k = NG < 8 ? 8 / NG : 1;
+        const int grid = NG < 8 ? 8 * G * ((Nb + k - 1) / k) : NG * G * Nb;
+        for (int bid = 0; bid < grid; ++bid) {
+            const rr::RowPlace p = NG < 8 ? rr::row_of_shared_group(bid, NG, G, Nb) : rr::row_of_whole_groups(bid, G, Nb);
+            printf("%d %d %d\n", p.grp, p.hl, p.mr);
+        }
+        printf("end\n");
+    }
+}
+'''
+
+SHAPES = [(NG, G, Nb) for NG in (1, 2, 4, 8, 16) for G in (1, 4, 7, 8, 32) for Nb in (1, 7, 8, 16, 17, 24, 32, 64)]
+
+
+@pytest.fixture(scope="module")
+def rows(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no C++ compiler")
+    d = tmp_path_factory.mktemp("rows")
+    (d / "rows.cpp").write_text(PROGRAM)
+    subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / "rows.cpp"), "-o", str(d / "rows")], check=True)
+    out = subprocess.run([str(d / "rows")] + [str(v) for s in SHAPES for v in s], check=True, capture_output=True, text=True).stdout
+    return {s: [tuple(map(int, line.split())) for line in part.strip().split("\n")]
+            for s, part in zip(SHAPES, out.split("end\n"))}
+
+
+@pytest.mark.parametrize("NG,G,Nb", SHAPES)
+def test_rows_are_taken_once_and_shared_evenly(rows, NG, G, Nb):
+    work, seen, groups = [0] * 8, set(), [set() for _ in range(8)]
+    for bid, (grp, hl, mr) in enumerate(rows[NG, G, Nb]):
+        if mr >= Nb:                                   # the last query blocks of a number that the XCDs do not divide
+            continue
+        assert 0 <= grp < NG and 0 <= hl < G and mr >= 0
+        assert (grp, hl, mr) not in seen
+        seen.add((grp, hl, mr))
+        work[bid & 7] += Nb - mr
+        groups[bid & 7].add(grp)
+    assert len(seen) == NG * G * Nb
+    for x in range(8):
+        assert groups[x] <= {x % NG} if NG < 8 else groups[x] == set(range(x, NG, 8))
+    if NG >= 8:
+        assert max(work) == min(work)
+        return
+    # k = 8 / NG XCDs share a group.  A turn is k query blocks of a head that lie side by side, one for each of them.  The turns of two
+    # levels of query blocks are taken forth and back and leave no difference; in those of a last odd level an XCD's place moves on by one from head to
+    # head, so that k turns leave none and j < k of them j (k - j) blocks at most; likewise in a level that k does not fill.
+    k = 8 // NG
+    odd, cut = G * (Nb // k % 2), G if Nb % k else 0
+    bound = sum((n % k) * (k - n % k) for n in (odd, cut))
+    assert max(work) - min(work) <= bound, work
