@@ -141,8 +141,9 @@ def make_shape(Q: torch.Tensor, K: torch.Tensor) -> rr_shape:
 def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
     if stream is not None:
         return stream.cuda_stream
-    # the handle of torch.cuda.current_stream(), without an object for it (2.9 -> 0.6 us)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the handle of torch.cuda.current_stream(), without an object for it where this torch hands it out (2.9 -> 0.6 us)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw is not None else torch.cuda.current_stream().cuda_stream
 
 
 @dataclass
