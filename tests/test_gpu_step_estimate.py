@@ -135,34 +135,64 @@ def test_row_with_a_query_that_is_not_finite_keeps_every_block(Hq, Hkv, L, Lq, S
         assert torch.equal(a[others], b[others])
 
 
-# new strides of a step, formed where they are scored up to 32 of them: within a tile of 32 strides, over two, from its first or last row on; a
-# context that ends inside a stride; S of one batch of keys, of two, and of fewer than a batch
-@pytest.mark.parametrize("S", [4, 8, 16, 32])
-@pytest.mark.parametrize("first,new,more", [(0, 1, 0), (31, 1, 2), (31, 2, 0), (17, 31, 1), (1, 32, 0), (0, 32, 3), (20, 33, 0)])
-def test_new_strides_of_a_step(S, first, new, more):
-    """The stride sums are known up to stride `first` of a tile; the step brings `new` more and `more` tokens of the next one.  As the call that forms all
-    sums itself, and what it left is what the next call takes."""
+def _new_strides(S, known, L, Lq):
+    """The stride sums of the first `known` positions are in the workspace, the step's last query is position L - 1.  As the call that forms
+    all sums itself, and what it left is what the next call takes."""
     import paper_2602_05853_amd as rr
-    Hq, Hkv, B = 4, 2, 128
-    known = (34 * 32 + first) * S
-    L = known + new * S + min(more, S - 1)
-    Lq = min(L - known, 2 * S + 1)
+    Hq, Hkv = 4, 2
     cap = -(-(L + B) // 4096) * 4096
-    g = torch.Generator(device="cuda:0").manual_seed(known + new)
+    g = torch.Generator(device="cuda:0").manual_seed(known + L)
     Q = torch.randn(1, Hq, Lq, 128, generator=g, device="cuda:0").bfloat16()
     K = torch.randn(1, Hkv, L + 1, 128, generator=g, device="cuda:0").bfloat16()
     room = K.new_empty((1, Hkv, cap, 128), device="meta")
     ws = torch.full((rr.rr_workspace_bytes(Q.new_empty((1, Hq, L, 128), device="meta"), room, S, B),), 0xFF, dtype=torch.uint8, device="cuda:0")
-    print(f"[new strides] S {S}: {new} behind {known // S}, {Lq} of {L}", flush=True)
+    print(f"[new strides] S {S}: {L // S - known // S} behind {known // S}, {Lq} of {L}", flush=True)
     rr.rr_estimate(Q[:, :, :1], K[:, :, :known], S, B, 0.9, flags=0, workspace=ws, ksum_capacity=cap)
+    one_sweep = []
     for end in (L, L + 1):
         queries, keys = Q if end == L else Q[:, :, :1], K[:, :, :end]
         kept = rr.rr_estimate(queries, keys, S, B, 0.9, flags=0, workspace=ws, block_mass=True, ksum_capacity=cap, ksum_valid=known if end == L else L)
-        plain = rr.rr_estimate(queries, keys, S, B, 0.9, flags=0, block_mass=True)
+        own, plain = _dirty(queries, keys, S, 1, Hq, Hkv, end, queries.shape[2])
+        rr.rr_estimate(queries, keys, S, B, 0.9, flags=0, out=plain, workspace=own)
         torch.cuda.synchronize()
+        one_sweep.append(_one_sweep(own))
         for name in ("row_count", "dense", "block_mass", "row_order"):
             assert torch.equal(getattr(kept, name), getattr(plain, name)), (name, end)
     sums = ws[:3 * Hkv * (cap // S) * 128 * 2].view(torch.bfloat16).view(3, Hkv, cap // S, 128)[:, :, :L // S].double().sum(0)
     ref = K[0, :, :L // S * S].double().view(Hkv, L // S, S, 128).sum(2)
     # three terms of 8 bits hold the 32-bit sum of up to 32 values exactly: its rounding
     assert ((sums - ref).abs() <= 2.0 ** -20 * K[0].double().abs().max() * S).all()
+    return one_sweep
+
+
+# new strides of a step, wherever they lie in a tile of 32 strides and in their block; a context that ends inside a stride.  (Most of
+# them have more than 32 strides to the end of their block and are summed by a launch of their own.)
+@pytest.mark.parametrize("S", [4, 8, 16, 32])
+@pytest.mark.parametrize("first,new,more", [(0, 1, 0), (31, 1, 2), (31, 2, 0), (17, 31, 1), (1, 32, 0), (0, 32, 3), (20, 33, 0)])
+def test_new_strides_of_a_step(S, first, new, more):
+    """The stride sums are known up to stride `first` of a tile; the step brings `new` more and `more` tokens of the next one."""
+    known = (34 * 32 + first) * S
+    L = known + new * S + min(more, S - 1)
+    _new_strides(S, known, L, min(L - known, 2 * S + 1))
+
+
+# New strides that are formed where they are scored: `to_end` strides without sums up to the end of the last block, at most 32, of which
+# `new` are complete; and one more than 32, which a launch of its own sums.  `blocks` puts that end at a tile's end or inside one, so that the
+# strides lie in one tile or two (`tiles`: how many of them in each); up to eight turns of four strides to a wavefront, whole and not.
+@pytest.mark.parametrize("S,blocks,to_end,new,more,tiles",
+                         [(4, 36, 32, 32, 0, (32,)), (4, 36, 32, 31, 3, (32,)), (4, 36, 32, 17, 1, (32,)), (4, 36, 27, 22, 0, (27,)), (4, 36, 5, 5, 0, (5,)),
+                          (4, 36, 33, 33, 0, (1, 32)), (4, 36, 33, 2, 1, (1, 32)),
+                          (8, 71, 32, 32, 0, (16, 16)), (8, 71, 32, 17, 5, (16, 16)), (8, 71, 20, 5, 1, (4, 16)), (8, 70, 32, 31, 7, (32,)),
+                          (8, 71, 33, 33, 0, (17, 16)), (8, 71, 33, 18, 1, (17, 16)),
+                          (16, 139, 32, 32, 0, (8, 24)), (16, 139, 32, 31, 15, (8, 24)), (16, 137, 12, 5, 1, (4, 8)), (16, 139, 22, 17, 3, (22,)),
+                          (16, 139, 33, 33, 0, (9, 24)),
+                          (32, 275, 32, 32, 0, (20, 12)), (32, 275, 32, 31, 9, (20, 12)), (32, 275, 17, 17, 0, (5, 12)), (32, 275, 7, 5, 31, (7,)),
+                          (32, 275, 33, 31, 1, (21, 12))])
+def test_new_strides_formed_where_they_are_scored(S, blocks, to_end, new, more, tiles):
+    Ls = blocks * B // S
+    first = Ls - to_end
+    L = (first + new) * S + more
+    # the path goes by the strides to the end of the padded last block
+    assert -(-L // B) == blocks and more < S and new + (more > 0) <= to_end and Ls > 1024
+    assert tuple(min(t + 32, Ls) - max(t, first) for t in range(first // 32 * 32, Ls, 32)) == tiles
+    assert _new_strides(S, first * S, L, min(L - first * S, 2 * S + 1))[0]
