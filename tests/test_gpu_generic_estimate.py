@@ -55,15 +55,17 @@ def test_generic_estimate_matches_the_oracle(B, S, d, Hq, Hkv, L, dtype):
     assert rep["failed"] == 0 and rep["mass_max_abs_err"] <= 1e-6, rep
 
 
-# blocks of 32 keys, a batch of more than 512 workgroups (four waves each) and its prompts alone (eight, up to 256 blocks)
-@pytest.mark.parametrize("S,batch,Nb", [(8, 130, 5), (4, 40, 16), (2, 9, 64), (1, 3, 200), (8, 5, 256), (4, 5, 257)])
-def test_workgroups_of_four_and_of_eight_waves(S, batch, Nb):
+# Blocks of 32 keys and 4 to 32 sampled queries: a batch of more than 512 workgroups (four waves each) and its prompts alone, of up to 512
+# (eight, up to 256 blocks: the last case has 257 and stays on four).  As many heads as KV heads, one to a workgroup.
+@pytest.mark.parametrize("S,batch,Nb,H", [(8, 130, 5, 4), (4, 40, 16, 4), (2, 9, 64, 4), (1, 3, 200, 2), (4, 3, 255, 2), (8, 5, 256, 2), (1, 3, 256, 2),
+                                          (4, 5, 257, 1)])
+def test_workgroups_of_four_and_of_eight_waves(S, batch, Nb, H):
     import paper_2602_05853_amd as rr
-    B, d, Hq, Hkv, L = 32, 40, 4, 4, 32 * Nb - 3
-    assert batch * Hq * Nb > 512
+    B, d, L = 32, 40, 32 * Nb - 3
+    assert batch * H * Nb > 512 and H * Nb <= 512
     g = torch.Generator(device="cuda:0").manual_seed(Nb)
-    Q, K = (2.0 * torch.randn(batch, h, L, d, generator=g, device="cuda:0") for h in (Hq, Hkv))
-    print(f"[waves] S {S}: {batch} prompts of {Nb} blocks", flush=True)
+    Q, K = (2.0 * torch.randn(batch, H, L, d, generator=g, device="cuda:0") for _ in range(2))
+    print(f"[waves] S {S}: {batch} prompts of {Nb} blocks, {H} heads", flush=True)
     whole = rr.rr_estimate(Q, K, S, B, 0.8, block_mass=True)
     for b in (0, batch - 1):
         one = rr.rr_estimate(Q[b:b + 1], K[b:b + 1], S, B, 0.8, block_mass=True)
