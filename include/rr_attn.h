@@ -112,10 +112,14 @@ typedef struct {
  *              list while it works.  The words must be zero when a launch starts; the launch leaves them
  *              zero, and rr_estimate / rr_mask_from_dense zero them when they fill row_order.  Two
  *              launches that overlap in time must not share a queue (give each mask its own).  NULL =
- *              one workgroup per row.  It never changes any result.  (Used for at least as many rows as
- *              workgroups and contexts of up to 256 blocks, where the start of a row is a visible share of it, or longer ones
- *              as long as the keys and values of eight KV heads fit 256 MB, where an XCD takes the rows of KV heads of its
- *              own; other calls are launched one workgroup per row either way.)
+ *              one workgroup per row.  It never changes any result.  Rows are drawn
+ *                - by KV head, every XCD from heads of its own: at least eight rows to a workgroup (four
+ *                  with more than eight KV heads in the batch), any context as long as the keys and
+ *                  values of min(batch * Hkv, 8) KV heads stay below 256 MB;
+ *                - in rank order: other calls of at least as many rows as workgroups, contexts of up to
+ *                  256 blocks, where the start of a row is a visible share of it.
+ *              Other calls are launched one workgroup per row either way.  (The launch has one workgroup
+ *              per compute unit, not two, where few rows leave room for twice the wavefronts to each.)
  * rr_sparse_attn reads only row_count, row_list, row_order and queue; entries of row_list must satisfy
  * 0 <= n <= m, strictly ascending (counts and entries outside these ranges are clamped into them
  * on the device, so a malformed list gives a wrong row but no stray memory access).  A row with

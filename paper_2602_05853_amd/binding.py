@@ -148,7 +148,11 @@ def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
 
 @dataclass
 class BlockMask:
-    """Device arrays of one block selection (the rr_mask of the C ABI)."""
+    """Device arrays of one block selection (the rr_mask of the C ABI).
+
+    `queue` holds the row counters of a running rr_sparse_attn.  Calls that may overlap in time (on two streams, or from two
+    threads) must not share it, at any context length: they would take each other's rows.  Give each a mask of its own or a
+    zeroed queue of its own, or leave it out: dataclasses.replace(mask, queue=None)."""
     B: int
     Nb: int
     row_count: torch.Tensor               # int32 [batch, Hq, rows]       rows = Lq / B (= Nb unless chunked)
@@ -212,8 +216,9 @@ class BlockMask:
 
 
 # Masks up to this size are views of one buffer: five allocations and fills were 10-20 us of a call that makes its own mask
-# (estimate + sparse, fp32, 1024 tokens 68 -> 56 us; bf16, 8K tokens, 32 heads 273 -> 259; with offsets worked out in plain statements and the
-# stream by its handle 57.8 -> 43.2).  Larger ones are separate tensors, so that keeping one of them does not keep the others' memory.
+# (estimate + sparse, fp32, 1024 tokens 68 -> 56 us; bf16, 8K tokens, 32 heads 273 -> 259; with offsets worked out in plain
+# statements and the stream by its handle 57.8 -> 43.2).  Larger ones are separate tensors, so that keeping one of them does
+# not keep the others' memory.
 _ONE_BUFFER_BYTES = 4 << 20
 
 

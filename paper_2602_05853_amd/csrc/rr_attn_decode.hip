@@ -42,8 +42,8 @@ struct DecodeArgs {
     float scale_log2;   // log2(e) / sqrt(d)
 };
 
-// QT: 16-column tiles of query rows, for G T <= 16 or 32; columns beyond G T repeat the last row and are never stored.  (QT = 1 also takes 32
-// rows in two workgroups to a part.)
+// QT: 16-column tiles of query rows, for G T <= 16 or 32; columns beyond G T repeat the last row and are never stored.  (QT = 1
+// also takes 32 rows in two workgroups to a part.)
 // KW: waves, four to a block of keys and with eight of them two blocks at a time.
 template <int QT, int KW>
 __global__ void __launch_bounds__(64 * KW, 2)
@@ -60,8 +60,8 @@ k_attn_decode(Geom g, DecodeArgs da) {
     const AttnArgs& a = da.a;
     int part = blockIdx.x, kv = blockIdx.y, b = blockIdx.z, half = 0;
     if (QT == 1 && da.halves == 2) {
-        // a grid of one axis: the two workgroups of a part are eight apart, on one XCD, where the second finds the keys in L2 (but for up to
-        // seven parts at the end)
+        // a grid of one axis: the two workgroups of a part are eight apart, on one XCD, where the second finds the keys in L2
+        // (but for up to seven parts at the end)
         const int items = (int)gridDim.x >> 1, full = items & ~7;
         int item = (int)blockIdx.x;
         if (item < 2 * full) {
@@ -295,7 +295,8 @@ k_attn_decode_combine(Geom g, AttnArgs a, int T) {
     if (tid < kDecMaxParts) s_w[tid] = w;
     __syncthreads();
     // wavefront wv takes the parts p = wv, wv + 4, ..; a lane two channels, eight parts requested at once (one at a time, a part
-    // of weight zero skipped, their latencies were the kernel: one token of 128K, 64 parts, 8.8 us, so 4.2; 16384 tokens, the whole call 22.1 -> 17.8)
+    // of weight zero skipped, their latencies were the kernel: one token of 128K, 64 parts, 8.8 us, so 4.2; 16384 tokens, the
+    // whole call 22.1 -> 17.8)
     constexpr int kAtOnce = 8;
     float den = 0.f, o0 = 0.f, o1 = 0.f;
     for (int p0 = wv; p0 < P; p0 += 4 * kAtOnce) {
@@ -370,11 +371,12 @@ int attn_decode_parts(const Geom& g, int B) {
     return (int)P;
 }
 
-// The bytes a call asks for: all parts of the shortest steps, and for the others no more than the launches that served
-// them before ask for, so that the size grows with the step and one workspace serves every step up to the one it was
-// sized for.  These parts are fewer than fill the chip where the heads of a group are many; eight waves to a workgroup
-// make up for some of it, and two workgroups to a part for more.  Dense, us, before the latter: all parts, these, (the split launch): 8 tokens at 64K, 32 / 8 heads 51, 56, (131); 4 tokens,
-// 28 / 4 heads 35, 45, (177); 64 / 8 heads 51, 89, (239); 32 / 1 heads, one token, 16 workgroups 30, 50, (218).
+// The bytes a call asks for: all parts of the shortest steps, and for the others no more than the launches that served them
+// before ask for, so that the size grows with the step and one workspace serves every step up to the one it was sized for.
+// These parts are fewer than fill the chip where the heads of a group are many; eight waves to a workgroup make up for some
+// of it, and two workgroups to a part for more.  Dense, us, before the latter: all parts, these, (the split launch): 8
+// tokens at 64K, 32 / 8 heads 51, 56, (131); 4 tokens, 28 / 4 heads 35, 45, (177); 64 / 8 heads 51, 89, (239); 32 / 1
+// heads, one token, 16 workgroups 30, 50, (218).
 size_t attn_decode_bytes(const Geom& g, int B) {
     const int P = attn_decode_parts(g, B);
     if (P < 1) return 0;
@@ -408,12 +410,15 @@ hipError_t launch_attn_decode(const Geom& g, const AttnArgs& a, hipStream_t st) 
     // fewer workgroups than compute units, with parts of some length: two blocks at a time (at 64K, 32 / 8 heads, 8 tokens, 128
     // workgroups 75 -> 56 us; 256 workgroups 51 and 52)
     const bool eight = (long long)a.nsplit * g.batch * g.Hkv < 256 && da.len >= 8;
-    // Of more than 16 rows: two workgroups to such a part, with 16 rows each, also where parts are short and both fit the compute units at
-    // once.  Both read the part's keys, the second from L2, and use the matrix and vector units of twice as many compute units; sparse, each walks the
-    // blocks of its own rows only.  Estimate and attention, or dense call, us, 32 rows in eight waves / this: 8 tokens of 64512, 32 / 8 heads, 90.2 / 84.4, of
-    // 30000 51.3 / 47.1, of 4000 (four waves) 40.8 / 38.2, of 90000, 8 / 2, 65.6 / 57.7; dense, 4 tokens of 131072, 28 / 4 90.4 / 83.8, 64 / 8 193.5 / 181.7, eight
-    // sequences of 5000, 28 / 4, 28.1 / 26.1 (31 with the two on different XCDs).  (The values of the next keys requested with these, which one tile of rows has registers
-    // for: 86.2 instead of 83.7, one token of 128K 97.3 instead of 95.9.)
+    // Of more than 16 rows: two workgroups to such a part, with 16 rows each, also where parts are short and both fit the
+    // compute units at once.  Both read the part's keys, the second from L2, and use the matrix and vector units of twice
+    // as many compute units; sparse, each walks the blocks of its own rows only.  32 rows in eight waves / this, us:
+    //   estimate and attention: 8 tokens of 64512, 32 / 8 heads, 90.2 / 84.4, of 30000 51.3 / 47.1, of 4000 (four waves)
+    //     40.8 / 38.2, of 90000, 8 / 2, 65.6 / 57.7
+    //   dense: 4 tokens of 131072, 28 / 4 90.4 / 83.8, 64 / 8 193.5 / 181.7, eight sequences of 5000, 28 / 4, 28.1 / 26.1
+    //     (31 with the two on different XCDs)
+    // (The values of the next keys requested with these, which one tile of rows has registers for: 86.2 instead of 83.7,
+    // one token of 128K 97.3 instead of 95.9.)
     da.halves = R > 16 && (eight || 2ll * a.nsplit * g.batch * g.Hkv <= 256) ? 2 : 1;
     const unsigned parts = (unsigned)a.nsplit;
     const dim3 grid = da.halves == 2 ? dim3(2 * parts * (unsigned)g.Hkv * (unsigned)g.batch) : dim3(parts, (unsigned)g.Hkv, (unsigned)g.batch);

@@ -92,27 +92,26 @@ typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr_t;
 __device__ __forceinline__ int k_swz(int key, int chunk) { return key * 256 + ((chunk ^ (key & 15)) << 4); }
 __device__ __forceinline__ int v_swz(int key, int chunk) { return key * 256 + ((chunk ^ ((key & 7) << 1)) << 4); }
 
-// workgroup id -> (batch, head, query block).  Workgroups are dealt to the 8 XCDs round-robin
-// (id % 8 picks the XCD) and start in id order.
-// Dense calls (by_group) where the groups divide into the XCDs or the XCDs into the groups: every XCD takes KV groups of its
-// own (rr_attn_rows.hpp), so that the rows that run on it, which walk their blocks in the same order, find each other's tiles in
-// its L2.  All groups cost the same there; XCDs that share a group take its rows in turn.  Against sets of groups over all XCDs
-// (below; the order before where Nb is a multiple of 8, elsewhere level with what was), dense, us: 32 / 8 heads, 4096 tokens
-// 157 / 147, 8192 533 / 512, 16384 2002 / 1946, 32768 7817 / 7506, 98304 67445 / 67180; four prompts of 16384 8014 / 7575, sixteen of
-// 2048 686 / 623 (group after group; rank by rank of all an XCD's groups 7704, 635).
-// Elsewhere, when Nb is a multiple of 8 the KV groups are
-// taken `gi` at a time GPU-wide, so that the keys and values in use stay cache resident and L2 misses of
-// the sparse walk stay off HBM (gi = 1 at 128K tokens, where one group's K and V are 64 MB);
-// XCD x takes the rows with rank = x (mod 8), the query heads of a group back to back, rows heaviest
-// (largest m) first.  Otherwise XCDs are given whole KV groups where the counts allow it.
-// Interleaving.  Inside a set of gi groups the launch goes rank by rank, not group by group: every group's
-// heaviest row, then every group's second, ...  Taken one after the other, each group would end with a tail
-// of light rows that leaves compute units idle while the next group's heavy rows have not started; with few
-// rows per compute unit (short contexts) those tails were a quarter of the launch.  The position of a group
-// inside a rank rotates with the rank, so that an XCD is not always handed the same (perhaps heaviest) group.
-// Ordered launches: the entry of the caller-supplied row order (rows of each KV group, heaviest first) that
-// launch rank `bid` stands for, with the batch index and the first query head of its KV group.  Sets of gi
-// groups, rank by rank inside a set, the group's position rotating with the rank.
+// workgroup id -> (batch, head, query block).  Workgroups are dealt to the 8 XCDs round-robin (id % 8 picks the XCD) and
+// start in id order.
+// Dense calls (by_group) where the groups divide into the XCDs or the XCDs into the groups: every XCD takes KV groups of
+// its own (rr_attn_rows.hpp), so that the rows that run on it, which walk their blocks in the same order, find each other's
+// tiles in its L2.  All groups cost the same there; XCDs that share a group take its rows in turn.  Against sets of groups
+// over all XCDs (below; the order before where Nb is a multiple of 8, elsewhere level with what was), dense, us: 32 / 8
+// heads, 4096 tokens 157 / 147, 8192 533 / 512, 16384 2002 / 1946, 32768 7817 / 7506, 98304 67445 / 67180; four prompts of
+// 16384 8014 / 7575, sixteen of 2048 686 / 623 (group after group; rank by rank of all an XCD's groups 7704, 635).
+// Elsewhere, when Nb is a multiple of 8 the KV groups are taken `gi` at a time GPU-wide, so that the keys and values in use
+// stay cache resident and L2 misses of the sparse walk stay off HBM (gi = 1 at 128K tokens, where one group's K and V are
+// 64 MB); XCD x takes the rows with rank = x (mod 8), the query heads of a group back to back, rows heaviest (largest m)
+// first.  Otherwise XCDs are given whole KV groups where the counts allow it.
+// Interleaving.  Inside a set of gi groups the launch goes rank by rank, not group by group: every group's heaviest row,
+// then every group's second, ...  Taken one after the other, each group would end with a tail of light rows that leaves
+// compute units idle while the next group's heavy rows have not started; with few rows per compute unit (short contexts)
+// those tails were a quarter of the launch.  The position of a group inside a rank rotates with the rank, so that an XCD is
+// not always handed the same (perhaps heaviest) group.
+// Ordered launches: the entry of the caller-supplied row order (rows of each KV group, heaviest first) that launch rank
+// `bid` stands for, with the batch index and the first query head of its KV group.  Sets of gi groups, rank by rank inside
+// a set, the group's position rotating with the rank.
 __device__ __forceinline__ int order_entry_of(int bid, const Geom& g, int Nb, const int32_t* order, int gi, int hoist,
                                               int& b, int& h0) {
     const int N = g.G * Nb, NG = g.batch * g.Hkv;
@@ -573,20 +572,20 @@ __device__ __forceinline__ kernarg_ptr_t kernel_args() {
 template <bool kRagged, bool kPersist, bool kWide>
 __global__ void __launch_bounds__(kWide ? 2 * kThreads : kThreads, 2)
 k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
-    // kRagged: the real length ends inside the last block (g.Lr < g.L) or the queries start inside their first
-    // block (g.qoff > 0): clamped Q rows, a clamped copy of the partial diagonal tile, predicated stores.  Compiled apart so
-    // that the plain launch carries none of it (both forms run at the same rate).
+    // kRagged: the real length ends inside the last block (g.Lr < g.L) or the queries start inside their first block
+    // (g.qoff > 0): clamped Q rows, a clamped copy of the partial diagonal tile, predicated stores.  Compiled apart so that
+    // the plain launch carries none of it (both forms run at the same rate).
     //
-    // kPersist (sparse launches with a row order and a queue): two workgroups per compute unit that take row after
-    // row.  A workgroup takes rows of one queue: by_group, its XCD's (x = workgroup mod 8, the XCD the dispatcher gave
-    // it) share of the KV groups, queue x mod NQ of NQ = min(groups, 8), with groups q, q + NQ, ..; or the launch ranks x + 8 t, so that every rank keeps
-    // the XCD the order was made for.  The first rows go by workgroup index, the others are drawn from the queue's
-    // counter, and the next row is looked up while the current one is merged and stored.  by_group, a workgroup whose queue is empty goes on
-    // with the one that has the most rows left (groups differ in what they keep).
+    // kPersist (sparse launches with a row order and a queue): two workgroups per compute unit that take row after row.  A
+    // workgroup takes rows of one queue.  by_group, queue x mod NQ (x = workgroup mod 8, the XCD the dispatcher gave it; NQ
+    // = min(groups, 8)) has the KV groups q, q + NQ, ..; else queue x has the launch ranks x + 8 t, so that every rank
+    // keeps the XCD the order was made for.  The first rows go by workgroup index, the others are drawn from the queue's
+    // counter, and the next row is looked up while the current one is merged and stored.  by_group, a workgroup whose queue
+    // is empty goes on with the one that has the most rows left (groups differ in what they keep).
     //
-    // kWide (launches whose time is that of a row, see launch_attn_mfma_bf16): two groups of four waves to a row, group
-    // hg with the keys 64 hg .. +63 of every block and tile buffers of its own; one workgroup per compute unit
-    // (the persistent form too).
+    // kWide (launches whose time is that of a row, see launch_attn_mfma_bf16): two groups of four waves to a row, group hg
+    // with the keys 64 hg .. +63 of every block and tile buffers of its own; one workgroup per compute unit (the persistent
+    // form too).
     (void)kernel_arguments;
     extern __shared__ __align__(16) unsigned char lds_generic[];
     lds_byte_t* lds = (lds_byte_t*)lds_generic;
@@ -679,8 +678,9 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
             }
             pb = grp / g.Hkv;
             ph = (grp - pb * g.Hkv) * g.G;
-            // The order is transposed inside runs of 8 G rows, for XCDs that take every eighth: here the rows as they were sorted,
-            // the heads of a query block together (32 / 8 heads, 50000 tokens 7866 -> 7785 us; packed prompts of 311 blocks, 28 / 4, 1395 -> 1382).
+            // The order is transposed inside runs of 8 G rows, for XCDs that take every eighth: here the rows as they were
+            // sorted, the heads of a query block together (32 / 8 heads, 50000 tokens 7866 -> 7785 us; packed prompts of 311
+            // blocks, 28 / 4, 1395 -> 1382).
             const int C = g.G, run = 8 * C;
             if (C > 1 && i < g.G * Nbq / run * run) {
                 const int base = i / run * run, w = i - base;
@@ -1182,34 +1182,44 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
 
 constexpr int kPersistMaxBlocks = 256;                 // contexts up to 32K tokens, see launch_attn_mfma_bf16
 
-// Whether the heaviest rows of all KV groups, one run of each group's row order (8 G rows, which one XCD each was chosen for),
-// may go in front of the sets: up to 64 heads in all, whose runs are no more than the 512 workgroups that run at once, or up to 128
-// heads of long prompts, whose runs are at most a sixteenth of the rows, unless the rows of a group are many.  More of them are a
-// visible share of the launch, mixed rows of many groups find less in L2, and the last set of a launch of many sets is a small
-// part of it.  Estimate and attention with the runs in front / without, us, gain of the inputs 3, tau 0.9:
-//   not taken: 64 / 8 heads, four prompts of 5000 tokens 902 / 857, of 12000 3674 / 3503, two of 9200 1130 / 1112, of 14000 2347 / 2290, of 30000
-//     9290 / 9213 (on another box 9657 / 9741), of 40000 16271 / 15879 (17025 / 17221); 32 / 8, four of 3000 229 / 221, of 9000 1153 / 1115, of 16000 3016 / 2976, eight of 6000 1251 / 1205,
-//     of 20000 9342 / 9221; 28 / 4, four of 10000 1196 / 1167, three of 36000 8677 / 8430; 8 / 2, sixteen of 8000 1016 / 979
-//   taken: 32 / 8, four of 18500 3743 / 3964, 24000 6298 / 6509, 33000 11314 / 11824, 45000 21541 / 21344 (22369 / 22346); 64 / 8, two of 20000 4379 / 4393, 26000 7102 /
-//     7167; 28 / 4, four of 20000 3899 / 3794, 25000 5704 / 5862; 16 / 4, eight of 24000 6298 / 6480; 8 / 2, sixteen of 20000 4631 / 4772
+// The order of launches that do not take their rows by KV group (by_group in launch_attn_mfma_bf16): the rules from here to
+// hoisted_rows are for launches without a queue, with too few rows for it, or whose groups' keys and values do not fit the
+// memory-side cache.  With a queue nearly all shapes of the three tables are taken by group now; their figures are those of
+// rows in rank order, drawn from a queue per XCD up to 256 blocks and one workgroup to a row beyond.
+//
+// Whether the heaviest rows of all KV groups, one run of each group's row order (8 G rows, which one XCD each was chosen
+// for), may go in front of the sets: up to 64 heads in all, whose runs are no more than the 512 workgroups that run at
+// once, or up to 128 heads of long prompts, whose runs are at most a sixteenth of the rows, unless the rows of a group are
+// many.  More of them are a visible share of the launch, mixed rows of many groups find less in L2, and the last set of a
+// launch of many sets is a small part of it.  Estimate and attention with the runs in front / without, us, gain of the
+// inputs 3, tau 0.9:
+//   not taken: 64 / 8 heads, four prompts of 5000 tokens 902 / 857, of 12000 3674 / 3503, two of 9200 1130 / 1112, of 14000
+//     2347 / 2290, of 30000 9290 / 9213 (on another box 9657 / 9741), of 40000 16271 / 15879 (17025 / 17221); 32 / 8, four
+//     of 3000 229 / 221, of 9000 1153 / 1115, of 16000 3016 / 2976, eight of 6000 1251 / 1205, of 20000 9342 / 9221;
+//     28 / 4, four of 10000 1196 / 1167, three of 36000 8677 / 8430; 8 / 2, sixteen of 8000 1016 / 979
+//   taken: 32 / 8, four of 18500 3743 / 3964, 24000 6298 / 6509, 33000 11314 / 11824, 45000 21541 / 21344 (22369 / 22346);
+//     64 / 8, two of 20000 4379 / 4393, 26000 7102 / 7167; 28 / 4, four of 20000 3899 / 3794, 25000 5704 / 5862; 16 / 4,
+//     eight of 24000 6298 / 6480; 8 / 2, sixteen of 20000 4631 / 4772
 bool first_runs_pay(const Geom& g) {
     const long long heads = (long long)g.batch * g.Hq;
     const int Nbq = g.Lq / 128;
     return heads <= 64 || (heads <= 128 && Nbq >= 128 && g.G * Nbq <= 1750);
 }
 
-// KV groups launched interleaved (decode_block, order_entry_of): the largest divisor of the number of groups that keeps K and V of
-// the set within 32 MB, the L2 capacity of the chip (8 x 4 MB), or within 38 MB for the row order of whole prompts where the first runs
-// pay and sets are at most 3000 rows long.  More groups to a set find less of each other's tiles in L2, fewer put more of a
-// launch's heavy rows late, which counts where there are few sets and they are over soon.  Measured, estimate and attention or dense
-// call, us, 38 MB / 32 MB, gain of the inputs 3 and tau 0.9 unless said:
-//   sets of up to 3000 rows: 32 / 8 heads, 18000 tokens 752 / 772, 37000 2772 / 2848; 16 / 4, 37000 1552 / 1736, tau 0.95 2168 / 2318; 8 / 2, 36000
-//     810 / 873, 38900 883 / 931 (weaker structure, tau 0.95, 38500 1709 / 1670; three packed prompts of 300 blocks 715 / 706)
-//   longer ones (32 MB): 64 / 8, 9000 538 / 520, 18000 1747 / 1725, 35000 5092 / 4881, 38500 7564 / 7389; 28 / 4, 17000 708 / 699, 18500 647 / 653,
-//     35000 2631 / 2587, 38000 3116 / 3056, packed prompts of 290 blocks 1286 / 1257
+// KV groups launched interleaved (decode_block, order_entry_of): the largest divisor of the number of groups that keeps K
+// and V of the set within 32 MB, the L2 capacity of the chip (8 x 4 MB), or within 38 MB for the row order of whole prompts
+// where the first runs pay and sets are at most 3000 rows long.  More groups to a set find less of each other's tiles in
+// L2, fewer put more of a launch's heavy rows late, which counts where there are few sets and they are over soon.
+// Measured, estimate and attention or dense call, us, 38 MB / 32 MB, gain of the inputs 3 and tau 0.9 unless said:
+//   sets of up to 3000 rows: 32 / 8 heads, 18000 tokens 752 / 772, 37000 2772 / 2848; 16 / 4, 37000 1552 / 1736, tau 0.95
+//     2168 / 2318; 8 / 2, 36000 810 / 873, 38900 883 / 931 (weaker structure, tau 0.95, 38500 1709 / 1670; three packed
+//     prompts of 300 blocks 715 / 706)
+//   longer ones (32 MB): 64 / 8, 9000 538 / 520, 18000 1747 / 1725, 35000 5092 / 4881, 38500 7564 / 7389; 28 / 4, 17000
+//     708 / 699, 18500 647 / 653, 35000 2631 / 2587, 38000 3116 / 3056, packed prompts of 290 blocks 1286 / 1257
 //   many short prompts (32 MB): 32 / 8, three of 12000 1402 / 1368, four of 9000 1118 / 1109
-//   no row order or not a whole prompt (32 MB): dense, 32 / 8, 38900 11363 / 11119, 8900 to 36000 level; planned chunks, 1000 of 35000, 64 / 8
-//     heads, 415 / 402 and 424 / 412, 1500 of 18500, 32 / 8, 209 / 203 and 200 / 203; sparse without a row order level
+//   no row order or not a whole prompt (32 MB): dense, 32 / 8, 38900 11363 / 11119, 8900 to 36000 level; planned chunks,
+//     1000 of 35000, 64 / 8 heads, 415 / 402 and 424 / 412, 1500 of 18500, 32 / 8, 209 / 203 and 200 / 203; sparse without
+//     a row order level
 int interleave_groups(const Geom& g, bool ordered) {
     const long long per_group = 2ll * g.L * g.d * 2;               // K and V of one KV head, bf16
     const int NG = g.batch * g.Hkv, rows = g.G * (g.Lq / 128);
@@ -1224,18 +1234,18 @@ int interleave_groups(const Geom& g, bool ordered) {
 // set, so sparse launches first take the heaviest rows of ALL groups, one run of the row order, and then the sets.
 // Not taken where
 // - first_runs_pay says no
-// - sets have 4096 rows and more (eight to each of the 512 workgroups that run at once), where it is even: 131072 tokens, 32 / 8
-//   heads, with it 0.2 and 0.4 % slower in two runs, at weaker structure 0.4 and 1.1 %, at tau 0.95 0.7 and 0.6 %; 65536, 64 / 8, S = 8, 1.2 and 1.1 %
-//   faster, 65500, tau 0.95, 0.6 and 0.9 %
-// - contexts of more than 256 blocks have fewer than eight groups: the last set is a large part of the launch there, and the mixed
-//   rows cost what they save.
+// - sets have 4096 rows and more (eight to each of the 512 workgroups that run at once), where it is even: 131072 tokens,
+//   32 / 8 heads, with it 0.2 and 0.4 % slower in two runs, at weaker structure 0.4 and 1.1 %, at tau 0.95 0.7 and 0.6 %; 65536,
+//   64 / 8, S = 8, 1.2 and 1.1 % faster, 65500, tau 0.95, 0.6 and 0.9 %
+// - contexts of more than 256 blocks have fewer than eight groups: the last set is a large part of the launch there, and the
+//   mixed rows cost what they save.
 // Measured, attention alone, tau 0.9, us; sets of 32 MB without the first run / sets of 1, 2, 4 groups with it:
-//   32 / 8 heads: 9000 tokens 265 / 208, 206, 206; 16384 628 / 580, 555, 541; 24000 1330 / 1217, 1171, 1158; 28000 1730 / 1580, 1532,
-//     1545; 36000 3020 / 2699, 2643, 2736; 50000 4950 / 4637, 4617, 4731; 65536 8350 / 7906, 7704, 8065 (weaker structure 14349 / 14201,
-//     14321, 15066); 98304 18126 / 18141, 18479, 19748
+//   32 / 8 heads: 9000 tokens 265 / 208, 206, 206; 16384 628 / 580, 555, 541; 24000 1330 / 1217, 1171, 1158; 28000 1730 / 1580,
+//     1532, 1545; 36000 3020 / 2699, 2643, 2736; 50000 4950 / 4637, 4617, 4731; 65536 8350 / 7906, 7704, 8065 (weaker structure
+//     14349 / 14201, 14321, 15066); 98304 18126 / 18141, 18479, 19748
 //   64 / 8: 12000 685 / 706, 694, 689; 20000 1704 / 1692, 1633, 1664
-//   28 / 4: 20000 806 / 773, 731, 739; 8 / 2: 20000 272 / 260, 271; not taken: 28 / 4 40000 2715 / 2672; 8 / 2 50000 1204 / 1226; 28 / 4, eight
-//     packed prompts (311 blocks) 1371 / 1385
+//   28 / 4: 20000 806 / 773, 731, 739; 8 / 2: 20000 272 / 260, 271; not taken: 28 / 4 40000 2715 / 2672; 8 / 2 50000 1204 / 1226;
+//     28 / 4, eight packed prompts (311 blocks) 1371 / 1385
 int hoisted_rows(const Geom& g, int interleave) {
     const int NG = g.batch * g.Hkv, rows = g.G * (g.Lq / 128);
     if (!first_runs_pay(g) || interleave == NG || interleave * rows >= 4096 || 8 * g.G >= rows ||
@@ -1416,8 +1426,9 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
 }
 
 // The cut rows: O = sum_p exp(lse_p - lse) O_p over the row's parts, rounded once.  Four query rows of a cut row's 128 to a
-// workgroup at a time, a wavefront each; the parts' lse values are read by one lane each, and four parts of a half are requested at once, so that nothing in the merge is a chain
-// of dependent loads (2048 tokens at 128K 557 -> 553 us in all, eight at once 559), and the two halves of the wavefront take every other part, a lane four channels.  At most 64 parts per row.
+// workgroup at a time, a wavefront each; the parts' lse values are read by one lane each, and four parts of a half are requested
+// at once, so that nothing in the merge is a chain of dependent loads (2048 tokens at 128K 557 -> 553 us in all, eight at once
+// 559), and the two halves of the wavefront take every other part, a lane four channels.  At most 64 parts per row.
 // The number of cut rows is on the device: a fixed grid takes them in turns (one workgroup for each that might be there, and
 // whole wavefronts per part: 37 us, so 20; 2048 tokens at 128K, 1329 parts of 70 rows).  The halves are added last, so
 // an output can differ from a merge of the parts one after the other by its last rounding.
@@ -1595,15 +1606,23 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     // costs (1139 tokens, 252 rows: 67 against 72 us).  Wide rows, attention alone: 2048 tokens, 28 / 4 heads 62 -> 47 us.
     const int NG = g.batch * g.Hkv;
     const bool queued = a.row_order != nullptr && a.queue != nullptr && resident >= 8 && a.nsplit == 1 && !planned && rows < 1 << 30;
-    // Rows drawn by KV group: at least eight to a workgroup, four where a queue has several groups (below that the groups' different
-    // lengths cost what the L2 hits give), and as long as the keys and values of the groups in flight fit the memory-side cache of
-    // 256 MB.  Estimate and attention, gain of the inputs 3, tau 0.9, us, rows in rank order over all XCDs / by group:
-    //   32 / 8 heads: 16384 tokens 708 / 681, 24000 1518 / 1430, 31907 3142 / 3034, 40000 4068 / 3864, 50000, weaker structure, 8088 / 7776; 64 / 8:
-    //     9000 533 / 521, 20000 2124 / 2040, 60000 17788 / 17407; 28 / 4: 20000 911 / 902, 32000 2247 / 2176, 50000 5442 / 5221; 16 / 4: 60000 4537 /
-    //     4312, 90000 10911 / 10725; 8 / 2: 40000 1087 / 1068; batches: four of 2000, 32 / 8, 162 / 152, sixteen 585 / 554, three of 12000 1360 / 1260, two of 45000 10346 /
-    //     9835, eight of 3000, 28 / 4, 357 / 342; packed prompts of 311 blocks, 28 / 4, 1452 / 1382, forty of 6 blocks, 32 / 8, 403 / 373
-    //   not taken: 2500, 32 / 8, (1.3 rows to a workgroup) 76 / 82, 6500 (3.2) 172 / 180, 8192 (4) level, 12000 (5.9) level; 28 / 4, 8000 (3.4) 217 / 229; 16 / 4,
-    //     16384 (4) 411 / 428; 65536, 64 / 8, 21131 / 21141, 98304, 32 / 8, 25889 / 25944, 131072 31994 / 32199
+    // Rows drawn by KV group: at least eight to a workgroup, four where a queue has several groups (below that the groups'
+    // different lengths cost what the L2 hits give), and as long as the keys and values of the groups in flight, one to a
+    // queue, fit the memory-side cache of 256 MB.  Estimate and attention, gain of the inputs 3, tau 0.9, us, rows in rank
+    // order over all XCDs / by group:
+    //   32 / 8 heads: 16384 tokens 708 / 681, 24000 1518 / 1430, 31907 3142 / 3034, 40000 4068 / 3864, 50000, weaker
+    //     structure, 8088 / 7776; 64 / 8: 9000 533 / 521, 20000 2124 / 2040, 60000 17788 / 17407; 28 / 4: 20000 911 / 902,
+    //     32000 2247 / 2176, 50000 5442 / 5221; 16 / 4: 60000 4537 / 4312, 90000 10911 / 10725; 8 / 2: 40000 1087 / 1068
+    //   batches: 32 / 8, four of 2000 162 / 152, sixteen 585 / 554, three of 12000 1360 / 1260, two of 45000 10346 / 9835;
+    //     28 / 4, eight of 3000 357 / 342; packed prompts of 311 blocks, 28 / 4, 1452 / 1382, forty of 6 blocks, 32 / 8,
+    //     403 / 373
+    //   not taken: 32 / 8, 2500 (1.3 rows to a workgroup) 76 / 82, 6500 (3.2) 172 / 180, 8192 (4) level, 12000 (5.9) level;
+    //     28 / 4, 8000 (3.4) 217 / 229; 16 / 4, 16384 (4) 411 / 428; 64 / 8, 65536 21131 / 21141; 32 / 8, 98304
+    //     25889 / 25944, 131072 31994 / 32199
+    // A queue of several groups starts with the heaviest rows of all of them, one run of each group's order.
+    // Without / with: 32 / 8, four of 4096 299 / 282, of 9000 1007 / 997, of 18500 3267 / 3303, sixteen of 1500 352 / 360;
+    // 64 / 8, eight of 2000 532 / 523, four of 5000 793 / 792, of 12000 3096 / 3135; 8 / 2, sixteen of 8000 885 / 866;
+    // 28 / 4, four of 10000 1077 / 1078 (rank order over all XCDs: 293, 1077, 3522, 375, 585, 836, 3266, 932, 1115).
     const bool by_group = queued && rows >= (NG > 8 ? 4ll : 8ll) * resident && std::min(NG, 8) * 4ll * g.L * g.d < 256ll << 20;
     const bool persist = by_group || (queued && a.Nb <= kPersistMaxBlocks && rows >= resident);
     // (a list without an order: its heavy rows, the last of every head, would meet on few XCDs)

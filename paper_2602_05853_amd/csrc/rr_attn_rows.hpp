@@ -17,16 +17,19 @@ constexpr RowPlace row_of_whole_groups(int bid, int G, int Nb) {
     return {x + 8 * (s / per), r % G, r / G};
 }
 
-// NG a divisor of eight: k = 8 / NG XCDs share a group, and each takes one of every k query blocks (a level) for all heads, whose
-// tiles then meet in its L2.  Levels are taken forth and back in pairs: with the same place in every level the heaviest of k
-// rows always went to one XCD, which had 21 % more key blocks than the mean for one KV head and 32 query blocks.  Where
-// no second level is left (an odd number of them, or a last one that k does not fill) the place moves on from head to head.
-// Dense, us, sets of groups over all XCDs / the same place in every level / this; in brackets the place that moves on from head to
-// head everywhere, as even, on another box of about the same speed:
-//   32 / 1 heads: 2048 tokens 51.5 / 55.8 / 45.7 (51.1), 4096 151.8 / 169.5 / 143.0 (154.5), 8192 521 / 553 / 516 (531), 20000 2973 / 2974 /
-//     2870 (2990); 64 / 1: 1500 73.2 / 72.7 / 62.1, 4096 288.7 / 317.7 / 276.3; 128 / 1, 4096 566 / 621 / 549; 8 / 1, 16384 529 / 538 / 517
+// NG a divisor of eight: k = 8 / NG XCDs share a group, and each takes one of every k query blocks (a level) for all heads,
+// whose tiles then meet in its L2.  Levels are taken forth and back in pairs: with the same place in every level the
+// heaviest of k rows always went to one XCD, which had 21 % more key blocks than the mean for one KV head and 32 query
+// blocks.  Where no second level is left (an odd number of them, or a last one that k does not fill) the place moves on
+// from head to head.
+// Dense, us, sets of groups over all XCDs / the same place in every level / this; in brackets the place that moves on from
+// head to head everywhere, as even, on another box of about the same speed:
+//   32 / 1 heads: 2048 tokens 51.5 / 55.8 / 45.7 (51.1), 4096 151.8 / 169.5 / 143.0 (154.5), 8192 521 / 553 / 516 (531),
+//     20000 2973 / 2974 / 2870 (2990); 64 / 1: 1500 73.2 / 72.7 / 62.1, 4096 288.7 / 317.7 / 276.3; 128 / 1, 4096
+//     566 / 621 / 549; 8 / 1, 16384 529 / 538 / 517
 //   32 / 2: 4096 152.1 / 155.3 / 142.8, 8192 519 / 531 / 509; 28 / 4: 8192 453 / 455 / 445, 16384 1715 / 1706 / 1690 (1742)
-//   lists without an order, 4900 tokens (blocks no multiple of eight), same place / this: 32 / 1 132.3 / 124.4, 32 / 4 105.7 / 104.7
+//   lists without an order, 4900 tokens (blocks no multiple of eight), same place / this: 32 / 1 132.3 / 124.4, 32 / 4
+//     105.7 / 104.7
 constexpr RowPlace row_of_shared_group(int bid, int NG, int G, int Nb) {
     const int k = 8 / NG, x = bid & 7, s = bid >> 3, q = s / G, c = x / NG;
     const bool paired = q < ((Nb / k) & ~1);

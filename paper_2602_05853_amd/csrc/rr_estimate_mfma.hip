@@ -46,9 +46,9 @@ constexpr int kTileBytes = 3 * kPlaneBytes;            // hi, mid, lo
 constexpr int kLdsBytes = 2 * kTileBytes;              // double buffered
 
 // ---- stride sums, split into three bf16 planes: Ksp[p][b][kv][j][c], j < LsCap ----
-// Eight channels of `nkeys` keys from src on, summed in fp32 in the order of the keys and split.  kAtOnce keys requested at once, eight
-// or sixteen (one at a time, a thread's S loads were a chain: 2048 new positions at 128K 11.4 -> 5.0 us, 8K tokens, all 8 KV heads
-// 8.3 -> 6.1, 128K 68 -> 63).
+// Eight channels of `nkeys` keys from src on, summed in fp32 in the order of the keys and split.  kAtOnce keys requested at
+// once, eight or sixteen (one at a time, a thread's S loads were a chain: 2048 new positions at 128K 11.4 -> 5.0 us, 8K
+// tokens, all 8 KV heads 8.3 -> 6.1, 128K 68 -> 63).
 template <int kAtOnce>
 __device__ __forceinline__ void stride_sum_parts(const Geom& g, const unsigned short* src, int nkeys, u32x4 (&part)[3]) {
     float acc[8];
@@ -188,10 +188,10 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
     const int GR = g.G * R;
     const int NR = mb * GR;                                        // rows of this workgroup
 
-    // ---- second launch of a key split: the softmax state of a query over ALL key strides, its states in the chunks brought to one
-    // reference.  A lane takes one of the wave's 64 queries and up to 32 chunks at once.  (Both lanes of a query for each of two
-    // queries, eight chunks at a time and twice, took 12.7 of the 43 us of such a workgroup for 2048 tokens at 128K, 32 chunks; so 3.5.
-    // 32K tokens, three chunks, 4.4 -> 2.4.)
+    // ---- second launch of a key split: the softmax state of a query over ALL key strides, its states in the chunks
+    // brought to one reference.  A lane takes one of the wave's 64 queries and up to 32 chunks at once.  (Both lanes of a
+    // query for each of two queries, eight chunks at a time and twice, took 12.7 of the 43 us of such a workgroup for 2048
+    // tokens at 128K, 32 chunks; so 3.5.  32K tokens, three chunks, 4.4 -> 2.4.)
     const float NEG_INF = -__builtin_huge_valf();
     float2* const my_stats = a.stats ? a.stats + (((long long)pr * ngroups + mg) * a.nsplit) * 256 : nullptr;
     float state_um = NEG_INF, state_z = 0.f;
@@ -521,18 +521,20 @@ k_stride_mass_mfma(Geom g, ScoreArgs a) {
 // ---- short contexts: scores, softmax, block mass and selection in one launch ----
 // Up to 1024 key strides the scores of 64 sampled queries against ALL of them fit the registers of one workgroup: eight
 // waves, each TPW tiles of 32 strides (tile w + 8 i) by two column tiles of queries.  The matrix work is then done once
-// instead of twice, the softmax needs no second sweep (the waves exchange maxima and sums through LDS), nothing is
-// left for another launch, and the workgroup selects its own 64 / R rows, whose masses meet in LDS.  A workgroup takes
-// 64 / R consecutive (query block, head) pairs of a KV head, so the heads of a query block share the stride sums it
-// reads; every wave has tiles of its own, copied through LDS of its own (see there).
-// What bounds it: the chain launch, queries, stride sums, softmax, selection of one row, each waiting for the one before.  Estimate and attention, us,
-// fragments straight from L2 to registers / through LDS: 32 / 8 heads, 2048 tokens 67.9 / 65.3, 8192 231.0 / 223.8, 16384 694.7 / 683.0; 8 / 2, 12000 195.9 / 187.0; 8
-// tokens of 12000 54.0 / 46.1, 700 of 16000 184.5 / 172.7; launches of two workgroups to a compute unit before, which LDS for one now excludes: three prompts of 3000, 64 / 8
-// heads, 293.3 / 294.0, four of 4000, 32 / 8, 324.3 / 323.7.
-// A score's exponent is one fma, score scale - round(largest score scale): that rounding is a factor that all strides of a query share, and it
-// goes with the sum.  Not where it is itself too large to be an exponent: beyond this reference (log2 units, rounded to at most
-// 1) the largest score is subtracted first, which leaves its own stride exactly 2^0.  (Without, one key of 1e12 made queries drop out of
-// their row, or the row have no estimate.  17 layers and steps with the test for it: 0.986 to 1.015 of the time without, twice without 0.992 to 1.008.)
+// instead of twice, the softmax needs no second sweep (the waves exchange maxima and sums through LDS), nothing is left for
+// another launch, and the workgroup selects its own 64 / R rows, whose masses meet in LDS.  A workgroup takes 64 / R
+// consecutive (query block, head) pairs of a KV head, so the heads of a query block share the stride sums it reads; every
+// wave has tiles of its own, copied through LDS of its own (see there).
+// What bounds it: the chain launch, queries, stride sums, softmax, selection of one row, each waiting for the one before.
+// Estimate and attention, us, fragments straight from L2 to registers / through LDS: 32 / 8 heads, 2048 tokens 67.9 / 65.3,
+// 8192 231.0 / 223.8, 16384 694.7 / 683.0; 8 / 2, 12000 195.9 / 187.0; 8 tokens of 12000 54.0 / 46.1, 700 of 16000
+// 184.5 / 172.7; launches of two workgroups to a compute unit before, which LDS for one now excludes: three prompts of
+// 3000, 64 / 8 heads, 293.3 / 294.0, four of 4000, 32 / 8, 324.3 / 323.7.
+// A score's exponent is one fma, score scale - round(largest score scale): that rounding is a factor that all strides of a
+// query share, and it goes with the sum.  Not where it is itself too large to be an exponent: beyond this reference (log2
+// units, rounded to at most 1) the largest score is subtracted first, which leaves its own stride exactly 2^0.  (Without,
+// one key of 1e12 made queries drop out of their row, or the row have no estimate.  17 layers and steps with the test for
+// it: 0.986 to 1.015 of the time without, twice without 0.992 to 1.008.)
 constexpr float kFarReference = 16777216.f;
 constexpr int kRowWaves = 8, kRowCols = 64;
 constexpr int kQuarterBytes = 3 * kTileStrides * 64;              // 32 channels of a tile's three planes
@@ -608,10 +610,12 @@ k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
     const unsigned short* kbase = a.Ksp + ((long long)(b * g.Hkv + kv) * a.LsCap) * g.d;
     const float NEG_INF = -__builtin_huge_valf();
 
-    // A wave's tiles, a quarter (32 channels, 3 planes, 6 KB) at a time through LDS of its own, the next quarter on its way meanwhile.
-    // The rows of a tile lie 256 bytes apart, so fragments loaded straight to registers took 32 bytes of a line with each of its visits
-    // (one a cycle and compute unit): 12 us for the longest workgroup at 8192 tokens; a copy takes 64.  LDS rows of 64 bytes, chunk c of row r
-    // in place c ^ (r / 4 mod 4): conflict-free reads.  (Waves read what they copied themselves: no barrier.)
+    // A wave's tiles, a quarter (32 channels, 3 planes, 6 KB) at a time through LDS of its own, the next quarter on its way
+    // meanwhile.
+    // The rows of a tile lie 256 bytes apart, so fragments loaded straight to registers took 32 bytes of a line with each
+    // of its visits (one a cycle and compute unit): 12 us for the longest workgroup at 8192 tokens; a copy takes 64.  LDS
+    // rows of 64 bytes, chunk c of row r in place c ^ (r / 4 mod 4): conflict-free reads.  (Waves read what they copied
+    // themselves: no barrier.)
     const unsigned stage = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_stage + (unsigned)(w * 2 * kQuarterBytes);
     const int copy_row = lane >> 2, copy_chunk = (lane & 3) ^ ((lane >> 4) & 3);
     auto issue_quarter = [&](int i, int q) {
@@ -781,11 +785,12 @@ k_estimate_rows(Geom g, ScoreArgs a, EstimateArgs ea) {
 }
 
 // ---- short steps: one sweep, then softmax, block masses, selection and row order in one launch ----
-// A step of a few tokens has a handful of sampled queries to a KV head, nst strides of each of its G heads, against all key strides: a
-// wavefront takes 32 key strides and all queries, 32 at a time, and leaves for each query the sum of 2^(score - reference) over
-// each key block and the tile's reference (its largest score).  The second launch, one workgroup to a KV head and one wavefront
-// to a row, brings the references together.  What bounds it: the chain of launches and, in each, of its loads; 8 tokens behind
-// 64512, 32 / 8 heads: 8 + 10 us, the sums of the new strides among them, where those, the two sweeps, the selection and the row order took 5 + 20 + 20 + 9 + 5.
+// A step of a few tokens has a handful of sampled queries to a KV head, nst strides of each of its G heads, against all key
+// strides: a wavefront takes 32 key strides and all queries, 32 at a time, and leaves for each query the sum of 2^(score -
+// reference) over each key block and the tile's reference (its largest score).  The second launch, one workgroup to a KV
+// head and one wavefront to a row, brings the references together.  What bounds it: the chain of launches and, in each, of
+// its loads; 8 tokens behind 64512, 32 / 8 heads: 8 + 10 us, the sums of the new strides among them, where those, the two
+// sweeps, the selection and the row order took 5 + 20 + 20 + 9 + 5.
 struct StepArgs {
     float* sums;                      // [pair][query][tiles * blocks of a tile]
     float* refs;                      // [pair][query][tiles], log2 units
@@ -805,7 +810,7 @@ k_step_scores(Geom g, ScoreArgs a, StepArgs sa) {
     if (jt >= sa.tiles) return;
     const int pr = blockIdx.y, b = pr / g.Hkv, kv = pr - b * g.Hkv, j0 = jt * kTileStrides;
     const long long plane = (long long)g.batch * g.Hkv * a.LsCap * g.d;
-    __shared__ u32x4 s_new[2][3][kTileStrides][16];                // new strides lie in two tiles at most
+    __shared__ u32x4 s_new[2][3][kTileStrides][16];                // up to 32 new strides: two tiles at most
     // (rows that have no sums, or do not exist: one that has)
     const unsigned short* kp = a.Ksp + ((long long)pr * a.LsCap + min(j0 + l32, min(a.Ls, sa.j_new) - 1)) * g.d + 8 * gsel;
     bf16x8 kf[8][3];
@@ -1014,10 +1019,17 @@ bool estimate_mfma_is_step(const Geom& g, const EstimateArgs& ea) {
 
 // k_estimate_rows takes the call.
 // One launch where its workgroups, which fill a compute unit each and do not overlap one's loads with another's products,
-// are less than three to a compute unit.  The whole estimate, us, two sweeps and selection / one launch (before its tiles went through LDS), with its workgroups:
-// 32 / 8 heads, S = 16: 2048 tokens (64) 33 / 20, 8192 (256) 57 / 33, 16384 (512) 73 / 64; two prompts of 8192 (512) 63 / 48, four
-// (1024) 83 / 86; 64 / 8: 10000 (632) 71 / 63, 12000 (752) 75 / 74, 16384 (1024) 98 / 111; S = 8, 8192 (1024) 90 / 98; S = 32, 16384 (512)
-// 69 / 56; eight prompts of 2048 (1024) 45 / 49.
+// are less than three to a compute unit.  The whole estimate, us, two sweeps and selection / one launch, with its
+// workgroups:
+//   32 / 8 heads, S = 16: 8192 tokens (256) 52.4 / 23.1, 12000 (376) 61.0 / 35.9, 16384 (512) 69.3 / 46.9; two prompts of
+//     8192 (512) 61.3 / 36.5, four of 5200 (672) 60.8 / 41.7, eight of 2048 (512) 40.7 / 30.6
+//   64 / 8: 9000 (568) 62.3 / 43.4, 11000 (688) 71.4 / 50.0; three of 3000 (576) 42.5 / 32.6; 8 / 2, four of 16384 (512)
+//     68.7 / 46.8
+//   S = 8: 4096, 32 / 8 (256) 50.3 / 22.4, two of 5500 (688) 68.2 / 45.4; S = 32: 16384, 64 / 8 (512) 65.8 / 45.7, 22000
+//     (688) 83.0 / 73.0, 32768, 32 / 8 (512) 79.2 / 64.1
+// The line was drawn for tiles that went straight to registers, which met the two sweeps there; through LDS they meet
+// later: 64 / 8, 16384 (1024) 94.3 / 78.6, S = 8, four of 3000 (768) 61.5 / 39.3, but S = 32, 26000 (816) 88.0 / 89.9, four
+// of 9000 (1152) 75.2 / 81.5.
 bool short_context(const Geom& g, const EstimateArgs& ea) {
     const int R = ea.B / ea.S, Nbq = g.Lq / ea.B, P = kRowCols / R;
     const int tiles = (g.L / ea.S + kTileStrides - 1) / kTileStrides;
@@ -1030,8 +1042,12 @@ hipError_t launch_estimate_mfma(const Geom& g, const EstimateArgs& ea, unsigned 
     const int S = ea.S, B = ea.B, Ls = g.L / S, R = B / S, Nb = g.L / B, Nbq = g.Lq / B;
     if (ls_cap < Ls || ls_valid < 0) return hipErrorInvalidValue;
     const int j0 = ls_valid < Ls ? ls_valid : Ls;
-    // A short step's few new strides are left to the wavefronts that score them: a launch of 5 us less.  Estimate and attention, us: 8 tokens
-    // of 64512, 32 / 8 heads, 85.2 -> 81.2, of 30000 47.8 -> 43.4, 1 of 50000 66.8 -> 62.5, 100 of 65000 level.
+    // A short step's few new strides are left to the wavefronts that score them: a launch of 5 us less.  The bound is on
+    // the strides up to the end of the last block, the padding's (which are written as zeros) among them: 32 lie in two
+    // tiles at most, which is what s_new holds.  A step that ends early in a block of many strides therefore counts up to a
+    // block more than it completes (S = 4: new strides of two blocks are beyond the bound).  Estimate and
+    // attention, us: 8 tokens of 64512, 32 / 8 heads, 85.2 -> 81.2, of 30000 47.8 -> 43.4, 1 of 50000 66.8 -> 62.5, 100 of
+    // 65000 level.
     const bool step = !short_context(g, ea) && estimate_mfma_is_step(g, ea);
     const bool sums_in_scores = step && j0 > 0 && Ls - j0 <= kTileStrides && g.Lr / S > g.q0 / S;
     if (j0 < Ls && !sums_in_scores) {

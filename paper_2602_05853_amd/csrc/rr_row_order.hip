@@ -144,8 +144,9 @@ hipError_t launch_row_order(const Geom& g, int Nb, const int32_t* row_count, int
     if (N > kMaxOrderedRows) return hipErrorInvalidValue;
     const dim3 grid(g.Hkv, g.batch);
     const int shift = row_order_shift(Nb);
-    // No more wavefronts than rows fill: they wait for each other at every barrier.  Estimate and attention with 1024 threads / these, us: fp32, 4096
-    // tokens, 8 / 2 heads (256 rows) 188.9 / 187.0, bf16, 2048, 32 / 8 (64) 65.5 / 64.8, 8153, 16 / 4 of 64 (512) 181.3 / 180.0.
+    // No more wavefronts than rows fill: they wait for each other at every barrier.  Estimate and attention with 1024
+    // threads / these, us: fp32, 4096 tokens, 8 / 2 heads (256 rows) 188.9 / 187.0, bf16, 2048, 32 / 8 (64) 65.5 / 64.8,
+    // 8153, 16 / 4 of 64 (512) 181.3 / 180.0.
     auto launch = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, g, Nb, shift, row_count, row_order, queue);
     };
