@@ -128,7 +128,7 @@ __device__ __forceinline__ int order_entry_of(int bid, const Geom& g, int Nb, co
 }
 
 __device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, const int32_t* order, int a_interleave, int hoist,
-                                             int by_group, int& b, int& h, int& m) {
+                                             int by_group, bool packed, int& b, int& h, int& m) {
     const int NG = g.batch * g.Hkv, G = g.G;
     int mr, grp, hl;
     if (order) {
@@ -161,7 +161,7 @@ __device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, con
         grp = x + 8 * (r / G);
         hl = r % G;
     } else if (8 % NG == 0) {
-        const RowPlace p = row_of_shared_group(bid, NG, G, Nb);
+        const RowPlace p = row_of_shared_group(bid, NG, G, Nb, packed);
         grp = p.grp; hl = p.hl; mr = p.mr;
     } else {
         mr = bid / (NG * G);
@@ -790,7 +790,8 @@ k_attn_mfma_bf16(AttnKernelArgs kernel_arguments) {
         } else {
             const int rank = (int)blockIdx.x - used;
             if (planned && rank >= grid_rows) return;
-            have_row = decode_block(kSplit && !planned ? rank / a.nsplit : rank, g, Nbq, a.row_order, a.interleave, a.hoist, a.by_group, b, h, mq);
+            have_row = decode_block(kSplit && !planned ? rank / a.nsplit : rank, g, Nbq, a.row_order, a.interleave, a.hoist, a.by_group,
+                                    a.seq_first != nullptr, b, h, mq);
             if (planned) part = 0;
         }
         if (!have_row) return;
@@ -1388,7 +1389,7 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
         int parts = 0, rid = -1;
         if (rank < grid_rows) {
             int b, h, mq;
-            if (decode_block(rank, g, Nbq, a.row_order, a.interleave, a.hoist, 0, b, h, mq)) {
+            if (decode_block(rank, g, Nbq, a.row_order, a.interleave, a.hoist, 0, a.seq_first != nullptr, b, h, mq)) {
                 rid = (b * g.Hq + h) * Nbq + mq;
                 const int count = count_of(rid);
                 if (count > len) parts = (count + len - 1) / len;

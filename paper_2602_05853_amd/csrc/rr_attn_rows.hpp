@@ -30,11 +30,21 @@ constexpr RowPlace row_of_whole_groups(int bid, int G, int Nb) {
 //   32 / 2: 4096 152.1 / 155.3 / 142.8, 8192 519 / 531 / 509; 28 / 4: 8192 453 / 455 / 445, 16384 1715 / 1706 / 1690 (1742)
 //   lists without an order, 4900 tokens (blocks no multiple of eight), same place / this: 32 / 1 132.3 / 124.4, 32 / 4
 //     105.7 / 104.7
-constexpr RowPlace row_of_shared_group(int bid, int NG, int G, int Nb) {
+// Packed prompts: a row's weight jumps where a prompt starts, and the XCDs on the heavy side of that level would have it
+// for all heads; the second half of the heads is therefore taken k / 2 places on.  Packed dense calls, us, sets of groups
+// over all XCDs / the same place in every level / forth and back / and halves:
+//   32 / 1: four prompts of 50 blocks 1252 / 1215 / 1349 / 1271, of 101 and 37 1394 / 1393 / 1475 / 1394, forty of 8
+//     517 / 638 / 501 / 478; 8 / 1: 65 and 28 179 / 180 / 191 / 184; 16 / 2: forty of 8 267 / 271 / 248 / 244; 28 / 4: 12,
+//     80 and 33 825 / 826 / 836 / 821; 75 packings of 1, 2 and 4 KV heads: 1 / 1.000 / 0.986 / 0.980 in the geometric mean,
+//     at worst 1.21 / 1.08 / 1.04 (8 / 1, seventeen of 13 blocks, 1768 rows).  (Halves without forth and back 0.985,
+//     quarters 0.982, eighths 0.982; single prompts with halves, 32 / 1, 4096 135 instead of 131, 8 / 1, 8192 135 instead
+//     of 131.)
+constexpr RowPlace row_of_shared_group(int bid, int NG, int G, int Nb, bool packed) {
     const int k = 8 / NG, x = bid & 7, s = bid >> 3, q = s / G, c = x / NG;
     const bool paired = q < ((Nb / k) & ~1);
-    const int at = !paired ? (c + s) % k : (q & 1 ? k - 1 - c : c);
-    return {x % NG, s - q * G, q * k + at};
+    const int hl = s - q * G, beyond = packed && 2 * hl >= G ? k / 2 : 0;
+    const int at = !paired ? (c + s) % k : ((q & 1 ? k - 1 - c : c) + beyond) % k;
+    return {x % NG, hl, q * k + at};
 }
 
 }  // namespace rr

@@ -13,12 +13,12 @@ PROGRAM = r'''
 #include <cstdlib>
 #include "rr_attn_rows.hpp"
 int main(int argc, char** argv) {
-    for (int a = 1; a + 2 < argc; a += 3) {
-        const int NG = atoi(argv[a]), G = atoi(argv[a + 1]), Nb = atoi(argv[a + 2]);
+    for (int a = 1; a + 3 < argc; a += 4) {
+        const int NG = atoi(argv[a]), G = atoi(argv[a + 1]), Nb = atoi(argv[a + 2]), packed = atoi(argv[a + 3]);
         const int k = NG < 8 ? 8 / NG : 1;
         const int grid = NG < 8 ? 8 * G * ((Nb + k - 1) / k) : NG * G * Nb;
         for (int bid = 0; bid < grid; ++bid) {
-            const rr::RowPlace p = NG < 8 ? rr::row_of_shared_group(bid, NG, G, Nb) : rr::row_of_whole_groups(bid, G, Nb);
+            const rr::RowPlace p = NG < 8 ? rr::row_of_shared_group(bid, NG, G, Nb, packed != 0) : rr::row_of_whole_groups(bid, G, Nb);
             printf("%d %d %d\n", p.grp, p.hl, p.mr);
         }
         printf("end\n");
@@ -26,7 +26,8 @@ int main(int argc, char** argv) {
 }
 '''
 
-SHAPES = [(NG, G, Nb) for NG in (1, 2, 4, 8, 16) for G in (1, 4, 7, 8, 32) for Nb in (1, 7, 8, 16, 17, 24, 32, 64)]
+SHAPES = [(NG, G, Nb, packed) for NG in (1, 2, 4, 8, 16) for G in (1, 4, 7, 8, 32) for Nb in (1, 7, 8, 16, 17, 24, 32, 64) for packed in (0, 1)]
+PROMPTS = [(NG, G, n0, n1) for NG in (1, 2, 4) for G in (1, 7, 32) for n0, n1 in ((100, 100), (37, 101), (96, 80), (65, 28), (12, 56))]
 
 
 @pytest.fixture(scope="module")
@@ -37,15 +38,16 @@ def rows(tmp_path_factory):
     d = tmp_path_factory.mktemp("rows")
     (d / "rows.cpp").write_text(PROGRAM)
     subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / "rows.cpp"), "-o", str(d / "rows")], check=True)
-    out = subprocess.run([str(d / "rows")] + [str(v) for s in SHAPES for v in s], check=True, capture_output=True, text=True).stdout
+    wanted = SHAPES + [(NG, G, n0 + n1, 1) for NG, G, n0, n1 in PROMPTS]
+    out = subprocess.run([str(d / "rows")] + [str(v) for s in wanted for v in s], check=True, capture_output=True, text=True).stdout
     return {s: [tuple(map(int, line.split())) for line in part.strip().split("\n")]
-            for s, part in zip(SHAPES, out.split("end\n"))}
+            for s, part in zip(wanted, out.split("end\n"))}
 
 
-@pytest.mark.parametrize("NG,G,Nb", SHAPES)
-def test_rows_are_taken_once_and_shared_evenly(rows, NG, G, Nb):
+@pytest.mark.parametrize("NG,G,Nb,packed", SHAPES)
+def test_rows_are_taken_once_and_shared_evenly(rows, NG, G, Nb, packed):
     work, seen, groups = [0] * 8, set(), [set() for _ in range(8)]
-    for bid, (grp, hl, mr) in enumerate(rows[NG, G, Nb]):
+    for bid, (grp, hl, mr) in enumerate(rows[NG, G, Nb, packed]):
         if mr >= Nb:                                   # the last query blocks of a number that the XCDs do not divide
             continue
         assert 0 <= grp < NG and 0 <= hl < G and mr >= 0
@@ -66,3 +68,17 @@ def test_rows_are_taken_once_and_shared_evenly(rows, NG, G, Nb):
     odd, cut = G * (Nb // k % 2), G if Nb % k else 0
     bound = sum((n % k) * (k - n % k) for n in (odd, cut))
     assert max(work) - min(work) <= bound, work
+
+
+@pytest.mark.parametrize("NG,G,n0,n1", PROMPTS)
+def test_two_packed_prompts_are_shared_evenly(rows, NG, G, n0, n1):
+    """The weight of a row jumps where a prompt starts: no XCD has the heavy side of that level for more than half of the heads of
+    a group beyond another."""
+    Nb, k = n0 + n1, 8 // NG
+    work = [0] * 8
+    for bid, (grp, hl, mr) in enumerate(rows[NG, G, Nb, 1]):
+        if mr < Nb:
+            m = Nb - 1 - mr
+            work[bid & 7] += m + 1 - (n0 if m >= n0 else 0)
+    # half of the heads times the jump, and up to k blocks a head in the level that is its partner, in an odd one and in one that k does not fill
+    assert max(work) - min(work) <= -(-G // 2) * n0 + 3 * k * G, work
