@@ -18,32 +18,36 @@ constexpr RowPlace row_of_whole_groups(int bid, int G, int Nb) {
 }
 
 // NG a divisor of eight: k = 8 / NG XCDs share a group, and each takes one of every k query blocks (a level) for all heads,
-// whose tiles then meet in its L2.  Levels are taken forth and back in pairs: with the same place in every level the
-// heaviest of k rows always went to one XCD, which had 21 % more key blocks than the mean for one KV head and 32 query
-// blocks.  Where no second level is left (an odd number of them, or a last one that k does not fill) the place moves on
-// from head to head.
-// Dense, us, sets of groups over all XCDs / the same place in every level / this; in brackets the place that moves on from
-// head to head everywhere, as even, on another box of about the same speed:
-//   32 / 1 heads: 2048 tokens 51.5 / 55.8 / 45.7 (51.1), 4096 151.8 / 169.5 / 143.0 (154.5), 8192 521 / 553 / 516 (531),
-//     20000 2973 / 2974 / 2870 (2990); 64 / 1: 1500 73.2 / 72.7 / 62.1, 4096 288.7 / 317.7 / 276.3; 128 / 1, 4096
-//     566 / 621 / 549; 8 / 1, 16384 529 / 538 / 517
-//   32 / 2: 4096 152.1 / 155.3 / 142.8, 8192 519 / 531 / 509; 28 / 4: 8192 453 / 455 / 445, 16384 1715 / 1706 / 1690 (1742)
-//   lists without an order, 4900 tokens (blocks no multiple of eight), same place / this: 32 / 1 132.3 / 124.4, 32 / 4
-//     105.7 / 104.7
+// whose tiles then meet in its L2.  Levels are taken forth and back: with the same place in every level the heaviest of k
+// rows always went to one XCD, which had 21 % more key blocks than the mean for one KV head and 32 query blocks.  Of less
+// than two whole levels the place moves on from head to head instead, so that no XCD is left without rows.
+// Dense, us, sets of groups over all XCDs / the same place in every level / this:
+//   32 / 1 heads: 2048 tokens 51.5 / 55.8 / 45.7, 3500 124 / 124 / 113, 4096 151.8 / 169.5 / 143.0, 8192 521 / 553 / 516,
+//     20000 2920 / 2921 / 2840
+//   64 / 1: 1500 70.2 / 70.0 / 58.6, 4096 288.7 / 317.7 / 276.3; 128 / 1, 4096 566 / 621 / 549; 8 / 1, 9000
+//     186 / 186 / 177, 16384 529 / 538 / 517
+//   32 / 2: 4096 152.1 / 155.3 / 142.8, 8192 519 / 531 / 509; 64 / 2, 2300 113 / 113 / 99; 28 / 4: 8192 453 / 455 / 445,
+//     10000 660 / 660 / 651, 16384 1715 / 1706 / 1690
+//   chunks: 1500 of 60000, 16 / 1, 854 / 855 / 710, 3000 of 20000 481 / 481 / 471, 4096 of 100000 level for 1, 2 and 4 KV
+//     heads
+//   lists without an order, 4900 tokens (blocks no multiple of eight), same place / this: 32 / 1 131 / 127, 32 / 2
+//     109 / 104; 9999, 16 / 1, 204 / 194; 20300, 28 / 4, 885 / 889
+// (The place that moves on from head to head in all levels: 32 / 1, 2048 tokens 51.1, 4096 154.5, 20000 2990, 28 / 4, 16384
+// 1742; only in a last level without a partner or that k does not fill: 32 / 1, 3500 124, 64 / 2, 2300 106, 4096 of 100000,
+// 16 / 1, 4029 instead of 3854.)
 // Packed prompts: a row's weight jumps where a prompt starts, and the XCDs on the heavy side of that level would have it
 // for all heads; the second half of the heads is therefore taken k / 2 places on.  Packed dense calls, us, sets of groups
 // over all XCDs / the same place in every level / forth and back / and halves:
 //   32 / 1: four prompts of 50 blocks 1252 / 1215 / 1349 / 1271, of 101 and 37 1394 / 1393 / 1475 / 1394, forty of 8
 //     517 / 638 / 501 / 478; 8 / 1: 65 and 28 179 / 180 / 191 / 184; 16 / 2: forty of 8 267 / 271 / 248 / 244; 28 / 4: 12,
 //     80 and 33 825 / 826 / 836 / 821; 75 packings of 1, 2 and 4 KV heads: 1 / 1.000 / 0.986 / 0.980 in the geometric mean,
-//     at worst 1.21 / 1.08 / 1.04 (8 / 1, seventeen of 13 blocks, 1768 rows).  (Halves without forth and back 0.985,
-//     quarters 0.982, eighths 0.982; single prompts with halves, 32 / 1, 4096 135 instead of 131, 8 / 1, 8192 135 instead
-//     of 131.)
+//     at worst 1.21 / 1.08 / 1.04 (8 / 1, seventeen of 13 blocks, 1768 rows)
+// (Halves without forth and back 0.985, quarters 0.982, eighths 0.982; single prompts with halves, 32 / 1, 4096 135 instead
+// of 131, 8 / 1, 8192 135 instead of 131.)
 constexpr RowPlace row_of_shared_group(int bid, int NG, int G, int Nb, bool packed) {
     const int k = 8 / NG, x = bid & 7, s = bid >> 3, q = s / G, c = x / NG;
-    const bool paired = q < ((Nb / k) & ~1);
     const int hl = s - q * G, beyond = packed && 2 * hl >= G ? k / 2 : 0;
-    const int at = !paired ? (c + s) % k : ((q & 1 ? k - 1 - c : c) + beyond) % k;
+    const int at = Nb < 2 * k ? (c + s) % k : ((q & 1 ? k - 1 - c : c) + beyond) % k;
     return {x % NG, hl, q * k + at};
 }
 

@@ -30,16 +30,20 @@ SHAPES = [(NG, G, Nb, packed) for NG in (1, 2, 4, 8, 16) for G in (1, 4, 7, 8, 3
 PROMPTS = [(NG, G, n0, n1) for NG in (1, 2, 4) for G in (1, 7, 32) for n0, n1 in ((100, 100), (37, 101), (96, 80), (65, 28), (12, 56))]
 
 
-@pytest.fixture(scope="module")
-def rows(tmp_path_factory):
+def _compile(d, name, text):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no C++ compiler")
-    d = tmp_path_factory.mktemp("rows")
-    (d / "rows.cpp").write_text(PROGRAM)
-    subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / "rows.cpp"), "-o", str(d / "rows")], check=True)
+    (d / f"{name}.cpp").write_text(text)
+    subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / f"{name}.cpp"), "-o", str(d / name)], check=True)
+    return str(d / name)
+
+
+@pytest.fixture(scope="module")
+def rows(tmp_path_factory):
+    exe = _compile(tmp_path_factory.mktemp("rows"), "rows", PROGRAM)
     wanted = SHAPES + [(NG, G, n0 + n1, 1) for NG, G, n0, n1 in PROMPTS]
-    out = subprocess.run([str(d / "rows")] + [str(v) for s in wanted for v in s], check=True, capture_output=True, text=True).stdout
+    out = subprocess.run([exe] + [str(v) for s in wanted for v in s], check=True, capture_output=True, text=True).stdout
     return {s: [tuple(map(int, line.split())) for line in part.strip().split("\n")]
             for s, part in zip(wanted, out.split("end\n"))}
 
@@ -61,12 +65,14 @@ def test_rows_are_taken_once_and_shared_evenly(rows, NG, G, Nb, packed):
     if NG >= 8:
         assert max(work) == min(work)
         return
-    # k = 8 / NG XCDs share a group.  A turn is k query blocks of a head that lie side by side, one for each of them.  The turns of two
-    # levels of query blocks are taken forth and back and leave no difference; in those of a last odd level an XCD's place moves on by one from head to
-    # head, so that k turns leave none and j < k of them j (k - j) blocks at most; likewise in a level that k does not fill.
+    # k = 8 / NG XCDs share a group.  A turn is k query blocks of a head that lie side by side, one for each of them.  Two levels of turns
+    # taken forth and back leave no difference; a last odd one leaves k - 1 blocks a head at most, one that k does not fill its heaviest
+    # row's.  Below two whole levels the place moves on by one from turn to turn: k turns leave none, j < k of them j (k - j) blocks.
     k = 8 // NG
-    odd, cut = G * (Nb // k % 2), G if Nb % k else 0
-    bound = sum((n % k) * (k - n % k) for n in (odd, cut))
+    if Nb < 2 * k:
+        bound = sum((n % k) * (k - n % k) for n in (G * (Nb // k), G if Nb % k else 0))
+    else:
+        bound = G * (k - 1) * (Nb // k % 2) + G * (Nb % k)
     assert max(work) - min(work) <= bound, work
 
 
@@ -80,5 +86,6 @@ def test_two_packed_prompts_are_shared_evenly(rows, NG, G, n0, n1):
         if mr < Nb:
             m = Nb - 1 - mr
             work[bid & 7] += m + 1 - (n0 if m >= n0 else 0)
-    # half of the heads times the jump, and up to k blocks a head in the level that is its partner, in an odd one and in one that k does not fill
+    # half of the heads times the jump, and up to k blocks a head in the level that is its partner, in an odd one and in one that k
+    # does not fill
     assert max(work) - min(work) <= -(-G // 2) * n0 + 3 * k * G, work
