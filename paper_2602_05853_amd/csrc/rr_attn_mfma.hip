@@ -94,12 +94,12 @@ __device__ __forceinline__ int v_swz(int key, int chunk) { return key * 256 + ((
 
 // workgroup id -> (batch, head, query block).  Workgroups are dealt to the 8 XCDs round-robin (id % 8 picks the XCD) and
 // start in id order.
-// Dense calls (by_group) where the groups divide into the XCDs or the XCDs into the groups: every XCD takes KV groups of
-// its own (rr_attn_rows.hpp), so that the rows that run on it, which walk their blocks in the same order, find each other's
-// tiles in its L2.  All groups cost the same there; XCDs that share a group take its rows in turn.  Against sets of groups
-// over all XCDs (below; the order before where Nb is a multiple of 8, elsewhere level with what was), dense, us: 32 / 8
-// heads, 4096 tokens 157 / 147, 8192 533 / 512, 16384 2002 / 1946, 32768 7817 / 7506, 98304 67445 / 67180; four prompts of
-// 16384 8014 / 7575, sixteen of 2048 686 / 623 (group after group; rank by rank of all an XCD's groups 7704, 635).
+// Dense calls (by_group) as own_groups_pay says: every XCD takes KV groups of its own (rr_attn_rows.hpp), so that the rows
+// that run on it, which walk their blocks in the same order, find each other's tiles in its L2.  All groups cost the same
+// there; XCDs that share a group take its rows in turn.  Against sets of groups over all XCDs (below; the order before
+// where Nb is a multiple of 8, elsewhere level with what was), dense, us: 32 / 8 heads, 4096 tokens 157 / 147, 8192
+// 533 / 512, 16384 2002 / 1946, 32768 7817 / 7506, 98304 67445 / 67180; four prompts of 16384 8014 / 7575, sixteen of 2048
+// 686 / 623 (group after group; rank by rank of all an XCD's groups 7704, 635).
 // Elsewhere, when Nb is a multiple of 8 the KV groups are taken `gi` at a time GPU-wide, so that the keys and values in use
 // stay cache resident and L2 misses of the sparse walk stay off HBM (gi = 1 at 128K tokens, where one group's K and V are
 // 64 MB); XCD x takes the rows with rank = x (mod 8), the query heads of a group back to back, rows heaviest (largest m)
@@ -1389,7 +1389,7 @@ k_split_plan(Geom g, AttnArgs a, int grid_rows) {
         int parts = 0, rid = -1;
         if (rank < grid_rows) {
             int b, h, mq;
-            if (decode_block(rank, g, Nbq, a.row_order, a.interleave, a.hoist, 0, a.seq_first != nullptr, b, h, mq)) {
+            if (decode_block(rank, g, Nbq, a.row_order, a.interleave, a.hoist, 0, false, b, h, mq)) {   // (a chunk is never packed)
                 rid = (b * g.Hq + h) * Nbq + mq;
                 const int count = count_of(rid);
                 if (count > len) parts = (count + len - 1) / len;
@@ -1627,7 +1627,7 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     const bool by_group = queued && rows >= (NG > 8 ? 4ll : 8ll) * resident && std::min(NG, 8) * 4ll * g.L * g.d < 256ll << 20;
     const bool persist = by_group || (queued && a.Nb <= kPersistMaxBlocks && rows >= resident);
     // (a list without an order: its heavy rows, the last of every head, would meet on few XCDs)
-    a.by_group = by_group || (!a.row_list && a.nsplit == 1 && !planned && ((NG & 7) == 0 || 8 % NG == 0));
+    a.by_group = by_group || (!a.row_list && a.nsplit == 1 && !planned && own_groups_pay(NG, g.L, g.d, g.q0));
     const unsigned grid_rows = grid_size(g, g.Lq / 128, a.row_order != nullptr);
     dim3 grid(grid_rows * (unsigned)a.nsplit + (planned ? (unsigned)a.split_budget : 0u));
     if (planned) {

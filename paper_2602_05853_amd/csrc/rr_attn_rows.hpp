@@ -4,6 +4,20 @@
 
 namespace rr {
 
+// Whether a dense call's KV groups (NG of them, L keys each) have XCDs of their own: where the groups divide into the XCDs or the
+// XCDs into the groups.  The rows of a chunk (first query q0 > 0) all walk nearly the whole context, so the keys and values of the
+// groups in flight, one to an XCD, must fit the memory-side cache of 256 MB; those of a prompt are half as long in the mean.
+// Sets of groups over all XCDs / this, us:
+//   chunks: 4096 of 65536, 32 / 8 heads (256 MB) 3698 / 3668, 8192 7193 / 7092, two sequences of 45000 (175) 3185 / 3111, 4096 of
+//     131072, 28 / 4 (256) 7358 / 7227; not taken: 2048 of 80000, 64 / 8 (312) 4565 / 4732, 8192 of 80000, 32 / 8 8826 / 8956, 4096 of
+//     131072 (512) 7452 / 7655, 16384 28547 / 28969, 64 / 8 14937 / 15372, 1024 of 400000, 32 / 2 (390) 5719 / 5820
+//   whole prompts: 65536, two of 32 / 8 (256) 60563 / 59704, 80000 (312) level, 98304 (384) 67351 / 67105, 131072 (512)
+//     119887 / 119418, 16 / 8 61205 / 59332
+constexpr bool own_groups_pay(int NG, int L, int d, int q0) {
+    const long long in_flight = (NG < 8 ? NG : 8) * 4ll * L * d;
+    return ((NG & 7) == 0 || 8 % NG == 0) && (q0 == 0 || in_flight <= 256ll << 20);
+}
+
 struct RowPlace {
     int grp;            // KV group, batch * Hkv of them
     int hl;             // query head inside the group

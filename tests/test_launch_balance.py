@@ -30,6 +30,16 @@ SHAPES = [(NG, G, Nb, packed) for NG in (1, 2, 4, 8, 16) for G in (1, 4, 7, 8, 3
 PROMPTS = [(NG, G, n0, n1) for NG in (1, 2, 4) for G in (1, 7, 32) for n0, n1 in ((100, 100), (37, 101), (96, 80), (65, 28), (12, 56))]
 
 
+RULE = r'''
+#include <cstdio>
+#include <cstdlib>
+#include "rr_attn_rows.hpp"
+int main(int argc, char** argv) {
+    for (int a = 1; a + 2 < argc; a += 3) printf("%d\n", rr::own_groups_pay(atoi(argv[a]), atoi(argv[a + 1]), 128, atoi(argv[a + 2])));
+}
+'''
+
+
 def _compile(d, name, text):
     gxx = shutil.which("g++")
     if gxx is None:
@@ -37,6 +47,17 @@ def _compile(d, name, text):
     (d / f"{name}.cpp").write_text(text)
     subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / f"{name}.cpp"), "-o", str(d / name)], check=True)
     return str(d / name)
+
+
+# KV groups, keys, first query: whole prompts of any length; chunks while the keys and values of the groups in flight are 256 MB at most;
+# numbers of groups that do not divide into the XCDs, or the XCDs into them, never
+@pytest.mark.parametrize("NG,L,q0,own", [(8, 131072, 0, 1), (16, 98304, 0, 1), (1, 512, 0, 1), (3, 4096, 0, 0), (12, 4096, 0, 0),
+                                         (8, 65536, 65536 - 4096, 1), (8, 65536 + 128, 65536 - 4096, 0), (8, 131072, 131072 - 2048, 0),
+                                         (16, 65536, 63488, 1), (16, 80000, 77952, 0), (4, 131072, 122880, 1), (4, 131200, 122880, 0),
+                                         (1, 524288, 524288 - 128, 1), (1, 600000, 599000, 0)])
+def test_dense_calls_whose_groups_have_xcds_of_their_own(tmp_path, NG, L, q0, own):
+    exe = _compile(tmp_path, "rule", RULE)
+    assert int(subprocess.run([exe, str(NG), str(L), str(q0)], check=True, capture_output=True, text=True).stdout) == own
 
 
 @pytest.fixture(scope="module")
