@@ -20,6 +20,7 @@
 // query head): 128K tokens, 32 / 8 heads, one token 112 -> 101 us (5.3 TB/s), two 176 -> 105; 64 / 8 heads, one token 175 ->
 // 104; 28 / 4 heads, one token 98 -> 56, four 286 -> 78; 16K tokens, one token 27 -> 23; 64K, 8 tokens 143 -> 56.
 #include "rr_attn_frag.hpp"
+#include "rr_attn_rows.hpp"
 
 #include <algorithm>
 
@@ -407,23 +408,13 @@ hipError_t launch_attn_decode(const Geom& g, const AttnArgs& a, hipStream_t st) 
     da.len = (da.nblocks + a.nsplit - 1) / a.nsplit;
     da.scale_log2 = (float)(1.4426950408889634 / sqrt((double)g.d));
     if (R > kDecMaxRows || da.len > kDecMaxLen) return hipErrorInvalidValue;
-    // fewer workgroups than compute units, with parts of some length: two blocks at a time (at 64K, 32 / 8 heads, 8 tokens, 128
-    // workgroups 75 -> 56 us; 256 workgroups 51 and 52)
-    const bool eight = (long long)a.nsplit * g.batch * g.Hkv < 256 && da.len >= 8;
-    // Of more than 16 rows: two workgroups to such a part, with 16 rows each, also where parts are short and both fit the
-    // compute units at once.  Both read the part's keys, the second from L2, and use the matrix and vector units of twice
-    // as many compute units; sparse, each walks the blocks of its own rows only.  32 rows in eight waves / this, us:
-    //   estimate and attention: 8 tokens of 64512, 32 / 8 heads, 90.2 / 84.4, of 30000 51.3 / 47.1, of 4000 (four waves)
-    //     40.8 / 38.2, of 90000, 8 / 2, 65.6 / 57.7
-    //   dense: 4 tokens of 131072, 28 / 4 90.4 / 83.8, 64 / 8 193.5 / 181.7, eight sequences of 5000, 28 / 4, 28.1 / 26.1
-    //     (31 with the two on different XCDs)
-    // (The values of the next keys requested with these, which one tile of rows has registers for: 86.2 instead of 83.7,
-    // one token of 128K 97.3 instead of 95.9.)
-    da.halves = R > 16 && (eight || 2ll * a.nsplit * g.batch * g.Hkv <= 256) ? 2 : 1;
+    const DecodeForm form = decode_form(R, (long long)a.nsplit * g.batch * g.Hkv, da.len);
+    da.halves = form.halves ? 2 : 1;
     const unsigned parts = (unsigned)a.nsplit;
     const dim3 grid = da.halves == 2 ? dim3(2 * parts * (unsigned)g.Hkv * (unsigned)g.batch) : dim3(parts, (unsigned)g.Hkv, (unsigned)g.batch);
-    if (R > 16 && da.halves == 1) hipLaunchKernelGGL((k_attn_decode<2, 4>), grid, dim3(256), 0, st, g, da);
-    else if (eight) hipLaunchKernelGGL((k_attn_decode<1, 8>), grid, dim3(512), 0, st, g, da);
+    if (R > 16 && da.halves == 1 && form.eight) hipLaunchKernelGGL((k_attn_decode<2, 8>), grid, dim3(512), 0, st, g, da);
+    else if (R > 16 && da.halves == 1) hipLaunchKernelGGL((k_attn_decode<2, 4>), grid, dim3(256), 0, st, g, da);
+    else if (form.eight) hipLaunchKernelGGL((k_attn_decode<1, 8>), grid, dim3(512), 0, st, g, da);
     else hipLaunchKernelGGL((k_attn_decode<1, 4>), grid, dim3(256), 0, st, g, da);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

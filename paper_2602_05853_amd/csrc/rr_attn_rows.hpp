@@ -1,5 +1,6 @@
-// Which row a workgroup of an attention launch without a row order takes where every XCD has KV groups of its own.  Plain C++
-// (HIP compiles constexpr functions for host and device), so that the map can be checked without a GPU.
+// Rules of the attention launches in plain C++ (HIP compiles constexpr functions for host and device), so that they can be checked
+// without a GPU: which row a workgroup of a launch without a row order takes where every XCD has KV groups of its own, and how
+// decode-sized steps are shared out.
 #pragma once
 
 namespace rr {
@@ -63,6 +64,29 @@ constexpr RowPlace row_of_shared_group(int bid, int NG, int G, int Nb, bool pack
     const int hl = s - q * G, beyond = packed && 2 * hl >= G ? k / 2 : 0;
     const int at = Nb < 2 * k ? (c + s) % k : ((q & 1 ? k - 1 - c : c) + beyond) % k;
     return {x % NG, hl, q * k + at};
+}
+
+// Decode-sized steps (rr_attn_decode.hip): how many waves take a part of the context and in how many workgroups, for R query rows
+// to a KV head and `parts` parts in all of `len` blocks each.
+struct DecodeForm {
+    bool eight;         // waves: eight, or four
+    bool halves;        // two workgroups to a part, 16 of its rows each
+};
+// Eight waves, two blocks at a time: fewer parts than compute units, of some length (at 64K, 32 / 8 heads, 8 tokens, 128 parts
+// 75 -> 56 us; 256 parts 51 and 52).
+// Halves, of more than 16 rows: where both fit the compute units at once, one of eight waves to a unit.  Both read the part's
+// keys, the second from L2, and use the matrix and vector units of twice as many compute units; sparse, each walks the blocks of
+// its own rows only.  32 rows in one workgroup / halves, us:
+//   estimate and attention: 8 tokens of 64512, 32 / 8 heads, 90.2 / 84.4, of 30000 51.3 / 47.1, of 4000 (four waves) 40.8 / 38.2, of
+//     90000, 8 / 2, 65.6 / 57.7
+//   dense: 4 tokens of 131072, 28 / 4 90.4 / 83.8, 64 / 8 193.5 / 181.7, eight sequences of 5000, 28 / 4, 28.1 / 26.1 (31 with the two
+//     on different XCDs)
+//   not taken, more than 128 parts, where halves make a second round of the launch: 8 tokens of 30000, 32 / 8, three sequences
+//     (144 parts) 78.0 / 122.4, five, 16 / 4 (140) 63.4 / 99.0; of 16435, 3 / 1, twelve (180) 24.3 / 32.8
+// (The values of the next keys requested with these, which one tile of rows has registers for: 86.2 instead of 83.7, one token of
+// 128K 97.3 instead of 95.9.)
+constexpr DecodeForm decode_form(int R, long long parts, int len) {
+    return {parts < 256 && len >= 8, R > 16 && 2 * parts <= 256};
 }
 
 }  // namespace rr

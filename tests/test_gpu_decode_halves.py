@@ -1,5 +1,5 @@
-"""Steps of 17 to 32 query rows per KV head on fewer workgroups than compute units: two workgroups to a part, 16 rows each, against attention
-in 64 bits.  Heads of which both workgroups have rows, steps that lie in two query blocks, numbers of (part, KV head) pairs that are no multiple of
+"""Steps of 17 to 32 query rows per KV head on fewer workgroups than compute units: two workgroups to a part, 16 rows each, up to 128 parts in
+all, and one of eight waves beyond (the last two cases), against attention in 64 bits.  Heads of which both workgroups have rows, steps that lie in two query blocks, numbers of (part, KV head) pairs that are no multiple of
 eight, parts of eight waves and of four, lists that differ from head to head and rows without a block; dense calls."""
 import pytest
 import torch
@@ -8,7 +8,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("batch,Hq,Hkv,T,L", [(1, 4, 1, 5, 128 * 40), (1, 7, 1, 3, 128 * 33 + 2), (1, 3, 1, 10, 128 * 17 + 100), (2, 32, 1, 1, 128 * 150 - 7),
-                                              (1, 6, 3, 16, 128 * 50 + 9), (3, 8, 2, 5, 128 * 21), (1, 17, 1, 1, 128 * 16), (1, 10, 2, 6, 128 * 90 + 3)])
+                                              (1, 6, 3, 16, 128 * 50 + 9), (3, 8, 2, 5, 128 * 21), (1, 17, 1, 1, 128 * 16), (1, 10, 2, 6, 128 * 90 + 3),
+                                              (12, 3, 1, 8, 128 * 129 - 77), (5, 16, 4, 8, 128 * 60 + 20)])
 @pytest.mark.parametrize("sparse", [True, False])
 def test_rows_in_two_workgroups(batch, Hq, Hkv, T, L, sparse):
     import paper_2602_05853_amd as rr
@@ -19,7 +20,8 @@ def test_rows_in_two_workgroups(batch, Hq, Hkv, T, L, sparse):
     K, V = (torch.randn(batch, Hkv, L, d, generator=g, device=dev).bfloat16() for _ in range(2))
     ws = torch.full((rr.rr_attn_workspace_bytes(Q, K, 128),), 0xFF, dtype=torch.uint8, device=dev)
     print(f"[halves] {batch} x {Hq}/{Hkv} heads, {T} of {L}, {ws.numel() // (batch * Hq * T * 129 * 4)} parts", flush=True)
-    assert ws.numel() // (batch * Hq * T * 129 * 4) * batch * Hkv < 256
+    parts = ws.numel() // (batch * Hq * T * 129 * 4) * batch * Hkv
+    assert parts <= 128 if batch < 5 else 128 < parts < 256
     pos = torch.arange(L, device=dev)
     sees = pos[None] <= torch.arange(L - T, L, device=dev)[:, None]                   # [T, L]
     sees = sees.expand(batch, Hq, T, L)

@@ -40,6 +40,20 @@ int main(int argc, char** argv) {
 '''
 
 
+DECODE = r'''
+#include <cstdio>
+#include "rr_attn_rows.hpp"
+int main() {
+    for (int R = 1; R <= 32; ++R)
+        for (int parts = 1; parts <= 600; ++parts)
+            for (int len = 2; len <= 20; ++len) {
+                const rr::DecodeForm f = rr::decode_form(R, parts, len);
+                printf("%d %d %d %d %d\n", R, parts, len, f.eight, f.halves);
+            }
+}
+'''
+
+
 def _compile(d, name, text):
     gxx = shutil.which("g++")
     if gxx is None:
@@ -110,3 +124,16 @@ def test_two_packed_prompts_are_shared_evenly(rows, NG, G, n0, n1):
     # half of the heads times the jump, and up to k blocks a head in the level that is its partner, in an odd one and in one that k
     # does not fill
     assert max(work) - min(work) <= -(-G // 2) * n0 + 3 * k * G, work
+
+
+def test_two_workgroups_to_a_part_run_at_once(tmp_path):
+    """A second workgroup to a part may not make a second round of the launch: with it there are no more workgroups than compute units (256;
+    one of eight waves fills a unit), and parts that fit them one by one still run on eight waves."""
+    out = subprocess.run([_compile(tmp_path, "decode", DECODE)], check=True, capture_output=True, text=True).stdout
+    taken = 0
+    for R, parts, length, eight, halves in (map(int, line.split()) for line in out.strip().split("\n")):
+        assert not halves or (R > 16 and 2 * parts <= 256), (R, parts, length)
+        assert halves or R <= 16 or 2 * parts > 256, (R, parts, length)
+        assert eight == (parts < 256 and length >= 8), (R, parts, length)
+        taken += halves
+    assert taken
