@@ -23,6 +23,7 @@
 #include "rr_attn_rows.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rr {
 
@@ -295,25 +296,31 @@ k_attn_decode_combine(Geom g, AttnArgs a, int T) {
     const float w = (tid < P && l != NEG_INF) ? expf(l - mx) : 0.f;
     if (tid < kDecMaxParts) s_w[tid] = w;
     __syncthreads();
-    // wavefront wv takes the parts p = wv, wv + 4, ..; a lane two channels, eight parts requested at once (one at a time, a part
-    // of weight zero skipped, their latencies were the kernel: one token of 128K, 64 parts, 8.8 us, so 4.2; 16384 tokens, the
-    // whole call 22.1 -> 17.8)
-    constexpr int kAtOnce = 8;
+    // wavefront wv takes the parts p = wv, wv + 4, ..; a lane two channels, up to eight parts requested at once (one at a time, a
+    // part of weight zero skipped, their latencies were the kernel: one token of 128K, 64 parts, 8.8 us, so 4.2; 16384 tokens, the
+    // whole call 22.1 -> 17.8) and no more than there are (always eight: 4 parts, 16 steps of 2 tokens at 2479, 60 / 4 heads,
+    // 21.3 -> 22.5, so 21.1)
     float den = 0.f, o0 = 0.f, o1 = 0.f;
-    for (int p0 = wv; p0 < P; p0 += 4 * kAtOnce) {
-        float2 v[kAtOnce];
+    int p0 = wv;
+    auto take = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        float2 v[N];
 #pragma unroll
-        for (int u = 0; u < kAtOnce; ++u)
+        for (int u = 0; u < N; ++u)
             v[u] = *reinterpret_cast<const float2*>(a.part_O + ((long long)min(p0 + 4 * u, P - 1) * nrows + row) * 128 + 2 * lane);
 #pragma unroll
-        for (int u = 0; u < kAtOnce; ++u) {
+        for (int u = 0; u < N; ++u) {
             const float wp = p0 + 4 * u < P ? s_w[p0 + 4 * u] : 0.f;
             if (wp == 0.f) continue;                          // (whatever it holds)
             den += wp;
             o0 = fmaf(wp, v[u].x, o0);
             o1 = fmaf(wp, v[u].y, o1);
         }
-    }
+        p0 += 4 * N;
+    };
+    while (p0 + 16 < P) take(std::integral_constant<int, 8>{});
+    if (p0 + 4 < P) take(std::integral_constant<int, 4>{});
+    if (p0 < P) take(std::integral_constant<int, 1>{});
     __syncthreads();
     if (lane == 0) s_red[wv] = den;
     s_o[wv][2 * lane] = o0;

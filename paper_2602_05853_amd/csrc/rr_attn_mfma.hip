@@ -1287,25 +1287,31 @@ k_attn_combine(Geom g, AttnArgs a) {
     for (int p = 0; p < a.nsplit; ++p) mx = fmaxf(mx, a.part_lse[(long long)p * nrows + row]);
     float den = 0.f, o0 = 0.f, o1 = 0.f;
     if (mx != NEG_INF) {
-        constexpr int kAtOnce = 8;                              // one after the other, 64 tokens of 65536 133 -> 127 us in all
-        for (int p0 = 0; p0 < a.nsplit; p0 += kAtOnce) {
-            float2 v[kAtOnce];
-            float l[kAtOnce];
+        // up to eight parts requested at once (one after the other, 64 tokens of 65536 133 -> 127 us in all), no more than there are
+        int p0 = 0;
+        auto take = [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            float2 v[N];
+            float l[N];
 #pragma unroll
-            for (int u = 0; u < kAtOnce; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const long long at = (long long)min(p0 + u, a.nsplit - 1) * nrows + row;
                 l[u] = a.part_lse[at];
                 v[u] = *reinterpret_cast<const float2*>(a.part_O + at * g.d + 2 * lane);
             }
 #pragma unroll
-            for (int u = 0; u < kAtOnce; ++u) {
+            for (int u = 0; u < N; ++u) {
                 if (p0 + u >= a.nsplit || l[u] == NEG_INF) continue;   // (a part without a block)
                 const float wgt = expf(l[u] - mx);
                 den += wgt;
                 o0 = fmaf(wgt, v[u].x, o0);
                 o1 = fmaf(wgt, v[u].y, o1);
             }
-        }
+            p0 += N;
+        };
+        while (p0 + 4 < a.nsplit) take(std::integral_constant<int, 8>{});
+        if (p0 + 1 < a.nsplit) take(std::integral_constant<int, 4>{});
+        if (p0 < a.nsplit) take(std::integral_constant<int, 1>{});
     }
     const float inv = den > 0.f ? 1.0f / den : 0.f;
     unsigned short* O = reinterpret_cast<unsigned short*>(a.O) + b * g.qsb + h * g.qsh + r * g.qsl;
@@ -1464,14 +1470,15 @@ k_attn_combine_plan(Geom g, AttnArgs a) {
         const float den = wave_sum_fixed(wgt);
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
         const float* src = a.part_O + ((long long)base * 128 + x) * g.d + 4 * (lane & 31);
-        constexpr int kAtOnce = 4;                                       // of a half's parts
-        for (int p0 = 0; p0 < parts; p0 += 2 * kAtOnce) {
-            f32x4 v[kAtOnce];
+        int p0 = 0;
+        auto take = [&](auto n) {                                        // N parts of each half
+            constexpr int N = decltype(n)::value;
+            f32x4 v[N];
 #pragma unroll
-            for (int u = 0; u < kAtOnce; ++u)
+            for (int u = 0; u < N; ++u)
                 v[u] = *reinterpret_cast<const f32x4*>(src + (long long)min(p0 + 2 * u + half, parts - 1) * 128 * g.d);
 #pragma unroll
-            for (int u = 0; u < kAtOnce; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const int p = p0 + 2 * u + half;
                 const float wp = __shfl(wgt, p & 63);
                 if (p < parts) {
@@ -1479,7 +1486,11 @@ k_attn_combine_plan(Geom g, AttnArgs a) {
                     for (int e = 0; e < 4; ++e) o[e] = fmaf(wp, v[u][e], o[e]);
                 }
             }
-        }
+            p0 += 2 * N;
+        };
+        while (p0 + 4 < parts) take(std::integral_constant<int, 4>{});
+        if (p0 + 2 < parts) take(std::integral_constant<int, 2>{});
+        if (p0 < parts) take(std::integral_constant<int, 1>{});
         const float inv = den > 0.f ? 1.0f / den : 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (o[e] + __shfl_xor(o[e], 32)) * inv;
