@@ -335,7 +335,7 @@ k_estimate_generic(Geom g, EstimateArgs a, EstPlan p, float scale_log2) {
             part += mass;
         }
         part = wave_sum_fixed(part);
-        if (lane == 0 && wv < 4) scanbuf[4 * hh + wv] = part;         // (W > 4: up to 256 blocks, nothing behind them)
+        if (lane == 0 && (W == 4 || wv < 4)) scanbuf[4 * hh + wv] = part;     // (W > 4: up to 256 blocks, nothing behind them)
     }
     __syncthreads();
 
