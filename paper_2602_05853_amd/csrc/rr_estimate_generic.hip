@@ -20,6 +20,7 @@
 // reference point inside the library.  k_select_rows is the selection stage of the MFMA path: the same
 // phase D on block masses that the MFMA kernel left in the workspace.
 #include "rr_common.hpp"
+#include "rr_estimate_rules.hpp"
 #include "rr_select.hpp"
 
 #include <type_traits>
@@ -453,13 +454,7 @@ hipError_t launch_estimate_generic(const Geom& g, int dtype, const EstimateArgs&
         hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), p.total, st, g, a, p, scale_log2);
         return hipGetLastError();
     };
-    // Eight waves where the launch has two workgroups to a compute unit at most: what bounds it then is the chain of score
-    // tiles of a wave (11 of the 21 us of the last row's workgroup for 4096 tokens, fp32).  Up to 256 blocks, whose masses
-    // the first four waves sum in the same order.  Estimate and attention, four waves / eight, us, with the workgroups:
-    // fp32, 4096 tokens, 8 / 2 heads of 128 (256) 192.2 / 188.7, 2048 (128) 82.8 / 79.9, 3000, 6 / 3 of 80 (282)
-    // 73.6 / 70.2; bf16, 6000, 6 / 3 of 96 (282) 93.0 / 89.7, 8000, 8 / 2 of 64 (500) 114.8 / 113.5, 4096, 16 / 4 of 64
-    // (512) 81.4 / 80.4; not taken: 8153, 16 / 4 of 64 (1024) 180.6 / 185.4; sixteen waves the same as eight.
-    const bool eight = a.Nb <= 256 && (long long)grid.x * grid.y * grid.z <= 512;
+    const bool eight = eight_waves_pay((long long)grid.x * grid.y * grid.z, g.batch, a.Nb, a.R, p.HP, g.d, p.total);
     auto launch_waves = [&](auto type, auto r) -> hipError_t {
         using T = decltype(type);
         constexpr int RF = decltype(r)::value;
