@@ -114,7 +114,7 @@ typedef struct {
  *              launches that overlap in time must not share a queue (give each mask its own).  NULL =
  *              one workgroup per row.  It never changes any result.  Rows are drawn
  *                - by KV head, every XCD from heads of its own: at least eight rows to a workgroup (four
- *                  with more than eight KV heads in the batch), any context as long as the keys and
+ *                  where XCDs have several KV heads of the batch, as many each), any context as long as the keys and
  *                  values of min(batch * Hkv, 8) KV heads stay below 256 MB;
  *                - in rank order: other calls of at least as many rows as workgroups, contexts of up to
  *                  256 blocks, where the start of a row is a visible share of it.

@@ -1618,24 +1618,7 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     // costs (1139 tokens, 252 rows: 67 against 72 us).  Wide rows, attention alone: 2048 tokens, 28 / 4 heads 62 -> 47 us.
     const int NG = g.batch * g.Hkv;
     const bool queued = a.row_order != nullptr && a.queue != nullptr && resident >= 8 && a.nsplit == 1 && !planned && rows < 1 << 30;
-    // Rows drawn by KV group: at least eight to a workgroup, four where a queue has several groups (below that the groups'
-    // different lengths cost what the L2 hits give), and as long as the keys and values of the groups in flight, one to a
-    // queue, fit the memory-side cache of 256 MB.  Estimate and attention, gain of the inputs 3, tau 0.9, us, rows in rank
-    // order over all XCDs / by group:
-    //   32 / 8 heads: 16384 tokens 708 / 681, 24000 1518 / 1430, 31907 3142 / 3034, 40000 4068 / 3864, 50000, weaker
-    //     structure, 8088 / 7776; 64 / 8: 9000 533 / 521, 20000 2124 / 2040, 60000 17788 / 17407; 28 / 4: 20000 911 / 902,
-    //     32000 2247 / 2176, 50000 5442 / 5221; 16 / 4: 60000 4537 / 4312, 90000 10911 / 10725; 8 / 2: 40000 1087 / 1068
-    //   batches: 32 / 8, four of 2000 162 / 152, sixteen 585 / 554, three of 12000 1360 / 1260, two of 45000 10346 / 9835;
-    //     28 / 4, eight of 3000 357 / 342; packed prompts of 311 blocks, 28 / 4, 1452 / 1382, forty of 6 blocks, 32 / 8,
-    //     403 / 373
-    //   not taken: 32 / 8, 2500 (1.3 rows to a workgroup) 76 / 82, 6500 (3.2) 172 / 180, 8192 (4) level, 12000 (5.9) level;
-    //     28 / 4, 8000 (3.4) 217 / 229; 16 / 4, 16384 (4) 411 / 428; 64 / 8, 65536 21131 / 21141; 32 / 8, 98304
-    //     25889 / 25944, 131072 31994 / 32199
-    // A queue of several groups starts with the heaviest rows of all of them, one run of each group's order.
-    // Without / with: 32 / 8, four of 4096 299 / 282, of 9000 1007 / 997, of 18500 3267 / 3303, sixteen of 1500 352 / 360;
-    // 64 / 8, eight of 2000 532 / 523, four of 5000 793 / 792, of 12000 3096 / 3135; 8 / 2, sixteen of 8000 885 / 866;
-    // 28 / 4, four of 10000 1077 / 1078 (rank order over all XCDs: 293, 1077, 3522, 375, 585, 836, 3266, 932, 1115).
-    const bool by_group = queued && rows >= (NG > 8 ? 4ll : 8ll) * resident && std::min(NG, 8) * 4ll * g.L * g.d < 256ll << 20;
+    const bool by_group = queued && rows_by_group(rows, resident, NG, a.interleave, g.L, g.d);
     const bool persist = by_group || (queued && a.Nb <= kPersistMaxBlocks && rows >= resident);
     // (a list without an order: its heavy rows, the last of every head, would meet on few XCDs)
     a.by_group = by_group || (!a.row_list && a.nsplit == 1 && !planned && own_groups_pay(NG, g.L, g.d, g.q0));
@@ -1651,7 +1634,7 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     if (by_group) {
         starts = 0;
         for (int x = 0; x < 8; ++x) starts += 1u << (4 * (x % std::min(NG, 8)));
-        a.hoist = 8 * g.G < g.G * (g.Lq / 128) ? 8 * g.G : 0;
+        a.hoist = front_rows_of_groups(NG, g.G, g.Lq / 128);
     }
     // How far a weight may exceed the softmax reference before the reference moves up to it, see the head of the file: 2^8, or 2^6
     // in planned launches.

@@ -5,13 +5,15 @@
 
 namespace rr {
 
-// Whether a dense call's KV groups (NG of them, L keys each) have XCDs of their own: where the groups divide into the XCDs or the
-// XCDs into the groups.  The rows of a chunk (first query q0 > 0) all walk nearly the whole context, so the keys and values of the
-// groups in flight, one to an XCD, must fit the memory-side cache of 256 MB; those of a prompt are half as long in the mean.
+// Whether a dense call's KV groups (NG of them, L keys each) have XCDs of their own: where the groups divide into the XCDs
+// or the XCDs into the groups.  The rows of a chunk (first query q0 > 0) all walk nearly the whole context, so the keys and
+// values of the groups in flight, one to an XCD, must fit the memory-side cache of 256 MB; those of a prompt are half as
+// long in the mean.
 // Sets of groups over all XCDs / this, us:
-//   chunks: 4096 of 65536, 32 / 8 heads (256 MB) 3698 / 3668, 8192 7193 / 7092, two sequences of 45000 (175) 3185 / 3111, 4096 of
-//     131072, 28 / 4 (256) 7358 / 7227; not taken: 2048 of 80000, 64 / 8 (312) 4565 / 4732, 8192 of 80000, 32 / 8 8826 / 8956, 4096 of
-//     131072 (512) 7452 / 7655, 16384 28547 / 28969, 64 / 8 14937 / 15372, 1024 of 400000, 32 / 2 (390) 5719 / 5820
+//   chunks: 4096 of 65536, 32 / 8 heads (256 MB) 3698 / 3668, 8192 7193 / 7092, two sequences of 45000 (175) 3185 / 3111,
+//     4096 of 131072, 28 / 4 (256) 7358 / 7227; not taken: 2048 of 80000, 64 / 8 (312) 4565 / 4732, 8192 of 80000, 32 / 8
+//     8826 / 8956, 4096 of 131072 (512) 7452 / 7655, 16384 28547 / 28969, 64 / 8 14937 / 15372, 1024 of 400000, 32 / 2
+//     (390) 5719 / 5820
 //   whole prompts: 65536, two of 32 / 8 (256) 60563 / 59704, 80000 (312) level, 98304 (384) 67351 / 67105, 131072 (512)
 //     119887 / 119418, 16 / 8 61205 / 59332
 constexpr bool own_groups_pay(int NG, int L, int d, int q0) {
@@ -66,25 +68,59 @@ constexpr RowPlace row_of_shared_group(int bid, int NG, int G, int Nb, bool pack
     return {x % NG, hl, q * k + at};
 }
 
+// Whether a sparse launch draws its rows by KV group (queue q of min(NG, 8): the groups q, q + 8, ..): `resident`
+// workgroups at once; interleave: the groups to a set in the other order, rank by rank over all XCDs.
+// At least eight rows to a workgroup, four where every queue has the same number of several groups or where the other order
+// has sets of two groups at most (below that the queues' different lengths cost what the L2 hits give), and as long as the
+// keys and values of the groups in flight, one to a queue, fit the memory-side cache of 256 MB.  Estimate and attention,
+// gain of the inputs 3, tau 0.9, us, rows in rank order over all XCDs / by group:
+//   32 / 8 heads: 16384 tokens 708 / 681, 24000 1518 / 1430, 31907 3142 / 3034, 40000 4068 / 3864, 50000, weaker structure,
+//     8088 / 7776; 64 / 8: 9000 533 / 521, 20000 2124 / 2040, 60000 17788 / 17407; 28 / 4: 20000 911 / 902, 32000
+//     2247 / 2176, 50000 5442 / 5221; 16 / 4: 60000 4537 / 4312, 90000 10911 / 10725; 8 / 2: 40000 1087 / 1068
+//   batches: 32 / 8, four of 2000 162 / 152, sixteen 585 / 554, three of 12000 1360 / 1260, two of 45000 10346 / 9835;
+//     28 / 4, eight of 3000 357 / 342; packed prompts of 311 blocks, 28 / 4, 1452 / 1382, forty of 6 blocks, 32 / 8,
+//     403 / 373
+//   queues of different numbers of groups: nine KV heads, 9 / 9, 30000 (8.3) 657 / 613, 36 / 9, 10000 (5.5, not taken)
+//     309 / 318, 16000 (8.8) 689 / 660; ten, 40 / 10, 14000 (8.6) 625 / 611; eleven, 22 / 11, 13000 (4.4) 454 / 404 and
+//     329 / 333; seventeen, 68 / 17, 4100 (4.4) 226 / 180; not taken: 36 / 9, 8000 (4.4) 223 / 246, 40 / 10, 7000 (4.3)
+//     199 / 223, 36 / 18, 8000 (4.4) 227 / 240
+//   not taken: 32 / 8, 2500 (1.3 rows to a workgroup) 76 / 82, 6500 (3.2) 172 / 180, 8192 (4) level, 12000 (5.9) level;
+//     28 / 4, 8000 (3.4) 217 / 229; 16 / 4, 16384 (4) 411 / 428; 64 / 8, 65536 21131 / 21141; 32 / 8, 98304 25889 / 25944,
+//     131072 31994 / 32199
+constexpr bool rows_by_group(long long rows, int resident, int NG, int interleave, int L, int d) {
+    const bool four = NG > 8 && (NG % 8 == 0 || interleave <= 2);
+    return rows >= (four ? 4ll : 8ll) * resident && (NG < 8 ? NG : 8) * 4ll * L * d < 256ll << 20;
+}
+// Rows of each group's order that a queue of several groups takes rank by rank, before the others group by group.
+// Queues of as many groups each: the heaviest, one run of the order (8 G rows).  Others: all, since the last group of a
+// longer queue would start late (heaviest first / all: 36 / 9, 16000 671 / 631, 30000 1968 / 1891, 24 / 12, 18000
+// 582 / 563).
+// Queues of as many, without / with: 32 / 8, four of 4096 299 / 282, of 9000 1007 / 997, of 18500 3267 / 3303, sixteen of
+// 1500 352 / 360; 64 / 8, eight of 2000 532 / 523, four of 5000 793 / 792, of 12000 3096 / 3135; 8 / 2, sixteen of 8000
+// 885 / 866; 28 / 4, four of 10000 1077 / 1078 (rank order over all XCDs: 293, 1077, 3522, 375, 585, 836, 3266, 932, 1115).
+constexpr int front_rows_of_groups(int NG, int G, int Nb) {
+    return NG > 8 && NG % 8 ? G * Nb : (8 * G < G * Nb ? 8 * G : 0);
+}
+
 // Decode-sized steps (rr_attn_decode.hip): how many waves take a part of the context and in how many workgroups, for R query rows
 // to a KV head and `parts` parts in all of `len` blocks each.
 struct DecodeForm {
     bool eight;         // waves: eight, or four
     bool halves;        // two workgroups to a part, 16 of its rows each
 };
-// Eight waves, two blocks at a time: fewer parts than compute units, of some length (at 64K, 32 / 8 heads, 8 tokens, 128 parts
-// 75 -> 56 us; 256 parts 51 and 52).
-// Halves, of more than 16 rows: where both fit the compute units at once, one of eight waves to a unit.  Both read the part's
-// keys, the second from L2, and use the matrix and vector units of twice as many compute units; sparse, each walks the blocks of
-// its own rows only.  32 rows in one workgroup / halves, us:
-//   estimate and attention: 8 tokens of 64512, 32 / 8 heads, 90.2 / 84.4, of 30000 51.3 / 47.1, of 4000 (four waves) 40.8 / 38.2, of
-//     90000, 8 / 2, 65.6 / 57.7
-//   dense: 4 tokens of 131072, 28 / 4 90.4 / 83.8, 64 / 8 193.5 / 181.7, eight sequences of 5000, 28 / 4, 28.1 / 26.1 (31 with the two
-//     on different XCDs)
-//   not taken, more than 128 parts, where halves make a second round of the launch: 8 tokens of 30000, 32 / 8, three sequences
-//     (144 parts) 78.0 / 122.4, five, 16 / 4 (140) 63.4 / 99.0; of 16435, 3 / 1, twelve (180) 24.3 / 32.8
-// (The values of the next keys requested with these, which one tile of rows has registers for: 86.2 instead of 83.7, one token of
-// 128K 97.3 instead of 95.9.)
+// Eight waves, two blocks at a time: fewer parts than compute units, of some length (at 64K, 32 / 8 heads, 8 tokens, 128
+// parts 75 -> 56 us; 256 parts 51 and 52).
+// Halves, of more than 16 rows: where both fit the compute units at once, one of eight waves to a unit.  Both read the
+// part's keys, the second from L2, and use the matrix and vector units of twice as many compute units; sparse, each walks
+// the blocks of its own rows only.  32 rows in one workgroup / halves, us:
+//   estimate and attention: 8 tokens of 64512, 32 / 8 heads, 90.2 / 84.4, of 30000 51.3 / 47.1, of 4000 (four waves)
+//     40.8 / 38.2, of 90000, 8 / 2, 65.6 / 57.7
+//   dense: 4 tokens of 131072, 28 / 4 90.4 / 83.8, 64 / 8 193.5 / 181.7, eight sequences of 5000, 28 / 4, 28.1 / 26.1 (31
+//     with the two on different XCDs)
+//   not taken, more than 128 parts, where halves make a second round of the launch: 8 tokens of 30000, 32 / 8, three
+//     sequences (144 parts) 78.0 / 122.4, five, 16 / 4 (140) 63.4 / 99.0; of 16435, 3 / 1, twelve (180) 24.3 / 32.8
+// (The values of the next keys requested with these, which one tile of rows has registers for: 86.2 instead of 83.7, one
+// token of 128K 97.3 instead of 95.9.)
 constexpr DecodeForm decode_form(int R, long long parts, int len) {
     return {parts < 256 && len >= 8, R > 16 && 2 * parts <= 256};
 }

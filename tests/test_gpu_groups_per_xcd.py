@@ -24,18 +24,18 @@ def _tensors(batch, L, Hq, Hkv):
 
 def _by_group(batch, L, Hq, Hkv):
     """Whether a sparse call with a row order and a queue draws its rows by KV group: enough rows to a workgroup, keys and values of the
-    groups in flight within 256 MB."""
+    groups in flight within 256 MB.  (Seventeen groups, a prime number, are one to a set otherwise.)"""
     Nb, NG = -(-L // 128), batch * Hkv
     rows = batch * Hq * Nb
     units = torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
     resident = (1 if rows <= min(15 * Nb + 64, 5000) else 2) * units
-    return rows >= (4 if NG > 8 else 8) * resident and min(NG, 8) * 4 * Nb * 128 * 128 < 256 << 20
+    return rows >= (4 if NG > 8 and (NG % 8 == 0 or NG == 17) else 8) * resident and min(NG, 8) * 4 * Nb * 128 * 128 < 256 << 20
 
 
-# one group to all XCDs, two, three (XCDs 0 and 1 have three each), seven, eight, nine (queue 0 has two groups), sixteen; rows of
+# one group to all XCDs, two, three (XCDs 0 and 1 have three each), seven, eight, nine and seventeen (queue 0 has one more), sixteen; rows of
 # eight waves beyond 256 blocks; lengths that end inside a block; fewer rows than the rule asks for
 @pytest.mark.parametrize("batch,L,Hq,Hkv", [(1, 16384, 32, 1), (1, 16300, 34, 2), (1, 16384, 33, 3), (1, 16000, 35, 7), (1, 16384, 32, 8),
-                                            (3, 16384, 6, 3), (2, 8100, 32, 8), (1, 33000, 8, 2), (1, 16256, 32, 8)])
+                                            (3, 16384, 12, 3), (1, 16000, 17, 17), (2, 8100, 32, 8), (1, 33000, 8, 2), (1, 16256, 32, 8)])
 def test_rows_by_group_equal_rows_one_by_one(batch, L, Hq, Hkv):
     import paper_2602_05853_amd as rr
     assert _by_group(batch, L, Hq, Hkv) == (L != 16256)

@@ -40,6 +40,18 @@ int main(int argc, char** argv) {
 '''
 
 
+GROUPS = r'''
+#include <cstdio>
+#include <cstdlib>
+#include "rr_attn_rows.hpp"
+int main(int argc, char** argv) {
+    int v[5];
+    for (int i = 0; i < 5 && i + 1 < argc; ++i) v[i] = atoi(argv[i + 1]);
+    printf("%d %d\n", rr::rows_by_group(v[0], v[1], v[2], v[3], v[4], 128), rr::front_rows_of_groups(v[2], v[0] / v[2] / (v[4] / 128), v[4] / 128));
+}
+'''
+
+
 DECODE = r'''
 #include <cstdio>
 #include "rr_attn_rows.hpp"
@@ -137,3 +149,20 @@ def test_two_workgroups_to_a_part_run_at_once(tmp_path):
         assert eight == (parts < 256 and length >= 8), (R, parts, length)
         taken += halves
     assert taken
+
+
+# rows, workgroups at once, KV groups, groups to a set in the other order, keys -> by group; heads of one block each
+@pytest.mark.parametrize("rows,resident,NG,interleave,L,own", [(4096, 512, 8, 4, 16384, 1), (4095, 512, 8, 4, 16384, 0), (2048, 512, 16, 8, 8192, 1),
+                                                               (2047, 512, 16, 8, 8192, 0), (2048, 256, 2, 2, 33024, 1),
+                                                               # queues of one group and of two, of two and of three
+                                                               (2268, 512, 9, 3, 8064, 0), (2844, 512, 9, 3, 10112, 0), (4500, 512, 9, 3, 16000, 1),
+                                                               (2200, 512, 10, 5, 7040, 0), (2268, 512, 18, 6, 8064, 0), (2304, 512, 18, 9, 4096, 0),
+                                                               (2200, 512, 20, 5, 7040, 0), (2244, 512, 11, 1, 13056, 1), (2156, 512, 22, 2, 12544, 1),
+                                                               (2125, 512, 17, 1, 16000, 1), (8192, 512, 8, 1, 65536, 0), (8192, 512, 8, 1, 65408, 1)])
+def test_rows_that_are_drawn_by_kv_group(tmp_path, rows, resident, NG, interleave, L, own):
+    exe = _compile(tmp_path, "groups", GROUPS)
+    out = subprocess.run([exe, *map(str, (rows, resident, NG, interleave, L))], check=True, capture_output=True, text=True).stdout.split()
+    assert int(out[0]) == own
+    # rank by rank throughout where the queues have different numbers of groups: the last of the groups would start late
+    G, Nb = rows // NG // (L // 128), L // 128
+    assert int(out[1]) == (G * Nb if NG > 8 and NG % 8 else (8 * G if Nb > 8 else 0))
