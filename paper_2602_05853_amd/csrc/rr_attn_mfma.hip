@@ -94,7 +94,7 @@ __device__ __forceinline__ int v_swz(int key, int chunk) { return key * 256 + ((
 
 // workgroup id -> (batch, head, query block).  Workgroups are dealt to the 8 XCDs round-robin (id % 8 picks the XCD) and
 // start in id order.
-// Dense calls (by_group) as own_groups_pay says: every XCD takes KV groups of its own (rr_attn_rows.hpp), so that the rows
+// Dense calls (by_group) as dense_order says: every XCD takes KV groups of its own (rr_attn_rows.hpp), so that the rows
 // that run on it, which walk their blocks in the same order, find each other's tiles in its L2.  All groups cost the same
 // there; XCDs that share a group take its rows in turn.  Against sets of groups over all XCDs (below; the order before
 // where Nb is a multiple of 8, elsewhere level with what was), dense, us: 32 / 8 heads, 4096 tokens 157 / 147, 8192
@@ -139,7 +139,7 @@ __device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, con
         h += hl;
         return true;
     }
-    if (by_group && (NG & 7) == 0) {
+    if (by_group == kGroupByGroup && (NG & 7) == 0) {
         const RowPlace p = row_of_whole_groups(bid, G, Nb);
         grp = p.grp; hl = p.hl; mr = p.mr;
     } else if ((Nb & 7) == 0 && !by_group) {
@@ -155,11 +155,8 @@ __device__ __forceinline__ bool decode_block(int bid, const Geom& g, int Nb, con
         // protected last row keeps all blocks) are then spread over the XCDs instead of piling up on one
         mr = level * 8 + ((x + grp * G + hl) & 7);
     } else if ((NG & 7) == 0) {
-        const int x = bid & 7, s = bid >> 3, per = (NG >> 3) * G;
-        mr = s / per;
-        const int r = s - mr * per;
-        grp = x + 8 * (r / G);
-        hl = r % G;
+        const RowPlace p = row_of_groups_by_rank(bid, NG, G);
+        grp = p.grp; hl = p.hl; mr = p.mr;
     } else if (8 % NG == 0) {
         const RowPlace p = row_of_shared_group(bid, NG, G, Nb, packed);
         grp = p.grp; hl = p.hl; mr = p.mr;
@@ -1621,7 +1618,8 @@ hipError_t launch_attn_mfma_bf16(const Geom& g, const AttnArgs& a_in, hipStream_
     const bool by_group = queued && rows_by_group(rows, resident, NG, a.interleave, g.L, g.d);
     const bool persist = by_group || (queued && a.Nb <= kPersistMaxBlocks && rows >= resident);
     // (a list without an order: its heavy rows, the last of every head, would meet on few XCDs)
-    a.by_group = by_group || (!a.row_list && a.nsplit == 1 && !planned && own_groups_pay(NG, g.L, g.d, g.q0));
+    a.by_group = by_group ? 1 : 0;
+    if (!a.row_list && a.nsplit == 1 && !planned) a.by_group = dense_order(NG, g.L, g.d, g.Lq, a.seq_first != nullptr, rows);
     const unsigned grid_rows = grid_size(g, g.Lq / 128, a.row_order != nullptr);
     dim3 grid(grid_rows * (unsigned)a.nsplit + (planned ? (unsigned)a.split_budget : 0u));
     if (planned) {

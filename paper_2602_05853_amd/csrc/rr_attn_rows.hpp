@@ -5,10 +5,15 @@
 
 namespace rr {
 
-// Whether a dense call's KV groups (NG of them, L keys each) have XCDs of their own: where the groups divide into the XCDs
-// or the XCDs into the groups.  The rows of a chunk (first query q0 > 0) all walk nearly the whole context, so the keys and
-// values of the groups in flight, one to an XCD, must fit the memory-side cache of 256 MB; those of a prompt are half as
-// long in the mean.
+// The order of a dense call's rows, for NG KV groups of L keys, the Lq / 128 last query blocks and `rows` rows in all.
+enum DenseOrder {
+    kSetsOfGroups = 0,  // over all XCDs
+    kGroupByGroup = 1,  // XCDs have KV groups of their own and take one after the other
+    kRankByRank = 2     // ... and take the heaviest row of each, then the second, ..
+};
+// Groups of their own: where the groups divide into the XCDs or the XCDs into the groups.  The rows of a chunk all walk
+// nearly the whole context, so the keys and values of the groups in flight, one to an XCD, must fit the memory-side cache
+// of 256 MB; those of a prompt are half as long in the mean.
 // Sets of groups over all XCDs / this, us:
 //   chunks: 4096 of 65536, 32 / 8 heads (256 MB) 3698 / 3668, 8192 7193 / 7092, two sequences of 45000 (175) 3185 / 3111,
 //     4096 of 131072, 28 / 4 (256) 7358 / 7227; not taken: 2048 of 80000, 64 / 8 (312) 4565 / 4732, 8192 of 80000, 32 / 8
@@ -16,9 +21,25 @@ namespace rr {
 //     (390) 5719 / 5820
 //   whole prompts: 65536, two of 32 / 8 (256) 60563 / 59704, 80000 (312) level, 98304 (384) 67351 / 67105, 131072 (512)
 //     119887 / 119418, 16 / 8 61205 / 59332
-constexpr bool own_groups_pay(int NG, int L, int d, int q0) {
+// Several groups to an XCD: one after the other their tiles stay in its L2 longer, but the last one's heavy rows start
+// late.  It pays from ten rows on to each of the 512 workgroups that run at once, and the earlier the less the rows differ:
+// by Lq of L blocks, of which one share is how many rows are unlike and one how late they are.  Packed prompts: heavy rows
+// in the middle of a group.
+// Sets / group by group / rank by rank, us:
+//   32 / 32 heads, 1531 tokens (0.8 rows to a workgroup) 37.7 / 42.3 / 37.5, 3195 92.4 / 108.9 / 92.1, 4096
+//     159 / 166 / 139, 8192 (4) 560 / 515 / 503, 16379 (8) 2159 / 1960 / 1949, 24059 (11.8) 4231 / 4155 / 4239; 24 / 24,
+//     2171 49.5 / 57.3 / 49.1; 32 / 8, four of 379 19.4 / 21.4 / 19.0, of 8192 (16) 2083 / 1975 / 1970, sixteen of 4096
+//     (32) 2294 / 2131 / 2218; 24 / 12, eight of 507 33.4 / 38.7 / 33.2, of 10875 (32) 5910 / 5219 / 5916
+//   chunks: 2000 of 20000, 32 / 32 (1.1) 811 / 754 / 811, 512 of 12000, sixteen of 32 / 8 (5) 1851 / 1721 / 1866, 1500 of
+//     3000, eight of 8 / 8 (1.6) 131 / 144 / 131
+//   packed: 32 / 32, forty of 8 blocks (20) 568 / 575 / 518, 64 / 16, two of 100 (25) 4899 / 4708 / 4723, 16 / 16, 6, 24, 1
+//     and 2 59.9 / 61.4 / 60.4
+constexpr DenseOrder dense_order(int NG, int L, int d, int Lq, bool packed, long long rows) {
     const long long in_flight = (NG < 8 ? NG : 8) * 4ll * L * d;
-    return ((NG & 7) == 0 || 8 % NG == 0) && (q0 == 0 || in_flight <= 256ll << 20);
+    const bool own = ((NG & 7) == 0 || 8 % NG == 0) && (Lq == L || in_flight <= 256ll << 20);
+    if (!own || NG <= 8) return own ? kGroupByGroup : kSetsOfGroups;
+    const double differ = (double)Lq / L;
+    return !packed && rows >= 512 && rows >= 5120.0 * differ * differ ? kGroupByGroup : kRankByRank;
 }
 
 struct RowPlace {
@@ -27,11 +48,15 @@ struct RowPlace {
     int mr;             // query block, counted from the heaviest; from Nb on: no row
 };
 
-// NG a multiple of eight: XCD x (workgroup mod 8) takes the groups x, x + 8, .. one after the other, rows by descending
-// weight, the heads of a query block together.
+// NG a multiple of eight: XCD x (workgroup mod 8) takes the groups x, x + 8, .., rows by descending weight, the heads of a query
+// block together; one group after the other, or all of them rank by rank.
 constexpr RowPlace row_of_whole_groups(int bid, int G, int Nb) {
     const int x = bid & 7, s = bid >> 3, per = Nb * G, r = s % per;
     return {x + 8 * (s / per), r % G, r / G};
+}
+constexpr RowPlace row_of_groups_by_rank(int bid, int NG, int G) {
+    const int x = bid & 7, s = bid >> 3, per = (NG >> 3) * G, r = s % per;
+    return {x + 8 * (r / G), r % G, s / per};
 }
 
 // NG a divisor of eight: k = 8 / NG XCDs share a group, and each takes one of every k query blocks (a level) for all heads,

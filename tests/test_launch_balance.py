@@ -18,7 +18,7 @@ int main(int argc, char** argv) {
         const int k = NG < 8 ? 8 / NG : 1;
         const int grid = NG < 8 ? 8 * G * ((Nb + k - 1) / k) : NG * G * Nb;
         for (int bid = 0; bid < grid; ++bid) {
-            const rr::RowPlace p = NG < 8 ? rr::row_of_shared_group(bid, NG, G, Nb, packed != 0) : rr::row_of_whole_groups(bid, G, Nb);
+            const rr::RowPlace p = NG < 8 ? rr::row_of_shared_group(bid, NG, G, Nb, packed != 0) : packed ? rr::row_of_groups_by_rank(bid, NG, G) : rr::row_of_whole_groups(bid, G, Nb);
             printf("%d %d %d\n", p.grp, p.hl, p.mr);
         }
         printf("end\n");
@@ -35,7 +35,9 @@ RULE = r'''
 #include <cstdlib>
 #include "rr_attn_rows.hpp"
 int main(int argc, char** argv) {
-    for (int a = 1; a + 2 < argc; a += 3) printf("%d\n", rr::own_groups_pay(atoi(argv[a]), atoi(argv[a + 1]), 128, atoi(argv[a + 2])));
+    int v[5];
+    for (int i = 0; i < 5 && i + 1 < argc; ++i) v[i] = atoi(argv[i + 1]);
+    printf("%d\n", (int)rr::dense_order(v[0], v[1], 128, v[2], v[3] != 0, v[4]));
 }
 '''
 
@@ -75,15 +77,23 @@ def _compile(d, name, text):
     return str(d / name)
 
 
-# KV groups, keys, first query: whole prompts of any length; chunks while the keys and values of the groups in flight are 256 MB at most;
-# numbers of groups that do not divide into the XCDs, or the XCDs into them, never
-@pytest.mark.parametrize("NG,L,q0,own", [(8, 131072, 0, 1), (16, 98304, 0, 1), (1, 512, 0, 1), (3, 4096, 0, 0), (12, 4096, 0, 0),
-                                         (8, 65536, 65536 - 4096, 1), (8, 65536 + 128, 65536 - 4096, 0), (8, 131072, 131072 - 2048, 0),
-                                         (16, 65536, 63488, 1), (16, 80000, 77952, 0), (4, 131072, 122880, 1), (4, 131200, 122880, 0),
-                                         (1, 524288, 524288 - 128, 1), (1, 600000, 599000, 0)])
-def test_dense_calls_whose_groups_have_xcds_of_their_own(tmp_path, NG, L, q0, own):
+# KV groups, keys, queries in whole blocks, packed, rows -> sets over all XCDs (0), groups of their own one after the other (1), rank by rank
+# (2).  Whole prompts of any length; chunks while the keys and values of the groups in flight are 256 MB at most; numbers of groups
+# that do not divide into the XCDs, or the XCDs into them, never.
+@pytest.mark.parametrize("NG,L,Lq,packed,rows,order",
+                         [(8, 131072, 131072, 0, 32768, 1), (1, 512, 512, 0, 128, 1), (3, 4096, 4096, 0, 1024, 0), (12, 4096, 4096, 0, 1536, 0),
+                          (8, 65536, 4096, 0, 1024, 1), (8, 65664, 4096, 0, 1024, 0), (8, 131072, 2048, 0, 512, 0), (16, 65536, 2048, 0, 1024, 1),
+                          (16, 80000, 2048, 0, 1024, 0), (4, 131072, 8192, 0, 1792, 1), (4, 131200, 8192, 0, 1792, 0), (1, 600064, 1024, 0, 256, 0),
+                          # several groups to an XCD: the last one's heavy rows must not start late
+                          (16, 98304, 98304, 0, 24576, 1), (32, 3200, 3200, 0, 800, 2), (32, 1536, 1536, 0, 384, 2), (24, 4224, 4224, 0, 792, 2),
+                          (128, 512, 512, 0, 2048, 2), (32, 24064, 24064, 0, 6016, 1), (40, 2560, 2560, 0, 800, 2),
+                          # rows of a deep chunk weigh nearly the same
+                          (32, 20096, 2176, 0, 544, 1), (64, 3072, 1664, 0, 832, 2), (96, 4096, 384, 0, 288, 2), (64, 12032, 640, 0, 2560, 1),
+                          (32, 5120, 5120, 1, 1280, 2), (32, 40960, 40960, 1, 10240, 2), (8, 40960, 40960, 1, 10240, 1)])
+def test_order_of_dense_calls(tmp_path, NG, L, Lq, packed, rows, order):
     exe = _compile(tmp_path, "rule", RULE)
-    assert int(subprocess.run([exe, str(NG), str(L), str(q0)], check=True, capture_output=True, text=True).stdout) == own
+    out = subprocess.run([exe, *map(str, (NG, L, Lq, packed, rows))], check=True, capture_output=True, text=True).stdout
+    assert int(out) == order
 
 
 @pytest.fixture(scope="module")
