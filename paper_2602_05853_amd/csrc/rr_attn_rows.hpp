@@ -117,14 +117,18 @@ constexpr bool rows_by_group(long long rows, int resident, int NG, int interleav
     return rows >= (four ? 4ll : 8ll) * resident && (NG < 8 ? NG : 8) * 4ll * L * d < 256ll << 20;
 }
 // Rows of each group's order that a queue of several groups takes rank by rank, before the others group by group.
-// Queues of as many groups each: the heaviest, one run of the order (8 G rows).  Others: all, since the last group of a
-// longer queue would start late (heaviest first / all: 36 / 9, 16000 671 / 631, 30000 1968 / 1891, 24 / 12, 18000
-// 582 / 563).
-// Queues of as many, without / with: 32 / 8, four of 4096 299 / 282, of 9000 1007 / 997, of 18500 3267 / 3303, sixteen of
-// 1500 352 / 360; 64 / 8, eight of 2000 532 / 523, four of 5000 793 / 792, of 12000 3096 / 3135; 8 / 2, sixteen of 8000
-// 885 / 866; 28 / 4, four of 10000 1077 / 1078 (rank order over all XCDs: 293, 1077, 3522, 375, 585, 836, 3266, 932, 1115).
+// Queues of as many groups each: the heaviest, 16 G of a queue in all (at least G of a group): more of them mix the tiles
+// of many groups in L2 for long.  Others: all, since the last group of a longer queue would start late (heaviest
+// first / all: 36 / 9, 16000 671 / 631, 30000 1968 / 1891, 24 / 12, 18000 582 / 563).
+// Queues of as many, rank order over all XCDs / none first / 8 G of each group / 2 G of each:
+//   32 groups to a queue: 32 / 32, eight of 7424 1488 / 1423 / 1557 / 1448, of 12000 3290 / 3039 / 3346 / 3076; 16: 8 / 2,
+//     sixty-four of 2000 541 / 498 / 512 / 495, 32 / 32, four of 7424 797 / 783 / 760 / 749; 8: 32 / 8, eight of 3000
+//     373 / 373 / 368 / 361, of 8000 1592 / 1537 / 1523 / 1508
+//   4: 32 / 8, four of 4096 268 / 273 / 262 / 255, of 9000 979 / 914 / 874 / 861; 2: 16 / 16, 20000 559 / - / 546 / 563,
+//     16 / 1, sixteen of 1500 163 / 162 / 162 / 166
 constexpr int front_rows_of_groups(int NG, int G, int Nb) {
-    return NG > 8 && NG % 8 ? G * Nb : (8 * G < G * Nb ? 8 * G : 0);
+    const int n = NG / 8 > 2 ? NG / 8 : 2, each = n < 16 ? 16 / n : 1;
+    return NG > 8 && NG % 8 ? G * Nb : (each < Nb ? each * G : 0);
 }
 
 // Decode-sized steps (rr_attn_decode.hip): how many waves take a part of the context and in how many workgroups, for R query rows

@@ -163,7 +163,7 @@ def test_two_workgroups_to_a_part_run_at_once(tmp_path):
 
 # rows, workgroups at once, KV groups, groups to a set in the other order, keys -> by group; heads of one block each
 @pytest.mark.parametrize("rows,resident,NG,interleave,L,own", [(4096, 512, 8, 4, 16384, 1), (4095, 512, 8, 4, 16384, 0), (2048, 512, 16, 8, 8192, 1),
-                                                               (2047, 512, 16, 8, 8192, 0), (2048, 256, 2, 2, 33024, 1),
+                                                               (2047, 512, 16, 8, 8192, 0), (4096, 512, 32, 8, 8192, 1), (8192, 512, 64, 8, 8192, 1), (16384, 512, 256, 8, 8192, 1), (2048, 256, 2, 2, 33024, 1),
                                                                # queues of one group and of two, of two and of three
                                                                (2268, 512, 9, 3, 8064, 0), (2844, 512, 9, 3, 10112, 0), (4500, 512, 9, 3, 16000, 1),
                                                                (2200, 512, 10, 5, 7040, 0), (2268, 512, 18, 6, 8064, 0), (2304, 512, 18, 9, 4096, 0),
@@ -175,4 +175,6 @@ def test_rows_that_are_drawn_by_kv_group(tmp_path, rows, resident, NG, interleav
     assert int(out[0]) == own
     # rank by rank throughout where the queues have different numbers of groups: the last of the groups would start late
     G, Nb = rows // NG // (L // 128), L // 128
-    assert int(out[1]) == (G * Nb if NG > 8 and NG % 8 else (8 * G if Nb > 8 else 0))
+    # queues of as many groups: sixteen rows a head in all, of each group the same number
+    each = 16 // max(NG // 8, 2) or 1
+    assert int(out[1]) == (G * Nb if NG > 8 and NG % 8 else (each * G if Nb > each else 0))
