@@ -155,7 +155,8 @@ struct AttnArgs {
     const int32_t* row_order;   // optional launch order of the rows per KV head (MFMA kernel only)
     int interleave;             // MFMA kernel: KV groups whose rows are launched interleaved (a divisor of batch * Hkv)
     int hoist;                  // MFMA kernel, with row_order: rows of every KV group that are launched before the sets of groups
-    int by_group;               // MFMA kernel: sparse, every XCD draws the rows of KV groups of its own; dense, a DenseOrder (rr_attn_rows.hpp)
+    int by_group;               // MFMA kernel: sparse, 1 where every XCD draws the rows of KV groups of its own; dense, a
+                                // DenseOrder (rr_attn_rows.hpp)
     int32_t* queue;             // MFMA kernel, with row_order: row counters of the persistent form (rr_mask.queue), or nullptr
     // MFMA kernel, launches of few rows (steps): the block list of a row is shared out among nsplit workgroups;
     // part p writes its own attention output and lse to part_O / part_lse ([nsplit][batch][Hq][rows][d] and
